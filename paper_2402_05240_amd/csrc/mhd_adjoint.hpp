@@ -17,7 +17,7 @@ VLCT_DEV bool takes_second_min(double a, double b) { return b < a; }
 VLCT_DEV bool takes_second_max(double a, double b) { return b > a; }
 // derivative of |x| on the branch taken (+1 at x = 0)
 VLCT_DEV double abs_slope(double x) { return x < 0.0 ? -1.0 : 1.0; }
-VLCT_DEV double sqrt_slope(double r) { return r > 0.0 ? 0.5 / r : 0.0; }  // d sqrt(q) / dq at r = sqrt(q)
+VLCT_DEV double sqrt_slope(double r) { return r > 0.0 ? 0.5 * mrcp(r) : 0.0; }  // d sqrt(q) / dq at r = sqrt(q)
 
 // ---------------------------------------------------------------------------
 // fast speed: cf2 = (gP + B^2 + disc) / (2 rho), disc = sqrt((gP - B^2)^2 + 4 gP B_perp^2)
@@ -103,7 +103,7 @@ VLCT_DEV void hlld_rev(const W7 &L, const W7 &R, double bn, double gam, double g
     const double sR = (umaxR ? R.u : L.u) + cmax;
     const double qL = (sL - L.u) * L.d;
     const double qR = (sR - R.u) * R.d;
-    const double iq = 1.0 / (qR - qL);
+    const double iq = mrcp(qR - qL);
     const double num_m = qR * R.u - qL * L.u - ptR + ptL;
     const double sM = num_m * iq;
     const double num_p = qR * ptL - qL * ptR + qL * qR * (R.u - L.u);
@@ -120,11 +120,11 @@ VLCT_DEV void hlld_rev(const W7 &L, const W7 &R, double bn, double gam, double g
         const double e = a == 0 ? eL : eR;
         su[a] = S - X.u;
         ssm[a] = S - sM;
-        issm[a] = 1.0 / ssm[a];
+        issm[a] = mrcp(ssm[a]);
         ds[a] = X.d * su[a] * issm[a];
         den[a] = X.d * su[a] * ssm[a] - bn2;
         degen[a] = fabs(den[a]) < kHlldDegen * pts;
-        iden[a] = 1.0 / den[a];
+        iden[a] = mrcp(den[a]);
         t1[a] = degen[a] ? 0.0 : bn * (sM - X.u) * iden[a];
         t2[a] = degen[a] ? 1.0 : (X.d * su[a] * su[a] - bn2) * iden[a];
         vs[a] = X.v - X.by * t1[a];
@@ -139,7 +139,7 @@ VLCT_DEV void hlld_rev(const W7 &L, const W7 &R, double bn, double gam, double g
     const double sg = bn >= 0.0 ? 1.0 : -1.0;
     const double irL = mrsqrt(ds[0]), irR = mrsqrt(ds[1]);
     const double rL = ds[0] * irL, rR = ds[1] * irR;
-    const double isum = 1.0 / (rL + rR);
+    const double isum = mrcp(rL + rR);
     const double nv = rL * vs[0] + rR * vs[1] + sg * (bys[1] - bys[0]);
     const double nw = rL * ws[0] + rR * ws[1] + sg * (bzs[1] - bzs[0]);
     const double nby = rL * bys[1] + rR * bys[0] + sg * rL * rR * (vs[1] - vs[0]);
@@ -427,7 +427,7 @@ VLCT_DEV void hlld_rev(const W7 &L, const W7 &R, double bn, double gam, double g
         double rq;
         fast_fwd(Xc, q, rq);
         const double i2d = (q.gp + q.b2 + q.disc) * rq * rq;
-        const double idc = q.disc > 0.0 ? 1.0 / q.disc : 0.0;
+        const double idc = q.disc > 0.0 ? mrcp(q.disc) : 0.0;
         double a_d = 0.0, a_p = 0.0, a_by = 0.0, a_bz = 0.0;
         fast_sq_rev(q, i2d, idc, bn, Xc.by, Xc.bz, gam, a_cmax * (Xc.d * rq), 0.0, a_d, a_p, a_bn,
                     a_by, a_bz);
@@ -496,17 +496,18 @@ VLCT_DEV void eigen_rev(const W7 &c, double bn_in, double gam, const EigenA &A, 
     const double ia2 = c.d * q * q;
     FastSq fq = fast_sq_terms(c.p, bn * bn, bt1, bt2, gam);
     const double bp2 = fq.bp2, disc = fq.disc;
-    const double cf2 = (gp + bn * bn + bp2 + disc) * (0.5 * id);
-    fq.cf2 = cf2;
-    const double cf = msqrt(cf2);
-    const double icf = 1.0 / cf;
-    const double kcs = a * r * icf;  // c_s / |B_n|
+    const double num = gp + bn * bn + bp2 + disc;
+    const double rq = mrsqrt(2.0 * c.d * num);
+    fq.cf2 = num * (0.5 * id);
+    const double cf = num * rq;
+    const double icf = 2.0 * c.d * rq;  // 1 / c_f
+    const double kcs = a * r * icf;     // c_s / |B_n|
     const double cs = kcs * fabs(bn);
     const bool haveperp = bp2 > tiny2;
     const double ibp = mrsqrt(haveperp ? bp2 : 1.0);
     const double tdiff = fq.t;
-    const bool split = disc > kCfCsTiny * c.d * cf2;
-    const double idisc = 0.5 / disc;
+    const bool split = disc > 0.5 * kCfCsTiny * num;
+    const double idisc = 0.5 * mrcp(disc);
     const double qfv = (disc + tdiff) * idisc, qsv = (disc - tdiff) * idisc;
     const double af2 = fmin(fmax(qfv, 0.0), 1.0);
     const double as2 = fmin(fmax(qsv, 0.0), 1.0);
@@ -689,59 +690,60 @@ VLCT_DEV void plmc_rev(const W7 &wm, const W7 &w0, const W7 &wp, double bn, doub
     to_arr(wm, xm);
     to_arr(w0, x0);
     to_arr(wp, xp);
-    double dl[7], dr[7], dc[7], dv[7];
+    double dl[7], dr[7], hv[7];
 #pragma unroll
     for (int c = 0; c < 7; ++c) {
         dl[c] = x0[c] - xm[c];
         dr[c] = xp[c] - x0[c];
-        dc[c] = 0.5 * (xp[c] - xm[c]);
         const double pr = dl[c] * dr[c];
-        dv[c] = pr > 0.0 ? 2.0 * pr / (dl[c] + dr[c]) : 0.0;
+        const double q = mdiv(pr, dl[c] + dr[c]);
+        hv[c] = pr > 0.0 ? q : 0.0;
     }
     Eigen E;
-    double al[7], ar[7], ac[7], av[7], am[7];
+    double al[7], ar[7], av[7], am[7];
     if (CHAR) {
         eigen_setup(w0, bn, gam, E);
         project(E, dl, al);
         project(E, dr, ar);
-        project(E, dc, ac);
-        project(E, dv, av);
+        project(E, hv, av);
     } else {
 #pragma unroll
         for (int c = 0; c < 7; ++c) {
             al[c] = dl[c];
             ar[c] = dr[c];
-            ac[c] = dc[c];
-            av[c] = dv[c];
+            av[c] = hv[c];
         }
     }
-    // limiter (the fmin order of plmc): which difference the limited slope
-    // took (0: left, 1: right, 2: centred, 3: van Leer) and its slope there
-    int pick[7];
-    double coef[7];
+    // limiter (half slopes and the fmin order of plmc): the slopes with which
+    // the limited half slope depends on the left and right differences and on
+    // the half van Leer one (the centred choice is a quarter of left plus right)
+    double cl[7], cr[7], cv[7];
 #pragma unroll
     for (int m = 0; m < 7; ++m) {
-        const double A2l = 2.0 * fabs(al[m]), A2r = 2.0 * fabs(ar[m]);
-        const double Ac = fabs(ac[m]), Av = fabs(av[m]);
-        const bool lr_r = takes_second_min(A2l, A2r);
-        const double mlr = lr_r ? A2r : A2l;
+        const double Al = fabs(al[m]), Ar = fabs(ar[m]);
+        const double ac = 0.25 * (al[m] + ar[m]);
+        const double Ac = fabs(ac), Av = fabs(av[m]);
+        const bool lr_r = takes_second_min(Al, Ar);
+        const double mlr = lr_r ? Ar : Al;
         const bool cv_v = takes_second_min(Ac, Av);
         const double mcv = cv_v ? Av : Ac;
         const bool pick_cv = takes_second_min(mlr, mcv);
         const double lim = pick_cv ? mcv : mlr;
         const bool on = al[m] * ar[m] > 0.0;
-        const double sgn = copysign(1.0, ac[m]);  // the sign copysign gives lim
+        const double sgn = copysign(1.0, al[m]);  // the sign copysign gives lim
         am[m] = on ? sgn * lim : 0.0;
-        const double g = on ? sgn : 0.0;
-        pick[m] = pick_cv ? (cv_v ? 3 : 2) : (lr_r ? 1 : 0);
-        const double x = pick_cv ? (cv_v ? av[m] : ac[m]) : (lr_r ? ar[m] : al[m]);
-        coef[m] = g * (pick_cv ? 1.0 : 2.0) * abs_slope(x);
+        const double x = pick_cv ? (cv_v ? av[m] : ac) : (lr_r ? ar[m] : al[m]);
+        const double k = on ? sgn * abs_slope(x) : 0.0;
+        const double kc = pick_cv && !cv_v ? 0.25 * k : 0.0;
+        cl[m] = !pick_cv && !lr_r ? k : kc;
+        cr[m] = !pick_cv && lr_r ? k : kc;
+        cv[m] = pick_cv && cv_v ? k : 0.0;
     }
-    // fp = x0 + dw / 2, fm = x0 - dw / 2
+    // fp = x0 + dw, fm = x0 - dw
     double adw[7], ax0[7];
 #pragma unroll
     for (int c = 0; c < 7; ++c) {
-        adw[c] = 0.5 * (a_fp[c] - a_fm[c]);
+        adw[c] = a_fp[c] - a_fm[c];
         ax0[c] = a_fp[c] + a_fm[c];
     }
     double aam[7] = {0, 0, 0, 0, 0, 0, 0};
@@ -753,45 +755,41 @@ VLCT_DEV void plmc_rev(const W7 &wm, const W7 &w0, const W7 &wp, double bn, doub
 #pragma unroll
         for (int c = 0; c < 7; ++c) aam[c] = adw[c];
     }
-    double aal[7], aar[7], aac[7], aav[7];
+    double aal[7], aar[7], aav[7];
 #pragma unroll
     for (int m = 0; m < 7; ++m) {
-        const double v = coef[m] * aam[m];
-        aal[m] = pick[m] == 0 ? v : 0.0;
-        aar[m] = pick[m] == 1 ? v : 0.0;
-        aac[m] = pick[m] == 2 ? v : 0.0;
-        aav[m] = pick[m] == 3 ? v : 0.0;
+        aal[m] = cl[m] * aam[m];
+        aar[m] = cr[m] * aam[m];
+        aav[m] = cv[m] * aam[m];
     }
     double adl[7] = {0, 0, 0, 0, 0, 0, 0}, adr[7] = {0, 0, 0, 0, 0, 0, 0};
-    double adc[7] = {0, 0, 0, 0, 0, 0, 0}, adv[7] = {0, 0, 0, 0, 0, 0, 0};
+    double adv[7] = {0, 0, 0, 0, 0, 0, 0};
     if (CHAR) {
         project_rev(E, dl, aal, adl, EA);
         project_rev(E, dr, aar, adr, EA);
-        project_rev(E, dc, aac, adc, EA);
-        project_rev(E, dv, aav, adv, EA);
+        project_rev(E, hv, aav, adv, EA);
     } else {
 #pragma unroll
         for (int c = 0; c < 7; ++c) {
             adl[c] = aal[c];
             adr[c] = aar[c];
-            adc[c] = aac[c];
             adv[c] = aav[c];
         }
     }
-    // van Leer difference, then the stencil differences
+    // half van Leer difference l r / (l + r), then the stencil differences
     double am_[7], ap_[7];
 #pragma unroll
     for (int c = 0; c < 7; ++c) {
-        const double pr = dl[c] * dr[c];
-        if (pr > 0.0) {
-            const double s = dl[c] + dr[c];
-            const double is2 = 1.0 / (s * s);
-            adl[c] = adl[c] + adv[c] * 2.0 * dr[c] * dr[c] * is2;
-            adr[c] = adr[c] + adv[c] * 2.0 * dl[c] * dl[c] * is2;
+        const double is = mrcp(dl[c] + dr[c]);
+        const double tl = dr[c] * is, tr = dl[c] * is;
+        const double v = dl[c] * dr[c] > 0.0 ? adv[c] : 0.0;
+        if (v != 0.0) {
+            adl[c] = adl[c] + v * tl * tl;
+            adr[c] = adr[c] + v * tr * tr;
         }
         ax0[c] = ax0[c] + adl[c] - adr[c];
-        am_[c] = -adl[c] - 0.5 * adc[c];
-        ap_[c] = adr[c] + 0.5 * adc[c];
+        am_[c] = -adl[c];
+        ap_[c] = adr[c];
     }
     W7 ae0{ax0[0], ax0[1], ax0[2], ax0[3], ax0[4], ax0[5], ax0[6]};
     if (CHAR) eigen_rev(w0, bn, gam, EA, ae0, a_bn);
@@ -890,8 +888,10 @@ VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, 
         fb = msqrt(w0.d) * fv;
     }
     const double floor_c[7] = {0.0, fv, fv, fv, 0.0, fb, fb};
-    double x0[7], xn[4][7], xs[4][7];
+    double x0[7], base[7], xn[4][7], xs[4][7];
     to_arr(w0, x0);
+#pragma unroll
+    for (int c = 0; c < 7; ++c) base[c] = kPpmTie * (fabs(x0[c]) + floor_c[c]);
     to_arr(wmm, xn[0]);
     to_arr(wm, xn[1]);
     to_arr(wp, xn[2]);
@@ -902,7 +902,7 @@ VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, 
 #pragma unroll
         for (int c = 0; c < 7; ++c) {
             const double d = xn[q][c] - x0[c];
-            tie[q][c] = fabs(d) <= kPpmTie * (fabs(xn[q][c]) + fabs(x0[c]) + floor_c[c]);
+            tie[q][c] = fabs(d) <= ppm_tol(xn[q][c], base[c]);
             xs[q][c] = tie[q][c] ? 0.0 : d;
         }
     double a[4][7];
@@ -929,7 +929,7 @@ VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, 
             if (d2 * d2c > 0.0 && d2 * d2l > 0.0 && d2 * d2r > 0.0)
                 lim = copysign(fmin(fmin(kPpmC * fabs(d2l), kPpmC * fabs(d2r)),
                                     fmin(kPpmC * fabs(d2c), fabs(d2))), d2);
-            const double ratio = d2 != 0.0 ? lim / d2 : 0.0;
+            const double ratio = d2 != 0.0 ? mdiv(lim, d2) : 0.0;
             dp = dp * ratio;
             dm = dm * ratio;
         } else {
@@ -965,7 +965,7 @@ VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, 
         const double up = x0[c] + wpl[c], um = x0[c] + wmi[c];
         const double vp = fmax(fmin(x0[c], xr), fmin(up, fmax(x0[c], xr)));
         const double vm = fmax(fmin(x0[c], xl), fmin(um, fmax(x0[c], xl)));
-        const double tol = kPpmTie * (fabs(x0[c]) + fabs(xl) + fabs(xr) + floor_c[c]);
+        const double tol = base[c] + kPpmTie * (fabs(xl) + fabs(xr));
         double a_vp = a_fp[c], a_vm = a_fm[c];
         if (fabs(vp - up) > tol || fabs(vm - um) > tol) {
             const double dpp = vp - x0[c], dmm = x0[c] - vm;
@@ -1043,7 +1043,7 @@ VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, 
                 lim_pick = pick2 ? (cd ? 3 : 2) : (lr ? 1 : 0);
                 lim = copysign(pick2 ? mcd : mlr, d2);
             }
-            ratio = d2 != 0.0 ? lim / d2 : 0.0;
+            ratio = d2 != 0.0 ? mdiv(lim, d2) : 0.0;
             dp = dp0 * ratio;
             dm = dm0 * ratio;
         } else {
@@ -1066,8 +1066,8 @@ VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, 
             const double a_ratio = dp0 * a_dp + dm0 * a_dm;
             double a_d2 = 0.0, a_lim = 0.0;
             if (d2 != 0.0) {
-                a_lim = a_ratio / d2;
-                a_d2 = -a_ratio * ratio / d2;
+                a_lim = mdiv(a_ratio, d2);
+                a_d2 = -ratio * a_lim;
             }
             // lim = sign(d2) min(...): all candidates share d2's sign
             double a_d2l = 0.0, a_d2r = 0.0, a_d2c = 0.0;

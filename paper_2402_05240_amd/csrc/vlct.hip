@@ -92,7 +92,7 @@ __device__ __forceinline__ uint32_t prims_store(const Geom &g, const Prims &P, i
     double d = u[0];
     uint32_t st = 0;
     if (!(d >= kFloorRho)) { d = kFloorRho; st |= kStatusDensityFloor; }
-    const double id = 1.0 / d;
+    const double id = mrcp(d);
     const double vx = u[1] * id, vy = u[2] * id, vz = u[3] * id;
     const double ke = 0.5 * d * (vx * vx + vy * vy + vz * vz);
     const double me = 0.5 * (bcx * bcx + bcy * bcy + bcz * bcz);
@@ -222,12 +222,13 @@ __device__ __forceinline__ void flux_pcm_body(const Geom &g, const StateP &s, co
     for (int e = 0; e < 3; ++e)
         m[e] = e == D ? map_face(x[e], g.n[e], g.bc[e]) : map_cell(x[e], g.n[e], g.bc[e]);
     const double bn = s.b[D][face_store(g, D, m[0], m[1], m[2])];
-    double f[7], upw;
+    double f[7];
+    int8_t upw;
     hlld(wl, wr, bn, g.gamma, g.gm1i, f, upw);
     if (st && status) atomicOr(status, st);
 #pragma unroll
     for (int c = 0; c < 7; ++c) F.f[D][c][t] = f[c];
-    F.sg[D][t] = (int8_t)upw;
+    F.sg[D][t] = upw;
 }
 
 // ---------------------------------------------------------------------------
@@ -300,12 +301,13 @@ __device__ __forceinline__ void recon_x_body(const Geom &g, const StateP &s, con
                     lds[4][t - 1], lds[5][t - 1], lds[6][t - 1]};
         const int mj = map_cell(j, g.n[1], g.bc[1]), mk = map_cell(k, g.n[2], g.bc[2]);
         const double bn = s.b[0][face_store(g, 0, map_face(c, nx, g.bc[0]), mj, mk)];
-        double f[7], upw;
+        double f[7];
+        int8_t upw;
         hlld(wl, fm, bn, g.gamma, g.gm1i, f, upw);
         const idx_t o = fidx(g, 0, c, j, k);
 #pragma unroll
         for (int v = 0; v < 7; ++v) F.f[0][v][o] = f[v];
-        F.sg[0][o] = (int8_t)upw;
+        F.sg[0][o] = upw;
     }
     if (st && status) atomicOr(status, st);
 }
@@ -368,14 +370,15 @@ __device__ __forceinline__ void march_body(const Geom &g, const StateP &s, const
             m[T] = mt;
             m[D] = map_face(c, nD, g.bc[D]);
             const double bn = s.b[D][face_store(g, D, m[0], m[1], m[2])];
-            double f[7], upw;
+            double f[7];
+            int8_t upw;
             hlld(prev, fm, bn, g.gamma, g.gm1i, f, upw);
             int q[3] = {x[0], x[1], x[2]};
             q[D] = c;
             const idx_t o = fidx(g, D, q[0], q[1], q[2]);
 #pragma unroll
             for (int v = 0; v < 7; ++v) F.f[D][v][o] = f[v];
-            F.sg[D][o] = (int8_t)upw;
+            F.sg[D][o] = upw;
         }
         prev = fp;
         if (c + 1 < s1) {
@@ -401,7 +404,7 @@ __device__ __forceinline__ double cell_cfl(const Geom &g, double d, double mx, d
                                            double mz, double e, const double b[3], uint32_t &st)
 {
     if (!(d >= kFloorRho)) { d = kFloorRho; st |= kStatusDensityFloor; }
-    const double id = 1.0 / d;
+    const double id = mrcp(d);
     const double v[3] = {mx * id, my * id, mz * id};
     const double ke = 0.5 * d * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
     const double me = 0.5 * (b[0] * b[0] + b[1] * b[1] + b[2] * b[2]);
@@ -411,7 +414,7 @@ __device__ __forceinline__ double cell_cfl(const Geom &g, double d, double mx, d
 #pragma unroll
     for (int l = 0; l < 3; ++l) {
         const double cf = fast_speed(d, p, b[l], b[(l + 1) % 3], b[(l + 2) % 3], g.gamma);
-        m = fmax(m, (fabs(v[l]) + cf) / g.dl[l]);
+        m = fmax(m, mdiv(fabs(v[l]) + cf, g.dl[l]));
     }
     return m;
 }
@@ -426,18 +429,18 @@ __device__ __forceinline__ double wave_max(double v)
 // ---------------------------------------------------------------------------
 // CT edge EMFs (Step 4 / Step 8; Eqs. emf-edge, emf-upwind-slope, emf-slope)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double upwind(double s, double lo, double hi)
+__device__ __forceinline__ double upwind(int s, double lo, double hi)
 {
-    return s > 0.0 ? lo : (s < 0.0 ? hi : 0.5 * (lo + hi));
+    return s > 0 ? lo : (s < 0 ? hi : 0.5 * (lo + hi));
 }
 
 // the edge field from the EMFs and upwind indicators of its four faces and the
 // reference fields of its four cells: B-faces at x0 and x0 - e_C, C-faces at
 // x0 and x0 - e_B
 __device__ __forceinline__ double edge_combine(double eb_c, double eb_cm, double ec_b,
-                                               double ec_bm, double sb_c, double sb_cm,
-                                               double sc_b, double sc_bm, double r00, double r10,
-                                               double r01, double r11)
+                                               double ec_bm, int sb_c, int sb_cm, int sc_b,
+                                               int sc_bm, double r00, double r10, double r01,
+                                               double r11)
 {
     const double avg = 0.25 * (eb_c + eb_cm + ec_b + ec_bm);
     const double t1 = upwind(sb_c, ec_bm - r10, ec_b - r00);
@@ -490,7 +493,8 @@ __device__ __forceinline__ double edge_emf_zcarry(const Geom &g, const Flux &F, 
     const idx_t ft_0 = fidx(g, T, i, j, k), ft_1 = fidx(g, T, xt[0], xt[1], xt[2]);
     // EMF component A: -F_B[B_t1] on a B-face, +F_C[B_t2] on a C-face
     constexpr int zcomp = Z == B ? 5 : 6, tcomp = T == B ? 5 : 6;
-    double e_lo, s_lo;
+    double e_lo;
+    int s_lo;
     if (FIRST) {
         const idx_t fz_lo = fidx(g, Z, i, j, k - 1);
         e_lo = Z == B ? -F.f[Z][zcomp][fz_lo] : F.f[Z][zcomp][fz_lo];
@@ -503,14 +507,14 @@ __device__ __forceinline__ double edge_emf_zcarry(const Geom &g, const Flux &F, 
     const int8_t s_hi = F.sg[Z][fz_hi];
     const double et0 = T == B ? -F.f[T][tcomp][ft_0] : F.f[T][tcomp][ft_0];
     const double et1 = T == B ? -F.f[T][tcomp][ft_1] : F.f[T][tcomp][ft_1];
-    const double st0 = F.sg[T][ft_0], st1 = F.sg[T][ft_1];
+    const int st0 = F.sg[T][ft_0], st1 = F.sg[T][ft_1];
     ez = e_hi;
     sz = s_hi;
     if (A == 0)  // B = y stacked along z (x0 - e_C = lower), C = z faces at x0 and x0 - e_y
-        return edge_combine(e_hi, e_lo, et0, et1, (double)s_hi, s_lo, st0, st1, r00, r10, r01,
+        return edge_combine(e_hi, e_lo, et0, et1, (int)s_hi, s_lo, st0, st1, r00, r10, r01,
                             r11);
     else  // B = z faces at x0 and x0 - e_x, C = x stacked along z (x0 - e_B = lower)
-        return edge_combine(et0, et1, e_hi, e_lo, st0, st1, (double)s_hi, s_lo, r00, r10, r01,
+        return edge_combine(et0, et1, e_hi, e_lo, st0, st1, (int)s_hi, s_lo, r00, r10, r01,
                             r11);
 }
 
@@ -797,20 +801,6 @@ struct PredShape {
     static constexpr int NEZ = (TY + 1) * (TX + 1), NEX = (TY + 1) * TX, NEY = TY * (TX + 1);
 };
 
-// edge field from its four face EMFs, their upwind indicators and the four
-// reference fields around the edge (the arithmetic of edge_emf)
-__device__ __forceinline__ double edge_value(double eb_c, double eb_cm, double ec_b, double ec_bm,
-                                             double sb_c, double sb_cm, double sc_b, double sc_bm,
-                                             double r00, double r10, double r01, double r11)
-{
-    const double avg = 0.25 * (eb_c + eb_cm + ec_b + ec_bm);
-    const double t1 = upwind(sb_c, ec_bm - r10, ec_b - r00);
-    const double t2 = upwind(sb_cm, ec_bm - r11, ec_b - r01);
-    const double t3 = upwind(sc_b, eb_cm - r01, eb_c - r00);
-    const double t4 = upwind(sc_bm, eb_cm - r11, eb_c - r10);
-    return avg + 0.25 * (t1 + t2 + t3 + t4);
-}
-
 // side0..2 (optional): the upwind side of every interior face, tape layout;
 // P (optional, P.w[0] == NULL skips it): the half-step primitives of the
 // interior cells are written there as k_prims would derive them from
@@ -926,7 +916,7 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
                 const double bcz = 0.5 * (bz0 + bz1);
                 double d = pf[0];
                 if (!(d >= kFloorRho)) { d = kFloorRho; st |= kStatusDensityFloor; }
-                const double id = 1.0 / d;
+                const double id = mrcp(d);
                 const double vx = pf[1] * id, vy = pf[2] * id, vz = pf[3] * id;
                 const double ke = 0.5 * d * (vx * vx + vy * vy + vz * vz);
                 const double me = 0.5 * (bcx * bcx + bcy * bcy + bcz * bcz);
@@ -951,7 +941,8 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
             if (live) {
                 const W7 wxr{PR(0, t), PR(1, t), PR(2, t), PR(3, t), PR(4, t), PR(6, t), PR(7, t)};
                 wz = W7{PR(0, t), PR(3, t), PR(1, t), PR(2, t), PR(4, t), PR(5, t), PR(6, t)};
-                double f[7], upw;
+                double f[7];
+                int8_t upw;
                 if (do_x) {
                     const int l = t - 1;
                     const W7 wl{PR(0, l), PR(1, l), PR(2, l), PR(3, l), PR(4, l), PR(6, l), PR(7, l)};
@@ -960,7 +951,7 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
                     for (int q = 0; q < 5; ++q) hxn[q] = f[q];
                     s_em[sm][0][t] = -f[5];
                     s_em[sm][1][t] = f[6];
-                    s_sg[sm][0][t] = (int8_t)upw;
+                    s_sg[sm][0][t] = upw;
                 }
                 if (do_y) {
                     const int l = t - CX;
@@ -971,7 +962,7 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
                     for (int q = 0; q < 5; ++q) hyn[q] = f[q];
                     s_em[sm][2][t] = -f[5];
                     s_em[sm][3][t] = f[6];
-                    s_sg[sm][1][t] = (int8_t)upw;
+                    s_sg[sm][1][t] = upw;
                 }
                 if (do_z && m >= k0) {
                     hlld(wz_prev, wz, bz0, g.gamma, g.gm1i, f, upw);
@@ -979,7 +970,7 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
                     for (int q = 0; q < 5; ++q) hzn[q] = f[q];
                     s_zem[0][t] = -f[5];
                     s_zem[1][t] = f[6];
-                    s_zsg[t] = (int8_t)upw;
+                    s_zsg[t] = upw;
                 }
             }
             __syncthreads();
@@ -1013,7 +1004,7 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
                         // E_z at (ie - 1/2, je - 1/2, m): B = x-faces, C = y-faces
                         if (ie <= nx && je <= ny) {
                             const int o = (ec + 1) * CX + ea + 1;  // column (ie, je)
-                            s_ez[sm][ec][ea] = edge_value(
+                            s_ez[sm][ec][ea] = edge_combine(
                                 s_em[sm][0][o], s_em[sm][0][o - CX], s_em[sm][3][o], s_em[sm][3][o - 1],
                                 s_sg[sm][0][o], s_sg[sm][0][o - CX], s_sg[sm][1][o], s_sg[sm][1][o - 1],
                                 s_rz[o], s_rz[o - 1], s_rz[o - CX], s_rz[o - CX - 1]);
@@ -1024,7 +1015,7 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
                         // E_x at (ie, je - 1/2, m - 1/2): B = y-faces (planes m, m - 1), C = z-faces
                         if (ie < nx && je <= ny) {
                             const int o = (ec + 1) * CX + ea + 1;
-                            s_ex[sm][ec][ea] = edge_value(
+                            s_ex[sm][ec][ea] = edge_combine(
                                 s_em[sm][2][o], s_em[sp][2][o], s_zem[1][o], s_zem[1][o - CX],
                                 s_sg[sm][1][o], s_sg[sp][1][o], s_zsg[o], s_zsg[o - CX],
                                 s_rx[sm][o], s_rx[sm][o - CX], s_rx[sp][o], s_rx[sp][o - CX]);
@@ -1035,7 +1026,7 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
                         // E_y at (ie - 1/2, je, m - 1/2): B = z-faces, C = x-faces (planes m, m - 1)
                         if (ie <= nx && je < ny) {
                             const int o = (ec + 1) * CX + ea + 1;
-                            s_ey[sm][ec][ea] = edge_value(
+                            s_ey[sm][ec][ea] = edge_combine(
                                 s_zem[0][o], s_zem[0][o - 1], s_em[sm][1][o], s_em[sp][1][o],
                                 s_zsg[o], s_zsg[o - 1], s_sg[sm][0][o], s_sg[sp][0][o],
                                 s_ry[sm][o], s_ry[sp][o], s_ry[sm][o - 1], s_ry[sp][o - 1]);

@@ -935,7 +935,7 @@ __global__ __launch_bounds__(kBlock) void k_ad_prims(Geom g, StateP st, Prims P,
     double d = st.u[0][t];
     const bool dfloor = !(d >= kFloorRho);
     if (dfloor) d = kFloorRho;
-    const double id = 1.0 / d;
+    const double id = mrcp(d);
     const double v[3] = {st.u[1][t] * id, st.u[2][t] * id, st.u[3][t] * id};
     const double ke = 0.5 * d * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
     const double me = 0.5 * (bc[0] * bc[0] + bc[1] * bc[1] + bc[2] * bc[2]);

@@ -299,9 +299,9 @@ inline unsigned xcd_grid(size_t logical_blocks) { return (unsigned)(kXcd * xcd_p
 
 // upwind side of a face from its CT indicator (the sign of S_M, Eq. emf-upwind):
 // 0 for S_M > 0, 1 for S_M < 0, 2 for neither
-__device__ __forceinline__ uint8_t side_code(double s)
+__device__ __forceinline__ uint8_t side_code(int s)
 {
-    return s > 0.0 ? (uint8_t)0 : (s < 0.0 ? (uint8_t)1 : (uint8_t)2);
+    return s > 0 ? (uint8_t)0 : (s < 0 ? (uint8_t)1 : (uint8_t)2);
 }
 
 // tape of one step (vlct_step_taped): the half-step state and the upwind side
