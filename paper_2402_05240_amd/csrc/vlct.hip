@@ -182,53 +182,63 @@ __device__ __forceinline__ void prims_ghost_body(const Geom &g, const StateP &s,
     if (st && status) atomicOr(status, st);
 }
 
-// sweep-frame state of a padded cell for axis D
-template <int D>
-__device__ __forceinline__ W7 load_w7(const Prims &P, idx_t o)
-{
-    constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
-    return W7{P.w[0][o], P.w[1 + D][o], P.w[1 + t1][o], P.w[1 + t2][o],
-              P.w[4][o], P.w[5 + t1][o], P.w[5 + t2][o]};
-}
-
 // ---------------------------------------------------------------------------
 // PCM interface states + HLLD on every face of axis D (Steps 2-3)
 // ---------------------------------------------------------------------------
-template <int D, int RECON>
-__device__ __forceinline__ void flux_pcm_body(const Geom &g, const StateP &s, const Prims &P,
-                                              const Flux &F, uint32_t *status, idx_t b)
+// position of a block's thread in a box of rows of X items (x fastest) and Y
+// rows per plane: block-uniform first plane k0, then the thread's column,
+// row and plane past k0
+struct BoxPos {
+    u32 k0, c, j, dk;
+};
+__device__ __forceinline__ BoxPos box_pos(u32 q0, u32 X, u32 Y)
 {
-    const idx_t X = flux_dim(g.n, D, 0), Y = flux_dim(g.n, D, 1), Z = flux_dim(g.n, D, 2);
-    const idx_t t = b * kBlock + threadIdx.x;
-    if (t >= X * Y * Z) return;
-    int x[3];
-    x[0] = (int)(t % X) - (D != 0);
-    const idx_t r = t / X;
-    x[1] = (int)(r % Y) - (D != 1);
-    x[2] = (int)(r / Y) - (D != 2);
-    // cells along D around the face x[D] - 1/2
-    auto cell_at = [&](int off) {
-        int c[3] = {x[0], x[1], x[2]};
-        c[D] += off;
-        return pidx(g, c[0], c[1], c[2]);
+    const u32 row0 = q0 / X, e = q0 - row0 * X + threadIdx.x, dr = row_div(e, X);
+    BoxPos p;
+    p.k0 = row0 / Y;
+    const u32 r = row0 - p.k0 * Y + dr;
+    p.dk = row_div(r, Y);
+    p.j = r - p.dk * Y;
+    p.c = e - dr * X;
+    return p;
+}
+
+template <int D>
+__device__ __forceinline__ void flux_pcm_body(const Geom &g, const StateP &s, const Prims &P,
+                                              const Flux &F, u32 b)
+{
+    constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
+    const u32 X = flux_dim(g.n, D, 0), Y = flux_dim(g.n, D, 1), Z = flux_dim(g.n, D, 2);
+    const u32 q0 = b * kBlock;
+    const BoxPos p = box_pos(q0, X, Y);
+    if (p.k0 + p.dk >= Z) return;
+    const int x[3] = {(int)p.c - (D != 0), (int)p.j - (D != 1), (int)(p.k0 + p.dk) - (D != 2)};
+    // right cell of the face, from the first padded plane of the block's box;
+    // the left one is `back` bytes lower
+    const idx_t base = (idx_t)(p.k0 + kGhost - (D != 2)) * g.p[1] * g.p[0];
+    const u32 o = 8u * ((p.dk * g.p[1] + p.j + kGhost - (D != 1)) * g.p[0] + p.c + kGhost - (D != 0));
+    const u32 back = 8u * (D == 0 ? 1u : (u32)g.p[0] * (D == 1 ? 1u : (u32)g.p[1]));
+    // the base sits one plane lower for z faces, so that o - back stays positive
+    const idx_t lower = D == 2 ? (idx_t)g.p[0] * g.p[1] : 0;
+    const u32 oh = D == 2 ? o + back : o;
+    auto cell = [&](u32 at) {
+        auto w = [&](int q) { return ld8(P.w[q] + (base - lower), at); };
+        return W7{w(0), w(1 + D), w(1 + T1), w(1 + T2), w(4), w(5 + T1), w(5 + T2)};
     };
-    static_assert(RECON == VLCT_RECON_PCM, "k_flux serves the PCM predictor");
-    const W7 wl = load_w7<D>(P, cell_at(-1));
-    const W7 wr = load_w7<D>(P, cell_at(0));
-    const uint32_t st = 0;
+    const W7 wl = cell(oh - back), wr = cell(oh);
     // stored normal field of this face (transverse indices mapped like cells)
     int m[3];
 #pragma unroll
     for (int e = 0; e < 3; ++e)
         m[e] = e == D ? map_face(x[e], g.n[e], g.bc[e]) : map_cell(x[e], g.n[e], g.bc[e]);
-    const double bn = s.b[D][face_store(g, D, m[0], m[1], m[2])];
+    const double bn = ld8(s.b[D] + face_store(g, D, m[0], m[1], m[2]), 0);
     double f[7];
     int8_t upw;
     hlld(wl, wr, bn, g.gamma, g.gm1i, f, upw);
-    if (st && status) atomicOr(status, st);
+    const idx_t fb = (idx_t)q0;
 #pragma unroll
-    for (int c = 0; c < 7; ++c) F.f[D][c][t] = f[c];
-    F.sg[D][t] = upw;
+    for (int c = 0; c < 7; ++c) st8(F.f[D][c] + fb, 8u * threadIdx.x, f[c]);
+    st1(F.sg[D] + fb, threadIdx.x, upw);
 }
 
 // ---------------------------------------------------------------------------
@@ -241,73 +251,56 @@ __device__ __forceinline__ void flux_pcm_body(const Geom &g, const StateP &s, co
 // solves the Riemann problem of the face between them (255 faces per block).
 // ---------------------------------------------------------------------------
 template <int RECON>
-__device__ __forceinline__ void recon_cell(const Prims &P, const Geom &g, int D, const int c[3],
-                                           W7 &fm, W7 &fp)
-{
-    (void)g;
-    auto at = [&](int off) {
-        int q[3] = {c[0], c[1], c[2]};
-        q[D] += off;
-        return pidx(g, q[0], q[1], q[2]);
-    };
-    const idx_t c0 = at(0);
-    const double bn = P.w[5 + D][c0];
-    constexpr bool kChar = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PPMC;
-    constexpr bool kLinear = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PLMP;
-    if (D == 0) {
-        if (kLinear)
-            plmc<kChar>(load_w7<0>(P, at(-1)), load_w7<0>(P, c0), load_w7<0>(P, at(1)), bn,
-                        g.gamma, fm, fp);
-        else
-            ppmc<kChar>(load_w7<0>(P, at(-2)), load_w7<0>(P, at(-1)), load_w7<0>(P, c0),
-                        load_w7<0>(P, at(1)), load_w7<0>(P, at(2)), bn, g.gamma, fm, fp);
-    }
-}
-
-template <int RECON>
 __device__ __forceinline__ void recon_x_body(const Geom &g, const StateP &s, const Prims &P,
-                                             const Flux &F, uint32_t *status, idx_t b)
+                                             const Flux &F, uint32_t *status, u32 b)
 {
     // items = (row, cell) with cells -1..nx of every row (j in [-1, ny],
     // k in [-1, nz]) in one flat sequence; a block reconstructs 256
     // consecutive items and solves the face between each item and its left
     // neighbour in the same row; consecutive blocks overlap by one item
+    constexpr bool kChar = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PPMC;
+    constexpr bool kLinear = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PLMP;
     __shared__ double lds[7][kBlock];
-    const int nx = g.n[0];
-    const idx_t per_row = nx + 2;
-    const idx_t items = per_row * (idx_t)(g.n[1] + 2) * (g.n[2] + 2);
-    const idx_t nblk = (items - 1 + kRowFaces - 1) / kRowFaces;
+    const u32 per_row = g.n[0] + 2, Y = g.n[1] + 2;
     const int t = threadIdx.x;
-    const idx_t q = b * kRowFaces + t;
-    const bool have = b < nblk && q < items;
-    const idx_t row = q / per_row;
-    const int c = (int)(q - row * per_row) - 1;
-    const int Y = g.n[1] + 2;
-    const int j = (int)(row % Y) - 1;
-    const int k = (int)(row / Y) - 1;
+    const BoxPos p = box_pos(b * kRowFaces, per_row, Y);
+    const bool have = p.k0 + p.dk < (u32)g.n[2] + 2;
     W7 fm{}, fp{};
     uint32_t st = 0;
     if (have) {
-        const int cc[3] = {c, j, k};
-        recon_cell<RECON>(P, g, 0, cc, fm, fp);
+        const idx_t base = (idx_t)(p.k0 + kGhost - 1) * g.p[1] * g.p[0];
+        const u32 o = 8u * ((p.dk * g.p[1] + p.j + kGhost - 1) * g.p[0] + p.c + kGhost - 1);
+        auto cell = [&](int off) {
+            auto w = [&](int q) { return ld8(P.w[q] + base, o + 8 * off); };
+            return W7{w(0), w(1), w(2), w(3), w(4), w(6), w(7)};
+        };
+        const double bn = ld8(P.w[5] + base, o);
+        if constexpr (kLinear)
+            plmc<kChar>(cell(-1), cell(0), cell(1), bn, g.gamma, fm, fp);
+        else
+            ppmc<kChar>(cell(-2), cell(-1), cell(0), cell(1), cell(2), bn, g.gamma, fm, fp);
         st |= floor_state(fm);
         st |= floor_state(fp);
     }
     lds[0][t] = fp.d; lds[1][t] = fp.u; lds[2][t] = fp.v; lds[3][t] = fp.w;
     lds[4][t] = fp.p; lds[5][t] = fp.by; lds[6][t] = fp.bz;
     __syncthreads();
-    if (t >= 1 && have && c >= 0) {
+    if (t >= 1 && have && p.c >= 1) {
         const W7 wl{lds[0][t - 1], lds[1][t - 1], lds[2][t - 1], lds[3][t - 1],
                     lds[4][t - 1], lds[5][t - 1], lds[6][t - 1]};
-        const int mj = map_cell(j, g.n[1], g.bc[1]), mk = map_cell(k, g.n[2], g.bc[2]);
-        const double bn = s.b[0][face_store(g, 0, map_face(c, nx, g.bc[0]), mj, mk)];
+        const int mj = map_cell((int)p.j - 1, g.n[1], g.bc[1]);
+        const int mk = map_cell((int)(p.k0 + p.dk) - 1, g.n[2], g.bc[2]);
+        // the stored face n of a periodic axis holds face 0's value
+        const double bn = ld8(s.b[0] + face_store(g, 0, (int)p.c - 1, mj, mk), 0);
         double f[7];
         int8_t upw;
         hlld(wl, fm, bn, g.gamma, g.gm1i, f, upw);
-        const idx_t o = fidx(g, 0, c, j, k);
+        const u32 X = g.n[0] + 1;
+        const idx_t fb = (idx_t)p.k0 * Y * X;
+        const u32 fo = (p.dk * Y + p.j) * X + p.c - 1;
 #pragma unroll
-        for (int v = 0; v < 7; ++v) F.f[0][v][o] = f[v];
-        F.sg[0][o] = upw;
+        for (int v = 0; v < 7; ++v) st8(F.f[0][v] + fb, 8u * fo, f[v]);
+        st1(F.sg[0] + fb, fo, upw);
     }
     if (st && status) atomicOr(status, st);
 }
@@ -316,46 +309,59 @@ __device__ __forceinline__ void recon_x_body(const Geom &g, const StateP &s, con
 // fastest, so loads and stores are coalesced); each thread marches along the
 // axis through a segment of M faces, keeping the stencil and the previous
 // cell's high-face state in registers (one extra reconstruction per segment).
+// A step along the column moves three byte offsets and one pointer by strides.
 template <int D, int RECON, int M = kMarch>
 __device__ __forceinline__ void march_body(const Geom &g, const StateP &s, const Prims &P,
-                                           const Flux &F, uint32_t *status, idx_t b)
+                                           const Flux &F, uint32_t *status, u32 b)
 {
     constexpr int T = D == 1 ? 2 : 1;         // the transverse axis other than x
+    constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
     constexpr bool kChar = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PPMC;
     constexpr int R = (RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PLMP) ? 1 : 2;
     const int nD = g.n[D];
     // columns (i, it), i in [-1, nx], it in [-1, n_T], flattened with i fastest
-    const idx_t cols = (idx_t)(g.n[0] + 2) * (g.n[T] + 2);
-    const idx_t ncb = (cols + kBlock - 1) / kBlock;
-    const int nseg = (nD + 1 + M - 1) / M;
-    const int seg = (int)(b / ncb);
-    const idx_t col = (b % ncb) * kBlock + threadIdx.x;
-    if (seg >= nseg || col >= cols) return;
-    const int i = (int)(col % (g.n[0] + 2)) - 1;
-    const int it = (int)(col / (g.n[0] + 2)) - 1;
+    const u32 X2 = g.n[0] + 2;
+    const u32 ncb = (X2 * (g.n[T] + 2) + kBlock - 1) / kBlock;
+    const u32 nseg = (nD + 1 + M - 1) / M;
+    const u32 seg = b / ncb, cb = b - seg * ncb;
+    if (seg >= nseg) return;
+    const u32 it0 = cb * kBlock / X2;  // first row of columns of the block
+    const u32 e = cb * kBlock - it0 * X2 + threadIdx.x, dr = row_div(e, X2);
+    const u32 i1 = e - dr * X2;  // i + 1
+    const int i = (int)i1 - 1, it = (int)(it0 + dr) - 1;
+    if (it > g.n[T]) return;
     const int s0 = seg * M;
     const int s1 = min(s0 + M, nD + 1);  // faces [s0, s1)
-    int x[3];
-    x[0] = i;
-    x[T] = it;
-    auto pid = [&](int along) {
-        int q[3] = {x[0], x[1], x[2]};
-        q[D] = along;
-        return pidx(g, q[0], q[1], q[2]);
+    // primitives: cell s0 - 1 - R of the column
+    const u32 px = g.p[0], py = g.p[1];
+    const idx_t pb = D == 1 ? ((idx_t)(it0 + kGhost - 1) * py + (s0 - 1 - R + kGhost)) * px
+                            : ((idx_t)(s0 - 1 - R + kGhost) * py + (it0 + kGhost - 1)) * px;
+    u32 po = 8u * ((D == 1 ? dr * px * py : dr * px) + i1 + kGhost - 1);
+    const u32 pstep = 8u * (D == 1 ? px : px * py);
+    auto cell = [&](u32 at, double &bn) {
+        auto w = [&](int q) { return ld8(P.w[q] + pb, at); };
+        bn = w(5 + D);
+        return W7{w(0), w(1 + D), w(1 + T1), w(1 + T2), w(4), w(5 + T1), w(5 + T2)};
     };
+    // fluxes: face s0
+    const u32 fx = X2, fy = g.n[1] + (D == 1 ? 1 : 2);
+    const idx_t fb = D == 1 ? ((idx_t)it0 * fy + s0) * fx : ((idx_t)s0 * fy + it0) * fx;
+    u32 fo = (D == 1 ? dr * fx * fy : dr * fx) + i1;
+    const u32 fstep = D == 1 ? fx : fx * fy;
+    // stored normal field: face s0 (the face n of a periodic axis holds face 0's value)
+    const int mt = map_cell(it, g.n[T], g.bc[T]), mi = map_cell(i, g.n[0], g.bc[0]);
+    const double *nb = s.b[D] + (D == 1 ? face_store(g, 1, mi, s0, mt) : face_store(g, 2, mi, mt, s0));
+    const idx_t nstep = D == 1 ? (idx_t)g.n[0] : (idx_t)g.n[0] * g.n[1];
     // stencil window of cells c-R .. c+R for c = s0 - 1
     W7 win[2 * R + 1];
     double bnc[2 * R + 1];
 #pragma unroll
     for (int q = 0; q < 2 * R + 1; ++q) {
-        const idx_t o = pid(s0 - 1 - R + q);
-        win[q] = load_w7<D>(P, o);
-        bnc[q] = P.w[5 + D][o];
+        win[q] = cell(po, bnc[q]);
+        po += pstep;
     }
     uint32_t st = 0;
     W7 prev{};
-    const int mt = map_cell(it, g.n[T], g.bc[T]);
-    const int mi = map_cell(i, g.n[0], g.bc[0]);
     for (int c = s0 - 1; c < s1; ++c) {
         W7 fm, fp;
         if constexpr (R == 1)
@@ -365,20 +371,15 @@ __device__ __forceinline__ void march_body(const Geom &g, const StateP &s, const
         st |= floor_state(fm);
         st |= floor_state(fp);
         if (c >= s0) {
-            int m[3];
-            m[0] = mi;
-            m[T] = mt;
-            m[D] = map_face(c, nD, g.bc[D]);
-            const double bn = s.b[D][face_store(g, D, m[0], m[1], m[2])];
+            const double bn = ld8(nb, 0);
+            nb += nstep;
             double f[7];
             int8_t upw;
             hlld(prev, fm, bn, g.gamma, g.gm1i, f, upw);
-            int q[3] = {x[0], x[1], x[2]};
-            q[D] = c;
-            const idx_t o = fidx(g, D, q[0], q[1], q[2]);
 #pragma unroll
-            for (int v = 0; v < 7; ++v) F.f[D][v][o] = f[v];
-            F.sg[D][o] = upw;
+            for (int v = 0; v < 7; ++v) st8(F.f[D][v] + fb, 8u * fo, f[v]);
+            st1(F.sg[D] + fb, fo, upw);
+            fo += fstep;
         }
         prev = fp;
         if (c + 1 < s1) {
@@ -387,9 +388,8 @@ __device__ __forceinline__ void march_body(const Geom &g, const StateP &s, const
                 win[q] = win[q + 1];
                 bnc[q] = bnc[q + 1];
             }
-            const idx_t o = pid(c + 1 + R);
-            win[2 * R] = load_w7<D>(P, o);
-            bnc[2 * R] = P.w[5 + D][o];
+            win[2 * R] = cell(po, bnc[2 * R]);
+            po += pstep;
         }
     }
     if (st && status) atomicOr(status, st);
@@ -1230,11 +1230,10 @@ __global__ void __launch_bounds__(kBlock) k_prims(Geom g, StateP s, Prims P, uin
     prims_body(g, s, P, status, xcd_block(nblk_prims(g)));
 }
 
-template <int D, int RECON>
-__global__ void __launch_bounds__(kBlock) k_flux(Geom g, StateP s, Prims P, Flux F,
-                                                 uint32_t *status)
+template <int D>
+__global__ void __launch_bounds__(kBlock) k_flux(Geom g, StateP s, Prims P, Flux F)
 {
-    flux_pcm_body<D, RECON>(g, s, P, F, status, xcd_block(nblk_flux(g, D)));
+    flux_pcm_body<D>(g, s, P, F, xcd_block(nblk_flux(g, D)));
 }
 
 template <int RECON>
@@ -1452,7 +1451,7 @@ __global__ void __launch_bounds__(kBlock) kb_flux_pcm(const Inst *tab, int count
     const StateP st = half ? const_view(I.half) : I.in;
     const Prims P = I.P;
     const Flux F = I.F;
-    flux_pcm_body<D, VLCT_RECON_PCM>(g, st, P, F, I.status, lb);
+    flux_pcm_body<D>(g, st, P, F, lb);
 }
 
 template <int RECON>
@@ -1648,7 +1647,7 @@ int launch_fluxes(const Geom &g, const StateP &st, const Prims &P, const Flux &F
 #define VLCT_FLUX(D)                                                                      \
     {                                                                                     \
         Observe o(VLCT_KERNEL_FLUX_PCM, s);                                               \
-        k_flux<D, VLCT_RECON_PCM><<<xcd_grid(nblk_flux(g, D)), kBlock, 0, s>>>(g, st, P, F, status); \
+        k_flux<D><<<xcd_grid(nblk_flux(g, D)), kBlock, 0, s>>>(g, st, P, F);             \
     }
         VLCT_FLUX(0) VLCT_FLUX(1) VLCT_FLUX(2)
 #undef VLCT_FLUX
@@ -1812,7 +1811,11 @@ static void batch_records(int count, const vlct_grid *grids, const vlct_state *i
         r.status = status_dev ? status_dev + i : nullptr;
         r.active = nullptr;
         r.t = nullptr;
-        const int cv = plan ? (plan[i] & 15) : 0, mv = plan ? (plan[i] >> 4) : 0;
+        const int cv = plan ? (plan[i] & 15) : 0;
+        int mv = plan ? (plan[i] >> 4) : 0;
+        // a 32-face march of planes this large would leave the 32-bit offsets
+        // of march_body (same results with 16)
+        if (mv == 1 && (idx_t)g.p[0] * g.p[1] * 8 * 38 >= (idx_t)1 << 32) mv = 0;
         idx_t nb[kSlots] = {};
         nb[kSlotPred] = nblk_pred_shares(g);
         nb[kSlotGhost] = (ghost_cells(g) + kBlock - 1) / kBlock;

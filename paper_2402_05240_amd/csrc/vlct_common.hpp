@@ -31,6 +31,36 @@ __device__ __forceinline__ idx_t xcd_block(idx_t n)
     return (b % kXcd) * xcd_per(n) + b / kXcd;
 }
 
+// Addressing.  A block touches a small box of each array, so its kernels form
+// the box's origin once as a block-uniform 64-bit base (scalar registers) and
+// address elements by 32-bit byte offsets from it: the load and store
+// instructions take a scalar base plus a 32-bit vector offset, so an element
+// costs one 32-bit add at most instead of a 64-bit index product and sum.
+// Offsets stay below 4 GiB: the largest box is a z march of 22 padded planes
+// of at most 4102^2 doubles, 3.0 GB.
+// Accesses go through the global address space explicitly: pointers that a
+// batched kernel reads from its instance table would otherwise be generic and
+// take flat instructions, which have no scalar base.
+using u32 = uint32_t;
+#define VLCT_GLOBAL __attribute__((address_space(1)))
+__device__ __forceinline__ double ld8(const double *base, u32 byte)
+{
+    const auto *p = (const VLCT_GLOBAL char *)(base) + byte;
+    return *(const VLCT_GLOBAL double *)p;
+}
+__device__ __forceinline__ void st8(double *base, u32 byte, double v)
+{
+    auto *p = (VLCT_GLOBAL char *)(base) + byte;
+    *(VLCT_GLOBAL double *)p = v;
+}
+__device__ __forceinline__ void st1(int8_t *base, u32 byte, int8_t v)
+{
+    *((VLCT_GLOBAL int8_t *)(base) + byte) = v;
+}
+// e / n for the position e of a thread past its block's first row of length n:
+// rows longer than a block take no division
+__device__ __forceinline__ u32 row_div(u32 e, u32 n) { return e < n ? 0u : (e - n < n ? 1u : e / n); }
+
 // ---------------------------------------------------------------------------
 // geometry shared by every kernel
 // ---------------------------------------------------------------------------
