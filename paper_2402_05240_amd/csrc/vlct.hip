@@ -83,11 +83,10 @@ __host__ __device__ __forceinline__ idx_t nblk_dt(const Geom &g)
 // Step 1); the boundary conditions are applied here by index mapping
 // ---------------------------------------------------------------------------
 // primitives of one cell from its conserved variables u and cell-centred
-// field, floored (the conserved state is never changed), stored at padded
-// index o; returns the floor status bits
-__device__ __forceinline__ uint32_t prims_store(const Geom &g, const Prims &P, idx_t o,
-                                                const double u[5], double bcx, double bcy,
-                                                double bcz)
+// field, floored (the conserved state is never changed); returns the floor
+// status bits
+__device__ __forceinline__ uint32_t prims_of(const Geom &g, const double u[5], double bcx,
+                                             double bcy, double bcz, double w[8])
 {
     double d = u[0];
     uint32_t st = 0;
@@ -98,14 +97,14 @@ __device__ __forceinline__ uint32_t prims_store(const Geom &g, const Prims &P, i
     const double me = 0.5 * (bcx * bcx + bcy * bcy + bcz * bcz);
     double pr = (g.gamma - 1.0) * (u[4] - ke - me);
     if (!(pr >= kFloorP)) { pr = kFloorP; st |= kStatusPressureFloor; }
-    P.w[0][o] = d;
-    P.w[1][o] = vx;
-    P.w[2][o] = vy;
-    P.w[3][o] = vz;
-    P.w[4][o] = pr;
-    P.w[5][o] = bcx;
-    P.w[6][o] = bcy;
-    P.w[7][o] = bcz;
+    w[0] = d;
+    w[1] = vx;
+    w[2] = vy;
+    w[3] = vz;
+    w[4] = pr;
+    w[5] = bcx;
+    w[6] = bcy;
+    w[7] = bcz;
     return st;
 }
 
@@ -125,8 +124,12 @@ __device__ __forceinline__ uint32_t prims_cell(const Geom &g, const StateP &s, c
     const double bz0 = s.b[2][face_store(g, 2, mi, mj, map_face(k, g.n[2], g.bc[2]))];
     const double bz1 = s.b[2][face_store(g, 2, mi, mj, map_face(k + 1, g.n[2], g.bc[2]))];
     const double u[5] = {s.u[0][c], s.u[1][c], s.u[2][c], s.u[3][c], s.u[4][c]};
-    return prims_store(g, P, pidx(g, i, j, k), u, 0.5 * (bx0 + bx1), 0.5 * (by0 + by1),
-                       0.5 * (bz0 + bz1));
+    double w[8];
+    const uint32_t st = prims_of(g, u, 0.5 * (bx0 + bx1), 0.5 * (by0 + by1), 0.5 * (bz0 + bz1), w);
+    const idx_t o = pidx(g, i, j, k);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) P.w[q][o] = w[q];
+    return st;
 }
 
 __device__ __forceinline__ void prims_body(const Geom &g, const StateP &s, const Prims &P,
@@ -702,11 +705,11 @@ __device__ __forceinline__ void ct_body(const Geom &g, const Prims &P, const Flu
                                        - cy * (sez[ty + 1][tx + 1] - sez[ty][tx + 1])
                                        + cz * (sey[hi][ty][tx + 1] - sey[lo][ty][tx + 1]);
                     const double by0 = base.b[1][face_store(g, 1, i, j, k)]
-                                       - cz * (sex[hi][ty][tx] - sex[lo][ty][tx])
-                                       + cx * (sez[ty][tx + 1] - sez[ty][tx]);
+                                       + cx * (sez[ty][tx + 1] - sez[ty][tx])
+                                       - cz * (sex[hi][ty][tx] - sex[lo][ty][tx]);
                     const double by1 = base.b[1][face_store(g, 1, i, map_face(j + 1, ny, g.bc[1]), k)]
-                                       - cz * (sex[hi][ty + 1][tx] - sex[lo][ty + 1][tx])
-                                       + cx * (sez[ty + 1][tx + 1] - sez[ty + 1][tx]);
+                                       + cx * (sez[ty + 1][tx + 1] - sez[ty + 1][tx])
+                                       - cz * (sex[hi][ty + 1][tx] - sex[lo][ty + 1][tx]);
                     const double bz0 = bzc
                                        - cx * (sey[lo][ty][tx + 1] - sey[lo][ty][tx])
                                        + cy * (sex[lo][ty + 1][tx] - sex[lo][ty][tx]);
@@ -728,8 +731,8 @@ __device__ __forceinline__ void ct_body(const Geom &g, const Prims &P, const Flu
             }
             if (i < nx) {  // face y (i, j-1/2, k)
                 const double b0 = base.b[1][face_store(g, 1, i, j, k)];
-                const double v = b0 - cz * (sex[hi][ty][tx] - sex[lo][ty][tx])
-                                 + cx * (sez[ty][tx + 1] - sez[ty][tx]);
+                const double v = b0 + cx * (sez[ty][tx + 1] - sez[ty][tx])
+                                 - cz * (sex[hi][ty][tx] - sex[lo][ty][tx]);
                 out.b[1][face_store(g, 1, i, j, k)] = v;
                 if (g.bc[1] == VLCT_BC_PERIODIC && j == 0) out.b[1][face_store(g, 1, i, ny, k)] = v;
                 if (FULL) bad |= !isfinite(v);
@@ -776,73 +779,66 @@ __device__ __forceinline__ void ct_body(const Geom &g, const Prims &P, const Flu
 // of the grid, in z slabs, are dealt out to the blocks in equal shares
 // (Geom::pred_slab, Geom::pred_chunk: one (slab, tile) per block, or a single
 // slab shared out evenly over one wave of resident blocks); a block marches
-// along z through each run [k0, k1) of planes of a TX x TY column tile that
-// its share holds.  Per new plane m it
-//   (A) derives the primitives of the tile plus a one-cell ring (Sec. 2.1,
-//       B_cc = face average, floors) and the reference field -(v x B),
-//   (B) solves PCM HLLD on the x- and y-faces of plane m and the z-face
-//       m - 1/2 (Steps 2-3; every thread owns one column and the faces on its
-//       low sides), keeping the hydro fluxes in registers and the face EMFs
-//       and upwind indicators in LDS,
-//   (C) forms the edge fields E_z of plane m and E_x, E_y of the half plane
-//       m - 1/2 (Step 4, Eqs. emf-edge, emf-upwind-slope, emf-slope),
-//   (D) updates the cells and the owned faces of plane m - 1 to t + dt/2
-//       (Step 5).
-// Nothing but U^n is read and nothing but U^{n+1/2} is written: primitives,
-// fluxes and edge fields stay on chip.  For each run the block also
-// evaluates the faces of the planes k0 - 1 and k1 (the edges of its first and
-// last half planes need them).  Arithmetic per quantity is that of k_prims,
-// k_flux and k_ct_update, whatever the runs.
+// along z through each run [k0, k1) of planes of a column tile that its share
+// holds.  A thread owns one column of the tile or of its one-cell ring, and
+// per new plane m
+//   (A) derives the primitives (Sec. 2.1, B_cc = face average, floors) and
+//       the reference field -(v x B) of its cell into LDS;
+//   (B) solves PCM HLLD on its cell's low x- and y-faces and on the z-face
+//       m - 1/2 (Steps 2-3); hydro fluxes and what the neighbours need of the
+//       face EMFs and upwind indicators go to LDS;
+//   (C) forms the three edge fields at its cell's low edges: E_z of plane m,
+//       E_x and E_y of the half plane m - 1/2 (Step 4, Eqs. emf-edge,
+//       emf-upwind-slope, emf-slope), and takes the x and y flux differences
+//       off its cell of plane m;
+//   (D) finishes the cell and the faces of plane m - 1 (Step 5), derives the
+//       half-step primitives of that cell for the corrector, and starts the
+//       faces of plane m.
+// What a thread alone uses of a plane stays in its registers until the next
+// (its own EMFs, references, partial updates), so U^n is read once, each
+// plane's three barriers separate LDS writes from reads and none closes the
+// plane, and the next plane's U^n is loaded before (C), its latency behind the
+// edge and update work.  For each run the block also evaluates the faces of
+// the planes k0 - 1 and k1 (the edges of its first and last half planes need
+// them).  Arithmetic per quantity is that of k_prims, k_flux and k_ct_update,
+// whatever the runs.
+//
+// One block per CU (133 KB of LDS, 256 registers: two waves per SIMD), bound
+// by FP64 issue and by the latency of three dependent Riemann solves between
+// barriers.  Against the form that kept every EMF and reference of two planes
+// in LDS, dealt the edges out by division and loaded U^n twice per plane
+// (2321 vector instructions, 116 LDS accesses; now 1801 and 81): 256^3 2.04 ->
+// 1.54 ms, 128^3 0.284 -> 0.225 ms, 32^3 52 -> 45 us.
 // ---------------------------------------------------------------------------
-template <int TX, int TY>
-struct PredShape {
-    static constexpr int CX = TX + 2, CY = TY + 2, NC = CX * CY;  // columns with the ring
-    static constexpr int NT = (NC + 63) / 64 * 64;                  // threads (whole waves)
-    static constexpr int NEZ = (TY + 1) * (TX + 1), NEX = (TY + 1) * TX, NEY = TY * (TX + 1);
-};
+constexpr int kPredThreads = 512;
+
+// some value, without an instruction to set it: for registers that lanes
+// without a part in a step leave unused
+__device__ __forceinline__ double any_value() { return __builtin_nondeterministic_value(0.0); }
 
 // side0..2 (optional): the upwind side of every interior face, tape layout;
-// P (optional, P.w[0] == NULL skips it): the half-step primitives of the
-// interior cells are written there as k_prims would derive them from
-// U^{n+1/2}; its ghost layers are left to k_prims_ghost.  Both are run-time
-// choices of one kernel, so a taped step runs the very code of a plain one.
+// a run-time choice of one kernel, so a taped step runs the very code of a
+// plain one.  P: the half-step primitives of the interior cells are written
+// there as k_prims would derive them from U^{n+1/2}; its ghost layers are left
+// to k_prims_ghost.
 // ONE_RUN: block b is the single run of tile b mod ntiles in z slab
 // b / ntiles (Geom::pred_chunk == 0); else its share of Geom::pred_chunk
 // pairs in slab order (a zero chunk taken as one slab's worth).
 template <int TX, int TY, bool ONE_RUN>
 __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const StateW &out,
                                           const Prims &P, const double *dt_dev, uint32_t *status,
-                                          idx_t b, uint8_t *side0, uint8_t *side1, uint8_t *side2)
+                                          u32 b, uint8_t *side0, uint8_t *side1, uint8_t *side2)
 {
-    using S = PredShape<TX, TY>;
-    constexpr int CX = S::CX, CY = S::CY, NC = S::NC;
-    constexpr int NEZ = S::NEZ, NEX = S::NEX, NEY = S::NEY;
-    // W of the newest plane (8 primitives) and the hydro fluxes of the plane
-    // being updated (x: 0-4, y: 5-9).  ONE_RUN keeps them apart (155 KB of
-    // LDS in all), so that the next plane's primitives can be written while
-    // the update still reads the fluxes and the barrier closing each plane
-    // goes; the share form (a run loop, more registers) keeps both in s_wh
-    // and the barrier, which measured faster there.
-    __shared__ double s_pr[ONE_RUN ? 8 : 1][ONE_RUN ? NC : 1];
-    __shared__ double s_wh[10][NC];
-    auto PR = [&](int q, int c) -> double & {
-        if constexpr (ONE_RUN) return s_pr[q][c];
-        else return s_wh[q][c];
-    };
-    // reference fields: x and y components of the two newest planes (slot =
-    // plane & 1), z component of the newest plane
-    __shared__ double s_rx[2][NC], s_ry[2][NC], s_rz[NC];
-    // face EMFs of the x- and y-faces of the two newest planes: x-face -F[B_y]
-    // (E_z) and F[B_z] (E_y), y-face -F[B_z] (E_x) and F[B_x] (E_z)
-    __shared__ double s_em[2][4][NC];
-    __shared__ int8_t s_sg[2][2][NC];
-    // z-face m - 1/2: -F[B_x] (E_y), F[B_y] (E_x) and its upwind indicator
-    __shared__ double s_zem[2][NC];
-    __shared__ int8_t s_zsg[NC];
-    // edge fields: E_z of the planes, E_x / E_y of the half planes (slot = index & 1)
-    __shared__ double s_ez[2][TY + 1][TX + 1];
-    __shared__ double s_ex[2][TY + 1][TX];
-    __shared__ double s_ey[2][TY][TX + 1];
+    constexpr int CX = TX + 2, CY = TY + 2, NC = CX * CY;  // columns with the ring
+    static_assert(NC <= kPredThreads, "one thread per column");
+    constexpr int N = kPredThreads;
+    __shared__ double s_pr[8][N];             // primitives of plane m
+    __shared__ double s_rx[2][N], s_ry[2][N], s_rz[N];  // -(v x B): x, y of planes m - 1, m (slot m & 1), z
+    __shared__ double s_fx[5][N], s_fy[5][N]; // hydro fluxes of the low x-, y-faces
+    __shared__ double s_xz[N], s_yz[N];       // E_z EMFs of the x-faces (-F[B_y]), y-faces (F[B_x])
+    __shared__ double s_zy[N], s_zx[N];       // E_y (-F[B_x]), E_x (F[B_y]) EMFs of the z-faces
+    __shared__ int8_t s_sx[N], s_sy[N], s_sz[N];        // upwind indicators
+    __shared__ double s_ez[N], s_ex[2][N], s_ey[2][N];  // edge fields (half planes: slot m & 1)
 
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
     const int ex = nx + (g.bc[0] == VLCT_BC_OUTFLOW), ey = ny + (g.bc[1] == VLCT_BC_OUTFLOW);
@@ -853,293 +849,245 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
     const int ntx = (ex + TX - 1) / TX, nty = (ey + TY - 1) / TY, ntiles = ntx * nty;
     const int npos = ntiles * nz;  // below 2^31 for sides up to kMaxN
     const int H = g.pred_slab, nfull = nz / H, rem = nz - nfull * H;
-    if (ONE_RUN && b >= (idx_t)ntiles * (nfull + (rem > 0))) return;
+    if (ONE_RUN && b >= (u32)(ntiles * (nfull + (rem > 0)))) return;
     const int chunk = g.pred_chunk > 0 ? g.pred_chunk : H;
-    if (!ONE_RUN && b * (idx_t)chunk >= npos) return;
+    if (!ONE_RUN && (idx_t)b * chunk >= npos) return;
     const double dt = 0.5 * dt_dev[0];
     const double cx = dt / g.dl[0], cy = dt / g.dl[1], cz = dt / g.dl[2];
 
     // this thread's column: (a, c) in the tile with its ring
     const int t = threadIdx.x;
-    const bool col = t < NC;
     const int a = t % CX, c = t / CX;
-    const int tx = a - 1, ty = c - 1;
     uint32_t st = 0;
     auto run = [&](const int tile, const int k0, const int k1) {
         const int i0 = (tile % ntx) * TX, j0 = (tile / ntx) * TY;
         // cell (ii, jj) of the column
         const int ii = i0 - 1 + a, jj = j0 - 1 + c;
-        const bool live = col && ii <= nx && jj <= ny;
-        const bool do_x = live && a >= 1, do_y = live && c >= 1;
-        const bool do_z = live && !((a == 0 || a == CX - 1) && (c == 0 || c == CY - 1));
+        const bool live = t < NC && ii <= nx && jj <= ny;
+        // columns to the left and below (the ring's first ones take themselves:
+        // what they solve there is not used)
+        const int lx = a >= 1 ? t - 1 : t, ly = c >= 1 ? t - CX : t;
+        const bool edge = live && a >= 1 && c >= 1;
         // owned positions: cells / faces of the tile proper
-        const bool own = live && a >= 1 && a <= TX && c >= 1 && c <= TY && ii < ex && jj < ey;
+        const bool own = edge && a <= TX && c <= TY && ii < ex && jj < ey;
         const bool interior = own && ii < nx && jj < ny;
+        // byte offsets of the column in a plane of each array
         const int mi = map_cell(ii, nx, g.bc[0]), mj = map_cell(jj, ny, g.bc[1]);
         const int fi0 = map_face(ii, nx, g.bc[0]), fi1 = map_face(ii + 1, nx, g.bc[0]);
         const int fj0 = map_face(jj, ny, g.bc[1]), fj1 = map_face(jj + 1, ny, g.bc[1]);
+        const u32 oc = 8u * (u32)(mj * nx + mi);
+        const u32 ox0 = 8u * (u32)(mj * (nx + 1) + fi0), ox1 = 8u * (u32)(mj * (nx + 1) + fi1);
+        const u32 oy0 = 8u * (u32)(fj0 * nx + mi), oy1 = 8u * (u32)(fj1 * nx + mi);
+        const u32 op = 8u * (u32)((jj + kGhost) * g.p[0] + ii + kGhost);
+        const idx_t sc = (idx_t)nx * ny, sbx = (idx_t)(nx + 1) * ny, sby = (idx_t)nx * (ny + 1);
+        const idx_t sp = (idx_t)g.p[0] * g.p[1];
+        // the primitives' and the output cells' arrays are equally spaced in
+        // their workspace: two pointers each in scalar registers
+        const idx_t pstep = P.w[1] - P.w[0], ostep = out.u[1] - out.u[0];
 
-        W7 wz_prev{};                   // own cell of the previous plane, z sweep frame
-        double hx[5] = {}, hy[5] = {};  // own x-, y-face hydro fluxes of the previous plane
-        double hz_lo[5] = {};           // own z-face hydro flux below the previous plane
-
-        // U^n of this thread's cell in a plane: 5 conserved values and the six faces
+        // U^n of this thread's cell in a plane: 5 conserved values, the six faces
         double pf[11];
         auto load_plane = [&](int m) {
-            const int mk = map_cell(m, nz, g.bc[2]);
-            const idx_t cc = cell_store(g, mi, mj, mk);
+            const idx_t mk = map_cell(m, nz, g.bc[2]);
 #pragma unroll
-            for (int q = 0; q < 5; ++q) pf[q] = s.u[q][cc];
-            pf[5] = s.b[0][face_store(g, 0, fi0, mj, mk)];
-            pf[6] = s.b[0][face_store(g, 0, fi1, mj, mk)];
-            pf[7] = s.b[1][face_store(g, 1, mi, fj0, mk)];
-            pf[8] = s.b[1][face_store(g, 1, mi, fj1, mk)];
-            pf[9] = s.b[2][face_store(g, 2, mi, mj, map_face(m, nz, g.bc[2]))];
-            pf[10] = s.b[2][face_store(g, 2, mi, mj, map_face(m + 1, nz, g.bc[2]))];
+            for (int q = 0; q < 5; ++q) pf[q] = ld8(s.u[q] + mk * sc, oc);
+            pf[5] = ld8(s.b[0] + mk * sbx, ox0);
+            pf[6] = ld8(s.b[0] + mk * sbx, ox1);
+            pf[7] = ld8(s.b[1] + mk * sby, oy0);
+            pf[8] = ld8(s.b[1] + mk * sby, oy1);
+            pf[9] = ld8(s.b[2] + map_face(m, nz, g.bc[2]) * sc, oc);
+            pf[10] = ld8(s.b[2] + map_face(m + 1, nz, g.bc[2]) * sc, oc);
         };
 
+        // of plane m - 1: the cell's update short of the z fluxes, the hydro flux
+        // of its low z-face, its faces short of the E_x and E_y terms (low and
+        // high x, y) and its finished low z-face
+        double up[5], hz_lo[5], bxp = any_value(), bxhp = any_value(), byp = any_value();
+        double byhp = any_value(), bzp = any_value();
+#pragma unroll
+        for (int q = 0; q < 5; ++q) up[q] = hz_lo[q] = any_value();
+        // own EMFs and indicators of plane m - 1 for the half-plane edges
+        double xy_p = any_value(), yx_p = any_value();
+        int sx_p = 0, sy_p = 0;
+        if (live) load_plane(k0 - 1);
         for (int m = k0 - 1; m <= k1; ++m) {
-            const int sm = m & 1, sp = sm ^ 1;
-            // (A) primitives and reference field of plane m; the cell's low faces
-            // are also the normal fields of the faces this thread solves in (B)
-            double bx0 = 0.0, by0 = 0.0, bz0 = 0.0;
+            const int hi = m & 1, lo = hi ^ 1;  // slots of the half planes m -+ 1/2
+            // (A)
+            double u0[5], bx0 = any_value(), bx1 = any_value(), by0 = any_value(), by1 = any_value();
+            double bz0 = any_value();
+#pragma unroll
+            for (int q = 0; q < 5; ++q) u0[q] = any_value();
+            W7 wz_prev{any_value(), any_value(), any_value(), any_value(),
+                       any_value(), any_value(), any_value()};  // own cell of plane m - 1, z sweep frame
             if (live) {
-                load_plane(m);
+                wz_prev = W7{s_pr[0][t], s_pr[3][t], s_pr[1][t], s_pr[2][t],
+                             s_pr[4][t], s_pr[5][t], s_pr[6][t]};
+#pragma unroll
+                for (int q = 0; q < 5; ++q) u0[q] = pf[q];
                 bx0 = pf[5];
-                const double bx1 = pf[6];
+                bx1 = pf[6];
                 by0 = pf[7];
-                const double by1 = pf[8];
+                by1 = pf[8];
                 bz0 = pf[9];
-                const double bz1 = pf[10];
-                const double bcx = 0.5 * (bx0 + bx1);
-                const double bcy = 0.5 * (by0 + by1);
-                const double bcz = 0.5 * (bz0 + bz1);
-                double d = pf[0];
-                if (!(d >= kFloorRho)) { d = kFloorRho; st |= kStatusDensityFloor; }
-                const double id = mrcp(d);
-                const double vx = pf[1] * id, vy = pf[2] * id, vz = pf[3] * id;
-                const double ke = 0.5 * d * (vx * vx + vy * vy + vz * vz);
-                const double me = 0.5 * (bcx * bcx + bcy * bcy + bcz * bcz);
-                double pr = (g.gamma - 1.0) * (pf[4] - ke - me);
-                if (!(pr >= kFloorP)) { pr = kFloorP; st |= kStatusPressureFloor; }
-                PR(0, t) = d;
-                PR(1, t) = vx;
-                PR(2, t) = vy;
-                PR(3, t) = vz;
-                PR(4, t) = pr;
-                PR(5, t) = bcx;
-                PR(6, t) = bcy;
-                PR(7, t) = bcz;
-                s_rx[sm][t] = -(vy * bcz - vz * bcy);
-                s_ry[sm][t] = -(vz * bcx - vx * bcz);
-                s_rz[t] = -(vx * bcy - vy * bcx);
+                double w[8];
+                st |= prims_of(g, u0, 0.5 * (bx0 + bx1), 0.5 * (by0 + by1), 0.5 * (bz0 + pf[10]), w);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) s_pr[q][t] = w[q];
+                s_rx[hi][t] = -(w[2] * w[7] - w[3] * w[6]);
+                s_ry[hi][t] = -(w[3] * w[5] - w[1] * w[7]);
+                s_rz[t] = -(w[1] * w[6] - w[2] * w[5]);
             }
             __syncthreads();
-            // (B) PCM HLLD on the x-, y-faces of plane m and the z-face m - 1/2
-            double hxn[5] = {}, hyn[5] = {}, hzn[5] = {};
-            W7 wz{};
+            // (B)
+            double hzn[5], xz = any_value(), xy = any_value(), yx = any_value(), yz = any_value();
+            double zx = any_value(), zy = any_value();
+#pragma unroll
+            for (int q = 0; q < 5; ++q) hzn[q] = any_value();
+            int8_t sx = 0, sy = 0, sz = 0;
             if (live) {
-                const W7 wxr{PR(0, t), PR(1, t), PR(2, t), PR(3, t), PR(4, t), PR(6, t), PR(7, t)};
-                wz = W7{PR(0, t), PR(3, t), PR(1, t), PR(2, t), PR(4, t), PR(5, t), PR(6, t)};
                 double f[7];
-                int8_t upw;
-                if (do_x) {
-                    const int l = t - 1;
-                    const W7 wl{PR(0, l), PR(1, l), PR(2, l), PR(3, l), PR(4, l), PR(6, l), PR(7, l)};
-                    hlld(wl, wxr, bx0, g.gamma, g.gm1i, f, upw);
-#pragma unroll
-                    for (int q = 0; q < 5; ++q) hxn[q] = f[q];
-                    s_em[sm][0][t] = -f[5];
-                    s_em[sm][1][t] = f[6];
-                    s_sg[sm][0][t] = upw;
-                }
-                if (do_y) {
-                    const int l = t - CX;
-                    const W7 wl{PR(0, l), PR(2, l), PR(3, l), PR(1, l), PR(4, l), PR(7, l), PR(5, l)};
-                    const W7 wr{PR(0, t), PR(2, t), PR(3, t), PR(1, t), PR(4, t), PR(7, t), PR(5, t)};
-                    hlld(wl, wr, by0, g.gamma, g.gm1i, f, upw);
-#pragma unroll
-                    for (int q = 0; q < 5; ++q) hyn[q] = f[q];
-                    s_em[sm][2][t] = -f[5];
-                    s_em[sm][3][t] = f[6];
-                    s_sg[sm][1][t] = upw;
-                }
-                if (do_z && m >= k0) {
-                    hlld(wz_prev, wz, bz0, g.gamma, g.gm1i, f, upw);
+                if (m >= k0) {
+                    const W7 wr{s_pr[0][t], s_pr[3][t], s_pr[1][t], s_pr[2][t],
+                                s_pr[4][t], s_pr[5][t], s_pr[6][t]};
+                    hlld(wz_prev, wr, bz0, g.gamma, g.gm1i, f, sz);
 #pragma unroll
                     for (int q = 0; q < 5; ++q) hzn[q] = f[q];
-                    s_zem[0][t] = -f[5];
-                    s_zem[1][t] = f[6];
-                    s_zsg[t] = upw;
+                    zy = -f[5];
+                    zx = f[6];
+                    s_zy[t] = zy;
+                    s_zx[t] = zx;
+                    s_sz[t] = sz;
+                }
+                {
+                    const W7 wl{s_pr[0][lx], s_pr[1][lx], s_pr[2][lx], s_pr[3][lx],
+                                s_pr[4][lx], s_pr[6][lx], s_pr[7][lx]};
+                    const W7 wr{s_pr[0][t], s_pr[1][t], s_pr[2][t], s_pr[3][t],
+                                s_pr[4][t], s_pr[6][t], s_pr[7][t]};
+                    hlld(wl, wr, bx0, g.gamma, g.gm1i, f, sx);
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) s_fx[q][t] = f[q];
+                    xz = -f[5];
+                    xy = f[6];
+                    s_xz[t] = xz;
+                    s_sx[t] = sx;
+                }
+                {
+                    const W7 wl{s_pr[0][ly], s_pr[2][ly], s_pr[3][ly], s_pr[1][ly],
+                                s_pr[4][ly], s_pr[7][ly], s_pr[5][ly]};
+                    const W7 wr{s_pr[0][t], s_pr[2][t], s_pr[3][t], s_pr[1][t],
+                                s_pr[4][t], s_pr[7][t], s_pr[5][t]};
+                    hlld(wl, wr, by0, g.gamma, g.gm1i, f, sy);
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) s_fy[q][t] = f[q];
+                    yx = -f[5];
+                    yz = f[6];
+                    s_yz[t] = yz;
+                    s_sy[t] = sy;
                 }
             }
             __syncthreads();
-            // (C) E_z of plane m, E_x / E_y of the half plane m - 1/2; the hydro
-            // fluxes of plane m - 1 go to LDS for the neighbours' updates.  The
-            // U^n values the update of plane m - 1 in (D) starts from are loaded
-            // first, so that their latency hides behind the edge computations.
-            const bool upd = m - 1 >= k0 && m - 1 < k1;
-            double u0[5] = {}, bxb = 0.0, byb = 0.0, bzb = 0.0, bxh = 0.0, byh = 0.0, bzh = 0.0;
-            if (upd && own) {
-                const int k = m - 1;
-                if (interior) {
-                    const idx_t cc = cell_store(g, ii, jj, k);
+            // (C)
+            if (live && m < k1) load_plane(m + 1);
+            double upn[5];
 #pragma unroll
-                    for (int q = 0; q < 5; ++q) u0[q] = s.u[q][cc];
-                    bzb = s.b[2][face_store(g, 2, ii, jj, k)];
-                    if (P.w[0]) {
-                        bxh = s.b[0][face_store(g, 0, map_face(ii + 1, nx, g.bc[0]), jj, k)];
-                        byh = s.b[1][face_store(g, 1, ii, map_face(jj + 1, ny, g.bc[1]), k)];
-                        bzh = s.b[2][face_store(g, 2, ii, jj, map_face(k + 1, nz, g.bc[2]))];
-                    }
-                }
-                if (jj < ny) bxb = s.b[0][face_store(g, 0, ii, jj, k)];
-                if (ii < nx) byb = s.b[1][face_store(g, 1, ii, jj, k)];
+            for (int q = 0; q < 5; ++q) upn[q] = any_value();
+            if (edge) {
+                // E_z at (ii - 1/2, jj - 1/2, m): x-faces here and at jj - 1, y-faces here and at ii - 1
+                s_ez[t] = edge_combine(xz, s_xz[ly], yz, s_yz[lx], sx, s_sx[ly], sy, s_sy[lx], s_rz[t],
+                                       s_rz[lx], s_rz[ly], s_rz[ly - 1]);
+                // E_x at (ii, jj - 1/2, m - 1/2): y-faces of planes m, m - 1, z-faces here and at jj - 1
+                s_ex[hi][t] = edge_combine(yx, yx_p, zx, s_zx[ly], sy, sy_p, sz, s_sz[ly], s_rx[hi][t],
+                                           s_rx[hi][ly], s_rx[lo][t], s_rx[lo][ly]);
+                // E_y at (ii - 1/2, jj, m - 1/2): z-faces here and at ii - 1, x-faces of planes m, m - 1
+                s_ey[hi][t] = edge_combine(zy, s_zy[lx], xy, xy_p, sz, s_sz[lx], sx, sx_p, s_ry[hi][t],
+                                           s_ry[lo][t], s_ry[hi][lx], s_ry[lo][lx]);
             }
-            if (m >= k0) {
-                const int nez = m < k1 ? NEZ : 0;
-                for (int q = threadIdx.x; q < nez + NEX + NEY; q += S::NT) {
-                    if (q < nez) {
-                        const int ea = q % (TX + 1), ec = q / (TX + 1), ie = i0 + ea, je = j0 + ec;
-                        // E_z at (ie - 1/2, je - 1/2, m): B = x-faces, C = y-faces
-                        if (ie <= nx && je <= ny) {
-                            const int o = (ec + 1) * CX + ea + 1;  // column (ie, je)
-                            s_ez[sm][ec][ea] = edge_combine(
-                                s_em[sm][0][o], s_em[sm][0][o - CX], s_em[sm][3][o], s_em[sm][3][o - 1],
-                                s_sg[sm][0][o], s_sg[sm][0][o - CX], s_sg[sm][1][o], s_sg[sm][1][o - 1],
-                                s_rz[o], s_rz[o - 1], s_rz[o - CX], s_rz[o - CX - 1]);
-                        }
-                    } else if (q < nez + NEX) {
-                        const int r = q - nez;
-                        const int ea = r % TX, ec = r / TX, ie = i0 + ea, je = j0 + ec;
-                        // E_x at (ie, je - 1/2, m - 1/2): B = y-faces (planes m, m - 1), C = z-faces
-                        if (ie < nx && je <= ny) {
-                            const int o = (ec + 1) * CX + ea + 1;
-                            s_ex[sm][ec][ea] = edge_combine(
-                                s_em[sm][2][o], s_em[sp][2][o], s_zem[1][o], s_zem[1][o - CX],
-                                s_sg[sm][1][o], s_sg[sp][1][o], s_zsg[o], s_zsg[o - CX],
-                                s_rx[sm][o], s_rx[sm][o - CX], s_rx[sp][o], s_rx[sp][o - CX]);
-                        }
-                    } else {
-                        const int r = q - nez - NEX;
-                        const int ea = r % (TX + 1), ec = r / (TX + 1), ie = i0 + ea, je = j0 + ec;
-                        // E_y at (ie - 1/2, je, m - 1/2): B = z-faces, C = x-faces (planes m, m - 1)
-                        if (ie <= nx && je < ny) {
-                            const int o = (ec + 1) * CX + ea + 1;
-                            s_ey[sm][ec][ea] = edge_combine(
-                                s_zem[0][o], s_zem[0][o - 1], s_em[sm][1][o], s_em[sp][1][o],
-                                s_zsg[o], s_zsg[o - 1], s_sg[sm][0][o], s_sg[sp][0][o],
-                                s_ry[sm][o], s_ry[sp][o], s_ry[sm][o - 1], s_ry[sp][o - 1]);
-                        }
-                    }
+            xy_p = xy;
+            yx_p = yx;
+            sx_p = sx;
+            sy_p = sy;
+            if (interior) {
+                auto dx = [&](int q) { return s_fx[q][t + 1] - s_fx[q][t]; };
+                auto dy = [&](int q) { return s_fy[q][t + CX] - s_fy[q][t]; };
+                upn[0] = u0[0] - cx * dx(0) - cy * dy(0);
+                upn[1] = u0[1] - cx * dx(1) - cy * dy(3);
+                upn[2] = u0[2] - cx * dx(2) - cy * dy(1);
+                upn[3] = u0[3] - cx * dx(3) - cy * dy(2);
+                upn[4] = u0[4] - cx * dx(4) - cy * dy(4);
+                // the tape: upwind sides of the cell's low faces
+                if (side0 && m >= k0 && m < k1) {
+                    const idx_t cc = (idx_t)m * sc + (oc >> 3);
+                    side0[cc] = side_code(sx);
+                    side1[cc] = side_code(sy);
+                    side2[cc] = side_code(sz);
                 }
-            }
-            if (upd && live) {
-#pragma unroll
-                for (int q = 0; q < 5; ++q) {
-                    s_wh[q][t] = hx[q];
-                    s_wh[5 + q][t] = hy[q];
-                }
-            }
-            // the tape: upwind sides of the interior cell's low faces in plane m
-            if (side0 && interior && m >= k0 && m < k1) {
-                const idx_t cc = cell_store(g, ii, jj, m);
-                side0[cc] = side_code(s_sg[sm][0][t]);
-                side1[cc] = side_code(s_sg[sm][1][t]);
-                side2[cc] = side_code(s_zsg[t]);
             }
             __syncthreads();
-            // (D) half-step update of plane k = m - 1 (Step 5); an interior cell
-            // also derives its half-step primitives (for the corrector), with its
-            // high faces recomputed from the same edge fields and in the same
-            // arithmetic as the threads or blocks that own them
-            if (upd && own) {
-                const int k = m - 1;
-                const int lo = sp, hi = sm;  // half planes k - 1/2 and k + 1/2
-                const int ke = k & 1;        // E_z slot of plane k
-                double u[5] = {}, bxl = 0.0, byl = 0.0, bzl = 0.0;
-                if (interior) {
-                    const idx_t cc = cell_store(g, ii, jj, k);
-                    const double dxr = s_wh[0][t + 1] - hx[0];
-                    const double dyr = s_wh[5][t + CX] - hy[0];
-                    const double dzr = hzn[0] - hz_lo[0];
-                    const double dxe = s_wh[4][t + 1] - hx[4];
-                    const double dye = s_wh[9][t + CX] - hy[4];
-                    const double dze = hzn[4] - hz_lo[4];
-                    const double dxmx = s_wh[1][t + 1] - hx[1];
-                    const double dxmy = s_wh[2][t + 1] - hx[2];
-                    const double dxmz = s_wh[3][t + 1] - hx[3];
-                    const double dymy = s_wh[6][t + CX] - hy[1];
-                    const double dymz = s_wh[7][t + CX] - hy[2];
-                    const double dymx = s_wh[8][t + CX] - hy[3];
-                    const double dzmz = hzn[1] - hz_lo[1];
-                    const double dzmx = hzn[2] - hz_lo[2];
-                    const double dzmy = hzn[3] - hz_lo[3];
-                    u[0] = u0[0] - cx * dxr - cy * dyr - cz * dzr;
-                    u[1] = u0[1] - cx * dxmx - cy * dymx - cz * dzmx;
-                    u[2] = u0[2] - cx * dxmy - cy * dymy - cz * dzmy;
-                    u[3] = u0[3] - cx * dxmz - cy * dymz - cz * dzmz;
-                    u[4] = u0[4] - cx * dxe - cy * dye - cz * dze;
+            // (D)
+            double bzn = any_value();
+            if (own) {
+                const idx_t k = m - 1;
+                // the low z-face of plane m: the high one of the cell of plane m - 1
+                bzn = bz0 - cx * (s_ey[hi][t + 1] - s_ey[hi][t]) + cy * (s_ex[hi][t + CX] - s_ex[hi][t]);
+                if (interior && m >= k0 && (m < k1 || (m == nz && g.bc[2] == VLCT_BC_OUTFLOW))) {
+                    st8(out.b[2] + m * sc, oc, bzn);
+                    if (g.bc[2] == VLCT_BC_PERIODIC && m == 0) st8(out.b[2] + nz * sc, oc, bzn);
+                }
+                if (m > k0) {
+                    double bxl = any_value(), byl = any_value();
+                    if (jj < ny) {  // face x (ii - 1/2, jj, k)
+                        bxl = bxp + cz * (s_ey[hi][t] - s_ey[lo][t]);
+                        st8(out.b[0] + k * sbx, ox0, bxl);
+                        if (g.bc[0] == VLCT_BC_PERIODIC && ii == 0)
+                            st8(out.b[0] + k * sbx, ox0 + 8u * (u32)nx, bxl);
+                    }
+                    if (ii < nx) {  // face y (ii, jj - 1/2, k)
+                        byl = byp - cz * (s_ex[hi][t] - s_ex[lo][t]);
+                        st8(out.b[1] + k * sby, oy0, byl);
+                        if (g.bc[1] == VLCT_BC_PERIODIC && jj == 0)
+                            st8(out.b[1] + k * sby, oy0 + 8u * (u32)(nx * ny), byl);
+                    }
+                    if (interior) {
+                        double u[5];
+                        u[0] = up[0] - cz * (hzn[0] - hz_lo[0]);
+                        u[1] = up[1] - cz * (hzn[2] - hz_lo[2]);
+                        u[2] = up[2] - cz * (hzn[3] - hz_lo[3]);
+                        u[3] = up[3] - cz * (hzn[1] - hz_lo[1]);
+                        u[4] = up[4] - cz * (hzn[4] - hz_lo[4]);
 #pragma unroll
-                    for (int q = 0; q < 5; ++q) out.u[q][cc] = u[q];
+                        for (int q = 0; q < 5; ++q) st8(out.u[0] + (q * ostep + k * sc), oc, u[q]);
+                        // half-step primitives; the high faces in the arithmetic of the
+                        // threads or blocks that own them
+                        const double bxu = bxhp + cz * (s_ey[hi][t + 1] - s_ey[lo][t + 1]);
+                        const double byu = byhp - cz * (s_ex[hi][t + CX] - s_ex[lo][t + CX]);
+                        double w[8];
+                        st |= prims_of(g, u, 0.5 * (bxl + bxu), 0.5 * (byl + byu),
+                                       0.5 * (bzp + bzn), w);
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) st8(P.w[0] + (q * pstep + (k + kGhost) * sp), op, w[q]);
+                    }
                 }
-                if (jj < ny) {  // face x (ii - 1/2, jj, k)
-                    const double v = bxb - cy * (s_ez[ke][ty + 1][tx] - s_ez[ke][ty][tx])
-                                     + cz * (s_ey[hi][ty][tx] - s_ey[lo][ty][tx]);
-                    out.b[0][face_store(g, 0, ii, jj, k)] = v;
-                    if (g.bc[0] == VLCT_BC_PERIODIC && ii == 0) out.b[0][face_store(g, 0, nx, jj, k)] = v;
-                    bxl = v;
-                }
-                if (ii < nx) {  // face y (ii, jj - 1/2, k)
-                    const double v = byb - cz * (s_ex[hi][ty][tx] - s_ex[lo][ty][tx])
-                                     + cx * (s_ez[ke][ty][tx + 1] - s_ez[ke][ty][tx]);
-                    out.b[1][face_store(g, 1, ii, jj, k)] = v;
-                    if (g.bc[1] == VLCT_BC_PERIODIC && jj == 0) out.b[1][face_store(g, 1, ii, ny, k)] = v;
-                    byl = v;
-                }
-                if (interior) {  // face z (ii, jj, k - 1/2)
-                    const double v = bzb - cx * (s_ey[lo][ty][tx + 1] - s_ey[lo][ty][tx])
-                                     + cy * (s_ex[lo][ty + 1][tx] - s_ex[lo][ty][tx]);
-                    out.b[2][face_store(g, 2, ii, jj, k)] = v;
-                    if (g.bc[2] == VLCT_BC_PERIODIC && k == 0) out.b[2][face_store(g, 2, ii, jj, nz)] = v;
-                    bzl = v;
-                }
-                if (interior && P.w[0]) {
-                    // high faces (a periodic one through the face map, as its owner computes it)
-                    const double bxu = bxh - cy * (s_ez[ke][ty + 1][tx + 1] - s_ez[ke][ty][tx + 1])
-                                       + cz * (s_ey[hi][ty][tx + 1] - s_ey[lo][ty][tx + 1]);
-                    const double byu = byh - cz * (s_ex[hi][ty + 1][tx] - s_ex[lo][ty + 1][tx])
-                                       + cx * (s_ez[ke][ty + 1][tx + 1] - s_ez[ke][ty + 1][tx]);
-                    const double bzu = bzh - cx * (s_ey[hi][ty][tx + 1] - s_ey[hi][ty][tx])
-                                       + cy * (s_ex[hi][ty + 1][tx] - s_ex[hi][ty][tx]);
-                    st |= prims_store(g, P, pidx(g, ii, jj, k), u, 0.5 * (bxl + bxu), 0.5 * (byl + byu),
-                                      0.5 * (bzl + bzu));
-                }
-            }
-            // the top z faces of an outflow axis, from the edges of the half plane nz - 1/2
-            if (m == k1 && k1 == nz && g.bc[2] == VLCT_BC_OUTFLOW && interior) {
-                const double b0 = s.b[2][face_store(g, 2, ii, jj, nz)];
-                const double v = b0 - cx * (s_ey[sm][ty][tx + 1] - s_ey[sm][ty][tx])
-                                 + cy * (s_ex[sm][ty + 1][tx] - s_ex[sm][ty][tx]);
-                out.b[2][face_store(g, 2, ii, jj, nz)] = v;
+                // start plane m
+                const double dz0 = s_ez[t + CX] - s_ez[t], dz1 = s_ez[t + CX + 1] - s_ez[t + 1];
+                const double dx0 = s_ez[t + 1] - s_ez[t], dx1 = s_ez[t + CX + 1] - s_ez[t + CX];
+                bxp = bx0 - cy * dz0;
+                bxhp = bx1 - cy * dz1;
+                byp = by0 + cx * dx0;
+                byhp = by1 + cx * dx1;
             }
 #pragma unroll
             for (int q = 0; q < 5; ++q) {
-                hx[q] = hxn[q];
-                hy[q] = hyn[q];
+                up[q] = upn[q];
                 hz_lo[q] = hzn[q];
             }
-            wz_prev = wz;
-            // ONE_RUN needs no barrier here: the next plane's (A) writes only
-            // s_pr and the reference fields, which (D) does not read, and
-            // everything (D) reads is next written after the barrier that
-            // closes (A)
-            if (!ONE_RUN) __syncthreads();
+            bzp = bzn;
         }
+        if (!ONE_RUN) __syncthreads();  // the next run writes what (D) reads
     };
     if (ONE_RUN) {
-        const int tile = (int)(b % ntiles), sl = (int)(b / ntiles);
-        run(tile, sl * H, min(sl * H + H, nz));
+        const int sl = (int)b / ntiles, tile = (int)b - sl * ntiles;
+        run(__builtin_amdgcn_readfirstlane(tile), __builtin_amdgcn_readfirstlane(sl * H),
+            __builtin_amdgcn_readfirstlane(min(sl * H + H, nz)));
     } else {
         const int pos0 = (int)b * chunk, pos1 = min(pos0 + chunk, npos);
         const int fullpos = nfull * ntiles * H;
@@ -1160,7 +1108,8 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
             }
             const int k1 = k0 + min(len, pos1 - pos);
             pos += k1 - k0;
-            run(tile, k0, k1);
+            run(__builtin_amdgcn_readfirstlane(tile), __builtin_amdgcn_readfirstlane(k0),
+                __builtin_amdgcn_readfirstlane(k1));
         }
     }
     if (st && status) atomicOr(status, st);
@@ -1268,7 +1217,6 @@ __global__ void __launch_bounds__(kCt, 4) k_ct_update(Geom g, Prims P, Flux F, S
                                 partial);
 }
 
-constexpr int kPredThreads = PredShape<kPredTx, kPredTy>::NT;
 static_assert(kPredThreads * kPredBlocksPerCU <= 1024,
               "the resident predictor blocks of a CU hold at most two waves per SIMD");
 

@@ -201,7 +201,7 @@ inline int tile_override(const char *key)
 
 // fused predictor column tile: kPredTx x kPredTy cells, its threads also
 // covering a one-cell ring (34 x 15 columns, 510 threads of 512); one block
-// per CU (123 KB of LDS, 256 VGPRs: two waves per SIMD)
+// per CU (133 KB of LDS, 256 VGPRs: two waves per SIMD)
 constexpr int kPredTx = 32, kPredTy = 13;
 constexpr int kPredBlocksPerCU = 1;
 constexpr int kPredWavesPerSimd = 2;
