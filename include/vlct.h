@@ -162,13 +162,12 @@ int vlct_step_batch(int count, const vlct_grid *grids, const vlct_state *in,
                     uint32_t *status_dev, void *ws, size_t ws_bytes, void *stream);
 
 /* Per-instance tile plan: vlct_step_batch with plan[i] (HOST array of `count`
- * bytes, NULL = all zero) choosing instance i's tiles: low nibble the CT
- * column tile (0: 64 x 8, 1: 32 x 16, 2: 16 x 32), high nibble the corrector
- * march segment along y and z (0: 16 faces, 1: 32, 2: 8).  Plan 0 takes
- * 64 x 8 CT tiles with vlct_step's planes per CT block and 16-face marches
- * (vlct_step itself marches 8 faces on small grids).  Every plan gives the
- * same results bit for bit (the tiles only regroup the same per-cell and
- * per-face arithmetic); VLCT_EINVAL for an unknown variant. */
+ * bytes, NULL = all zero) choosing instance i's tiles: low nibble the columns
+ * of a CT block, its one-cell ring included (0: vlct_step's own choice,
+ * 1: 32 x 16, 2: 16 x 32), high nibble the corrector march segment along y and
+ * z (0: 16 cells, 1: 32, 2: 8).  Every plan gives the same results bit for bit
+ * (the tiles only regroup the same per-cell and per-face arithmetic);
+ * VLCT_EINVAL for an unknown variant. */
 int vlct_step_batch_plan(int count, const vlct_grid *grids, const vlct_state *in,
                          const vlct_state *out, const double *dt_dev, double *next_dt_dev,
                          uint32_t *status_dev, const uint8_t *plan, void *ws, size_t ws_bytes,
@@ -294,11 +293,12 @@ int vlct_curl_potential_adjoint(const vlct_grid *g, const double *lbx, const dou
  * observer belongs to this call alone: no state outlives it or is visible to
  * other threads.  cb must not be NULL (VLCT_EINVAL). */
 #define VLCT_KERNEL_PRIMS 0        /* primitive variables (both stages) */
-#define VLCT_KERNEL_FLUX_PCM 1     /* predictor: PCM states + HLLD, one launch per axis */
-#define VLCT_KERNEL_FLUX_RECON 2   /* corrector: PLMC/PPMC states + HLLD, one launch per axis */
+#define VLCT_KERNEL_FLUX_PCM 1     /* PCM corrector: HLLD and the cells' update, one launch per axis */
+#define VLCT_KERNEL_FLUX_RECON 2   /* corrector: PLMC/PPMC states, HLLD and the cells' update, one
+                                      launch per axis */
 #define VLCT_KERNEL_EDGES 3        /* reserved (edge fields are computed inside the updates) */
-#define VLCT_KERNEL_UPDATE_HALF 4  /* CT edge fields + half-step cell and face update */
-#define VLCT_KERNEL_UPDATE_FULL 5  /* CT edge fields + full-step cell and face update */
+#define VLCT_KERNEL_UPDATE_HALF 4  /* reserved (part of the predictor kernel) */
+#define VLCT_KERNEL_UPDATE_FULL 5  /* CT edge fields + full-step face update */
 #define VLCT_KERNEL_DT 6           /* CFL reduction over a state (two launches: vlct_cfl_dt, in-place steps) */
 #define VLCT_KERNEL_DT_FINAL 7     /* last launch of a step's CFL reduction whose per-block
                                       maxima the full update computed */

@@ -965,7 +965,7 @@ VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, 
         const double up = x0[c] + wpl[c], um = x0[c] + wmi[c];
         const double vp = fmax(fmin(x0[c], xr), fmin(up, fmax(x0[c], xr)));
         const double vm = fmax(fmin(x0[c], xl), fmin(um, fmax(x0[c], xl)));
-        const double tol = base[c] + kPpmTie * (fabs(xl) + fabs(xr));
+        const double tol = kPpmTie * (fabs(xl) + fabs(xr) + fabs(x0[c]) + floor_c[c]);
         double a_vp = a_fp[c], a_vm = a_fm[c];
         if (fabs(vp - up) > tol || fabs(vm - um) > tol) {
             const double dpp = vp - x0[c], dmm = x0[c] - vm;

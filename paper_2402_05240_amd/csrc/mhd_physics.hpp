@@ -579,7 +579,8 @@ VLCT_DEV void ppmc(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp,
         double vm = fmax(fmin(x0[c], xl[c]), fmin(um, fmax(x0[c], xl[c])));
         // a bound that acted beyond rounding: Colella-Woodward monotonicity
         // constraints on this primitive's interface pair
-        const double tol = base[c] + kPpmTie * (fabs(xl[c]) + fabs(xr[c]));
+        // (written out: keeping `base` alive to here costs 14 registers)
+        const double tol = kPpmTie * (fabs(xl[c]) + fabs(xr[c]) + fabs(x0[c]) + floor_c[c]);
         if (fabs(vp - up) > tol || fabs(vm - um) > tol) {
             const double dpp = vp - x0[c], dmm = x0[c] - vm;
             if (dpp * dmm <= 0.0) {

@@ -2,15 +2,16 @@
 // "Cholla-MHD", Sec. 2.2) behind the C ABI of include/vlct.h.
 //
 // Step structure (all kernels on the caller's stream, state resident in HBM):
-//   stage(U^n, PCM)        : prims -> 3 x (HLLD fluxes) -> CT edge EMFs + half update
-//   stage(U^{n+1/2}, PLMC) : prims -> 3 x (reconstruction + HLLD)
-//                            -> CT edge EMFs + full update from U^n, with the
-//                               per-block CFL maxima of the new state -> final
-//                               next-dt reduction (an in-place step reduces the
-//                               CFL condition in a kernel of its own)
-// Boundary conditions enter only through the primitive kernel, which fills a
-// ghost-padded primitive array by index mapping (wrap / clamp), and through
-// face-index mapping when the stored normal field is read.
+//   U^n       : the whole predictor (Steps 2-5) in one kernel, writing U^{n+1/2}
+//               and its primitives; their ghost layers
+//   U^{n+1/2} : x, y, z: reconstruction + HLLD, the hydro fluxes taken off the
+//               cells, the face EMFs stored -> CT edge EMFs + faces, with the
+//               per-block CFL maxima of the new state -> final next-dt
+//               reduction (an in-place step reduces the CFL condition in a
+//               kernel of its own)
+// Boundary conditions enter through index mapping (wrap / clamp): in the
+// predictor's loads, in the ghost layers of the half-step primitives, and when
+// the stored normal field is read.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -28,50 +29,35 @@ namespace vlct {
 // ---------------------------------------------------------------------------
 // logical block counts of the kernels (host launches and batch offsets)
 // ---------------------------------------------------------------------------
-constexpr int kRowFaces = kBlock - 1;
-constexpr int kMarch = 16;
-constexpr int kTx = 64, kTy = 8;  // CT column tile (z planes per block: Geom::ct_planes)
-constexpr int kCt = kTx * kTy;  // threads of a CT block: one per column of the tile
+constexpr int kRowCells = kBlock - 2;  // cells a block of the x kernel updates
 
-// tile variants a batched step can give each instance (its plan byte: CT
-// variant in the low nibble, march variant in the high nibble); variant 0 is
-// the single-instance CT tile and the 16-face march (single steps on small
-// grids march 8 faces; every variant computes the same bits)
-constexpr int kCtVariants = 3;     // CT column tiles 64 x 8, 32 x 16, 16 x 32 (kCt threads)
-constexpr int kMarchVariants = 3;  // march segments of 16, 32 and 8 faces
-__host__ __device__ constexpr int ct_tx(int v) { return v == 0 ? 64 : (v == 1 ? 32 : 16); }
-__host__ __device__ constexpr int ct_ty(int v) { return kCt / ct_tx(v); }
-__host__ __device__ constexpr int march_len(int v) { return v == 0 ? 16 : (v == 1 ? 32 : 8); }
+// tile variants a batched step can give each instance (its plan byte: CT tile
+// in the low nibble, march segment in the high nibble); variant 0 of the tile
+// is the single-instance choice, the others fix the block's columns (ring
+// included) at 32 x 16 and 16 x 32
+constexpr int kCtVariants = 3;
+constexpr int kMarchVariants = 3;  // march segments of 16, 32 and 8 cells
+constexpr int kCtThreads = 512;
+static int march_len(int v) { return v == 0 ? 16 : (v == 1 ? 32 : 8); }
 
 __host__ __device__ __forceinline__ idx_t nblk_prims(const Geom &g)
 {
     return ((idx_t)g.p[0] * g.p[1] * g.p[2] + kBlock - 1) / kBlock;
 }
-__host__ __device__ __forceinline__ idx_t flux_dim3(const Geom &g, int d)
-{
-    return flux_dim(g.n, d, 0) * flux_dim(g.n, d, 1) * flux_dim(g.n, d, 2);
-}
-__host__ __device__ __forceinline__ idx_t nblk_flux(const Geom &g, int d)
-{
-    return (flux_dim3(g, d) + kBlock - 1) / kBlock;
-}
 __host__ __device__ __forceinline__ idx_t nblk_row(const Geom &g)
 {
     const idx_t items = (idx_t)(g.n[0] + 2) * (g.n[1] + 2) * (g.n[2] + 2);
-    return (items - 1 + kRowFaces - 1) / kRowFaces;
+    return (items - 1 + kRowCells - 1) / kRowCells;
 }
-__host__ __device__ __forceinline__ idx_t nblk_march(const Geom &g, int d, int m = kMarch)
+__host__ __device__ __forceinline__ idx_t nblk_march(const Geom &g, int d)
 {
     const int t = d == 1 ? 2 : 1;
     const idx_t cols = (idx_t)(g.n[0] + 2) * (g.n[t] + 2);
-    return ((cols + kBlock - 1) / kBlock) * ((g.n[d] + 1 + m - 1) / m);
+    return ((cols + kBlock - 1) / kBlock) * ((g.n[d] + g.march - 1) / g.march);
 }
-__host__ __device__ __forceinline__ idx_t nblk_ct(const Geom &g, int tx = kTx, int ty = kTy)
+__host__ __device__ __forceinline__ idx_t nblk_ct(const Geom &g)
 {
-    const int ntx = (g.n[0] + (g.bc[0] == VLCT_BC_OUTFLOW) + tx - 1) / tx;
-    const int nty = (g.n[1] + (g.bc[1] == VLCT_BC_OUTFLOW) + ty - 1) / ty;
-    const int ntz = (g.n[2] + g.ct_planes - 1) / g.ct_planes;
-    return (idx_t)ntx * nty * ntz;
+    return ct_tiles(g) * ((g.n[2] + g.ct_planes - 1) / g.ct_planes);
 }
 __host__ __device__ __forceinline__ idx_t nblk_dt(const Geom &g)
 {
@@ -185,9 +171,10 @@ __device__ __forceinline__ void prims_ghost_body(const Geom &g, const StateP &s,
     if (st && status) atomicOr(status, st);
 }
 
-// ---------------------------------------------------------------------------
-// PCM interface states + HLLD on every face of axis D (Steps 2-3)
-// ---------------------------------------------------------------------------
+// some value, without an instruction to set it: for registers that lanes
+// without a part in a step leave unused
+__device__ __forceinline__ double any_value() { return __builtin_nondeterministic_value(0.0); }
+
 // position of a block's thread in a box of rows of X items (x fastest) and Y
 // rows per plane: block-uniform first plane k0, then the thread's column,
 // row and plane past k0
@@ -206,126 +193,145 @@ __device__ __forceinline__ BoxPos box_pos(u32 q0, u32 X, u32 Y)
     return p;
 }
 
-template <int D>
-__device__ __forceinline__ void flux_pcm_body(const Geom &g, const StateP &s, const Prims &P,
-                                              const Flux &F, u32 b)
-{
-    constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-    const u32 X = flux_dim(g.n, D, 0), Y = flux_dim(g.n, D, 1), Z = flux_dim(g.n, D, 2);
-    const u32 q0 = b * kBlock;
-    const BoxPos p = box_pos(q0, X, Y);
-    if (p.k0 + p.dk >= Z) return;
-    const int x[3] = {(int)p.c - (D != 0), (int)p.j - (D != 1), (int)(p.k0 + p.dk) - (D != 2)};
-    // right cell of the face, from the first padded plane of the block's box;
-    // the left one is `back` bytes lower
-    const idx_t base = (idx_t)(p.k0 + kGhost - (D != 2)) * g.p[1] * g.p[0];
-    const u32 o = 8u * ((p.dk * g.p[1] + p.j + kGhost - (D != 1)) * g.p[0] + p.c + kGhost - (D != 0));
-    const u32 back = 8u * (D == 0 ? 1u : (u32)g.p[0] * (D == 1 ? 1u : (u32)g.p[1]));
-    // the base sits one plane lower for z faces, so that o - back stays positive
-    const idx_t lower = D == 2 ? (idx_t)g.p[0] * g.p[1] : 0;
-    const u32 oh = D == 2 ? o + back : o;
-    auto cell = [&](u32 at) {
-        auto w = [&](int q) { return ld8(P.w[q] + (base - lower), at); };
-        return W7{w(0), w(1 + D), w(1 + T1), w(1 + T2), w(4), w(5 + T1), w(5 + T2)};
-    };
-    const W7 wl = cell(oh - back), wr = cell(oh);
-    // stored normal field of this face (transverse indices mapped like cells)
-    int m[3];
-#pragma unroll
-    for (int e = 0; e < 3; ++e)
-        m[e] = e == D ? map_face(x[e], g.n[e], g.bc[e]) : map_cell(x[e], g.n[e], g.bc[e]);
-    const double bn = ld8(s.b[D] + face_store(g, D, m[0], m[1], m[2]), 0);
-    double f[7];
-    int8_t upw;
-    hlld(wl, wr, bn, g.gamma, g.gm1i, f, upw);
-    const idx_t fb = (idx_t)q0;
-#pragma unroll
-    for (int c = 0; c < 7; ++c) st8(F.f[D][c] + fb, 8u * threadIdx.x, f[c]);
-    st1(F.sg[D] + fb, threadIdx.x, upw);
-}
-
 // ---------------------------------------------------------------------------
-// corrector fluxes without duplicated reconstruction: every cell is
-// reconstructed once per axis and its two interface states feed the faces on
-// either side.
-//
-// x axis: a block of 256 threads reconstructs 256 consecutive cells of one
-// row; the high-face states go through LDS to the right neighbour, which
-// solves the Riemann problem of the face between them (255 faces per block).
+// corrector (Steps 6, 7 and the cells of Step 9).  Every cell is reconstructed
+// once per axis and its two interface states feed the faces on either side;
+// the hydro fluxes of a face end in the flux differences of its two cells on
+// chip, so the x, y and z kernels hand the partly updated cells on (out.u =
+// base - x, then - y, then - z) and store only the faces' EMFs and upwind
+// indicators for the CT update.  Per cell that is 5 doubles read and written
+// per axis and 2 stored per face, where storing the fluxes took 7 written and
+// 5 read back per face and the cells again (795 -> about 700 bytes per cell
+// for the whole corrector, and the CT update keeps none of the hydro work).
+// The linear reconstructions run near the copy rate of the card (256^3 PLMC
+// 0.68-0.73 ms per axis, 3.9 of 4.7 TB/s; 0.58-0.60 ms when the fluxes were
+// stored, with the CT update at 1.42 instead of 0.76 ms), the parabolic ones
+// at FP64 issue with two waves per SIMD (PPMC 1.07-1.22 ms).
 // ---------------------------------------------------------------------------
 template <int RECON>
+struct Recon {
+    static constexpr bool kChar = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PPMC;
+    static constexpr int R = RECON == VLCT_RECON_PCM ? 0  // stencil radius
+                             : RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PLMP ? 1 : 2;
+    // waves per SIMD the marches are held to (512 / waves registers)
+    static constexpr int kWaves = R == 0 ? 3 : 2;
+    // interface states of the middle cell of the window, floored
+    static __device__ __forceinline__ uint32_t states(const W7 *win, double bn, double gam, W7 &fm,
+                                                      W7 &fp)
+    {
+        if constexpr (R == 0) {
+            fm = fp = win[0];
+            return 0;  // floored already
+        } else {
+            if constexpr (R == 1)
+                plmc<kChar>(win[0], win[1], win[2], bn, gam, fm, fp);
+            else
+                ppmc<kChar>(win[0], win[1], win[2], win[3], win[4], bn, gam, fm, fp);
+            const uint32_t st = floor_state(fm);
+            return st | floor_state(fp);
+        }
+    }
+};
+
+// x axis: items = (row, cell) with cells -1..nx of every row (j in [-1, ny],
+// k in [-1, nz]) in one flat sequence; a block reconstructs 256 consecutive
+// items, solves the face between each item and its left neighbour in the same
+// row (the high-face states go to the right through LDS) and updates the 254
+// cells whose two faces it has (the fluxes go to the left through LDS);
+// consecutive blocks overlap by two items
+template <int RECON>
 __device__ __forceinline__ void recon_x_body(const Geom &g, const StateP &s, const Prims &P,
-                                             const Flux &F, uint32_t *status, u32 b)
+                                             const Flux &F, const StateP &base, const StateW &out,
+                                             const double *dt_dev, uint32_t *status, u32 b)
 {
-    // items = (row, cell) with cells -1..nx of every row (j in [-1, ny],
-    // k in [-1, nz]) in one flat sequence; a block reconstructs 256
-    // consecutive items and solves the face between each item and its left
-    // neighbour in the same row; consecutive blocks overlap by one item
-    constexpr bool kChar = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PPMC;
-    constexpr bool kLinear = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PLMP;
+    constexpr int R = Recon<RECON>::R;
     __shared__ double lds[7][kBlock];
-    const u32 per_row = g.n[0] + 2, Y = g.n[1] + 2;
+    const u32 nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    const u32 per_row = nx + 2, Y = ny + 2;
     const int t = threadIdx.x;
-    const BoxPos p = box_pos(b * kRowFaces, per_row, Y);
-    const bool have = p.k0 + p.dk < (u32)g.n[2] + 2;
+    const BoxPos p = box_pos(b * kRowCells, per_row, Y);
+    const u32 k1 = p.k0 + p.dk;  // k + 1
+    const bool have = k1 < nz + 2;
+    const bool mine = t >= 1 && t <= kRowCells;  // the item this block answers for
+    const bool cell = have && mine && p.c >= 1 && p.c <= nx && p.j >= 1 && p.j <= ny && k1 >= 1 &&
+                      k1 <= nz;
+    const u32 kb = p.k0 >= 1 ? p.k0 - 1 : 0;  // first interior plane of the block
+    const idx_t ub = (idx_t)kb * ny * nx;
+    const u32 uo = 8u * (((k1 - 1 - kb) * ny + p.j - 1) * nx + p.c - 1);
+    double u[5];
+    if (cell) {
+#pragma unroll
+        for (int q = 0; q < 5; ++q) u[q] = ld8(base.u[q] + ub, uo);
+    }
     W7 fm{}, fp{};
     uint32_t st = 0;
     if (have) {
-        const idx_t base = (idx_t)(p.k0 + kGhost - 1) * g.p[1] * g.p[0];
+        const idx_t pb = (idx_t)(p.k0 + kGhost - 1) * g.p[1] * g.p[0];
         const u32 o = 8u * ((p.dk * g.p[1] + p.j + kGhost - 1) * g.p[0] + p.c + kGhost - 1);
-        auto cell = [&](int off) {
-            auto w = [&](int q) { return ld8(P.w[q] + base, o + 8 * off); };
-            return W7{w(0), w(1), w(2), w(3), w(4), w(6), w(7)};
-        };
-        const double bn = ld8(P.w[5] + base, o);
-        if constexpr (kLinear)
-            plmc<kChar>(cell(-1), cell(0), cell(1), bn, g.gamma, fm, fp);
-        else
-            ppmc<kChar>(cell(-2), cell(-1), cell(0), cell(1), cell(2), bn, g.gamma, fm, fp);
-        st |= floor_state(fm);
-        st |= floor_state(fp);
+        W7 win[2 * R + 1];
+#pragma unroll
+        for (int q = 0; q <= 2 * R; ++q) {
+            auto w = [&](int f) { return ld8(P.w[f] + pb, o + 8 * (q - R)); };
+            win[q] = W7{w(0), w(1), w(2), w(3), w(4), w(6), w(7)};
+        }
+        st = Recon<RECON>::states(win, ld8(P.w[5] + pb, o), g.gamma, fm, fp);
     }
     lds[0][t] = fp.d; lds[1][t] = fp.u; lds[2][t] = fp.v; lds[3][t] = fp.w;
     lds[4][t] = fp.p; lds[5][t] = fp.by; lds[6][t] = fp.bz;
     __syncthreads();
-    if (t >= 1 && have && p.c >= 1) {
+    const bool face = t >= 1 && have && p.c >= 1;
+    double f[7];
+    if (face) {
         const W7 wl{lds[0][t - 1], lds[1][t - 1], lds[2][t - 1], lds[3][t - 1],
                     lds[4][t - 1], lds[5][t - 1], lds[6][t - 1]};
         const int mj = map_cell((int)p.j - 1, g.n[1], g.bc[1]);
-        const int mk = map_cell((int)(p.k0 + p.dk) - 1, g.n[2], g.bc[2]);
+        const int mk = map_cell((int)k1 - 1, g.n[2], g.bc[2]);
         // the stored face n of a periodic axis holds face 0's value
         const double bn = ld8(s.b[0] + face_store(g, 0, (int)p.c - 1, mj, mk), 0);
-        double f[7];
         int8_t upw;
         hlld(wl, fm, bn, g.gamma, g.gm1i, f, upw);
-        const u32 X = g.n[0] + 1;
-        const idx_t fb = (idx_t)p.k0 * Y * X;
-        const u32 fo = (p.dk * Y + p.j) * X + p.c - 1;
+        if (mine) {
+            const u32 X = nx + 1;
+            const idx_t fb = (idx_t)p.k0 * Y * X;
+            const u32 fo = (p.dk * Y + p.j) * X + p.c - 1;
+            st8(F.e[0][0] + fb, 8u * fo, -f[5]);
+            st8(F.e[0][1] + fb, 8u * fo, f[6]);
+            st1(F.sg[0] + fb, fo, upw);
+        }
+    }
+    __syncthreads();
+    if (face) {
 #pragma unroll
-        for (int v = 0; v < 7; ++v) st8(F.f[0][v] + fb, 8u * fo, f[v]);
-        st1(F.sg[0] + fb, fo, upw);
+        for (int q = 0; q < 5; ++q) lds[q][t] = f[q];
+    }
+    __syncthreads();
+    if (cell) {
+        const double cx = dt_dev[0] / g.dl[0];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) st8(out.u[q] + ub, uo, u[q] - cx * (lds[q][t + 1] - f[q]));
     }
     if (st && status) atomicOr(status, st);
 }
 
 // y and z axes: one thread per transverse column (columns flattened with x
 // fastest, so loads and stores are coalesced); each thread marches along the
-// axis through a segment of M faces, keeping the stencil and the previous
-// cell's high-face state in registers (one extra reconstruction per segment).
-// A step along the column moves three byte offsets and one pointer by strides.
-template <int D, int RECON, int M = kMarch>
+// axis through a segment of Geom::march cells, keeping the stencil, the
+// previous cell's high-face state and the previous face's hydro flux in
+// registers (two extra reconstructions and one extra face per segment).  A
+// step along the column moves three byte offsets and one pointer by strides.
+template <int D, int RECON>
 __device__ __forceinline__ void march_body(const Geom &g, const StateP &s, const Prims &P,
-                                           const Flux &F, uint32_t *status, u32 b)
+                                           const Flux &F, const StateW &out, const double *dt_dev,
+                                           uint32_t *status, u32 b)
 {
-    constexpr int T = D == 1 ? 2 : 1;         // the transverse axis other than x
+    constexpr int T = D == 1 ? 2 : 1;  // the transverse axis other than x
     constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-    constexpr bool kChar = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PPMC;
-    constexpr int R = (RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PLMP) ? 1 : 2;
+    constexpr int R = Recon<RECON>::R;
     const int nD = g.n[D];
     // columns (i, it), i in [-1, nx], it in [-1, n_T], flattened with i fastest
     const u32 X2 = g.n[0] + 2;
     const u32 ncb = (X2 * (g.n[T] + 2) + kBlock - 1) / kBlock;
-    const u32 nseg = (nD + 1 + M - 1) / M;
+    const u32 nseg = (nD + g.march - 1) / g.march;
     const u32 seg = b / ncb, cb = b - seg * ncb;
     if (seg >= nseg) return;
     const u32 it0 = cb * kBlock / X2;  // first row of columns of the block
@@ -333,68 +339,110 @@ __device__ __forceinline__ void march_body(const Geom &g, const StateP &s, const
     const u32 i1 = e - dr * X2;  // i + 1
     const int i = (int)i1 - 1, it = (int)(it0 + dr) - 1;
     if (it > g.n[T]) return;
-    const int s0 = seg * M;
-    const int s1 = min(s0 + M, nD + 1);  // faces [s0, s1)
+    const int s0 = seg * g.march;
+    const int s1 = min(s0 + g.march, nD);  // cells [s0, s1), faces [s0, s1]
+    const bool interior = i >= 0 && i < g.n[0] && it >= 0 && it < g.n[T];
     // primitives: cell s0 - 1 - R of the column
     const u32 px = g.p[0], py = g.p[1];
     const idx_t pb = D == 1 ? ((idx_t)(it0 + kGhost - 1) * py + (s0 - 1 - R + kGhost)) * px
                             : ((idx_t)(s0 - 1 - R + kGhost) * py + (it0 + kGhost - 1)) * px;
     u32 po = 8u * ((D == 1 ? dr * px * py : dr * px) + i1 + kGhost - 1);
     const u32 pstep = 8u * (D == 1 ? px : px * py);
-    auto cell = [&](u32 at, double &bn) {
+    auto cell = [&](u32 at) {
         auto w = [&](int q) { return ld8(P.w[q] + pb, at); };
-        bn = w(5 + D);
         return W7{w(0), w(1 + D), w(1 + T1), w(1 + T2), w(4), w(5 + T1), w(5 + T2)};
     };
-    // fluxes: face s0
+    // EMFs: face s0
     const u32 fx = X2, fy = g.n[1] + (D == 1 ? 1 : 2);
     const idx_t fb = D == 1 ? ((idx_t)it0 * fy + s0) * fx : ((idx_t)s0 * fy + it0) * fx;
     u32 fo = (D == 1 ? dr * fx * fy : dr * fx) + i1;
     const u32 fstep = D == 1 ? fx : fx * fy;
+    // cells: cell s0
+    const u32 tb = it0 >= 1 ? it0 - 1 : 0;  // first interior row of columns of the block
+    const idx_t ub = D == 1 ? ((idx_t)tb * g.n[1] + s0) * g.n[0] : ((idx_t)s0 * g.n[1] + tb) * g.n[0];
+    u32 uo = 8u * ((D == 1 ? (it - (int)tb) * g.n[1] * g.n[0] : (it - (int)tb) * g.n[0]) + i);
+    const u32 ustep = 8u * (D == 1 ? g.n[0] : g.n[0] * g.n[1]);
     // stored normal field: face s0 (the face n of a periodic axis holds face 0's value)
     const int mt = map_cell(it, g.n[T], g.bc[T]), mi = map_cell(i, g.n[0], g.bc[0]);
     const double *nb = s.b[D] + (D == 1 ? face_store(g, 1, mi, s0, mt) : face_store(g, 2, mi, mt, s0));
     const idx_t nstep = D == 1 ? (idx_t)g.n[0] : (idx_t)g.n[0] * g.n[1];
+    const double cd = uniform(dt_dev[0] / g.dl[D]);
     // stencil window of cells c-R .. c+R for c = s0 - 1
     W7 win[2 * R + 1];
-    double bnc[2 * R + 1];
 #pragma unroll
     for (int q = 0; q < 2 * R + 1; ++q) {
-        win[q] = cell(po, bnc[q]);
+        win[q] = cell(po);
         po += pstep;
     }
+    double bnc = ld8(P.w[5 + D] + pb, po - (R + 1) * pstep);  // the middle cell's B_n
     uint32_t st = 0;
-    W7 prev{};
-    for (int c = s0 - 1; c < s1; ++c) {
+    bool bad = false;
+    // the previous cell's high-face state and the previous face's hydro flux
+    // wait in LDS (thread-private): 24 registers that the parabolic window
+    // would otherwise spill
+    __shared__ double park[12][kBlock];
+    auto dopark = [&](const W7 &w) {
+        double x[7];
+        to_arr(w, x);
+#pragma unroll
+        for (int q = 0; q < 7; ++q) park[q][threadIdx.x] = x[q];
+    };
+    auto unpark = [&](int o) {
+        const int t = threadIdx.x;
+        return W7{park[o][t], park[o + 1][t], park[o + 2][t], park[o + 3][t],
+                  park[o + 4][t], park[o + 5][t], park[o + 6][t]};
+    };
+    double bn = ld8(nb, 0);
+    for (int c = s0 - 1; c <= s1; ++c) {
         W7 fm, fp;
-        if constexpr (R == 1)
-            plmc<kChar>(win[0], win[1], win[2], bnc[1], g.gamma, fm, fp);
-        else
-            ppmc<kChar>(win[0], win[1], win[2], win[3], win[4], bnc[2], g.gamma, fm, fp);
-        st |= floor_state(fm);
-        st |= floor_state(fp);
+        st |= Recon<RECON>::states(win, bnc, g.gamma, fm, fp);
+        // the next cell of the window, the cell to update and the next face's
+        // field, behind the Riemann solve and ahead of its stores (loads
+        // return in order with the stores issued before them)
+        double u[5], bn_next = any_value();
+        const bool upd = interior && c > s0;  // cell c - 1
+        if (upd) {
+#pragma unroll
+            for (int q = 0; q < 5; ++q) u[q] = ld8(out.u[q] + ub, uo);
+        }
+        if (c < s1) {
+#pragma unroll
+            for (int q = 0; q < 2 * R; ++q) win[q] = win[q + 1];
+            win[2 * R] = cell(po);
+            po += pstep;
+            bnc = ld8(P.w[5 + D] + pb, po - (R + 1) * pstep);
+            if (c >= s0) {
+                nb += nstep;
+                bn_next = ld8(nb, 0);
+            }
+        }
         if (c >= s0) {
-            const double bn = ld8(nb, 0);
-            nb += nstep;
             double f[7];
             int8_t upw;
-            hlld(prev, fm, bn, g.gamma, g.gm1i, f, upw);
-#pragma unroll
-            for (int v = 0; v < 7; ++v) st8(F.f[D][v] + fb, 8u * fo, f[v]);
-            st1(F.sg[D] + fb, fo, upw);
-            fo += fstep;
-        }
-        prev = fp;
-        if (c + 1 < s1) {
-#pragma unroll
-            for (int q = 0; q < 2 * R; ++q) {
-                win[q] = win[q + 1];
-                bnc[q] = bnc[q + 1];
+            hlld(unpark(0), fm, bn, g.gamma, g.gm1i, f, upw);
+            bn = bn_next;
+            if (c < s1 || c == nD) {  // the face s1 belongs to the next segment
+                st8(F.e[D][0] + fb, 8u * fo, -f[5]);
+                st8(F.e[D][1] + fb, 8u * fo, f[6]);
+                st1(F.sg[D] + fb, fo, upw);
             }
-            win[2 * R] = cell(po, bnc[2 * R]);
-            po += pstep;
+            fo += fstep;
+            if (upd) {
+                constexpr int comp[5] = {0, 1 + D, 1 + T1, 1 + T2, 4};
+#pragma unroll
+                for (int q = 0; q < 5; ++q) {
+                    const double v = u[comp[q]] - cd * (f[q] - park[7 + q][threadIdx.x]);
+                    st8(out.u[comp[q]] + ub, uo, v);
+                    if (D == 2) bad |= !isfinite(v);
+                }
+                uo += ustep;
+            }
+#pragma unroll
+            for (int q = 0; q < 5; ++q) park[7 + q][threadIdx.x] = f[q];
         }
+        dopark(fp);
     }
+    if (bad) st |= kStatusNonfinite;
     if (st && status) atomicOr(status, st);
 }
 
@@ -409,15 +457,20 @@ __device__ __forceinline__ double cell_cfl(const Geom &g, double d, double mx, d
     if (!(d >= kFloorRho)) { d = kFloorRho; st |= kStatusDensityFloor; }
     const double id = mrcp(d);
     const double v[3] = {mx * id, my * id, mz * id};
+    const double sq[3] = {b[0] * b[0], b[1] * b[1], b[2] * b[2]};
+    const double b2 = sq[0] + sq[1] + sq[2];
     const double ke = 0.5 * d * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-    const double me = 0.5 * (b[0] * b[0] + b[1] * b[1] + b[2] * b[2]);
-    double p = (g.gamma - 1.0) * (e - ke - me);
+    double p = (g.gamma - 1.0) * (e - ke - 0.5 * b2);
     if (!(p >= kFloorP)) { p = kFloorP; st |= kStatusPressureFloor; }
+    // c_f,l^2 = (gP + B^2 + disc_l) / (2 rho), the terms without l once
+    const double gp = g.gamma * p, t2 = (gp - b2) * (gp - b2), hid = 0.5 * id;
     double m = 0.0;
 #pragma unroll
     for (int l = 0; l < 3; ++l) {
-        const double cf = fast_speed(d, p, b[l], b[(l + 1) % 3], b[(l + 2) % 3], g.gamma);
-        m = fmax(m, mdiv(fabs(v[l]) + cf, g.dl[l]));
+        const double disc = msqrt(t2 + 4.0 * gp * (sq[(l + 1) % 3] + sq[(l + 2) % 3]));
+        const double s = fabs(v[l]) + msqrt((gp + b2 + disc) * hid);
+        const double q = s * g.idl[l];
+        m = fmax(m, fma(fma(-g.dl[l], q, s), g.idl[l], q));  // s / d_l
     }
     return m;
 }
@@ -453,322 +506,223 @@ __device__ __forceinline__ double edge_combine(double eb_c, double eb_cm, double
     return avg + 0.25 * (t1 + t2 + t3 + t4);
 }
 
-template <int A>
-__device__ __forceinline__ double edge_emf(const Geom &g, const Flux &F, int i, int j, int k,
-                                           double r00, double r10, double r01, double r11)
-{
-    // r00, r10, r01, r11: cell-centred -(v x B)_A of the cells at x0, x0 - e_B,
-    // x0 - e_C and x0 - e_B - e_C around the edge
-    constexpr int B = (A + 1) % 3, C = (A + 2) % 3;
-    int x0[3] = {i, j, k};
-    int xb[3] = {i, j, k};
-    xb[B] -= 1;
-    int xc[3] = {i, j, k};
-    xc[C] -= 1;
-    const idx_t fb_c = fidx(g, B, x0[0], x0[1], x0[2]);
-    const idx_t fb_cm = fidx(g, B, xc[0], xc[1], xc[2]);
-    const idx_t fc_b = fidx(g, C, x0[0], x0[1], x0[2]);
-    const idx_t fc_bm = fidx(g, C, xb[0], xb[1], xb[2]);
-    // B-face EMF component A = -F_B[B_t1]; C-face EMF component A = +F_C[B_t2]
-    return edge_combine(-F.f[B][5][fb_c], -F.f[B][5][fb_cm], F.f[C][6][fc_b], F.f[C][6][fc_bm],
-                        F.sg[B][fb_c], F.sg[B][fb_cm], F.sg[C][fc_b], F.sg[C][fc_bm], r00, r10,
-                        r01, r11);
-}
-
-// E_x (A = 0) or E_y (A = 1) at the half plane k - 1/2 for a block marching up
-// in z: of its four faces, the one at x0 - e_z (the B-face for E_x, the
-// C-face for E_y) is the face at x0 of the half plane below, so its EMF and
-// upwind indicator come in through (ez, sz) and those at x0 go out through
-// them for the next half plane.  FIRST: the lower face is read, as edge_emf
-// reads it.
-template <int A, bool FIRST>
-__device__ __forceinline__ double edge_emf_zcarry(const Geom &g, const Flux &F, int i, int j,
-                                                  int k, double r00, double r10, double r01,
-                                                  double r11, double &ez, int8_t &sz)
-{
-    static_assert(A == 0 || A == 1, "the z-marching carry serves E_x and E_y");
-    constexpr int B = (A + 1) % 3, C = (A + 2) % 3;
-    constexpr int Z = A == 0 ? B : C;  // the face axis whose faces stack along z
-    constexpr int T = A == 0 ? C : B;  // the face axis whose two faces share the plane
-    const idx_t fz_hi = fidx(g, Z, i, j, k);
-    int xt[3] = {i, j, k};
-    xt[A == 0 ? B : C] -= 1;  // the in-plane neighbour of the T-faces
-    const idx_t ft_0 = fidx(g, T, i, j, k), ft_1 = fidx(g, T, xt[0], xt[1], xt[2]);
-    // EMF component A: -F_B[B_t1] on a B-face, +F_C[B_t2] on a C-face
-    constexpr int zcomp = Z == B ? 5 : 6, tcomp = T == B ? 5 : 6;
-    double e_lo;
-    int s_lo;
-    if (FIRST) {
-        const idx_t fz_lo = fidx(g, Z, i, j, k - 1);
-        e_lo = Z == B ? -F.f[Z][zcomp][fz_lo] : F.f[Z][zcomp][fz_lo];
-        s_lo = F.sg[Z][fz_lo];
-    } else {
-        e_lo = ez;
-        s_lo = sz;
-    }
-    const double e_hi = Z == B ? -F.f[Z][zcomp][fz_hi] : F.f[Z][zcomp][fz_hi];
-    const int8_t s_hi = F.sg[Z][fz_hi];
-    const double et0 = T == B ? -F.f[T][tcomp][ft_0] : F.f[T][tcomp][ft_0];
-    const double et1 = T == B ? -F.f[T][tcomp][ft_1] : F.f[T][tcomp][ft_1];
-    const int st0 = F.sg[T][ft_0], st1 = F.sg[T][ft_1];
-    ez = e_hi;
-    sz = s_hi;
-    if (A == 0)  // B = y stacked along z (x0 - e_C = lower), C = z faces at x0 and x0 - e_y
-        return edge_combine(e_hi, e_lo, et0, et1, (int)s_hi, s_lo, st0, st1, r00, r10, r01,
-                            r11);
-    else  // B = z faces at x0 and x0 - e_x, C = x stacked along z (x0 - e_B = lower)
-        return edge_combine(et0, et1, e_hi, e_lo, st0, st1, (int)s_hi, s_lo, r00, r10, r01,
-                            r11);
-}
-
 // ---------------------------------------------------------------------------
-// fused CT + update (Steps 4-5 and 8-9): a block owns a 64 x 8 column tile and
-// marches along z.  For each plane k it computes the edge fields it needs once
-// into LDS -- E_z of plane k, E_x / E_y of the plane above (k+1/2); those of
-// the plane below are kept from the previous iteration -- and then updates the
-// plane's cells and the faces owned by them.  Same arithmetic as k_edges and
-// k_update, without the round trip of the edge arrays through HBM.
+// CT update (Steps 8-9: edge fields and faces).  A block marches along z
+// through Geom::ct_planes planes of a column tile; a thread owns one column of
+// the tile or of its one-cell ring, and per new plane m
+//   (A) shares the reference field -(v x B) of its cell and the EMFs and
+//       upwind indicators of its low faces that the neighbours need (LDS);
+//   (C) forms the three edge fields at its cell's low edges, E_z of plane m,
+//       E_x and E_y of the half plane m - 1/2, from its own registers and one
+//       neighbour each way, and shares them;
+//   (D) finishes the faces of plane m - 1 and starts those of plane m.
+// Two barriers per plane; the next plane's loads fly during (D) and, with two
+// blocks per CU (126 registers, 67 KB of LDS), behind the other block's work.
+// Bound by load latency: 187 bytes per cell at 256^3 in 0.76 ms (4.1 TB/s),
+// 1.42 ms for the form with the hydro update and the edges dealt out by
+// division from global memory; 32^3 37 -> 21 us.
+// DT: the CFL condition of the updated cells is reduced on the way, one
+// maximum per block into partial[b]: the ring's columns finish the high faces
+// of the tile too (in the arithmetic of the blocks that own them), plane m - 1
+// shares its finished faces, and its cells are evaluated after the next
+// barrier.  An in-place step runs without it (the high faces' base values may
+// have been overwritten by their owners) and reduces the CFL condition apart.
 // ---------------------------------------------------------------------------
-
-// DT (full step only): the CFL condition of the updated cells is reduced on
-// the way, one maximum per block into partial[b]; the cell-centred field
-// takes the cell's high faces recomputed from the same edge fields as the
-// threads (or blocks) that own them.
-template <bool FULL, int TX = kTx, int TY = kTy, bool DT = false>
+template <bool DT>
 __device__ __forceinline__ void ct_body(const Geom &g, const Prims &P, const Flux &F,
                                         const StateP &base, const StateW &out,
-                                        const double *dt_dev, uint32_t *status, idx_t b,
-                                        double *partial = nullptr)
+                                        const double *dt_dev, uint32_t *status, u32 b,
+                                        double *partial)
 {
-    static_assert(FULL || !DT, "the CFL reduction belongs to the full step");
-    __shared__ double sez[TY + 1][TX + 1];
-    __shared__ double sex[2][TY + 1][TX];
-    __shared__ double sey[2][TY][TX + 1];
-    // cell-centred -(v x B) of the tile plus a one-cell halo below in x and y,
-    // two planes in flight: plane kk lives in slot (kk - k0 + 1) & 1
-    __shared__ double sref[2][3][TY + 2][TX + 2];
-    // EMF and upwind indicator of each horizontal edge's face stacked along z
-    __shared__ double szc_e[(TY + 1) * TX + TY * (TX + 1)];
-    __shared__ int8_t szc_s[(TY + 1) * TX + TY * (TX + 1)];
+    constexpr int N = kCtThreads;
+    __shared__ double s_rx[2][N], s_ry[2][N], s_rz[N];  // -(v x B): x, y of planes m - 1, m (slot m & 1), z
+    __shared__ double s_xz[N], s_yz[N], s_zy[N], s_zx[N];  // EMFs: E_z of x- and y-faces, E_y and E_x of z-faces
+    __shared__ int8_t s_sx[N], s_sy[N], s_sz[N];
+    __shared__ double s_ez[N], s_ex[2][N], s_ey[2][N];  // edge fields (half planes: slot m & 1)
+    __shared__ double s_bx[DT ? N : 1], s_by[DT ? N : 1];  // finished low x-, y-faces of plane m - 1
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
     // positions owned by threads: cells/faces i in [0, ex), j in [0, ey)
     const int ex = nx + (g.bc[0] == VLCT_BC_OUTFLOW), ey = ny + (g.bc[1] == VLCT_BC_OUTFLOW);
-    const int tz = g.ct_planes;
-    const int ntx = (ex + TX - 1) / TX, nty = (ey + TY - 1) / TY, ntz = (nz + tz - 1) / tz;
-    if (b >= (idx_t)ntx * nty * ntz) return;
-    const int bx = (int)(b % ntx), by = (int)((b / ntx) % nty), bz = (int)(b / ((idx_t)ntx * nty));
-    const int i0 = bx * TX, j0 = by * TY, k0 = bz * tz, k1 = min(k0 + tz, nz);
-    const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
-    const int i = i0 + tx, j = j0 + ty;
-    const double dt = FULL ? dt_dev[0] : 0.5 * dt_dev[0];
-    const double cx = dt / g.dl[0], cy = dt / g.dl[1], cz = dt / g.dl[2];
-    constexpr int NEZ = (TY + 1) * (TX + 1), NEX = (TY + 1) * TX, NEY = TY * (TX + 1);
+    const int TX = g.ct_tx, TY = g.ct_ty, CX = TX + 2;
+    const u32 ntx = (ex + TX - 1) / TX, nty = (ey + TY - 1) / TY;
+    const u32 zb = b / (ntx * nty), tile = b - zb * (ntx * nty);
+    const int k0 = __builtin_amdgcn_readfirstlane(zb * g.ct_planes);
+    if (k0 >= nz) return;
+    const int k1 = min(k0 + g.ct_planes, nz);
+    const int i0 = (tile % ntx) * TX, j0 = (tile / ntx) * TY;
+    const int t = threadIdx.x, c = t / CX, a = t - c * CX;
+    const int ii = i0 - 1 + a, jj = j0 - 1 + c;
+    const bool live = c < TY + 2 && ii <= nx && jj <= ny;
+    const bool edge = live && a >= 1 && c >= 1;
+    const bool own = edge && a <= TX && c <= TY && ii < ex && jj < ey;
+    const bool interior = own && ii < nx && jj < ny;
+    // low faces this thread finishes (and stores where it owns the position)
+    const bool xface = edge && c <= TY && jj < ny && (DT || own);
+    const bool yface = edge && a <= TX && ii < nx && (DT || own);
+    const int lx = t - 1, ly = t - CX;
+    const double dt = dt_dev[0];
+    const double cx = uniform(dt / g.dl[0]), cy = uniform(dt / g.dl[1]), cz = uniform(dt / g.dl[2]);
+    // byte offsets of the column in a plane of each array
+    u32 op = 8u * (u32)((jj + kGhost) * g.p[0] + ii + kGhost);
+    u32 oc = 8u * (u32)(jj * nx + ii);
+    u32 ox = 8u * (u32)(jj * (nx + 1) + map_face(ii, nx, g.bc[0]));
+    u32 oy = 8u * (u32)(map_face(jj, ny, g.bc[1]) * nx + ii);
+    // (the ring's first columns have no low x- or y-face: those of the next are read)
+    u32 fxo = (u32)((jj + 1) * (nx + 1) + max(ii, 0)), fyo = (u32)(max(jj, 0) * (nx + 2) + ii + 1);
+    u32 fzo = (u32)((jj + 1) * (nx + 2) + ii + 1);
+    const idx_t sp = (idx_t)g.p[0] * g.p[1], sc = (idx_t)nx * ny;
+    const idx_t sbx = (idx_t)(nx + 1) * ny, sby = (idx_t)nx * (ny + 1);
+    const idx_t sfx = (idx_t)(nx + 1) * (ny + 2), sfy = (idx_t)(nx + 2) * (ny + 1);
+    const idx_t sfz = (idx_t)(nx + 2) * (ny + 2);
+    const idx_t pstep = P.w[1] - P.w[0];  // the primitive arrays are equally spaced
 
-    constexpr int NREF = (TY + 2) * (TX + 2);
-    auto slot = [&](int kk) { return (kk - k0 + 1) & 1; };
-    // reference EMFs of plane kk (cells up to n: the highest edges are at n - 1/2)
-    auto stage_ref = [&](int kk) {
-        const int sl = slot(kk);
-        for (int q = threadIdx.x; q < NREF; q += (TX * TY)) {
-            const int a = q % (TX + 2), c = q / (TX + 2), ii = i0 - 1 + a, jj = j0 - 1 + c;
-            if (ii <= nx && jj <= ny) {
-                const idx_t o = pidx(g, ii, jj, kk);
-                const double vx = P.w[1][o], vy = P.w[2][o], vz = P.w[3][o];
-                const double bx = P.w[5][o], by = P.w[6][o], bz = P.w[7][o];
-                sref[sl][0][c][a] = -(vy * bz - vz * by);
-                sref[sl][1][c][a] = -(vz * bx - vx * bz);
-                sref[sl][2][c][a] = -(vx * by - vy * bx);
+    // plane m: velocity and field, EMFs and indicators of the low faces, base faces
+    double w[6], em[6], bf[3];
+    int sg[3] = {0, 0, 0};
+    auto load_plane = [&](int m) {
+        if (live) {
+            const idx_t o = (idx_t)(m + kGhost) * sp;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) w[q] = ld8(P.w[0] + ((q < 3 ? 1 + q : 2 + q) * pstep + o), op);
+            const idx_t px = (idx_t)(m + 1) * sfx, py = (idx_t)(m + 1) * sfy, pz = (idx_t)m * sfz;
+            em[0] = ld8(F.e[0][0] + px, 8u * fxo);
+            em[1] = ld8(F.e[0][1] + px, 8u * fxo);
+            em[2] = ld8(F.e[1][0] + py, 8u * fyo);
+            em[3] = ld8(F.e[1][1] + py, 8u * fyo);
+            sg[0] = ld1(F.sg[0] + px, fxo);
+            sg[1] = ld1(F.sg[1] + py, fyo);
+            if (m >= k0) {
+                em[4] = ld8(F.e[2][0] + pz, 8u * fzo);
+                em[5] = ld8(F.e[2][1] + pz, 8u * fzo);
+                sg[2] = ld1(F.sg[2] + pz, fzo);
             }
         }
-    };
-    // LDS coordinates of cell (ii, jj): [jj - j0 + 1][ii - i0 + 1]
-    // edge q of the plane kk - 1/2 (E_x for q < NEX, else E_y, at edge index
-    // kk) into slot h; szc_e / szc_s[q] carry the EMF and upwind indicator of
-    // its face stacked along z from one half plane to the next (first: read
-    // them).  Only the thread working on edge q touches entry q within a plane.
-    auto horizontal_edge = [&](int q, int kk, int h, bool first) {
-        const int up = slot(kk), dn = slot(kk - 1);
-        const int qe = q;
-        if (q < NEX) {
-            const int a = q % TX, c = q / TX, ii = i0 + a, jj = j0 + c;
-            // E_x at (ii, jj - 1/2, kk - 1/2): B = y, C = z
-            if (ii < nx && jj <= ny) {
-                const double r00 = sref[up][0][c + 1][a + 1], r10 = sref[up][0][c][a + 1];
-                const double r01 = sref[dn][0][c + 1][a + 1], r11 = sref[dn][0][c][a + 1];
-                sex[h][c][a] = first ? edge_emf_zcarry<0, true>(g, F, ii, jj, kk, r00, r10, r01, r11,
-                                                                szc_e[qe], szc_s[qe])
-                                     : edge_emf_zcarry<0, false>(g, F, ii, jj, kk, r00, r10, r01, r11,
-                                                                 szc_e[qe], szc_s[qe]);
-            }
-        } else {
-            q -= NEX;
-            const int a = q % (TX + 1), c = q / (TX + 1), ii = i0 + a, jj = j0 + c;
-            // E_y at (ii - 1/2, jj, kk - 1/2): B = z, C = x
-            if (ii <= nx && jj < ny) {
-                const double r00 = sref[up][1][c + 1][a + 1], r10 = sref[dn][1][c + 1][a + 1];
-                const double r01 = sref[up][1][c + 1][a], r11 = sref[dn][1][c + 1][a];
-                sey[h][c][a] = first ? edge_emf_zcarry<1, true>(g, F, ii, jj, kk, r00, r10, r01, r11,
-                                                                szc_e[qe], szc_s[qe])
-                                     : edge_emf_zcarry<1, false>(g, F, ii, jj, kk, r00, r10, r01, r11,
-                                                                 szc_e[qe], szc_s[qe]);
-            }
+        if (m >= k0) {
+            if (xface && m < k1) bf[0] = ld8(base.b[0] + m * sbx, ox);
+            if (yface && m < k1) bf[1] = ld8(base.b[1] + m * sby, oy);
+            if (interior && (DT || m < k1 || g.bc[2] == VLCT_BC_OUTFLOW))
+                bf[2] = ld8(base.b[2] + map_face(m, nz, g.bc[2]) * sc, oc);
         }
     };
-    // two barriers per plane: (1) E_z of plane k and E_x / E_y of plane
-    // k + 1/2 as one flat loop (reads the reference EMFs of planes k, k + 1);
-    // (2) the update of plane k, then the reference EMFs of plane k + 2 into
-    // the slot of plane k, which (1) no longer reads
-    int lo = 0;
-    stage_ref(k0 - 1);
-    stage_ref(k0);
-    __syncthreads();
-    for (int q = threadIdx.x; q < NEX + NEY; q += (TX * TY)) horizontal_edge(q, k0, lo, true);
-    __syncthreads();
-    stage_ref(k0 + 1);  // into the slot of plane k0 - 1, no longer read
-    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 6; ++q) w[q] = em[q] = any_value();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) bf[q] = any_value();
+    load_plane(k0 - 1);
+    // of plane m - 1: own EMFs and indicators, the low x- and y-face short of
+    // their E_y and E_x terms and the finished low z-face
+    double xy_p = any_value(), yx_p = any_value(), bxp = any_value(), byp = any_value();
+    double bzp = any_value();
+    // of the plane whose CFL condition is due: the cells and B_cc,z
+    double u[5], bcz = any_value();
+#pragma unroll
+    for (int q = 0; q < 5; ++q) u[q] = any_value();
+    int sx_p = 0, sy_p = 0;
     bool bad = false;
     double mcfl = 0.0;
     uint32_t stcfl = 0;
-    // the cell's z-face fluxes and (DT) base B_z at its low face k, read at k0
-    // and carried up from the high face of the plane below
-    const bool owner = i < ex && j < ey && i < nx && j < ny;
-    double fzc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    double bzc = 0.0;
-    if (owner) {
-        const idx_t fz0 = fidx(g, 2, i, j, k0);
-#pragma unroll
-        for (int q = 0; q < 5; ++q) fzc[q] = F.f[2][q][fz0];
-        if (DT) bzc = base.b[2][face_store(g, 2, i, j, k0)];
-    }
-    for (int k = k0; k < k1; ++k) {
-        const int sk = slot(k);
-        for (int q = threadIdx.x; q < NEZ + NEX + NEY; q += (TX * TY)) {
-            if (q < NEZ) {
-                const int a = q % (TX + 1), c = q / (TX + 1), ii = i0 + a, jj = j0 + c;
-                // E_z at (ii - 1/2, jj - 1/2, k): B = x, C = y
-                if (ii <= nx && jj <= ny)
-                    sez[c][a] = edge_emf<2>(g, F, ii, jj, k, sref[sk][2][c + 1][a + 1],
-                                            sref[sk][2][c + 1][a], sref[sk][2][c][a + 1],
-                                            sref[sk][2][c][a]);
-            } else {
-                horizontal_edge(q - NEZ, k + 1, 1 - lo, false);
-            }
+    auto cfl = [&]() {
+        const double bcc[3] = {0.5 * (s_bx[t] + s_bx[t + 1]), 0.5 * (s_by[t] + s_by[t + CX]), bcz};
+        mcfl = fmax(mcfl, cell_cfl(g, u[0], u[1], u[2], u[3], u[4], bcc, stcfl));
+    };
+    for (int m = k0 - 1; m <= k1; ++m) {
+        const int hi = m & 1, lo = hi ^ 1;
+        pin(op), pin(oc), pin(ox), pin(oy), pin(fxo), pin(fyo), pin(fzo);
+        // (A)
+        const double xz = em[0], xy = em[1], yx = em[2], yz = em[3], zy = em[4], zx = em[5];
+        const int sx = sg[0], sy = sg[1], sz = sg[2];
+        const double bx0 = bf[0], by0 = bf[1], bz0 = bf[2];
+        if (live) {
+            s_rx[hi][t] = -(w[1] * w[5] - w[2] * w[4]);
+            s_ry[hi][t] = -(w[2] * w[3] - w[0] * w[5]);
+            s_rz[t] = -(w[0] * w[4] - w[1] * w[3]);
+            s_xz[t] = xz;
+            s_yz[t] = yz;
+            s_zy[t] = zy;
+            s_zx[t] = zx;
+            s_sx[t] = (int8_t)sx;
+            s_sy[t] = (int8_t)sy;
+            s_sz[t] = (int8_t)sz;
         }
         __syncthreads();
-        const int hi = 1 - lo;
-        double bzn = 0.0;
-        if (i < ex && j < ey) {
-            if (i < nx && j < ny) {
-                const idx_t c = cell_store(g, i, j, k);
-                const idx_t fx0 = fidx(g, 0, i, j, k), fx1 = fidx(g, 0, i + 1, j, k);
-                const idx_t fy0 = fidx(g, 1, i, j, k), fy1 = fidx(g, 1, i, j + 1, k);
-                const idx_t fz1 = fidx(g, 2, i, j, k + 1);
-                double fzn[5];
+        // (C)
+        if (DT && interior && m > k0 + 1) cfl();
+        if (edge) {
+            // E_z at (ii - 1/2, jj - 1/2, m): x-faces here and at jj - 1, y-faces here and at ii - 1
+            s_ez[t] = edge_combine(xz, s_xz[ly], yz, s_yz[lx], sx, s_sx[ly], sy, s_sy[lx], s_rz[t],
+                                   s_rz[lx], s_rz[ly], s_rz[ly - 1]);
+            // E_x at (ii, jj - 1/2, m - 1/2): y-faces of planes m, m - 1, z-faces here and at jj - 1
+            s_ex[hi][t] = edge_combine(yx, yx_p, zx, s_zx[ly], sy, sy_p, sz, s_sz[ly], s_rx[hi][t],
+                                       s_rx[hi][ly], s_rx[lo][t], s_rx[lo][ly]);
+            // E_y at (ii - 1/2, jj, m - 1/2): z-faces here and at ii - 1, x-faces of planes m, m - 1
+            s_ey[hi][t] = edge_combine(zy, s_zy[lx], xy, xy_p, sz, s_sz[lx], sx, sx_p, s_ry[hi][t],
+                                       s_ry[lo][t], s_ry[hi][lx], s_ry[lo][lx]);
+        }
+        xy_p = xy;
+        yx_p = yx;
+        sx_p = sx;
+        sy_p = sy;
+        // the next plane, behind the updates (and not above the edge work, whose
+        // registers it would take)
+        __builtin_amdgcn_sched_barrier(0);
+        if (m < k1) load_plane(m + 1);
+        __syncthreads();
+        // (D)
+        const idx_t k = m - 1;
+        if (DT && interior && m > k0) {
 #pragma unroll
-                for (int q = 0; q < 5; ++q) fzn[q] = F.f[2][q][fz1];
-                const double dxr = F.f[0][0][fx1] - F.f[0][0][fx0];
-                const double dyr = F.f[1][0][fy1] - F.f[1][0][fy0];
-                const double dzr = fzn[0] - fzc[0];
-                const double dxe = F.f[0][4][fx1] - F.f[0][4][fx0];
-                const double dye = F.f[1][4][fy1] - F.f[1][4][fy0];
-                const double dze = fzn[4] - fzc[4];
-                const double dxmx = F.f[0][1][fx1] - F.f[0][1][fx0];
-                const double dxmy = F.f[0][2][fx1] - F.f[0][2][fx0];
-                const double dxmz = F.f[0][3][fx1] - F.f[0][3][fx0];
-                const double dymy = F.f[1][1][fy1] - F.f[1][1][fy0];
-                const double dymz = F.f[1][2][fy1] - F.f[1][2][fy0];
-                const double dymx = F.f[1][3][fy1] - F.f[1][3][fy0];
-                const double dzmz = fzn[1] - fzc[1];
-                const double dzmx = fzn[2] - fzc[2];
-                const double dzmy = fzn[3] - fzc[3];
-#pragma unroll
-                for (int q = 0; q < 5; ++q) fzc[q] = fzn[q];
-                const double u0 = base.u[0][c] - cx * dxr - cy * dyr - cz * dzr;
-                const double u1 = base.u[1][c] - cx * dxmx - cy * dymx - cz * dzmx;
-                const double u2 = base.u[2][c] - cx * dxmy - cy * dymy - cz * dzmy;
-                const double u3 = base.u[3][c] - cx * dxmz - cy * dymz - cz * dzmz;
-                const double u4 = base.u[4][c] - cx * dxe - cy * dye - cz * dze;
-                out.u[0][c] = u0;
-                out.u[1][c] = u1;
-                out.u[2][c] = u2;
-                out.u[3][c] = u3;
-                out.u[4][c] = u4;
-                if (FULL) bad |= !isfinite(u0) || !isfinite(u1) || !isfinite(u2) || !isfinite(u3) ||
-                                 !isfinite(u4);
-                if (DT) {
-                    // faces (i, j, k) low and high of the updated cell (a periodic
-                    // high face through the face map, as its owner computes it)
-                    const double bx0 = base.b[0][face_store(g, 0, i, j, k)]
-                                       - cy * (sez[ty + 1][tx] - sez[ty][tx])
-                                       + cz * (sey[hi][ty][tx] - sey[lo][ty][tx]);
-                    const double bx1 = base.b[0][face_store(g, 0, map_face(i + 1, nx, g.bc[0]), j, k)]
-                                       - cy * (sez[ty + 1][tx + 1] - sez[ty][tx + 1])
-                                       + cz * (sey[hi][ty][tx + 1] - sey[lo][ty][tx + 1]);
-                    const double by0 = base.b[1][face_store(g, 1, i, j, k)]
-                                       + cx * (sez[ty][tx + 1] - sez[ty][tx])
-                                       - cz * (sex[hi][ty][tx] - sex[lo][ty][tx]);
-                    const double by1 = base.b[1][face_store(g, 1, i, map_face(j + 1, ny, g.bc[1]), k)]
-                                       + cx * (sez[ty + 1][tx + 1] - sez[ty + 1][tx])
-                                       - cz * (sex[hi][ty + 1][tx] - sex[lo][ty + 1][tx]);
-                    const double bz0 = bzc
-                                       - cx * (sey[lo][ty][tx + 1] - sey[lo][ty][tx])
-                                       + cy * (sex[lo][ty + 1][tx] - sex[lo][ty][tx]);
-                    bzn = base.b[2][face_store(g, 2, i, j, map_face(k + 1, nz, g.bc[2]))];
-                    const double bz1 = bzn
-                                       - cx * (sey[hi][ty][tx + 1] - sey[hi][ty][tx])
-                                       + cy * (sex[hi][ty + 1][tx] - sex[hi][ty][tx]);
-                    const double bcc[3] = {0.5 * (bx0 + bx1), 0.5 * (by0 + by1), 0.5 * (bz0 + bz1)};
-                    mcfl = fmax(mcfl, cell_cfl(g, u0, u1, u2, u3, u4, bcc, stcfl));
+            for (int q = 0; q < 5; ++q) u[q] = ld8(out.u[q] + k * sc, oc);
+        }
+        double bzn = any_value();
+        if (interior) {
+            bzn = bz0 - cx * (s_ey[hi][t + 1] - s_ey[hi][t]) + cy * (s_ex[hi][t + CX] - s_ex[hi][t]);
+            if (m >= k0 && (m < k1 || (m == nz && g.bc[2] == VLCT_BC_OUTFLOW))) {
+                st8(out.b[2] + m * sc, oc, bzn);
+                if (g.bc[2] == VLCT_BC_PERIODIC && m == 0) st8(out.b[2] + nz * sc, oc, bzn);
+                bad |= !isfinite(bzn);
+            }
+            bcz = 0.5 * (bzp + bzn);
+        }
+        if (m > k0) {
+            if (xface) {  // face x (ii - 1/2, jj, k)
+                const double v = bxp + cz * (s_ey[hi][t] - s_ey[lo][t]);
+                if (DT) s_bx[t] = v;
+                if (own) {
+                    st8(out.b[0] + k * sbx, ox, v);
+                    if (g.bc[0] == VLCT_BC_PERIODIC && ii == 0) st8(out.b[0] + k * sbx, ox + 8u * (u32)nx, v);
+                    bad |= !isfinite(v);
                 }
             }
-            if (j < ny) {  // face x (i-1/2, j, k)
-                const double b0 = base.b[0][face_store(g, 0, i, j, k)];
-                const double v = b0 - cy * (sez[ty + 1][tx] - sez[ty][tx])
-                                 + cz * (sey[hi][ty][tx] - sey[lo][ty][tx]);
-                out.b[0][face_store(g, 0, i, j, k)] = v;
-                if (g.bc[0] == VLCT_BC_PERIODIC && i == 0) out.b[0][face_store(g, 0, nx, j, k)] = v;
-                if (FULL) bad |= !isfinite(v);
-            }
-            if (i < nx) {  // face y (i, j-1/2, k)
-                const double b0 = base.b[1][face_store(g, 1, i, j, k)];
-                const double v = b0 + cx * (sez[ty][tx + 1] - sez[ty][tx])
-                                 - cz * (sex[hi][ty][tx] - sex[lo][ty][tx]);
-                out.b[1][face_store(g, 1, i, j, k)] = v;
-                if (g.bc[1] == VLCT_BC_PERIODIC && j == 0) out.b[1][face_store(g, 1, i, ny, k)] = v;
-                if (FULL) bad |= !isfinite(v);
-            }
-            if (i < nx && j < ny) {  // face z (i, j, k-1/2)
-                const double b0 = DT ? bzc : base.b[2][face_store(g, 2, i, j, k)];
-                const double v = b0 - cx * (sey[lo][ty][tx + 1] - sey[lo][ty][tx])
-                                 + cy * (sex[lo][ty + 1][tx] - sex[lo][ty][tx]);
-                out.b[2][face_store(g, 2, i, j, k)] = v;
-                if (g.bc[2] == VLCT_BC_PERIODIC && k == 0) out.b[2][face_store(g, 2, i, j, nz)] = v;
-                if (FULL) bad |= !isfinite(v);
-                if (DT) bzc = bzn;
+            if (yface) {  // face y (ii, jj - 1/2, k)
+                const double v = byp - cz * (s_ex[hi][t] - s_ex[lo][t]);
+                if (DT) s_by[t] = v;
+                if (own) {
+                    st8(out.b[1] + k * sby, oy, v);
+                    if (g.bc[1] == VLCT_BC_PERIODIC && jj == 0)
+                        st8(out.b[1] + k * sby, oy + 8u * (u32)(nx * ny), v);
+                    bad |= !isfinite(v);
+                }
             }
         }
-        if (k + 2 <= k1) stage_ref(k + 2);
+        // start plane m
+        if (xface) bxp = bx0 - cy * (s_ez[t + CX] - s_ez[t]);
+        if (yface) byp = by0 + cx * (s_ez[t + 1] - s_ez[t]);
+        bzp = bzn;
+    }
+    if (DT) {
         __syncthreads();
-        lo = hi;
+        if (interior) cfl();
     }
-    // the top z faces of an outflow axis, from the last plane of edges
-    if (k1 == nz && g.bc[2] == VLCT_BC_OUTFLOW && i < nx && j < ny && i < ex && j < ey) {
-        const double b0 = base.b[2][face_store(g, 2, i, j, nz)];
-        const double v = b0 - cx * (sey[lo][ty][tx + 1] - sey[lo][ty][tx])
-                         + cy * (sex[lo][ty + 1][tx] - sex[lo][ty][tx]);
-        out.b[2][face_store(g, 2, i, j, nz)] = v;
-        if (FULL) bad |= !isfinite(v);
-    }
-    if (FULL && bad && status) atomicOr(status, kStatusNonfinite);
+    if (bad && status) atomicOr(status, kStatusNonfinite);
     if (DT) {
         if (stcfl && status) atomicOr(status, stcfl);
-        __shared__ double red[(TX * TY) / 64];
-        const double m = wave_max(mcfl);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+        __shared__ double red[N / 64];
+        const double mx = wave_max(mcfl);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
         __syncthreads();
         if (threadIdx.x == 0) {
             double r = red[0];
-            for (int q = 1; q < (TX * TY) / 64; ++q) r = fmax(r, red[q]);
+            for (int q = 1; q < N / 64; ++q) r = fmax(r, red[q]);
             partial[b] = r;
         }
     }
@@ -812,10 +766,6 @@ __device__ __forceinline__ void ct_body(const Geom &g, const Prims &P, const Flu
 // ---------------------------------------------------------------------------
 constexpr int kPredThreads = 512;
 
-// some value, without an instruction to set it: for registers that lanes
-// without a part in a step leave unused
-__device__ __forceinline__ double any_value() { return __builtin_nondeterministic_value(0.0); }
-
 // side0..2 (optional): the upwind side of every interior face, tape layout;
 // a run-time choice of one kernel, so a taped step runs the very code of a
 // plain one.  P: the half-step primitives of the interior cells are written
@@ -853,7 +803,7 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
     const int chunk = g.pred_chunk > 0 ? g.pred_chunk : H;
     if (!ONE_RUN && (idx_t)b * chunk >= npos) return;
     const double dt = 0.5 * dt_dev[0];
-    const double cx = dt / g.dl[0], cy = dt / g.dl[1], cz = dt / g.dl[2];
+    const double cx = uniform(dt / g.dl[0]), cy = uniform(dt / g.dl[1]), cz = uniform(dt / g.dl[2]);
 
     // this thread's column: (a, c) in the tile with its ring
     const int t = threadIdx.x;
@@ -875,10 +825,10 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
         const int mi = map_cell(ii, nx, g.bc[0]), mj = map_cell(jj, ny, g.bc[1]);
         const int fi0 = map_face(ii, nx, g.bc[0]), fi1 = map_face(ii + 1, nx, g.bc[0]);
         const int fj0 = map_face(jj, ny, g.bc[1]), fj1 = map_face(jj + 1, ny, g.bc[1]);
-        const u32 oc = 8u * (u32)(mj * nx + mi);
-        const u32 ox0 = 8u * (u32)(mj * (nx + 1) + fi0), ox1 = 8u * (u32)(mj * (nx + 1) + fi1);
-        const u32 oy0 = 8u * (u32)(fj0 * nx + mi), oy1 = 8u * (u32)(fj1 * nx + mi);
-        const u32 op = 8u * (u32)((jj + kGhost) * g.p[0] + ii + kGhost);
+        u32 oc = 8u * (u32)(mj * nx + mi);
+        u32 ox0 = 8u * (u32)(mj * (nx + 1) + fi0), ox1 = 8u * (u32)(mj * (nx + 1) + fi1);
+        u32 oy0 = 8u * (u32)(fj0 * nx + mi), oy1 = 8u * (u32)(fj1 * nx + mi);
+        u32 op = 8u * (u32)((jj + kGhost) * g.p[0] + ii + kGhost);
         const idx_t sc = (idx_t)nx * ny, sbx = (idx_t)(nx + 1) * ny, sby = (idx_t)nx * (ny + 1);
         const idx_t sp = (idx_t)g.p[0] * g.p[1];
         // the primitives' and the output cells' arrays are equally spaced in
@@ -912,6 +862,7 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
         if (live) load_plane(k0 - 1);
         for (int m = k0 - 1; m <= k1; ++m) {
             const int hi = m & 1, lo = hi ^ 1;  // slots of the half planes m -+ 1/2
+            pin(oc), pin(ox0), pin(ox1), pin(oy0), pin(oy1), pin(op);
             // (A)
             double u0[5], bx0 = any_value(), bx1 = any_value(), by0 = any_value(), by1 = any_value();
             double bz0 = any_value();
@@ -1179,42 +1130,28 @@ __global__ void __launch_bounds__(kBlock) k_prims(Geom g, StateP s, Prims P, uin
     prims_body(g, s, P, status, xcd_block(nblk_prims(g)));
 }
 
-template <int D>
-__global__ void __launch_bounds__(kBlock) k_flux(Geom g, StateP s, Prims P, Flux F)
-{
-    flux_pcm_body<D>(g, s, P, F, xcd_block(nblk_flux(g, D)));
-}
-
 template <int RECON>
 __global__ void __launch_bounds__(kBlock) k_flux_recon_x(Geom g, StateP s, Prims P, Flux F,
-                                                          uint32_t *status)
+                                                          StateP base, StateW out,
+                                                          const double *dt_dev, uint32_t *status)
 {
-    recon_x_body<RECON>(g, s, P, F, status, xcd_block(nblk_row(g)));
+    recon_x_body<RECON>(g, s, P, F, base, out, dt_dev, status, xcd_block(nblk_row(g)));
 }
 
-template <int D, int RECON, int M = kMarch>
-__global__ void __launch_bounds__(kBlock) k_flux_recon_march(Geom g, StateP s, Prims P, Flux F,
+template <int D, int RECON>
+__global__ void __launch_bounds__(kBlock, Recon<RECON>::kWaves) k_flux_recon_march(Geom g, StateP s, Prims P, Flux F,
+                                                              StateW out, const double *dt_dev,
                                                               uint32_t *status)
 {
-    march_body<D, RECON, M>(g, s, P, F, status, xcd_block(nblk_march(g, D, M)));
+    march_body<D, RECON>(g, s, P, F, out, dt_dev, status, xcd_block(nblk_march(g, D)));
 }
 
-// march segment of a single step's corrector: 16 faces, or 8 when the
-// 16-face launch would have fewer than 1024 blocks (4 per CU)
-static int march_segment(const Geom &g, int d)
+template <bool DT>
+__global__ void __launch_bounds__(kCtThreads, 4) k_ct_update(Geom g, Prims P, Flux F, StateP base,
+                                                             StateW out, const double *dt_dev,
+                                                             uint32_t *status, double *partial)
 {
-    const int o = tile_override("march");
-    if (o == 8 || o == kMarch) return o;
-    return nblk_march(g, d, kMarch) < 1024 ? 8 : kMarch;
-}
-
-template <bool FULL, bool DT = false>
-__global__ void __launch_bounds__(kCt, 4) k_ct_update(Geom g, Prims P, Flux F, StateP base,
-                                                       StateW out, const double *dt_dev,
-                                                       uint32_t *status, double *partial)
-{
-    ct_body<FULL, kTx, kTy, DT>(g, P, F, base, out, dt_dev, status, xcd_block(nblk_ct(g)),
-                                partial);
+    ct_body<DT>(g, P, F, base, out, dt_dev, status, xcd_block(nblk_ct(g)), partial);
 }
 
 static_assert(kPredThreads * kPredBlocksPerCU <= 1024,
@@ -1267,22 +1204,8 @@ __global__ void __launch_bounds__(kBlock) k_dt_partial(Geom g, StateP s, double 
 // body as the single-instance kernel, so an instance's result equals its
 // single-instance step bit for bit.
 // ---------------------------------------------------------------------------
-// launches of a batched step; the march and CT launches come once per tile
-// variant (an instance has blocks only in the slot of its own variant)
-enum Slot {
-    kSlotPred,
-    kSlotGhost,
-    kSlotPrims,
-    kSlotFlux0,
-    kSlotFlux1,
-    kSlotFlux2,
-    kSlotRow,
-    kSlotMarch1,
-    kSlotMarch2 = kSlotMarch1 + kMarchVariants,
-    kSlotCt = kSlotMarch2 + kMarchVariants,
-    kSlotDt = kSlotCt + kCtVariants,
-    kSlots
-};
+// launches of a batched step
+enum Slot { kSlotPred, kSlotGhost, kSlotRow, kSlotMarch1, kSlotMarch2, kSlotCt, kSlotDt, kSlots };
 
 struct Inst {
     Geom g;
@@ -1370,38 +1293,6 @@ __global__ void __launch_bounds__(kBlock) kb_prims_ghost(const Inst *tab, int co
     prims_ghost_body(g, st, P, I.status, lb);
 }
 
-// half = 0: primitives of U^n, 1: of U^{n+1/2}
-__global__ void __launch_bounds__(kBlock) kb_prims(const Inst *tab, int count, idx_t total,
-                                                   int half)
-{
-    const idx_t gb = xcd_block(total);
-    if (gb >= total) return;
-    idx_t lb;
-    const Inst &I = find_inst(tab, count, kSlotPrims, gb, lb);
-    if (retired(I)) return;
-    const Geom g = I.g;
-    const StateP st = half ? const_view(I.half) : I.in;
-    const Prims P = I.P;
-    prims_body(g, st, P, I.status, lb);
-}
-
-// half = 0: predictor on U^n, 1: PCM corrector on U^{n+1/2}
-template <int D>
-__global__ void __launch_bounds__(kBlock) kb_flux_pcm(const Inst *tab, int count, idx_t total,
-                                                      int half)
-{
-    const idx_t gb = xcd_block(total);
-    if (gb >= total) return;
-    idx_t lb;
-    const Inst &I = find_inst(tab, count, kSlotFlux0 + D, gb, lb);
-    if (retired(I)) return;
-    const Geom g = I.g;
-    const StateP st = half ? const_view(I.half) : I.in;
-    const Prims P = I.P;
-    const Flux F = I.F;
-    flux_pcm_body<D>(g, st, P, F, lb);
-}
-
 template <int RECON>
 __global__ void __launch_bounds__(kBlock) kb_recon_x(const Inst *tab, int count, idx_t total)
 {
@@ -1411,41 +1302,38 @@ __global__ void __launch_bounds__(kBlock) kb_recon_x(const Inst *tab, int count,
     const Inst &I = find_inst(tab, count, kSlotRow, gb, lb);
     if (retired(I)) return;
     const Geom g = I.g;
-    const StateP st = const_view(I.half);
     const Prims P = I.P;
     const Flux F = I.F;
-    recon_x_body<RECON>(g, st, P, F, I.status, lb);
+    recon_x_body<RECON>(g, const_view(I.half), P, F, I.in, I.out, I.dt, I.status, lb);
 }
 
-template <int D, int RECON, int V>
-__global__ void __launch_bounds__(kBlock) kb_march(const Inst *tab, int count, idx_t total)
+template <int D, int RECON>
+__global__ void __launch_bounds__(kBlock, Recon<RECON>::kWaves) kb_march(const Inst *tab, int count, idx_t total)
 {
     const idx_t gb = xcd_block(total);
     if (gb >= total) return;
     idx_t lb;
-    const Inst &I = find_inst(tab, count, (D == 1 ? kSlotMarch1 : kSlotMarch2) + V, gb, lb);
+    const Inst &I = find_inst(tab, count, D == 1 ? kSlotMarch1 : kSlotMarch2, gb, lb);
     if (retired(I)) return;
     const Geom g = I.g;
-    const StateP st = const_view(I.half);
     const Prims P = I.P;
     const Flux F = I.F;
-    march_body<D, RECON, march_len(V)>(g, st, P, F, I.status, lb);
+    march_body<D, RECON>(g, const_view(I.half), P, F, I.out, I.dt, I.status, lb);
 }
 
-template <bool FULL, int V>
-__global__ void __launch_bounds__(kCt, 4) kb_ct(const Inst *tab, int count, idx_t total)
+// DT: the CFL maxima of the new state ride along, one per block
+template <bool DT>
+__global__ void __launch_bounds__(kCtThreads, 4) kb_ct(const Inst *tab, int count, idx_t total)
 {
     const idx_t gb = xcd_block(total);
     if (gb >= total) return;
     idx_t lb;
-    const Inst &I = find_inst(tab, count, kSlotCt + V, gb, lb);
+    const Inst &I = find_inst(tab, count, kSlotCt, gb, lb);
     if (retired(I)) return;
     const Geom g = I.g;
     const Prims P = I.P;
     const Flux F = I.F;
-    const StateP base = I.in;
-    const StateW out = FULL ? I.out : I.half;
-    ct_body<FULL, ct_tx(V), ct_ty(V)>(g, P, F, base, out, I.dt, I.status, lb);
+    ct_body<DT>(g, P, F, I.in, I.out, I.dt, I.status, lb, I.partial);
 }
 
 __global__ void __launch_bounds__(kBlock) kb_dt_partial(const Inst *tab, int count, idx_t total)
@@ -1460,13 +1348,14 @@ __global__ void __launch_bounds__(kBlock) kb_dt_partial(const Inst *tab, int cou
     dt_partial_body(g, const_view(I.out), I.partial, I.status, lb);
 }
 
-// one block per instance: dt = cfl / max over that instance's partials; an
-// instance with an end time also advances its time by the step it took
-__global__ void __launch_bounds__(1024) kb_dt_final(const Inst *tab)
+// one block per instance: dt = cfl / max over that instance's partials (of the
+// CT blocks, or of kb_dt_partial); an instance with an end time also advances
+// its time by the step it took
+__global__ void __launch_bounds__(1024) kb_dt_final(const Inst *tab, bool ct)
 {
     const Inst &I = tab[blockIdx.x];
     if (retired(I)) return;
-    const int n = (int)nblk_dt(I.g);
+    const int n = (int)(ct ? nblk_ct(I.g) : nblk_dt(I.g));
     __shared__ double red[1024 / 64];
     double m = 0.0;
     for (int q = threadIdx.x; q < n; q += blockDim.x) m = fmax(m, I.partial[q]);
@@ -1502,9 +1391,22 @@ __global__ void kb_clip(int count, const double *dt, const double *t, const doub
 
 
 struct Layout {
-    size_t half[8], prims, flux[3], partial, total;
+    size_t half[8], prims, flux[3], partial, ct_partial, total;
     size_t prims_len, flux_len[3], npartial;
 };
+
+// partials the layout has always left room for (CT blocks of 64 x 8 columns and
+// 4 to 32 planes): kept as the size is, so that workspace and scratch checks
+// answer as before
+static size_t partial_room(const Geom &g)
+{
+    const size_t cols = (size_t)((g.n[0] + (g.bc[0] == VLCT_BC_OUTFLOW) + 63) / 64) *
+                        ((g.n[1] + (g.bc[1] == VLCT_BC_OUTFLOW) + 7) / 8);
+    auto blocks = [&](int p) { return cols * ((g.n[2] + p - 1) / p); };
+    int p = 32;
+    while (p > 8 && blocks(p) < 1024) p /= 2;
+    return blocks(p == 8 && blocks(8) < 256 ? 4 : p);
+}
 
 static Layout layout(const Geom &g)
 {
@@ -1525,8 +1427,9 @@ static Layout layout(const Geom &g)
     const size_t N = (size_t)g.n[0] * g.n[1] * g.n[2];
     L.npartial = (N + kBlock - 1) / kBlock;  // partials of the CFL kernel
     L.partial = off;
-    // room also for one partial per CT block (the CFL reduction fused into the full step)
-    off += align_up(std::max<size_t>(L.npartial, (size_t)nblk_ct(g)) * sizeof(double));
+    off += align_up(std::max(L.npartial, partial_room(g)) * sizeof(double));
+    // one partial per CT block goes to the x axis' spare flux components
+    L.ct_partial = L.flux[0] + 2 * align_up(L.flux_len[0] * sizeof(double));
     L.total = off;
     return L;
 }
@@ -1558,7 +1461,7 @@ struct Bound {
     Prims P;
     Flux F;
     StateW half;
-    double *partial;
+    double *partial, *ct_partial;  // CFL maxima per block of k_dt_partial, of the CT update
 };
 
 static Bound bind(const Layout &L, void *ws)
@@ -1573,6 +1476,7 @@ static Bound bind(const Layout &L, void *ws)
         B.P.w[f] = reinterpret_cast<double *>(b + L.prims + f * align_up(L.prims_len * sizeof(double)));
     B.F = bind_flux(b, L.flux, L.flux_len);
     B.partial = reinterpret_cast<double *>(b + L.partial);
+    B.ct_partial = reinterpret_cast<double *>(b + L.ct_partial);
     return B;
 }
 
@@ -1586,67 +1490,48 @@ int launch_prims(const Geom &g, const StateP &st, const Prims &P, uint32_t *stat
     return hipGetLastError() == hipSuccess ? VLCT_OK : VLCT_EHIP;
 }
 
-// face fluxes of a stage from its primitives P (and its stored face fields)
 int launch_fluxes(const Geom &g, const StateP &st, const Prims &P, const Flux &F, int recon,
-                  uint32_t *status, hipStream_t s)
+                  const StateP &base, const StateW &out, const double *dt_dev, uint32_t *status,
+                  hipStream_t s)
 {
-    if (recon == VLCT_RECON_PCM) {
-        // one thread per face
-#define VLCT_FLUX(D)                                                                      \
-    {                                                                                     \
-        Observe o(VLCT_KERNEL_FLUX_PCM, s);                                               \
-        k_flux<D><<<xcd_grid(nblk_flux(g, D)), kBlock, 0, s>>>(g, st, P, F);             \
-    }
-        VLCT_FLUX(0) VLCT_FLUX(1) VLCT_FLUX(2)
-#undef VLCT_FLUX
-    } else {
-        // one reconstruction per cell and axis, x by rows, y and z by column marches
-        const int kid = VLCT_KERNEL_FLUX_RECON;
+    const int kid = recon == VLCT_RECON_PCM ? VLCT_KERNEL_FLUX_PCM : VLCT_KERNEL_FLUX_RECON;
 #define VLCT_RECON3(R)                                                                        \
     {                                                                                         \
-        { Observe o(kid, s); k_flux_recon_x<R><<<xcd_grid(nblk_row(g)), kBlock, 0, s>>>(g, st, P, F, status); } \
-        { Observe o(kid, s);                                                                  \
-          if (march_segment(g, 1) == 8)                                                        \
-              k_flux_recon_march<1, R, 8><<<xcd_grid(nblk_march(g, 1, 8)), kBlock, 0, s>>>(g, st, P, F, status); \
-          else                                                                                 \
-              k_flux_recon_march<1, R><<<xcd_grid(nblk_march(g, 1)), kBlock, 0, s>>>(g, st, P, F, status); } \
-        { Observe o(kid, s);                                                                  \
-          if (march_segment(g, 2) == 8)                                                        \
-              k_flux_recon_march<2, R, 8><<<xcd_grid(nblk_march(g, 2, 8)), kBlock, 0, s>>>(g, st, P, F, status); \
-          else                                                                                 \
-              k_flux_recon_march<2, R><<<xcd_grid(nblk_march(g, 2)), kBlock, 0, s>>>(g, st, P, F, status); } \
+        { Observe o(kid, s); k_flux_recon_x<R><<<xcd_grid(nblk_row(g)), kBlock, 0, s>>>(g, st, P, F, base, out, dt_dev, status); } \
+        { Observe o(kid, s); k_flux_recon_march<1, R><<<xcd_grid(nblk_march(g, 1)), kBlock, 0, s>>>(g, st, P, F, out, dt_dev, status); } \
+        { Observe o(kid, s); k_flux_recon_march<2, R><<<xcd_grid(nblk_march(g, 2)), kBlock, 0, s>>>(g, st, P, F, out, dt_dev, status); } \
     }
-        switch (recon) {
-        case VLCT_RECON_PLMC: VLCT_RECON3(VLCT_RECON_PLMC) break;
-        case VLCT_RECON_PPMC: VLCT_RECON3(VLCT_RECON_PPMC) break;
-        case VLCT_RECON_PLMP: VLCT_RECON3(VLCT_RECON_PLMP) break;
-        default: VLCT_RECON3(VLCT_RECON_PPMP) break;
-        }
+    switch (recon) {
+    case VLCT_RECON_PCM: VLCT_RECON3(VLCT_RECON_PCM) break;
+    case VLCT_RECON_PLMC: VLCT_RECON3(VLCT_RECON_PLMC) break;
+    case VLCT_RECON_PPMC: VLCT_RECON3(VLCT_RECON_PPMC) break;
+    case VLCT_RECON_PLMP: VLCT_RECON3(VLCT_RECON_PLMP) break;
+    default: VLCT_RECON3(VLCT_RECON_PPMP) break;
+    }
 #undef VLCT_RECON3
-    }
     return hipGetLastError() == hipSuccess ? VLCT_OK : VLCT_EHIP;
 }
 
-// CT edge fields + update: full = false is the half step into `out` (Steps
-// 4-5), full = true the full step from `base` (Steps 8-9)
-int launch_ct(const Geom &g, bool full, const Prims &P, const Flux &F, const StateP &base,
-              const StateW &out, const double *dt_dev, uint32_t *status, hipStream_t s)
+// the full step's CT edge fields and faces (Steps 8-9); with `partial` the CFL
+// maxima of the new state, one per block
+static int launch_ct(const Geom &g, const Prims &P, const Flux &F, const StateP &base,
+                     const StateW &out, const double *dt_dev, uint32_t *status, double *partial,
+                     hipStream_t s)
 {
-    Observe o(full ? VLCT_KERNEL_UPDATE_FULL : VLCT_KERNEL_UPDATE_HALF, s);
-    if (full)
-        k_ct_update<true><<<xcd_grid(nblk_ct(g)), kCt, 0, s>>>(g, P, F, base, out, dt_dev, status,
-                                                               nullptr);
+    Observe o(VLCT_KERNEL_UPDATE_FULL, s);
+    if (partial)
+        k_ct_update<true><<<xcd_grid(nblk_ct(g)), kCtThreads, 0, s>>>(g, P, F, base, out, dt_dev,
+                                                                     status, partial);
     else
-        k_ct_update<false><<<xcd_grid(nblk_ct(g)), kCt, 0, s>>>(g, P, F, base, out, dt_dev,
-                                                                status, nullptr);
+        k_ct_update<false><<<xcd_grid(nblk_ct(g)), kCtThreads, 0, s>>>(g, P, F, base, out, dt_dev,
+                                                                      status, nullptr);
     return hipGetLastError() == hipSuccess ? VLCT_OK : VLCT_EHIP;
 }
 
 // the whole predictor (Steps 2-5) in one kernel: U^n -> U^{n+1/2}; with
 // `side` (3 arrays, tape layout) it also records the faces' upwind sides
-static int launch_pred(const Geom &g, const StateP &st, const StateW &half, const Prims &P,
-                       const double *dt_dev, uint32_t *status, uint8_t *const *side,
-                       hipStream_t s)
+int launch_pred(const Geom &g, const StateP &st, const StateW &half, const Prims &P,
+                const double *dt_dev, uint32_t *status, uint8_t *const *side, hipStream_t s)
 {
     {
         Observe o(VLCT_KERNEL_PREDICTOR, s);
@@ -1663,22 +1548,6 @@ static int launch_pred(const Geom &g, const StateP &st, const StateW &half, cons
     Observe o(VLCT_KERNEL_PRIMS, s);
     k_prims_ghost<<<xcd_grid((ghost_cells(g) + kBlock - 1) / kBlock), kBlock, 0, s>>>(
         g, as_const(half), P, status);
-    return hipGetLastError() == hipSuccess ? VLCT_OK : VLCT_EHIP;
-}
-
-// the full step's CT update with the CFL reduction of the new state fused in
-// (one partial per CT block), then the final reduction into dt_out
-static int launch_ct_dt(const Geom &g, const Prims &P, const Flux &F, const StateP &base,
-                        const StateW &out, const double *dt_dev, uint32_t *status,
-                        double *partial, double *dt_out, hipStream_t s)
-{
-    {
-        Observe o(VLCT_KERNEL_UPDATE_FULL, s);
-        k_ct_update<true, true><<<xcd_grid(nblk_ct(g)), kCt, 0, s>>>(g, P, F, base, out, dt_dev,
-                                                                     status, partial);
-    }
-    Observe o(VLCT_KERNEL_DT_FINAL, s);
-    k_dt_final<<<1, 1024, 0, s>>>(partial, (int)nblk_ct(g), g.cfl, dt_out);
     return hipGetLastError() == hipSuccess ? VLCT_OK : VLCT_EHIP;
 }
 
@@ -1711,6 +1580,25 @@ static int launch_dt(const Geom &g, const StateP &st, const Bound &B, const Layo
     return hipGetLastError() == hipSuccess ? VLCT_OK : VLCT_EHIP;
 }
 
+// the corrector (Steps 6-9) from the half-step state and its primitives in
+// B.P, then the next CFL step: its reduction rides on the CT update unless the
+// step is in place (it reads the base field on faces that other threads update)
+static int corrector(const Geom &g, int recon, const StateP &half, const Bound &B, const Layout &L,
+                     const StateP &base, const StateW &out, bool inplace, const double *dt_dev,
+                     double *next_dt, uint32_t *status, uint8_t *const *side, hipStream_t s)
+{
+    const bool ride = next_dt && !inplace;
+    int rc = launch_fluxes(g, half, B.P, B.F, recon, base, out, dt_dev, status, s);
+    if (!rc)
+        rc = launch_ct(g, B.P, B.F, base, out, dt_dev, status, ride ? B.ct_partial : nullptr, s);
+    if (!rc && side) rc = launch_pack_sides(g, B.F, side, s);
+    if (rc || !next_dt) return rc;
+    if (!ride) return launch_dt(g, as_const(out), B, L, next_dt, status, s);
+    Observe o(VLCT_KERNEL_DT_FINAL, s);
+    k_dt_final<<<1, 1024, 0, s>>>(B.ct_partial, (int)nblk_ct(g), g.cfl, next_dt);
+    return hipGetLastError() == hipSuccess ? VLCT_OK : VLCT_EHIP;
+}
+
 constexpr int kMaxBatch = 1 << 16;
 
 // the instance table, then the clipped dt and active flag of every instance
@@ -1731,19 +1619,34 @@ static int *batch_active(void *ws, int count)
                                    align_up((size_t)count * sizeof(double)));
 }
 
+// an instance's tiles as its plan byte asks
+static void plan_tiles(Geom &g, uint8_t plan)
+{
+    const int cv = plan & 15, mv = plan >> 4;
+    if (cv > 0) {
+        g.ct_tx = cv == 1 ? 30 : 14;
+        g.ct_ty = kCtThreads / (g.ct_tx + 2) - 2;
+    }
+    g.march = march_len(mv);
+    // a 32-cell march of planes this large would leave the 32-bit offsets of
+    // march_body (same results with 16)
+    if (mv == 1 && (idx_t)g.p[0] * g.p[1] * 8 * 38 >= (idx_t)1 << 32) g.march = 16;
+}
+
 // instance records with workspace regions and flattened block offsets;
 // returns the per-slot block totals through `total`
 static void batch_records(int count, const vlct_grid *grids, const vlct_state *in,
                           const vlct_state *out, const double *dt_dev, double *next_dt_dev,
-                          uint32_t *status_dev, const uint8_t *plan, void *ws,
+                          uint32_t *status_dev, const uint8_t *plan, void *ws, bool ride,
                           std::vector<Inst> &rec, idx_t total[kSlots])
 {
     rec.resize(count);
     size_t off = batch_table_bytes(count);
     for (int s = 0; s < kSlots; ++s) total[s] = 0;
     for (int i = 0; i < count; ++i) {
-        const Geom g = make_geom(&grids[i]);
-        const Layout L = layout(g);
+        Geom g = make_geom(&grids[i]);
+        const Layout L = layout(g);  // of the unplanned geometry, as the size query counts it
+        plan_tiles(g, plan ? plan[i] : 0);
         const Bound B = bind(L, static_cast<char *>(ws) + off);
         off += L.total;
         Inst &r = rec[i];
@@ -1753,26 +1656,19 @@ static void batch_records(int count, const vlct_grid *grids, const vlct_state *i
         r.half = B.half;
         r.P = B.P;
         r.F = B.F;
-        r.partial = B.partial;
+        r.partial = ride ? B.ct_partial : B.partial;
         r.dt = dt_dev + i;
         r.next_dt = next_dt_dev ? next_dt_dev + i : nullptr;
         r.status = status_dev ? status_dev + i : nullptr;
         r.active = nullptr;
         r.t = nullptr;
-        const int cv = plan ? (plan[i] & 15) : 0;
-        int mv = plan ? (plan[i] >> 4) : 0;
-        // a 32-face march of planes this large would leave the 32-bit offsets
-        // of march_body (same results with 16)
-        if (mv == 1 && (idx_t)g.p[0] * g.p[1] * 8 * 38 >= (idx_t)1 << 32) mv = 0;
         idx_t nb[kSlots] = {};
         nb[kSlotPred] = nblk_pred_shares(g);
         nb[kSlotGhost] = (ghost_cells(g) + kBlock - 1) / kBlock;
-        nb[kSlotPrims] = nblk_prims(g);
-        for (int d = 0; d < 3; ++d) nb[kSlotFlux0 + d] = nblk_flux(g, d);
         nb[kSlotRow] = nblk_row(g);
-        nb[kSlotMarch1 + mv] = nblk_march(g, 1, march_len(mv));
-        nb[kSlotMarch2 + mv] = nblk_march(g, 2, march_len(mv));
-        nb[kSlotCt + cv] = nblk_ct(g, ct_tx(cv), ct_ty(cv));
+        nb[kSlotMarch1] = nblk_march(g, 1);
+        nb[kSlotMarch2] = nblk_march(g, 2);
+        nb[kSlotCt] = nblk_ct(g);
         nb[kSlotDt] = nblk_dt(g);
         for (int s = 0; s < kSlots; ++s) {
             r.start[s] = total[s];
@@ -1903,21 +1799,11 @@ int vlct_step(const vlct_grid *vg, const vlct_state *in, const vlct_state *out,
     const Bound B = bind(L, ws);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const StateP sin = as_const(in);
-    // predictor (Steps 2-5)
-    int rc = launch_pred(g, sin, B.half, B.P, dt_dev, status_dev, nullptr, s);
-    // corrector (Steps 6-9) on the half-step primitives the predictor left in B.P
-    const StateP half = as_const(B.half);
-    if (!rc) rc = launch_fluxes(g, half, B.P, B.F, vg->recon, status_dev, s);
+    // predictor (Steps 2-5), corrector (Steps 6-9)
+    const int rc = launch_pred(g, sin, B.half, B.P, dt_dev, status_dev, nullptr, s);
     if (rc) return rc;
-    // the CFL reduction rides on the full update unless the step is in place
-    // (it reads the base field on faces that other threads update)
-    if (next_dt_dev && !all_same)
-        return launch_ct_dt(g, B.P, B.F, sin, as_mut(out), dt_dev, status_dev, B.partial,
-                            next_dt_dev, s);
-    rc = launch_ct(g, true, B.P, B.F, sin, as_mut(out), dt_dev, status_dev, s);
-    if (rc) return rc;
-    if (next_dt_dev) return launch_dt(g, as_const(out), B, L, next_dt_dev, status_dev, s);
-    return VLCT_OK;
+    return corrector(g, vg->recon, as_const(B.half), B, L, sin, as_mut(out), all_same, dt_dev,
+                     next_dt_dev, status_dev, nullptr, s);
 }
 
 int vlct_step_noalloc(const vlct_grid *vg, const vlct_state *in, const vlct_state *out,
@@ -1964,20 +1850,10 @@ int vlct_step_taped(const vlct_grid *vg, const vlct_state *in, const vlct_state 
     const StateP sin = as_const(in);
     // the steps of vlct_step with the half-step state and both stages' upwind
     // sides kept in the tape
-    int rc = launch_pred(g, sin, half, B.P, dt_dev, status_dev, side[0], s);
-    const StateP hc = as_const(half);
-    if (!rc) rc = launch_fluxes(g, hc, B.P, B.F, vg->recon, status_dev, s);
-    if (!rc) rc = launch_pack_sides(g, B.F, side[1], s);
+    const int rc = launch_pred(g, sin, half, B.P, dt_dev, status_dev, side[0], s);
     if (rc) return rc;
-    // the CFL reduction rides on the full update unless the step is in place
-    // (it reads the base field on faces that other threads update)
-    if (next_dt_dev && !all_same)
-        return launch_ct_dt(g, B.P, B.F, sin, as_mut(out), dt_dev, status_dev, B.partial,
-                            next_dt_dev, s);
-    rc = launch_ct(g, true, B.P, B.F, sin, as_mut(out), dt_dev, status_dev, s);
-    if (rc) return rc;
-    if (next_dt_dev) return launch_dt(g, as_const(out), B, L, next_dt_dev, status_dev, s);
-    return VLCT_OK;
+    return corrector(g, vg->recon, as_const(half), B, L, sin, as_mut(out), all_same, dt_dev,
+                     next_dt_dev, status_dev, side[1], s);
 }
 
 const char *vlct_strerror(int code)
@@ -2058,7 +1934,12 @@ static int batch_step(int count, const vlct_grid *grids, const vlct_state *in,
     hipStream_t s = static_cast<hipStream_t>(stream);
     std::vector<Inst> rec;
     idx_t tot[kSlots];
-    batch_records(count, grids, in, out, dt_dev, next_dt_dev, status_dev, plan, ws, rec, tot);
+    // the CFL reduction rides on the CT update unless an instance steps in
+    // place (it reads the base field on faces that other threads update)
+    bool inplace = false;
+    for (int i = 0; i < count; ++i) inplace |= in[i].rho == out[i].rho;
+    const bool ride = next_dt_dev && !inplace;
+    batch_records(count, grids, in, out, dt_dev, next_dt_dev, status_dev, plan, ws, ride, rec, tot);
     if (t_dev) {
         double *dt_eff = batch_dt_eff(ws, count);
         int *active = batch_active(ws, count);
@@ -2089,48 +1970,37 @@ static int batch_step(int count, const vlct_grid *grids, const vlct_state *in,
         Observe o(VLCT_KERNEL_PRIMS, s);
         kb_prims_ghost<<<xcd_grid(tot[kSlotGhost]), kBlock, 0, s>>>(tab, count, tot[kSlotGhost]);
     }
-#define VLCT_BCT(FULL, V)                                                                 \
-    if (tot[kSlotCt + V]) {                                                                   \
-        Observe o(FULL ? VLCT_KERNEL_UPDATE_FULL : VLCT_KERNEL_UPDATE_HALF, s);                \
-        kb_ct<FULL, V><<<xcd_grid(tot[kSlotCt + V]), kCt, 0, s>>>(tab, count, tot[kSlotCt + V]); \
-    }
     // corrector (Steps 6-9); the predictor wrote the interior primitives
-#define VLCT_BMARCH(D, R, V)                                                                  \
-    if (tot[(D == 1 ? kSlotMarch1 : kSlotMarch2) + V]) {                                      \
-        const idx_t n = tot[(D == 1 ? kSlotMarch1 : kSlotMarch2) + V];                        \
-        Observe o(VLCT_KERNEL_FLUX_RECON, s);                                                 \
-        kb_march<D, R, V><<<xcd_grid(n), kBlock, 0, s>>>(tab, count, n);                      \
-    }
+    const int kid = recon == VLCT_RECON_PCM ? VLCT_KERNEL_FLUX_PCM : VLCT_KERNEL_FLUX_RECON;
 #define VLCT_BRECON(R)                                                                        \
     {                                                                                         \
-        { Observe o(VLCT_KERNEL_FLUX_RECON, s);                                                \
+        { Observe o(kid, s);                                                                  \
           kb_recon_x<R><<<xcd_grid(tot[kSlotRow]), kBlock, 0, s>>>(tab, count, tot[kSlotRow]); } \
-        VLCT_BMARCH(1, R, 0) VLCT_BMARCH(1, R, 1) VLCT_BMARCH(1, R, 2)                        \
-        VLCT_BMARCH(2, R, 0) VLCT_BMARCH(2, R, 1) VLCT_BMARCH(2, R, 2)                        \
+        { Observe o(kid, s);                                                                  \
+          kb_march<1, R><<<xcd_grid(tot[kSlotMarch1]), kBlock, 0, s>>>(tab, count, tot[kSlotMarch1]); } \
+        { Observe o(kid, s);                                                                  \
+          kb_march<2, R><<<xcd_grid(tot[kSlotMarch2]), kBlock, 0, s>>>(tab, count, tot[kSlotMarch2]); } \
     }
     switch (recon) {
-    case VLCT_RECON_PCM:
-        for (int d = 0; d < 3; ++d) {
-            Observe o(VLCT_KERNEL_FLUX_PCM, s);
-            const idx_t n = tot[kSlotFlux0 + d];
-            if (d == 0) kb_flux_pcm<0><<<xcd_grid(n), kBlock, 0, s>>>(tab, count, n, 1);
-            if (d == 1) kb_flux_pcm<1><<<xcd_grid(n), kBlock, 0, s>>>(tab, count, n, 1);
-            if (d == 2) kb_flux_pcm<2><<<xcd_grid(n), kBlock, 0, s>>>(tab, count, n, 1);
-        }
-        break;
+    case VLCT_RECON_PCM: VLCT_BRECON(VLCT_RECON_PCM) break;
     case VLCT_RECON_PLMC: VLCT_BRECON(VLCT_RECON_PLMC) break;
     case VLCT_RECON_PPMC: VLCT_BRECON(VLCT_RECON_PPMC) break;
     case VLCT_RECON_PLMP: VLCT_BRECON(VLCT_RECON_PLMP) break;
     default: VLCT_BRECON(VLCT_RECON_PPMP) break;
     }
 #undef VLCT_BRECON
-#undef VLCT_BMARCH
-    VLCT_BCT(true, 0) VLCT_BCT(true, 1) VLCT_BCT(true, 2)
-#undef VLCT_BCT
+    {
+        Observe o(VLCT_KERNEL_UPDATE_FULL, s);
+        if (ride)
+            kb_ct<true><<<xcd_grid(tot[kSlotCt]), kCtThreads, 0, s>>>(tab, count, tot[kSlotCt]);
+        else
+            kb_ct<false><<<xcd_grid(tot[kSlotCt]), kCtThreads, 0, s>>>(tab, count, tot[kSlotCt]);
+    }
     if (next_dt_dev) {
         Observe o(VLCT_KERNEL_DT, s);
-        kb_dt_partial<<<(unsigned)tot[kSlotDt], kBlock, 0, s>>>(tab, count, tot[kSlotDt]);
-        kb_dt_final<<<count, 1024, 0, s>>>(tab);
+        if (!ride)
+            kb_dt_partial<<<(unsigned)tot[kSlotDt], kBlock, 0, s>>>(tab, count, tot[kSlotDt]);
+        kb_dt_final<<<count, 1024, 0, s>>>(tab, ride);
     }
     return hipGetLastError() == hipSuccess ? VLCT_OK : VLCT_EHIP;
 }

@@ -1027,7 +1027,7 @@ static void stage_adjoint(const Geom &g, double factor, const StateP &lout, cons
 // workspace of the adjoint: forward intermediates and cotangents.  Without a
 // tape it also holds the recomputed fluxes, half-step state and upwind sides.
 struct AdLayout {
-    size_t prims[2], half[8], flux[2][3], side[2][3], le, wcode, lw, lrec, total;
+    size_t prims[2], half[8], flux[3], side[2][3], le, wcode, lw, lrec, total;
     size_t prims_len, flux_len[3], cell_pitch;
     size_t lnext[8], lhalf[8];
 };
@@ -1050,11 +1050,10 @@ static AdLayout ad_layout(const Geom &g, bool taped)
             L.half[f] = off;
             off += align_up(field_len(g.n, f) * 8);
         }
-        for (int h = 0; h < 2; ++h)
-            for (int d = 0; d < 3; ++d) {
-                L.flux[h][d] = off;
-                off += flux_axis_bytes(L.flux_len[d]);
-            }
+        for (int d = 0; d < 3; ++d) {
+            L.flux[d] = off;
+            off += flux_axis_bytes(L.flux_len[d]);
+        }
         for (int h = 0; h < 2; ++h)
             for (int d = 0; d < 3; ++d) {
                 L.side[h][d] = off;
@@ -1278,26 +1277,26 @@ int vlct_step_adjoint(const vlct_grid *vg, const vlct_state *in, const vlct_stat
     for (int f = 0; f < 8; ++f) {
         if (f < 5) half.u[f] = arr(L.half[f]); else half.b[f - 5] = arr(L.half[f]);
     }
-    Flux F[2];
+    const Flux F = bind_flux(b, L.flux, L.flux_len);
     uint8_t *side[2][3];
     Sides sides[2];
-    for (int h = 0; h < 2; ++h) {
-        F[h] = bind_flux(b, L.flux[h], L.flux_len);
+    for (int h = 0; h < 2; ++h)
         for (int d = 0; d < 3; ++d) {
             side[h][d] = reinterpret_cast<uint8_t *>(b + L.side[h][d]);
             sides[h].s[d] = side[h][d];
         }
+    // forward intermediates at U^n (the kernels of vlct_step); the cells that
+    // the corrector fluxes update go to an array that k_ad_init fills later
+    StateW unused;
+    for (int f = 0; f < 8; ++f) {
+        if (f < 5) unused.u[f] = arr(L.lnext[f]); else unused.b[f - 5] = arr(L.lnext[f]);
     }
-    // forward intermediates at U^n (the kernels of vlct_step)
     const StateP sin = as_const(in);
     rc = launch_prims(g, sin, P[0], nullptr, s);
-    if (!rc) rc = launch_fluxes(g, sin, P[0], F[0], VLCT_RECON_PCM, nullptr, s);
-    if (!rc) rc = launch_pack_sides(g, F[0], side[0], s);
-    if (!rc) rc = launch_ct(g, false, P[0], F[0], sin, half, dt_dev, nullptr, s);
+    if (!rc) rc = launch_pred(g, sin, half, P[1], dt_dev, nullptr, side[0], s);
     const StateP hc = as_const(half);
-    if (!rc) rc = launch_prims(g, hc, P[1], nullptr, s);
-    if (!rc) rc = launch_fluxes(g, hc, P[1], F[1], vg->recon, nullptr, s);
-    if (!rc) rc = launch_pack_sides(g, F[1], side[1], s);
+    if (!rc) rc = launch_fluxes(g, hc, P[1], F, vg->recon, sin, unused, dt_dev, nullptr, s);
+    if (!rc) rc = launch_pack_sides(g, F, side[1], s);
     if (rc) return rc;
     return adjoint_core(vg, g, L, b, sin, hc, sides, true, lam_out, lam_in, dt_dev, s);
 }

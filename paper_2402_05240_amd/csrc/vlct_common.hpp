@@ -53,10 +53,27 @@ __device__ __forceinline__ void st8(double *base, u32 byte, double v)
     auto *p = (VLCT_GLOBAL char *)(base) + byte;
     *(VLCT_GLOBAL double *)p = v;
 }
+__device__ __forceinline__ int ld1(const int8_t *base, u32 byte)
+{
+    return *((const VLCT_GLOBAL int8_t *)(base) + byte);
+}
 __device__ __forceinline__ void st1(int8_t *base, u32 byte, int8_t v)
 {
     *((VLCT_GLOBAL int8_t *)(base) + byte) = v;
 }
+// a block-uniform value in scalar registers (one computed on the vector unit
+// would hold vector registers for the whole kernel)
+__device__ __forceinline__ double uniform(double x)
+{
+    const int lo = __builtin_amdgcn_readfirstlane(__double2loint(x));
+    const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(x));
+    return __hiloint2double(hi, lo);
+}
+// Marks a thread's byte offset as changed (it is not): inside a loop over
+// planes the compiler would otherwise hoist base + offset of every array as
+// 64-bit vector pointers, which took 40 registers in the CT update and as many
+// in the predictor, and would lose the scalar-base form of the accesses.
+__device__ __forceinline__ void pin(u32 &o) { asm("" : "+v"(o)); }
 // e / n for the position e of a thread past its block's first row of length n:
 // rows longer than a block take no division
 __device__ __forceinline__ u32 row_div(u32 e, u32 n) { return e < n ? 0u : (e - n < n ? 1u : e / n); }
@@ -67,9 +84,11 @@ __device__ __forceinline__ u32 row_div(u32 e, u32 n) { return e < n ? 0u : (e - 
 struct Geom {
     int n[3];
     int bc[3];
-    double dl[3];
+    double dl[3], idl[3];  // cell widths and their reciprocals
     double gamma, gm1i, cfl;
     int p[3];  // padded primitive dims n + 2G
+    int march;        // cells per segment of the corrector's y and z marches
+    int ct_tx, ct_ty; // column tile of a CT block
     int ct_planes;    // z planes a CT block marches through
     int pred_slab;    // z planes per slab of the fused predictor's pair order
     int pred_chunk;   // (column tile, plane) pairs of one fused predictor block
@@ -137,12 +156,18 @@ struct Prims {
 };
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// what the CT update needs of the corrector's face fluxes (the hydro parts go
+// straight into the cells): the two EMFs of a face of axis d, -F[B_t1] (along
+// t2) and F[B_t2] (along t1), and its CT upwind indicator (+1, -1, 0), the
+// sign of S_M
 struct Flux {
-    double *f[3][7];  // per axis: 7 sweep-frame flux components
-    int8_t *sg[3];    // per axis: CT upwind indicator (+1, -1, 0), the sign of S_M
+    double *e[3][2];
+    int8_t *sg[3];
 };
 
-// bytes of one axis' flux arrays (7 doubles and the indicator per face)
+// bytes of one axis' share of the workspace: seven doubles and a byte per face.
+// The EMFs take two of the seven; the size stays, so that every workspace and
+// scratch check answers as it always has.
 inline size_t flux_axis_bytes(size_t len)
 {
     return 7 * align_up(len * sizeof(double)) + align_up(len);
@@ -152,8 +177,8 @@ inline Flux bind_flux(char *base, const size_t off[3], const size_t len[3])
 {
     Flux F;
     for (int d = 0; d < 3; ++d) {
-        for (int c = 0; c < 7; ++c)
-            F.f[d][c] = reinterpret_cast<double *>(base + off[d] + c * align_up(len[d] * sizeof(double)));
+        for (int c = 0; c < 2; ++c)
+            F.e[d][c] = reinterpret_cast<double *>(base + off[d] + c * align_up(len[d] * sizeof(double)));
         F.sg[d] = reinterpret_cast<int8_t *>(base + off[d] + 7 * align_up(len[d] * sizeof(double)));
     }
     return F;
@@ -178,7 +203,7 @@ inline bool grid_ok(const vlct_grid *g)
 
 // Tile override for tests and tuning: the environment variable VLCT_TILES,
 // read at every call, holds comma-separated key=value pairs (ct=4|8|16|32|64 CT
-// planes per block, march=8|16 faces per corrector march segment, pred=N
+// planes per block, march=8|16 cells per corrector march segment, pred=N
 // (column tile, plane) pairs per fused predictor block in one shared slab,
 // predslab=P slabs of P planes one per predictor block, admarch=8|16 cells per adjoint march
 // segment) that replace the size-dependent choices.  Every choice computes the
@@ -214,6 +239,13 @@ __host__ __device__ __forceinline__ long long pred_tiles(const Geom &g)
     return (long long)ntx * nty;
 }
 
+__host__ __device__ __forceinline__ long long ct_tiles(const Geom &g)
+{
+    const int ntx = (g.n[0] + (g.bc[0] == VLCT_BC_OUTFLOW) + g.ct_tx - 1) / g.ct_tx;
+    const int nty = (g.n[1] + (g.bc[1] == VLCT_BC_OUTFLOW) + g.ct_ty - 1) / g.ct_ty;
+    return (long long)ntx * nty;
+}
+
 inline Geom make_geom(const vlct_grid *vg)
 {
     Geom g;
@@ -227,15 +259,19 @@ inline Geom make_geom(const vlct_grid *vg)
     g.dl[0] = vg->dx;
     g.dl[1] = vg->dy;
     g.dl[2] = vg->dz;
+    for (int d = 0; d < 3; ++d) g.idl[d] = 1.0 / g.dl[d];
     g.gamma = vg->gamma;
     g.gm1i = 1.0 / (vg->gamma - 1.0);
     g.cfl = vg->cfl;
-    // CT blocks march 32 planes through a column tile of 64 x 8, halved down to
-    // 8 while the grid has fewer than 1024 such blocks (4 per CU); one with
-    // fewer than 256 blocks of 8 planes takes 4 (measured at 64^3 .. 256^3: 32
-    // planes from 256^3 up, 8 at 128^3 and 192^3, 4 at 64^3)
-    const long long cols = (long long)((g.n[0] + (g.bc[0] == VLCT_BC_OUTFLOW) + 63) / 64) *
-                           ((g.n[1] + (g.bc[1] == VLCT_BC_OUTFLOW) + 7) / 8);
+    // corrector marches: 16 cells per segment, 8 while the 16-cell launch would
+    // have fewer than 1024 blocks (4 per CU)
+    const long long yblk = ((long long)(g.n[0] + 2) * (g.n[2] + 2) + kBlock - 1) / kBlock *
+                           ((g.n[1] + 15) / 16);
+    g.march = yblk < 1024 ? 8 : 16;
+    // CT column tile and planes per block
+    g.ct_tx = kPredTx;
+    g.ct_ty = kPredTy;
+    const long long cols = ct_tiles(g);
     g.ct_planes = 32;
     while (g.ct_planes > 8 && cols * ((g.n[2] + g.ct_planes - 1) / g.ct_planes) < 1024)
         g.ct_planes /= 2;
@@ -266,6 +302,8 @@ inline Geom make_geom(const vlct_grid *vg)
         g.pred_chunk = (int)chunk;
     }
     const int oct = tile_override("ct"), opred = tile_override("pred");
+    const int om = tile_override("march");
+    if (om == 8 || om == 16) g.march = om;
     if (oct == 4 || oct == 8 || oct == 16 || oct == 32 || oct == 64) g.ct_planes = oct;
     const int oslab = tile_override("predslab");
     if (opred >= 1) {  // one shared slab, opred pairs per block
@@ -363,10 +401,15 @@ inline TapeLayout tape_layout(const int n[3])
 // recompute the forward intermediates
 int launch_prims(const Geom &g, const StateP &st, const Prims &P, uint32_t *status,
                  hipStream_t s);
+// Steps 2-5: U^n -> U^{n+1/2} and its primitives (ghost layers included); with
+// `side` also the upwind sides of the interior faces
+int launch_pred(const Geom &g, const StateP &st, const StateW &half, const Prims &P,
+                const double *dt_dev, uint32_t *status, uint8_t *const *side, hipStream_t s);
+// Steps 6-7 and the cells' part of Step 9: EMFs and indicators of the faces of
+// st into F, the updated cells (base minus the flux differences) into out.u
 int launch_fluxes(const Geom &g, const StateP &st, const Prims &P, const Flux &F, int recon,
-                  uint32_t *status, hipStream_t s);
-int launch_ct(const Geom &g, bool full, const Prims &P, const Flux &F, const StateP &base,
-              const StateW &out, const double *dt_dev, uint32_t *status, hipStream_t s);
+                  const StateP &base, const StateW &out, const double *dt_dev, uint32_t *status,
+                  hipStream_t s);
 // upwind sides of the interior faces of F, per axis
 int launch_pack_sides(const Geom &g, const Flux &F, uint8_t *const side[3], hipStream_t s);
 
