@@ -36,9 +36,8 @@ constexpr int kRowCells = kBlock - 2;  // cells a block of the x kernel updates
 // is the single-instance choice, the others fix the block's columns (ring
 // included) at 32 x 16 and 16 x 32
 constexpr int kCtVariants = 3;
-constexpr int kMarchVariants = 3;  // march segments of 16, 32 and 8 cells
+constexpr int kMarchVariants = 3;  // march segments: automatic, 32 and 8 cells
 constexpr int kCtThreads = 512;
-static int march_len(int v) { return v == 0 ? 16 : (v == 1 ? 32 : 8); }
 
 __host__ __device__ __forceinline__ idx_t nblk_prims(const Geom &g)
 {
@@ -53,7 +52,7 @@ __host__ __device__ __forceinline__ idx_t nblk_march(const Geom &g, int d)
 {
     const int t = d == 1 ? 2 : 1;
     const idx_t cols = (idx_t)(g.n[0] + 2) * (g.n[t] + 2);
-    return ((cols + kBlock - 1) / kBlock) * ((g.n[d] + g.march - 1) / g.march);
+    return ((cols + kBlock - 1) / kBlock) * ((g.n[d] + g.march[d] - 1) / g.march[d]);
 }
 __host__ __device__ __forceinline__ idx_t nblk_ct(const Geom &g)
 {
@@ -331,7 +330,7 @@ __device__ __forceinline__ void march_body(const Geom &g, const StateP &s, const
     // columns (i, it), i in [-1, nx], it in [-1, n_T], flattened with i fastest
     const u32 X2 = g.n[0] + 2;
     const u32 ncb = (X2 * (g.n[T] + 2) + kBlock - 1) / kBlock;
-    const u32 nseg = (nD + g.march - 1) / g.march;
+    const u32 nseg = (nD + g.march[D] - 1) / g.march[D];
     const u32 seg = b / ncb, cb = b - seg * ncb;
     if (seg >= nseg) return;
     const u32 it0 = cb * kBlock / X2;  // first row of columns of the block
@@ -339,8 +338,8 @@ __device__ __forceinline__ void march_body(const Geom &g, const StateP &s, const
     const u32 i1 = e - dr * X2;  // i + 1
     const int i = (int)i1 - 1, it = (int)(it0 + dr) - 1;
     if (it > g.n[T]) return;
-    const int s0 = seg * g.march;
-    const int s1 = min(s0 + g.march, nD);  // cells [s0, s1), faces [s0, s1]
+    const int s0 = seg * g.march[D];
+    const int s1 = min(s0 + g.march[D], nD);  // cells [s0, s1), faces [s0, s1]
     const bool interior = i >= 0 && i < g.n[0] && it >= 0 && it < g.n[T];
     // primitives: cell s0 - 1 - R of the column
     const u32 px = g.p[0], py = g.p[1];
@@ -729,13 +728,11 @@ __device__ __forceinline__ void ct_body(const Geom &g, const Prims &P, const Flu
 }
 
 // ---------------------------------------------------------------------------
-// fused predictor (Steps 2-5 in one kernel): the (column tile, plane) pairs
-// of the grid, in z slabs, are dealt out to the blocks in equal shares
-// (Geom::pred_slab, Geom::pred_chunk: one (slab, tile) per block, or a single
-// slab shared out evenly over one wave of resident blocks); a block marches
-// along z through each run [k0, k1) of planes of a column tile that its share
-// holds.  A thread owns one column of the tile or of its one-cell ring, and
-// per new plane m
+// fused predictor (Steps 2-5 in one kernel): a block marches along z through
+// the planes [k0, k1) of a column tile (Geom::pr_tx x pr_ty columns and
+// pred_slab planes); neighbouring tiles of a slab are neighbouring blocks, so
+// that they share their ring columns in L2.  A thread owns one column of the
+// tile or of its one-cell ring, and per new plane m
 //   (A) derives the primitives (Sec. 2.1, B_cc = face average, floors) and
 //       the reference field -(v x B) of its cell into LDS;
 //   (B) solves PCM HLLD on its cell's low x- and y-faces and on the z-face
@@ -752,17 +749,18 @@ __device__ __forceinline__ void ct_body(const Geom &g, const Prims &P, const Flu
 // (its own EMFs, references, partial updates), so U^n is read once, each
 // plane's three barriers separate LDS writes from reads and none closes the
 // plane, and the next plane's U^n is loaded before (C), its latency behind the
-// edge and update work.  For each run the block also evaluates the faces of
-// the planes k0 - 1 and k1 (the edges of its first and last half planes need
-// them).  Arithmetic per quantity is that of k_prims, k_flux and k_ct_update,
-// whatever the runs.
+// edge and update work.  The block also evaluates the faces of the planes
+// k0 - 1 and k1 (the edges of its first and last half planes need them).
+// Arithmetic per quantity is that of k_prims and k_ct_update, whatever the
+// tiles.
 //
 // One block per CU (133 KB of LDS, 256 registers: two waves per SIMD), bound
 // by FP64 issue and by the latency of three dependent Riemann solves between
 // barriers.  Against the form that kept every EMF and reference of two planes
 // in LDS, dealt the edges out by division and loaded U^n twice per plane
 // (2321 vector instructions, 116 LDS accesses; now 1801 and 81): 256^3 2.04 ->
-// 1.54 ms, 128^3 0.284 -> 0.225 ms, 32^3 52 -> 45 us.
+// 1.54 ms, 128^3 0.284 -> 0.225 ms, 32^3 52 -> 45 us (17 with tiles of 256
+// threads and one plane).
 // ---------------------------------------------------------------------------
 constexpr int kPredThreads = 512;
 
@@ -771,16 +769,12 @@ constexpr int kPredThreads = 512;
 // plain one.  P: the half-step primitives of the interior cells are written
 // there as k_prims would derive them from U^{n+1/2}; its ghost layers are left
 // to k_prims_ghost.
-// ONE_RUN: block b is the single run of tile b mod ntiles in z slab
-// b / ntiles (Geom::pred_chunk == 0); else its share of Geom::pred_chunk
-// pairs in slab order (a zero chunk taken as one slab's worth).
-template <int TX, int TY, bool ONE_RUN>
+// Block b is the run of tile b mod ntiles through z slab b / ntiles.
 __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const StateW &out,
                                           const Prims &P, const double *dt_dev, uint32_t *status,
                                           u32 b, uint8_t *side0, uint8_t *side1, uint8_t *side2)
 {
-    constexpr int CX = TX + 2, CY = TY + 2, NC = CX * CY;  // columns with the ring
-    static_assert(NC <= kPredThreads, "one thread per column");
+    const int TX = g.pr_tx, TY = g.pr_ty, CX = TX + 2;  // columns along x with the ring
     constexpr int N = kPredThreads;
     __shared__ double s_pr[8][N];             // primitives of plane m
     __shared__ double s_rx[2][N], s_ry[2][N], s_rz[N];  // -(v x B): x, y of planes m - 1, m (slot m & 1), z
@@ -792,276 +786,240 @@ __device__ __forceinline__ void pred_body(const Geom &g, const StateP &s, const 
 
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
     const int ex = nx + (g.bc[0] == VLCT_BC_OUTFLOW), ey = ny + (g.bc[1] == VLCT_BC_OUTFLOW);
-    // the block's share: positions [pos0, pos1) of the sequence of (column
-    // tile, plane) pairs ordered by z slab of Geom::pred_slab planes (the last
-    // slab holds the remainder), then tile, then plane; it marches each run of
-    // one tile's planes in turn
-    const int ntx = (ex + TX - 1) / TX, nty = (ey + TY - 1) / TY, ntiles = ntx * nty;
-    const int npos = ntiles * nz;  // below 2^31 for sides up to kMaxN
-    const int H = g.pred_slab, nfull = nz / H, rem = nz - nfull * H;
-    if (ONE_RUN && b >= (u32)(ntiles * (nfull + (rem > 0)))) return;
-    const int chunk = g.pred_chunk > 0 ? g.pred_chunk : H;
-    if (!ONE_RUN && (idx_t)b * chunk >= npos) return;
+    const u32 ntx = (ex + TX - 1) / TX, nty = (ey + TY - 1) / TY, ntiles = ntx * nty;
+    const u32 slab = b / ntiles, tile = b - slab * ntiles;
+    const int k0 = __builtin_amdgcn_readfirstlane(slab * g.pred_slab);
+    if (k0 >= nz) return;
+    const int k1 = min(k0 + g.pred_slab, nz);
     const double dt = 0.5 * dt_dev[0];
     const double cx = uniform(dt / g.dl[0]), cy = uniform(dt / g.dl[1]), cz = uniform(dt / g.dl[2]);
 
     // this thread's column: (a, c) in the tile with its ring
     const int t = threadIdx.x;
-    const int a = t % CX, c = t / CX;
+    const int c = t / CX, a = t - c * CX;
     uint32_t st = 0;
-    auto run = [&](const int tile, const int k0, const int k1) {
-        const int i0 = (tile % ntx) * TX, j0 = (tile / ntx) * TY;
-        // cell (ii, jj) of the column
-        const int ii = i0 - 1 + a, jj = j0 - 1 + c;
-        const bool live = t < NC && ii <= nx && jj <= ny;
-        // columns to the left and below (the ring's first ones take themselves:
-        // what they solve there is not used)
-        const int lx = a >= 1 ? t - 1 : t, ly = c >= 1 ? t - CX : t;
-        const bool edge = live && a >= 1 && c >= 1;
-        // owned positions: cells / faces of the tile proper
-        const bool own = edge && a <= TX && c <= TY && ii < ex && jj < ey;
-        const bool interior = own && ii < nx && jj < ny;
-        // byte offsets of the column in a plane of each array
-        const int mi = map_cell(ii, nx, g.bc[0]), mj = map_cell(jj, ny, g.bc[1]);
-        const int fi0 = map_face(ii, nx, g.bc[0]), fi1 = map_face(ii + 1, nx, g.bc[0]);
-        const int fj0 = map_face(jj, ny, g.bc[1]), fj1 = map_face(jj + 1, ny, g.bc[1]);
-        u32 oc = 8u * (u32)(mj * nx + mi);
-        u32 ox0 = 8u * (u32)(mj * (nx + 1) + fi0), ox1 = 8u * (u32)(mj * (nx + 1) + fi1);
-        u32 oy0 = 8u * (u32)(fj0 * nx + mi), oy1 = 8u * (u32)(fj1 * nx + mi);
-        u32 op = 8u * (u32)((jj + kGhost) * g.p[0] + ii + kGhost);
-        const idx_t sc = (idx_t)nx * ny, sbx = (idx_t)(nx + 1) * ny, sby = (idx_t)nx * (ny + 1);
-        const idx_t sp = (idx_t)g.p[0] * g.p[1];
-        // the primitives' and the output cells' arrays are equally spaced in
-        // their workspace: two pointers each in scalar registers
-        const idx_t pstep = P.w[1] - P.w[0], ostep = out.u[1] - out.u[0];
+    const int i0 = (int)(tile % ntx) * TX, j0 = (int)(tile / ntx) * TY;
+    // cell (ii, jj) of the column
+    const int ii = i0 - 1 + a, jj = j0 - 1 + c;
+    const bool live = c < TY + 2 && ii <= nx && jj <= ny;
+    // columns to the left and below (the ring's first ones take themselves:
+    // what they solve there is not used)
+    const int lx = a >= 1 ? t - 1 : t, ly = c >= 1 ? t - CX : t;
+    const bool edge = live && a >= 1 && c >= 1;
+    // owned positions: cells / faces of the tile proper
+    const bool own = edge && a <= TX && c <= TY && ii < ex && jj < ey;
+    const bool interior = own && ii < nx && jj < ny;
+    // byte offsets of the column in a plane of each array
+    const int mi = map_cell(ii, nx, g.bc[0]), mj = map_cell(jj, ny, g.bc[1]);
+    const int fi0 = map_face(ii, nx, g.bc[0]), fi1 = map_face(ii + 1, nx, g.bc[0]);
+    const int fj0 = map_face(jj, ny, g.bc[1]), fj1 = map_face(jj + 1, ny, g.bc[1]);
+    u32 oc = 8u * (u32)(mj * nx + mi);
+    u32 ox0 = 8u * (u32)(mj * (nx + 1) + fi0), ox1 = 8u * (u32)(mj * (nx + 1) + fi1);
+    u32 oy0 = 8u * (u32)(fj0 * nx + mi), oy1 = 8u * (u32)(fj1 * nx + mi);
+    u32 op = 8u * (u32)((jj + kGhost) * g.p[0] + ii + kGhost);
+    const idx_t sc = (idx_t)nx * ny, sbx = (idx_t)(nx + 1) * ny, sby = (idx_t)nx * (ny + 1);
+    const idx_t sp = (idx_t)g.p[0] * g.p[1];
+    // the primitives' and the output cells' arrays are equally spaced in
+    // their workspace: two pointers each in scalar registers
+    const idx_t pstep = P.w[1] - P.w[0], ostep = out.u[1] - out.u[0];
 
-        // U^n of this thread's cell in a plane: 5 conserved values, the six faces
-        double pf[11];
-        auto load_plane = [&](int m) {
-            const idx_t mk = map_cell(m, nz, g.bc[2]);
+    // U^n of this thread's cell in a plane: 5 conserved values, the six faces
+    double pf[11];
+    auto load_plane = [&](int m) {
+        const idx_t mk = map_cell(m, nz, g.bc[2]);
 #pragma unroll
-            for (int q = 0; q < 5; ++q) pf[q] = ld8(s.u[q] + mk * sc, oc);
-            pf[5] = ld8(s.b[0] + mk * sbx, ox0);
-            pf[6] = ld8(s.b[0] + mk * sbx, ox1);
-            pf[7] = ld8(s.b[1] + mk * sby, oy0);
-            pf[8] = ld8(s.b[1] + mk * sby, oy1);
-            pf[9] = ld8(s.b[2] + map_face(m, nz, g.bc[2]) * sc, oc);
-            pf[10] = ld8(s.b[2] + map_face(m + 1, nz, g.bc[2]) * sc, oc);
-        };
-
-        // of plane m - 1: the cell's update short of the z fluxes, the hydro flux
-        // of its low z-face, its faces short of the E_x and E_y terms (low and
-        // high x, y) and its finished low z-face
-        double up[5], hz_lo[5], bxp = any_value(), bxhp = any_value(), byp = any_value();
-        double byhp = any_value(), bzp = any_value();
-#pragma unroll
-        for (int q = 0; q < 5; ++q) up[q] = hz_lo[q] = any_value();
-        // own EMFs and indicators of plane m - 1 for the half-plane edges
-        double xy_p = any_value(), yx_p = any_value();
-        int sx_p = 0, sy_p = 0;
-        if (live) load_plane(k0 - 1);
-        for (int m = k0 - 1; m <= k1; ++m) {
-            const int hi = m & 1, lo = hi ^ 1;  // slots of the half planes m -+ 1/2
-            pin(oc), pin(ox0), pin(ox1), pin(oy0), pin(oy1), pin(op);
-            // (A)
-            double u0[5], bx0 = any_value(), bx1 = any_value(), by0 = any_value(), by1 = any_value();
-            double bz0 = any_value();
-#pragma unroll
-            for (int q = 0; q < 5; ++q) u0[q] = any_value();
-            W7 wz_prev{any_value(), any_value(), any_value(), any_value(),
-                       any_value(), any_value(), any_value()};  // own cell of plane m - 1, z sweep frame
-            if (live) {
-                wz_prev = W7{s_pr[0][t], s_pr[3][t], s_pr[1][t], s_pr[2][t],
-                             s_pr[4][t], s_pr[5][t], s_pr[6][t]};
-#pragma unroll
-                for (int q = 0; q < 5; ++q) u0[q] = pf[q];
-                bx0 = pf[5];
-                bx1 = pf[6];
-                by0 = pf[7];
-                by1 = pf[8];
-                bz0 = pf[9];
-                double w[8];
-                st |= prims_of(g, u0, 0.5 * (bx0 + bx1), 0.5 * (by0 + by1), 0.5 * (bz0 + pf[10]), w);
-#pragma unroll
-                for (int q = 0; q < 8; ++q) s_pr[q][t] = w[q];
-                s_rx[hi][t] = -(w[2] * w[7] - w[3] * w[6]);
-                s_ry[hi][t] = -(w[3] * w[5] - w[1] * w[7]);
-                s_rz[t] = -(w[1] * w[6] - w[2] * w[5]);
-            }
-            __syncthreads();
-            // (B)
-            double hzn[5], xz = any_value(), xy = any_value(), yx = any_value(), yz = any_value();
-            double zx = any_value(), zy = any_value();
-#pragma unroll
-            for (int q = 0; q < 5; ++q) hzn[q] = any_value();
-            int8_t sx = 0, sy = 0, sz = 0;
-            if (live) {
-                double f[7];
-                if (m >= k0) {
-                    const W7 wr{s_pr[0][t], s_pr[3][t], s_pr[1][t], s_pr[2][t],
-                                s_pr[4][t], s_pr[5][t], s_pr[6][t]};
-                    hlld(wz_prev, wr, bz0, g.gamma, g.gm1i, f, sz);
-#pragma unroll
-                    for (int q = 0; q < 5; ++q) hzn[q] = f[q];
-                    zy = -f[5];
-                    zx = f[6];
-                    s_zy[t] = zy;
-                    s_zx[t] = zx;
-                    s_sz[t] = sz;
-                }
-                {
-                    const W7 wl{s_pr[0][lx], s_pr[1][lx], s_pr[2][lx], s_pr[3][lx],
-                                s_pr[4][lx], s_pr[6][lx], s_pr[7][lx]};
-                    const W7 wr{s_pr[0][t], s_pr[1][t], s_pr[2][t], s_pr[3][t],
-                                s_pr[4][t], s_pr[6][t], s_pr[7][t]};
-                    hlld(wl, wr, bx0, g.gamma, g.gm1i, f, sx);
-#pragma unroll
-                    for (int q = 0; q < 5; ++q) s_fx[q][t] = f[q];
-                    xz = -f[5];
-                    xy = f[6];
-                    s_xz[t] = xz;
-                    s_sx[t] = sx;
-                }
-                {
-                    const W7 wl{s_pr[0][ly], s_pr[2][ly], s_pr[3][ly], s_pr[1][ly],
-                                s_pr[4][ly], s_pr[7][ly], s_pr[5][ly]};
-                    const W7 wr{s_pr[0][t], s_pr[2][t], s_pr[3][t], s_pr[1][t],
-                                s_pr[4][t], s_pr[7][t], s_pr[5][t]};
-                    hlld(wl, wr, by0, g.gamma, g.gm1i, f, sy);
-#pragma unroll
-                    for (int q = 0; q < 5; ++q) s_fy[q][t] = f[q];
-                    yx = -f[5];
-                    yz = f[6];
-                    s_yz[t] = yz;
-                    s_sy[t] = sy;
-                }
-            }
-            __syncthreads();
-            // (C)
-            if (live && m < k1) load_plane(m + 1);
-            double upn[5];
-#pragma unroll
-            for (int q = 0; q < 5; ++q) upn[q] = any_value();
-            if (edge) {
-                // E_z at (ii - 1/2, jj - 1/2, m): x-faces here and at jj - 1, y-faces here and at ii - 1
-                s_ez[t] = edge_combine(xz, s_xz[ly], yz, s_yz[lx], sx, s_sx[ly], sy, s_sy[lx], s_rz[t],
-                                       s_rz[lx], s_rz[ly], s_rz[ly - 1]);
-                // E_x at (ii, jj - 1/2, m - 1/2): y-faces of planes m, m - 1, z-faces here and at jj - 1
-                s_ex[hi][t] = edge_combine(yx, yx_p, zx, s_zx[ly], sy, sy_p, sz, s_sz[ly], s_rx[hi][t],
-                                           s_rx[hi][ly], s_rx[lo][t], s_rx[lo][ly]);
-                // E_y at (ii - 1/2, jj, m - 1/2): z-faces here and at ii - 1, x-faces of planes m, m - 1
-                s_ey[hi][t] = edge_combine(zy, s_zy[lx], xy, xy_p, sz, s_sz[lx], sx, sx_p, s_ry[hi][t],
-                                           s_ry[lo][t], s_ry[hi][lx], s_ry[lo][lx]);
-            }
-            xy_p = xy;
-            yx_p = yx;
-            sx_p = sx;
-            sy_p = sy;
-            if (interior) {
-                auto dx = [&](int q) { return s_fx[q][t + 1] - s_fx[q][t]; };
-                auto dy = [&](int q) { return s_fy[q][t + CX] - s_fy[q][t]; };
-                upn[0] = u0[0] - cx * dx(0) - cy * dy(0);
-                upn[1] = u0[1] - cx * dx(1) - cy * dy(3);
-                upn[2] = u0[2] - cx * dx(2) - cy * dy(1);
-                upn[3] = u0[3] - cx * dx(3) - cy * dy(2);
-                upn[4] = u0[4] - cx * dx(4) - cy * dy(4);
-                // the tape: upwind sides of the cell's low faces
-                if (side0 && m >= k0 && m < k1) {
-                    const idx_t cc = (idx_t)m * sc + (oc >> 3);
-                    side0[cc] = side_code(sx);
-                    side1[cc] = side_code(sy);
-                    side2[cc] = side_code(sz);
-                }
-            }
-            __syncthreads();
-            // (D)
-            double bzn = any_value();
-            if (own) {
-                const idx_t k = m - 1;
-                // the low z-face of plane m: the high one of the cell of plane m - 1
-                bzn = bz0 - cx * (s_ey[hi][t + 1] - s_ey[hi][t]) + cy * (s_ex[hi][t + CX] - s_ex[hi][t]);
-                if (interior && m >= k0 && (m < k1 || (m == nz && g.bc[2] == VLCT_BC_OUTFLOW))) {
-                    st8(out.b[2] + m * sc, oc, bzn);
-                    if (g.bc[2] == VLCT_BC_PERIODIC && m == 0) st8(out.b[2] + nz * sc, oc, bzn);
-                }
-                if (m > k0) {
-                    double bxl = any_value(), byl = any_value();
-                    if (jj < ny) {  // face x (ii - 1/2, jj, k)
-                        bxl = bxp + cz * (s_ey[hi][t] - s_ey[lo][t]);
-                        st8(out.b[0] + k * sbx, ox0, bxl);
-                        if (g.bc[0] == VLCT_BC_PERIODIC && ii == 0)
-                            st8(out.b[0] + k * sbx, ox0 + 8u * (u32)nx, bxl);
-                    }
-                    if (ii < nx) {  // face y (ii, jj - 1/2, k)
-                        byl = byp - cz * (s_ex[hi][t] - s_ex[lo][t]);
-                        st8(out.b[1] + k * sby, oy0, byl);
-                        if (g.bc[1] == VLCT_BC_PERIODIC && jj == 0)
-                            st8(out.b[1] + k * sby, oy0 + 8u * (u32)(nx * ny), byl);
-                    }
-                    if (interior) {
-                        double u[5];
-                        u[0] = up[0] - cz * (hzn[0] - hz_lo[0]);
-                        u[1] = up[1] - cz * (hzn[2] - hz_lo[2]);
-                        u[2] = up[2] - cz * (hzn[3] - hz_lo[3]);
-                        u[3] = up[3] - cz * (hzn[1] - hz_lo[1]);
-                        u[4] = up[4] - cz * (hzn[4] - hz_lo[4]);
-#pragma unroll
-                        for (int q = 0; q < 5; ++q) st8(out.u[0] + (q * ostep + k * sc), oc, u[q]);
-                        // half-step primitives; the high faces in the arithmetic of the
-                        // threads or blocks that own them
-                        const double bxu = bxhp + cz * (s_ey[hi][t + 1] - s_ey[lo][t + 1]);
-                        const double byu = byhp - cz * (s_ex[hi][t + CX] - s_ex[lo][t + CX]);
-                        double w[8];
-                        st |= prims_of(g, u, 0.5 * (bxl + bxu), 0.5 * (byl + byu),
-                                       0.5 * (bzp + bzn), w);
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) st8(P.w[0] + (q * pstep + (k + kGhost) * sp), op, w[q]);
-                    }
-                }
-                // start plane m
-                const double dz0 = s_ez[t + CX] - s_ez[t], dz1 = s_ez[t + CX + 1] - s_ez[t + 1];
-                const double dx0 = s_ez[t + 1] - s_ez[t], dx1 = s_ez[t + CX + 1] - s_ez[t + CX];
-                bxp = bx0 - cy * dz0;
-                bxhp = bx1 - cy * dz1;
-                byp = by0 + cx * dx0;
-                byhp = by1 + cx * dx1;
-            }
-#pragma unroll
-            for (int q = 0; q < 5; ++q) {
-                up[q] = upn[q];
-                hz_lo[q] = hzn[q];
-            }
-            bzp = bzn;
-        }
-        if (!ONE_RUN) __syncthreads();  // the next run writes what (D) reads
+        for (int q = 0; q < 5; ++q) pf[q] = ld8(s.u[q] + mk * sc, oc);
+        pf[5] = ld8(s.b[0] + mk * sbx, ox0);
+        pf[6] = ld8(s.b[0] + mk * sbx, ox1);
+        pf[7] = ld8(s.b[1] + mk * sby, oy0);
+        pf[8] = ld8(s.b[1] + mk * sby, oy1);
+        pf[9] = ld8(s.b[2] + map_face(m, nz, g.bc[2]) * sc, oc);
+        pf[10] = ld8(s.b[2] + map_face(m + 1, nz, g.bc[2]) * sc, oc);
     };
-    if (ONE_RUN) {
-        const int sl = (int)b / ntiles, tile = (int)b - sl * ntiles;
-        run(__builtin_amdgcn_readfirstlane(tile), __builtin_amdgcn_readfirstlane(sl * H),
-            __builtin_amdgcn_readfirstlane(min(sl * H + H, nz)));
-    } else {
-        const int pos0 = (int)b * chunk, pos1 = min(pos0 + chunk, npos);
-        const int fullpos = nfull * ntiles * H;
-        for (int pos = pos0; pos < pos1;) {
-            int tile, k0, len;
-            if (pos < fullpos) {
-                const int sl = pos / (ntiles * H), r = pos - sl * ntiles * H;
-                tile = r / H;
-                const int kk = r - tile * H;
-                k0 = sl * H + kk;
-                len = H - kk;
-            } else {
-                const int r = pos - fullpos;
-                tile = r / rem;
-                const int kk = r - tile * rem;
-                k0 = nfull * H + kk;
-                len = rem - kk;
-            }
-            const int k1 = k0 + min(len, pos1 - pos);
-            pos += k1 - k0;
-            run(__builtin_amdgcn_readfirstlane(tile), __builtin_amdgcn_readfirstlane(k0),
-                __builtin_amdgcn_readfirstlane(k1));
+
+    // of plane m - 1: the cell's update short of the z fluxes, the hydro flux
+    // of its low z-face, its faces short of the E_x and E_y terms (low and
+    // high x, y) and its finished low z-face
+    double up[5], hz_lo[5], bxp = any_value(), bxhp = any_value(), byp = any_value();
+    double byhp = any_value(), bzp = any_value();
+#pragma unroll
+    for (int q = 0; q < 5; ++q) up[q] = hz_lo[q] = any_value();
+    // own EMFs and indicators of plane m - 1 for the half-plane edges
+    double xy_p = any_value(), yx_p = any_value();
+    int sx_p = 0, sy_p = 0;
+    if (live) load_plane(k0 - 1);
+    for (int m = k0 - 1; m <= k1; ++m) {
+        const int hi = m & 1, lo = hi ^ 1;  // slots of the half planes m -+ 1/2
+        pin(oc), pin(ox0), pin(ox1), pin(oy0), pin(oy1), pin(op);
+        // (A)
+        double u0[5], bx0 = any_value(), bx1 = any_value(), by0 = any_value(), by1 = any_value();
+        double bz0 = any_value();
+#pragma unroll
+        for (int q = 0; q < 5; ++q) u0[q] = any_value();
+        W7 wz_prev{any_value(), any_value(), any_value(), any_value(),
+                   any_value(), any_value(), any_value()};  // own cell of plane m - 1, z sweep frame
+        if (live) {
+            wz_prev = W7{s_pr[0][t], s_pr[3][t], s_pr[1][t], s_pr[2][t],
+                         s_pr[4][t], s_pr[5][t], s_pr[6][t]};
+#pragma unroll
+            for (int q = 0; q < 5; ++q) u0[q] = pf[q];
+            bx0 = pf[5];
+            bx1 = pf[6];
+            by0 = pf[7];
+            by1 = pf[8];
+            bz0 = pf[9];
+            double w[8];
+            st |= prims_of(g, u0, 0.5 * (bx0 + bx1), 0.5 * (by0 + by1), 0.5 * (bz0 + pf[10]), w);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s_pr[q][t] = w[q];
+            s_rx[hi][t] = -(w[2] * w[7] - w[3] * w[6]);
+            s_ry[hi][t] = -(w[3] * w[5] - w[1] * w[7]);
+            s_rz[t] = -(w[1] * w[6] - w[2] * w[5]);
         }
+        __syncthreads();
+        // (B)
+        double hzn[5], xz = any_value(), xy = any_value(), yx = any_value(), yz = any_value();
+        double zx = any_value(), zy = any_value();
+#pragma unroll
+        for (int q = 0; q < 5; ++q) hzn[q] = any_value();
+        int8_t sx = 0, sy = 0, sz = 0;
+        if (live) {
+            double f[7];
+            if (m >= k0) {
+                const W7 wr{s_pr[0][t], s_pr[3][t], s_pr[1][t], s_pr[2][t],
+                            s_pr[4][t], s_pr[5][t], s_pr[6][t]};
+                hlld(wz_prev, wr, bz0, g.gamma, g.gm1i, f, sz);
+#pragma unroll
+                for (int q = 0; q < 5; ++q) hzn[q] = f[q];
+                zy = -f[5];
+                zx = f[6];
+                s_zy[t] = zy;
+                s_zx[t] = zx;
+                s_sz[t] = sz;
+            }
+            {
+                const W7 wl{s_pr[0][lx], s_pr[1][lx], s_pr[2][lx], s_pr[3][lx],
+                            s_pr[4][lx], s_pr[6][lx], s_pr[7][lx]};
+                const W7 wr{s_pr[0][t], s_pr[1][t], s_pr[2][t], s_pr[3][t],
+                            s_pr[4][t], s_pr[6][t], s_pr[7][t]};
+                hlld(wl, wr, bx0, g.gamma, g.gm1i, f, sx);
+#pragma unroll
+                for (int q = 0; q < 5; ++q) s_fx[q][t] = f[q];
+                xz = -f[5];
+                xy = f[6];
+                s_xz[t] = xz;
+                s_sx[t] = sx;
+            }
+            {
+                const W7 wl{s_pr[0][ly], s_pr[2][ly], s_pr[3][ly], s_pr[1][ly],
+                            s_pr[4][ly], s_pr[7][ly], s_pr[5][ly]};
+                const W7 wr{s_pr[0][t], s_pr[2][t], s_pr[3][t], s_pr[1][t],
+                            s_pr[4][t], s_pr[7][t], s_pr[5][t]};
+                hlld(wl, wr, by0, g.gamma, g.gm1i, f, sy);
+#pragma unroll
+                for (int q = 0; q < 5; ++q) s_fy[q][t] = f[q];
+                yx = -f[5];
+                yz = f[6];
+                s_yz[t] = yz;
+                s_sy[t] = sy;
+            }
+        }
+        __syncthreads();
+        // (C)
+        if (live && m < k1) load_plane(m + 1);
+        double upn[5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) upn[q] = any_value();
+        if (edge) {
+            // E_z at (ii - 1/2, jj - 1/2, m): x-faces here and at jj - 1, y-faces here and at ii - 1
+            s_ez[t] = edge_combine(xz, s_xz[ly], yz, s_yz[lx], sx, s_sx[ly], sy, s_sy[lx], s_rz[t],
+                                   s_rz[lx], s_rz[ly], s_rz[ly - 1]);
+            // E_x at (ii, jj - 1/2, m - 1/2): y-faces of planes m, m - 1, z-faces here and at jj - 1
+            s_ex[hi][t] = edge_combine(yx, yx_p, zx, s_zx[ly], sy, sy_p, sz, s_sz[ly], s_rx[hi][t],
+                                       s_rx[hi][ly], s_rx[lo][t], s_rx[lo][ly]);
+            // E_y at (ii - 1/2, jj, m - 1/2): z-faces here and at ii - 1, x-faces of planes m, m - 1
+            s_ey[hi][t] = edge_combine(zy, s_zy[lx], xy, xy_p, sz, s_sz[lx], sx, sx_p, s_ry[hi][t],
+                                       s_ry[lo][t], s_ry[hi][lx], s_ry[lo][lx]);
+        }
+        xy_p = xy;
+        yx_p = yx;
+        sx_p = sx;
+        sy_p = sy;
+        if (interior) {
+            auto dx = [&](int q) { return s_fx[q][t + 1] - s_fx[q][t]; };
+            auto dy = [&](int q) { return s_fy[q][t + CX] - s_fy[q][t]; };
+            upn[0] = u0[0] - cx * dx(0) - cy * dy(0);
+            upn[1] = u0[1] - cx * dx(1) - cy * dy(3);
+            upn[2] = u0[2] - cx * dx(2) - cy * dy(1);
+            upn[3] = u0[3] - cx * dx(3) - cy * dy(2);
+            upn[4] = u0[4] - cx * dx(4) - cy * dy(4);
+            // the tape: upwind sides of the cell's low faces
+            if (side0 && m >= k0 && m < k1) {
+                const idx_t cc = (idx_t)m * sc + (oc >> 3);
+                side0[cc] = side_code(sx);
+                side1[cc] = side_code(sy);
+                side2[cc] = side_code(sz);
+            }
+        }
+        __syncthreads();
+        // (D)
+        double bzn = any_value();
+        if (own) {
+            const idx_t k = m - 1;
+            // the low z-face of plane m: the high one of the cell of plane m - 1
+            bzn = bz0 - cx * (s_ey[hi][t + 1] - s_ey[hi][t]) + cy * (s_ex[hi][t + CX] - s_ex[hi][t]);
+            if (interior && m >= k0 && (m < k1 || (m == nz && g.bc[2] == VLCT_BC_OUTFLOW))) {
+                st8(out.b[2] + m * sc, oc, bzn);
+                if (g.bc[2] == VLCT_BC_PERIODIC && m == 0) st8(out.b[2] + nz * sc, oc, bzn);
+            }
+            if (m > k0) {
+                double bxl = any_value(), byl = any_value();
+                if (jj < ny) {  // face x (ii - 1/2, jj, k)
+                    bxl = bxp + cz * (s_ey[hi][t] - s_ey[lo][t]);
+                    st8(out.b[0] + k * sbx, ox0, bxl);
+                    if (g.bc[0] == VLCT_BC_PERIODIC && ii == 0)
+                        st8(out.b[0] + k * sbx, ox0 + 8u * (u32)nx, bxl);
+                }
+                if (ii < nx) {  // face y (ii, jj - 1/2, k)
+                    byl = byp - cz * (s_ex[hi][t] - s_ex[lo][t]);
+                    st8(out.b[1] + k * sby, oy0, byl);
+                    if (g.bc[1] == VLCT_BC_PERIODIC && jj == 0)
+                        st8(out.b[1] + k * sby, oy0 + 8u * (u32)(nx * ny), byl);
+                }
+                if (interior) {
+                    double u[5];
+                    u[0] = up[0] - cz * (hzn[0] - hz_lo[0]);
+                    u[1] = up[1] - cz * (hzn[2] - hz_lo[2]);
+                    u[2] = up[2] - cz * (hzn[3] - hz_lo[3]);
+                    u[3] = up[3] - cz * (hzn[1] - hz_lo[1]);
+                    u[4] = up[4] - cz * (hzn[4] - hz_lo[4]);
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) st8(out.u[0] + (q * ostep + k * sc), oc, u[q]);
+                    // half-step primitives; the high faces in the arithmetic of the
+                    // threads or blocks that own them
+                    const double bxu = bxhp + cz * (s_ey[hi][t + 1] - s_ey[lo][t + 1]);
+                    const double byu = byhp - cz * (s_ex[hi][t + CX] - s_ex[lo][t + CX]);
+                    double w[8];
+                    st |= prims_of(g, u, 0.5 * (bxl + bxu), 0.5 * (byl + byu),
+                                   0.5 * (bzp + bzn), w);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) st8(P.w[0] + (q * pstep + (k + kGhost) * sp), op, w[q]);
+                }
+            }
+            // start plane m
+            const double dz0 = s_ez[t + CX] - s_ez[t], dz1 = s_ez[t + CX + 1] - s_ez[t + 1];
+            const double dx0 = s_ez[t + 1] - s_ez[t], dx1 = s_ez[t + CX + 1] - s_ez[t + CX];
+            bxp = bx0 - cy * dz0;
+            bxhp = bx1 - cy * dz1;
+            byp = by0 + cx * dx0;
+            byhp = by1 + cx * dx1;
+        }
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            up[q] = upn[q];
+            hz_lo[q] = hzn[q];
+        }
+        bzp = bzn;
     }
     if (st && status) atomicOr(status, st);
 }
@@ -1157,31 +1115,18 @@ __global__ void __launch_bounds__(kCtThreads, 4) k_ct_update(Geom g, Prims P, Fl
 static_assert(kPredThreads * kPredBlocksPerCU <= 1024,
               "the resident predictor blocks of a CU hold at most two waves per SIMD");
 
-// blocks of the fused predictor: one per (slab, tile) (Geom::pred_chunk == 0),
-// else shares of Geom::pred_chunk (tile, plane) pairs
+// blocks of the fused predictor: one per (slab, tile)
 __host__ __device__ __forceinline__ idx_t nblk_pred(const Geom &g)
 {
-    const idx_t nsl = (g.n[2] + g.pred_slab - 1) / g.pred_slab;
-    if (g.pred_chunk == 0) return pred_tiles(g) * nsl;
-    const idx_t npos = pred_tiles(g) * g.n[2];
-    return (npos + g.pred_chunk - 1) / g.pred_chunk;
-}
-// blocks of the share form (the batched step's), a zero chunk taken as one slab
-__host__ __device__ __forceinline__ idx_t nblk_pred_shares(const Geom &g)
-{
-    const idx_t npos = pred_tiles(g) * g.n[2];
-    const idx_t chunk = g.pred_chunk > 0 ? g.pred_chunk : g.pred_slab;
-    return (npos + chunk - 1) / chunk;
+    return pred_tiles(g) * ((g.n[2] + g.pred_slab - 1) / g.pred_slab);
 }
 
-template <bool ONE_RUN>
 __global__ void __launch_bounds__(kPredThreads, kPredWavesPerSimd) k_pred(Geom g, StateP s, StateW out, Prims P,
                                                         const double *dt_dev, uint32_t *status,
                                                         uint8_t *side0, uint8_t *side1,
                                                         uint8_t *side2)
 {
-    pred_body<kPredTx, kPredTy, ONE_RUN>(g, s, out, P, dt_dev, status, xcd_block(nblk_pred(g)),
-                                         side0, side1, side2);
+    pred_body(g, s, out, P, dt_dev, status, xcd_block(nblk_pred(g)), side0, side1, side2);
 }
 
 __global__ void __launch_bounds__(kBlock) k_prims_ghost(Geom g, StateP s, Prims P,
@@ -1275,8 +1220,7 @@ __global__ void __launch_bounds__(kPredThreads, kPredWavesPerSimd) kb_pred(const
     const StateP in = I.in;
     const StateW half = I.half;
     const Prims P = I.P;
-    pred_body<kPredTx, kPredTy, false>(g, in, half, P, I.dt, I.status, lb, nullptr, nullptr,
-                                       nullptr);
+    pred_body(g, in, half, P, I.dt, I.status, lb, nullptr, nullptr, nullptr);
 }
 
 // ghost-layer primitives of the half-step state of every instance
@@ -1537,12 +1481,8 @@ int launch_pred(const Geom &g, const StateP &st, const StateW &half, const Prims
         Observe o(VLCT_KERNEL_PREDICTOR, s);
         uint8_t *s0 = side ? side[0] : nullptr, *s1 = side ? side[1] : nullptr,
                 *s2 = side ? side[2] : nullptr;
-        if (g.pred_chunk == 0)
-            k_pred<true><<<xcd_grid(nblk_pred(g)), kPredThreads, 0, s>>>(g, st, half, P, dt_dev,
-                                                                        status, s0, s1, s2);
-        else
-            k_pred<false><<<xcd_grid(nblk_pred(g)), kPredThreads, 0, s>>>(g, st, half, P, dt_dev,
-                                                                         status, s0, s1, s2);
+        k_pred<<<xcd_grid(nblk_pred(g)), kPredThreads, 0, s>>>(g, st, half, P, dt_dev, status, s0,
+                                                               s1, s2);
     }
     // ghost layers of the half-step primitives
     Observe o(VLCT_KERNEL_PRIMS, s);
@@ -1627,10 +1567,21 @@ static void plan_tiles(Geom &g, uint8_t plan)
         g.ct_tx = cv == 1 ? 30 : 14;
         g.ct_ty = kCtThreads / (g.ct_tx + 2) - 2;
     }
-    g.march = march_len(mv);
-    // a 32-cell march of planes this large would leave the 32-bit offsets of
-    // march_body (same results with 16)
-    if (mv == 1 && (idx_t)g.p[0] * g.p[1] * 8 * 38 >= (idx_t)1 << 32) g.march = 16;
+    const int m = mv == 1 ? 32 : 8;
+    if (mv > 0 && march_fits(g, m)) g.march[1] = g.march[2] = m;
+}
+
+// an instance's share, by cells, of the blocks that run at a time: one
+// predictor block per CU and two of the other kernels, more where the batch
+// gives each of them more than 16 planes of a tile (against a whole chip each:
+// 64 runs of 16..96 cells a side 3.83 -> 3.45 ms; 12 of 16..40 260 -> 165 us,
+// 6 of 12..90, third order, 295)
+static Slots batch_slots(const vlct_grid *vg, double cells)
+{
+    const double share = kNumCUs * ((double)vg->nx * vg->ny * vg->nz / cells);
+    const double rounds = std::max(1.0, cells / (kNumCUs * 16.0 * kPredTx * kPredTy));
+    auto part = [&](double f) { return std::max(1, (int)(share * f)); };
+    return Slots{part(2.0), part(rounds), part(std::max(2.0, rounds))};
 }
 
 // instance records with workspace regions and flattened block offsets;
@@ -1643,8 +1594,10 @@ static void batch_records(int count, const vlct_grid *grids, const vlct_state *i
     rec.resize(count);
     size_t off = batch_table_bytes(count);
     for (int s = 0; s < kSlots; ++s) total[s] = 0;
+    double cells = 0.0;
+    for (int i = 0; i < count; ++i) cells += (double)grids[i].nx * grids[i].ny * grids[i].nz;
     for (int i = 0; i < count; ++i) {
-        Geom g = make_geom(&grids[i]);
+        Geom g = make_geom(&grids[i], batch_slots(&grids[i], cells));
         const Layout L = layout(g);  // of the unplanned geometry, as the size query counts it
         plan_tiles(g, plan ? plan[i] : 0);
         const Bound B = bind(L, static_cast<char *>(ws) + off);
@@ -1663,7 +1616,7 @@ static void batch_records(int count, const vlct_grid *grids, const vlct_state *i
         r.active = nullptr;
         r.t = nullptr;
         idx_t nb[kSlots] = {};
-        nb[kSlotPred] = nblk_pred_shares(g);
+        nb[kSlotPred] = nblk_pred(g);
         nb[kSlotGhost] = (ghost_cells(g) + kBlock - 1) / kBlock;
         nb[kSlotRow] = nblk_row(g);
         nb[kSlotMarch1] = nblk_march(g, 1);

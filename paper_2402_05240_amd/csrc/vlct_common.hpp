@@ -4,6 +4,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
@@ -87,12 +88,11 @@ struct Geom {
     double dl[3], idl[3];  // cell widths and their reciprocals
     double gamma, gm1i, cfl;
     int p[3];  // padded primitive dims n + 2G
-    int march;        // cells per segment of the corrector's y and z marches
+    int march[3];     // cells per segment of the corrector's marches along y and z ([1], [2])
+    int pr_tx, pr_ty; // column tile of a predictor block
     int ct_tx, ct_ty; // column tile of a CT block
     int ct_planes;    // z planes a CT block marches through
-    int pred_slab;    // z planes per slab of the fused predictor's pair order
-    int pred_chunk;   // (column tile, plane) pairs of one fused predictor block
-                      // (0: one (slab, tile) per block)
+    int pred_slab;    // z planes a predictor block marches through
 };
 
 __host__ __device__ __forceinline__ int map_cell(int i, int n, int bc)
@@ -202,18 +202,18 @@ inline bool grid_ok(const vlct_grid *g)
 }
 
 // Tile override for tests and tuning: the environment variable VLCT_TILES,
-// read at every call, holds comma-separated key=value pairs (ct=4|8|16|32|64 CT
-// planes per block, march=8|16 cells per corrector march segment, pred=N
-// (column tile, plane) pairs per fused predictor block in one shared slab,
-// predslab=P slabs of P planes one per predictor block, admarch=8|16 cells per adjoint march
-// segment) that replace the size-dependent choices.  Every choice computes the
+// read at every call, holds comma-separated key=value pairs (ct=N and pred=N or
+// predslab=N planes per CT and predictor block, cttile=NX and predtile=NX columns
+// along x of their tiles, march=N cells per corrector march segment, 1 to 32,
+// admarch=8|16 cells per adjoint march segment) that replace the
+// size-dependent choices.  Every choice computes the
 // same per-cell and per-face arithmetic; the forward results are bitwise the
 // same, the adjoint's equal to the summation order of its accumulations.
 // Returns 0 when `key` is not set.
 inline int tile_override(const char *key)
 {
     const char *env = std::getenv("VLCT_TILES");
-    if (!env) return 0;
+    if (!env || !*env) return 0;
     const size_t kl = std::strlen(key);
     for (const char *p = env; *p;) {
         if (std::strncmp(p, key, kl) == 0 && p[kl] == '=') return std::atoi(p + kl + 1);
@@ -224,18 +224,19 @@ inline int tile_override(const char *key)
     return 0;
 }
 
-// fused predictor column tile: kPredTx x kPredTy cells, its threads also
-// covering a one-cell ring (34 x 15 columns, 510 threads of 512); one block
-// per CU (133 KB of LDS, 256 VGPRs: two waves per SIMD)
-constexpr int kPredTx = 32, kPredTy = 13;
+// blocks of the predictor and of the CT update: up to 512 threads, one per
+// column of the tile and of its one-cell ring (32 x 13 columns: 34 x 15 = 510
+// threads).  The predictor has one block per CU (133 KB of LDS, 256 VGPRs: two
+// waves per SIMD), the CT update two.
+constexpr int kPredTx = 32, kPredTy = 13, kTileThreads = 512;
 constexpr int kPredBlocksPerCU = 1;
 constexpr int kPredWavesPerSimd = 2;
 constexpr int kNumCUs = 256;  // gfx950 (MI355X)
 
 __host__ __device__ __forceinline__ long long pred_tiles(const Geom &g)
 {
-    const int ntx = (g.n[0] + (g.bc[0] == VLCT_BC_OUTFLOW) + kPredTx - 1) / kPredTx;
-    const int nty = (g.n[1] + (g.bc[1] == VLCT_BC_OUTFLOW) + kPredTy - 1) / kPredTy;
+    const int ntx = (g.n[0] + (g.bc[0] == VLCT_BC_OUTFLOW) + g.pr_tx - 1) / g.pr_tx;
+    const int nty = (g.n[1] + (g.bc[1] == VLCT_BC_OUTFLOW) + g.pr_ty - 1) / g.pr_ty;
     return (long long)ntx * nty;
 }
 
@@ -246,7 +247,61 @@ __host__ __device__ __forceinline__ long long ct_tiles(const Geom &g)
     return (long long)ntx * nty;
 }
 
-inline Geom make_geom(const vlct_grid *vg)
+// Column tile and planes per block for a kernel that marches tiles along z:
+// minimises the time of the launch, taken as rounds of one block per CU times
+// (planes + 2) (a run of planes also evaluates the plane beyond each end) times
+// `unit` of a round, over the tiles of at most kTileThreads columns (and of half
+// of them: one wave per SIMD, a shorter plane but more blocks) and the planes
+// that fill 1 to 6 rounds.  The 32-column tile stays unless another is 3% better.
+struct TileChoice {
+    int tx, ty, planes;
+    double cost;
+};
+template <class Unit>
+inline TileChoice choose_tile(int ex, int ey, int nz, int slots, Unit unit)
+{
+    TileChoice best{0, 0, 0, 0.0};
+    auto offer = [&](int tx, int threads) {
+        int ty = threads / (tx + 2) - 2;
+        if (ty < 1) return;
+        const int nty = (ey + ty - 1) / ty;
+        ty = (ey + nty - 1) / nty;
+        const long long tiles = (long long)((ex + tx - 1) / tx) * nty;
+        for (int r = 1; r <= 6; ++r) {
+            const long long slabs = (long long)slots * r / tiles;
+            if (slabs < 1) continue;
+            const int p = slabs >= nz ? 1 : (int)((nz + slabs - 1) / slabs);
+            if (p > 64) continue;
+            const long long blocks = tiles * ((nz + p - 1) / p);
+            const int rounds = (int)((blocks + slots - 1) / slots);
+            const double cost = (p + 2) * unit((tx + 2) * (ty + 2), rounds);
+            if (best.tx == 0 || cost < 0.97 * best.cost || (tx == best.tx && ty == best.ty && cost < best.cost))
+                best = TileChoice{tx, ty, p, cost};
+        }
+    };
+    offer(ex < kPredTx ? ex : kPredTx, kTileThreads);
+    const int least = ex < 14 ? ex : 14;
+    for (int threads = kTileThreads; threads >= kTileThreads / 2; threads /= 2)
+        for (int ntx = (ex + 125) / 126; (ex + ntx - 1) / ntx >= least; ++ntx) {
+            offer((ex + ntx - 1) / ntx, threads);
+            if (ntx >= ex) break;
+        }
+    return best;
+}
+
+// a march of m cells keeps its byte offsets (padded planes) below 2^32
+inline bool march_fits(const Geom &g, int m)
+{
+    return (idx_t)g.p[0] * g.p[1] * 8 * (m + 6) < (idx_t)1 << 32;
+}
+
+// blocks of a grid that run at a time in each kernel, for the choices below
+// (one per CU; a batched step: its instance's share)
+struct Slots {
+    int march = kNumCUs, pred = kNumCUs, ct = kNumCUs;
+};
+
+inline Geom make_geom(const vlct_grid *vg, const Slots &slots = Slots())
 {
     Geom g;
     g.n[0] = vg->nx;
@@ -263,56 +318,91 @@ inline Geom make_geom(const vlct_grid *vg)
     g.gamma = vg->gamma;
     g.gm1i = 1.0 / (vg->gamma - 1.0);
     g.cfl = vg->cfl;
-    // corrector marches: 16 cells per segment, 8 while the 16-cell launch would
-    // have fewer than 1024 blocks (4 per CU)
-    const long long yblk = ((long long)(g.n[0] + 2) * (g.n[2] + 2) + kBlock - 1) / kBlock *
-                           ((g.n[1] + 15) / 16);
-    g.march = yblk < 1024 ? 8 : 16;
-    // CT column tile and planes per block
-    g.ct_tx = kPredTx;
-    g.ct_ty = kPredTy;
-    const long long cols = ct_tiles(g);
-    g.ct_planes = 32;
-    while (g.ct_planes > 8 && cols * ((g.n[2] + g.ct_planes - 1) / g.ct_planes) < 1024)
-        g.ct_planes /= 2;
-    if (g.ct_planes == 8 && cols * ((g.n[2] + 7) / 8) < 256) g.ct_planes = 4;
-    // fused predictor (a run of p planes also solves the faces of one plane
-    // beyond each end): either one (z slab of p planes, column tile) per block,
-    // neighbouring tiles of a slab in neighbouring blocks so that they share
-    // their ring columns in L2, p minimising (waves of resident blocks) x
-    // (p + 2); or, where that leaves much of the last wave idle, the grid as
-    // one slab shared out evenly over one wave, at least 4 planes a block
-    // (measured: slabs at 64^3 and 256^3, one shared slab at 128^3)
-    const long long tiles = pred_tiles(g), resident = (long long)kNumCUs * kPredBlocksPerCU;
+    const int ex = g.n[0] + (g.bc[0] == VLCT_BC_OUTFLOW), ey = g.n[1] + (g.bc[1] == VLCT_BC_OUTFLOW);
+    const int nz = g.n[2];
+    // corrector marches: 16 cells per segment where that is four blocks per CU
+    // or more (256^3: 0.73 ms per axis, 0.75 with 8); below, the m up to 32 that
+    // minimises rounds of blocks x (m + 1) Riemann solves in a row (both axes,
+    // against 8: 32^3 16 -> with m = 1 ... 125 -> 98 us a step, 512 x 16 x 16
+    // 180 -> 142, 64^3 142 -> 131, 128^3 608 -> 590)
+    for (int d = 1; d <= 2; ++d) {
+        const long long cols = ((long long)(g.n[0] + 2) * (g.n[3 - d] + 2) + kBlock - 1) / kBlock;
+        auto blocks = [&](int m) { return cols * ((g.n[d] + m - 1) / m); };
+        g.march[d] = 16;
+        if (blocks(16) < 4 * slots.march) {
+            long long best = 0;
+            for (int m = 32; m >= 1; --m) {
+                const long long cost = (blocks(m) + slots.march - 1) / slots.march * (m + 1);
+                if (march_fits(g, m) && (best == 0 || cost < best)) {
+                    best = cost;
+                    g.march[d] = m;
+                }
+            }
+        }
+    }
+    // fused predictor, one block per CU at a time: the 32 x 13 tile with the
+    // planes (a power of two) of least cost where no choice fills at most six
+    // rounds, else the cheapest choice.  A plane takes a lone block of 512
+    // threads 7.0 us and one of 256 threads 4.6 (32^3: 6 planes in 3 blocks 45
+    // us, 3 in 28 smaller ones 17; 100 x 75 x 50: 47 -> 37 us)
+    g.pr_tx = kPredTx;
+    g.pr_ty = kPredTy;
     double best = -1.0;
     for (int p = 64; p >= 4; p /= 2) {
-        const long long blocks = tiles * ((g.n[2] + p - 1) / p);
-        const double cost = (double)((blocks + resident - 1) / resident) * (p + 2);
+        const long long blocks = pred_tiles(g) * ((nz + p - 1) / p);
+        const double cost = (double)((blocks + slots.pred - 1) / slots.pred) * (p + 2);
         if (best < 0.0 || cost < best) {
             best = cost;
             g.pred_slab = p;
-            g.pred_chunk = 0;  // one (slab, tile) per block
         }
     }
-    long long chunk = (tiles * g.n[2] + resident - 1) / resident;
-    if (chunk < 4) chunk = 4;
-    const double shared = (double)chunk + 2.0 * (1.0 + (double)chunk / g.n[2]);
-    if (shared < 0.9 * best) {
-        g.pred_slab = g.n[2];
-        g.pred_chunk = (int)chunk;
+    const TileChoice pr = choose_tile(ex, ey, nz, slots.pred, [](int threads, int rounds) {
+        return (threads > kTileThreads / 2 ? 1.0 : 0.66) * rounds;
+    });
+    if (pr.tx && pr.cost < best) {
+        g.pr_tx = pr.tx;
+        g.pr_ty = pr.ty;
+        g.pred_slab = pr.planes;
     }
-    const int oct = tile_override("ct"), opred = tile_override("pred");
-    const int om = tile_override("march");
-    if (om == 8 || om == 16) g.march = om;
-    if (oct == 4 || oct == 8 || oct == 16 || oct == 32 || oct == 64) g.ct_planes = oct;
-    const int oslab = tile_override("predslab");
-    if (opred >= 1) {  // one shared slab, opred pairs per block
-        g.pred_slab = g.n[2];
-        g.pred_chunk = opred;
+    // CT update: 8 to 32 planes of the 32 x 13 tile where that is four blocks
+    // per CU or more; below, the cheapest choice, a lone block taking 1.65 us a
+    // plane and a round of several per CU 1.4 (32^3 21 -> 9 us, 96^3 60 -> 40,
+    // 100 x 75 x 50 33 -> 23)
+    g.ct_tx = kPredTx;
+    g.ct_ty = kPredTy;
+    const long long cols = ct_tiles(g);
+    auto ctblocks = [&](int p) { return cols * ((nz + p - 1) / p); };
+    g.ct_planes = 32;
+    while (g.ct_planes > 8 && ctblocks(g.ct_planes) < 4 * slots.ct) g.ct_planes /= 2;
+    if (ctblocks(8) < 4 * slots.ct) {
+        const TileChoice ct = choose_tile(ex, ey, nz, slots.ct, [](int threads, int rounds) {
+            return rounds == 1 ? (threads > kTileThreads / 2 ? 1.2 : 1.0) : rounds;
+        });
+        if (ct.tx) {
+            g.ct_tx = ct.tx;
+            g.ct_ty = ct.ty;
+            g.ct_planes = ct.planes;
+        }
     }
-    if (oslab >= 1) {  // slabs of oslab planes, one (slab, tile) per block
-        g.pred_slab = oslab;
-        g.pred_chunk = 0;
+    auto forced = [](const char *key, int &v, int lo, int hi) {
+        const int o = tile_override(key);
+        if (o >= lo && o <= hi) v = o;
+    };
+    forced("ct", g.ct_planes, 1, kMaxN);
+    forced("pred", g.pred_slab, 1, kMaxN);
+    forced("predslab", g.pred_slab, 1, kMaxN);
+    int m = 0, ctx = 0, prx = 0;
+    forced("march", m, 1, 32);
+    if (m > 0 && march_fits(g, m)) g.march[1] = g.march[2] = m;
+    forced("cttile", ctx, 1, kTileThreads / 3 - 2);
+    if (ctx > 0) {
+        g.ct_tx = ctx;
+        g.ct_ty = kTileThreads / (ctx + 2) - 2;
+    }
+    forced("predtile", prx, 1, kTileThreads / 3 - 2);
+    if (prx > 0) {
+        g.pr_tx = prx;
+        g.pr_ty = kTileThreads / (prx + 2) - 2;
     }
     return g;
 }
