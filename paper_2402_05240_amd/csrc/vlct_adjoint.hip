@@ -270,34 +270,41 @@ __global__ __launch_bounds__(kBlock, 2) void k_ad_faces(Geom g, Prims P, StateP 
 }
 
 // faces of axis D = y or z with a reconstructing corrector, one thread per
-// column (i, j or k) and segment of kAdMarch cells along D: each cell is
+// column (i, j or k) and segment of M cells along D: each cell is
 // reconstructed once and its high-face state carried to the next face.  Per
 // face the same work as k_ad_faces_row.
-constexpr int kAdMarch = 16;
-
-__host__ __device__ __forceinline__ idx_t ad_march_blocks(const Geom &g, int D,
-                                                          int m = kAdMarch)
+__host__ __device__ __forceinline__ idx_t ad_march_blocks(const Geom &g, int D, int m)
 {
     const int T = D == 1 ? 2 : 1;
     const idx_t cols = (idx_t)g.n[0] * g.n[T];
     return ((cols + kBlock - 1) / kBlock) * ((g.n[D] + m - 1) / m);
 }
 
-// segment of the fused adjoint marches: 16 cells, or 8 on a grid whose
-// 16-cell launch would have fewer than 256 blocks (64^3 adjoint 0.93 -> 0.74
-// ms; 128^3, 512 blocks, is faster with 16)
+// cells per segment of the adjoint marches: one block per CU at a time and
+// m + 1 reversals in a row in each, so the m up to 32 of least rounds x (m + 1)
+// (64^3, third order, against 16 and 8: faces 131 -> 44 us an axis, reversed
+// reconstructions 166 -> 104; 128^3, 32 and 16 are the same)
 static int ad_march_segment(const Geom &g, int D)
 {
     const int o = tile_override("admarch");
-    if (o == 8 || o == kAdMarch) return o;
-    return ad_march_blocks(g, D, kAdMarch) < 256 ? 8 : kAdMarch;
+    if (o >= 1 && o <= 64) return o;
+    idx_t best = 0;
+    int len = 1;
+    for (int m = 32; m >= 1; --m) {
+        const idx_t cost = (ad_march_blocks(g, D, m) + kNumCUs - 1) / kNumCUs * (m + 1);
+        if (best == 0 || cost < best) {
+            best = cost;
+            len = m;
+        }
+    }
+    return len;
 }
 
 template <int D, int RECON>
 __global__ __launch_bounds__(kBlock) void k_ad_faces_march(Geom g, Prims P, StateP st,
                                                            StateP lout, AdStage S,
                                                            StateW lacc, const double *dt_dev,
-                                                           double factor)
+                                                           double factor, int M)
 {
     static_assert(D == 1 || D == 2, "columns march along y or z");
     constexpr int T = D == 1 ? 2 : 1;
@@ -314,7 +321,7 @@ __global__ __launch_bounds__(kBlock) void k_ad_faces_march(Geom g, Prims P, Stat
     int x[3];
     x[0] = (int)(col % g.n[0]);
     x[T] = (int)(col / g.n[0]);
-    const int s0 = seg * kAdMarch, s1 = min(s0 + kAdMarch, nD);  // cells [s0, s1)
+    const int s0 = seg * M, s1 = min(s0 + M, nD);  // cells [s0, s1)
     const double c = factor * dt_dev[0] / g.dl[D];
     auto pid = [&](int along) {
         int q[3] = {x[0], x[1], x[2]};
@@ -464,11 +471,11 @@ __global__ __launch_bounds__(kBlock, 2) void k_ad_faces_row(Geom g, Prims P, Sta
 // above it (whose cotangent the top cell needs; its normal-field cotangent
 // stays with the segment that owns it), and as soon as a cell has the
 // cotangents of both its interface states it reverses its reconstruction.
-template <int D, int RECON, int M = kAdMarch>
+template <int D, int RECON>
 __global__ __launch_bounds__(kBlock) void k_ad_march_fused(Geom g, Prims P, StateP st,
                                                            StateP lout, AdStage S,
                                                            StateW lacc, const double *dt_dev,
-                                                           double factor)
+                                                           double factor, int M)
 {
     static_assert(D == 1 || D == 2, "columns march along y or z");
     static_assert(RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PLMP, "linear reconstructions");
@@ -780,8 +787,8 @@ __global__ __launch_bounds__(kBlock) void k_ad_recon(Geom g, Prims P, AdStage S)
 // (segments share two cells at each end, so every departure stays atomic).
 // The cell's own B_n cotangent comes from its reversal alone and is added
 // in place.
-template <int D, int RECON, int M = kAdMarch>
-__global__ __launch_bounds__(kBlock) void k_ad_recon_march(Geom g, Prims P, AdStage S)
+template <int D, int RECON>
+__global__ __launch_bounds__(kBlock) void k_ad_recon_march(Geom g, Prims P, AdStage S, int M)
 {
     static_assert(D == 1 || D == 2, "columns march along y or z");
     static_assert(RECON == VLCT_RECON_PPMC || RECON == VLCT_RECON_PPMP, "parabolic reconstructions");
@@ -967,39 +974,23 @@ static void stage_adjoint(const Geom &g, double factor, const StateP &lout, cons
 {
     const unsigned gc = nblocks((size_t)g.n[0] * g.n[1] * g.n[2]);
     k_ad_edges<<<gc, kBlock, 0, s>>>(g, lout, sd, S, dt, factor, recon != VLCT_RECON_PCM);
-#define VLCT_AD_FACES(R)                                                             \
+    const int m1 = ad_march_segment(g, 1), m2 = ad_march_segment(g, 2);
+    const unsigned b1 = (unsigned)ad_march_blocks(g, 1, m1), b2 = (unsigned)ad_march_blocks(g, 2, m2);
+#define VLCT_AD_FACES(R)                                                                   \
     k_ad_faces_row<R><<<(unsigned)ad_row_blocks(g), kBlock, 0, s>>>(g, P, st, lout, S,     \
                                                                      lacc, dt, factor);    \
-    k_ad_faces_march<1, R><<<(unsigned)ad_march_blocks(g, 1), kBlock, 0, s>>>(             \
-        g, P, st, lout, S, lacc, dt, factor);                                              \
-    k_ad_faces_march<2, R><<<(unsigned)ad_march_blocks(g, 2), kBlock, 0, s>>>(             \
-        g, P, st, lout, S, lacc, dt, factor);
+    k_ad_faces_march<1, R><<<b1, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor, m1); \
+    k_ad_faces_march<2, R><<<b2, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor, m2);
 #define VLCT_AD_FUSED(R)                                                                   \
     k_ad_row_fused<R><<<(unsigned)ad_row_fused_blocks(g), kBlock, 0, s>>>(g, P, st, lout,  \
                                                                            S, lacc, dt,    \
                                                                            factor);        \
-    if (ad_march_segment(g, 1) == 8)                                                       \
-        k_ad_march_fused<1, R, 8><<<(unsigned)ad_march_blocks(g, 1, 8), kBlock, 0, s>>>(   \
-            g, P, st, lout, S, lacc, dt, factor);                                          \
-    else                                                                                   \
-        k_ad_march_fused<1, R><<<(unsigned)ad_march_blocks(g, 1), kBlock, 0, s>>>(         \
-            g, P, st, lout, S, lacc, dt, factor);                                          \
-    if (ad_march_segment(g, 2) == 8)                                                       \
-        k_ad_march_fused<2, R, 8><<<(unsigned)ad_march_blocks(g, 2, 8), kBlock, 0, s>>>(   \
-            g, P, st, lout, S, lacc, dt, factor);                                          \
-    else                                                                                   \
-        k_ad_march_fused<2, R><<<(unsigned)ad_march_blocks(g, 2), kBlock, 0, s>>>(         \
-            g, P, st, lout, S, lacc, dt, factor);
+    k_ad_march_fused<1, R><<<b1, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor, m1); \
+    k_ad_march_fused<2, R><<<b2, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor, m2);
 #define VLCT_AD_RECON(R)                                                                   \
     k_ad_recon<0, R><<<gc, kBlock, 0, s>>>(g, P, S);                                       \
-    if (ad_march_segment(g, 1) == 8)                                                       \
-        k_ad_recon_march<1, R, 8><<<(unsigned)ad_march_blocks(g, 1, 8), kBlock, 0, s>>>(g, P, S); \
-    else                                                                                   \
-        k_ad_recon_march<1, R><<<(unsigned)ad_march_blocks(g, 1), kBlock, 0, s>>>(g, P, S); \
-    if (ad_march_segment(g, 2) == 8)                                                       \
-        k_ad_recon_march<2, R, 8><<<(unsigned)ad_march_blocks(g, 2, 8), kBlock, 0, s>>>(g, P, S); \
-    else                                                                                   \
-        k_ad_recon_march<2, R><<<(unsigned)ad_march_blocks(g, 2), kBlock, 0, s>>>(g, P, S);
+    k_ad_recon_march<1, R><<<b1, kBlock, 0, s>>>(g, P, S, m1);                             \
+    k_ad_recon_march<2, R><<<b2, kBlock, 0, s>>>(g, P, S, m2);
     if (recon == VLCT_RECON_PCM) {
         k_ad_faces<0><<<gc, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor);
         k_ad_faces<1><<<gc, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor);
