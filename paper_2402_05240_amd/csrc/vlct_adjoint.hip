@@ -44,19 +44,47 @@ struct AdStage {
 
 __device__ __forceinline__ int wrapc(int i, int n) { return map_cell(i, n, VLCT_BC_PERIODIC); }
 
-__device__ __forceinline__ idx_t cell_of(const Geom &g, int i, int j, int k)
+// Flat indices are 32-bit: a field of 2^32 elements would be 32 GiB, and the
+// adjoint's workspace alone holds more than 80 of them.  Coordinates passed
+// here lie in the grid; neighbours are reached by adding a step that wraps.
+__device__ __forceinline__ u32 cell_at(const Geom &g, int i, int j, int k)
 {
-    return cell_store(g, wrapc(i, g.n[0]), wrapc(j, g.n[1]), wrapc(k, g.n[2]));
+    return ((u32)k * (u32)g.n[1] + (u32)j) * (u32)g.n[0] + (u32)i;
 }
-__device__ __forceinline__ idx_t cell_of(const Geom &g, const int x[3])
+template <int D>
+__device__ __forceinline__ u32 face_at(const Geom &g, int i, int j, int k)
 {
-    return cell_of(g, x[0], x[1], x[2]);
+    return ((u32)k * (u32)(g.n[1] + (D == 1)) + (u32)j) * (u32)(g.n[0] + (D == 0)) + (u32)i;
 }
-__device__ __forceinline__ void cell_coords(const Geom &g, idx_t t, int x[3])
+// padded primitive index, i, j, k in [-G, n + G - 1]
+__device__ __forceinline__ u32 prim_at(const Geom &g, int i, int j, int k)
 {
-    x[0] = (int)(t % g.n[0]);
-    x[1] = (int)((t / g.n[0]) % g.n[1]);
-    x[2] = (int)(t / ((idx_t)g.n[0] * g.n[1]));
+    return ((u32)(k + kGhost) * (u32)g.p[1] + (u32)(j + kGhost)) * (u32)g.p[0] + (u32)(i + kGhost);
+}
+__device__ __forceinline__ void cell_coords(const Geom &g, u32 t, int x[3])
+{
+    const u32 r = t / (u32)g.n[0], k = r / (u32)g.n[1];
+    x[0] = (int)(t - r * (u32)g.n[0]);
+    x[1] = (int)(r - k * (u32)g.n[1]);
+    x[2] = (int)k;
+}
+template <int A>
+__device__ __forceinline__ u32 cell_stride(const Geom &g)
+{
+    return A == 0 ? 1u : (A == 1 ? (u32)g.n[0] : (u32)g.n[0] * (u32)g.n[1]);
+}
+// steps of a flat cell index to the neighbour below and above along A
+template <int A>
+__device__ __forceinline__ u32 step_lo(const Geom &g, const int x[3])
+{
+    const u32 s = cell_stride<A>(g);
+    return x[A] > 0 ? 0u - s : (u32)(g.n[A] - 1) * s;
+}
+template <int A>
+__device__ __forceinline__ u32 step_hi(const Geom &g, const int x[3])
+{
+    const u32 s = cell_stride<A>(g);
+    return x[A] < g.n[A] - 1 ? s : 0u - (u32)(g.n[A] - 1) * s;
 }
 
 // lab component of the primitive array for sweep-frame slot s of axis d:
@@ -75,7 +103,7 @@ __host__ __device__ __forceinline__ int lab_cons(int d, int c)
     return 1 + (d + c - 1) % 3;
 }
 
-__device__ __forceinline__ W7 w7_at(const Prims &P, int d, idx_t o)
+__device__ __forceinline__ W7 w7_at(const Prims &P, int d, u32 o)
 {
     return W7{P.w[0][o], P.w[lab_slot(d, 1)][o], P.w[lab_slot(d, 2)][o], P.w[lab_slot(d, 3)][o],
               P.w[4][o], P.w[lab_slot(d, 5)][o], P.w[lab_slot(d, 6)][o]};
@@ -87,185 +115,349 @@ struct Sides {
     const uint8_t *s[3];
 };
 
-// 8-bit code of edge (A, x0): the sides of the faces F_B(x0), F_B(x0 - e_C),
-// F_C(x0), F_C(x0 - e_B) (the four upwind terms of the edge field)
+// 8-bit code of edge (A, x): the sides of the faces F_B(x), F_B(x - e_C),
+// F_C(x), F_C(x - e_B) (the four upwind terms of the edge field)
 template <int A>
-__device__ __forceinline__ uint32_t edge_code(const Geom &g, const Sides &sd, const int x0[3])
+__device__ __forceinline__ u32 edge_code(const Geom &g, const Sides &sd, const int x[3], u32 t)
 {
     constexpr int B = (A + 1) % 3, C = (A + 2) % 3;
-    int xb[3] = {x0[0], x0[1], x0[2]}, xc[3] = {x0[0], x0[1], x0[2]};
-    xb[B] -= 1;
-    xc[C] -= 1;
-    return (uint32_t)sd.s[B][cell_of(g, x0)] | ((uint32_t)sd.s[B][cell_of(g, xc)] << 2) |
-           ((uint32_t)sd.s[C][cell_of(g, x0)] << 4) | ((uint32_t)sd.s[C][cell_of(g, xb)] << 6);
+    return (u32)sd.s[B][t] | ((u32)sd.s[B][t + step_lo<C>(g, x)] << 2) | ((u32)sd.s[C][t] << 4) |
+           ((u32)sd.s[C][t + step_lo<B>(g, x)] << 6);
 }
 
-// upwind weights of edge (A, x0): w[0..7] = w1l, w1h, w2l, w2h, w3l, w3h, w4l, w4h
-template <int A>
-__device__ __forceinline__ void edge_weights(const Geom &g, const AdStage &S, const int x0[3],
-                                             double w[8])
+// twice the weight (1, 0 or 1/2 by the side) of the low side of upwind term q
+// of edge field A at flat cell index t; the high side has the rest
+__device__ __forceinline__ int low2(u32 code, int q) { return (0x52 >> (2 * ((code >> (2 * q)) & 3u))) & 3; }
+__device__ __forceinline__ int high2(u32 code, int q) { return 2 - low2(code, q); }
+
+// the cotangent of the state that a stage starts from: before the stage's own
+// terms it is that of the step's result (each periodic duplicate face folded
+// into face 0, which the step copies to it) plus that of the half step (add),
+// or nothing (the corrector's, whose input state enters through it alone)
+struct AdBase {
+    StateP lam, half;
+    int add;
+};
+template <int D>
+__device__ __forceinline__ double folded(const Geom &g, const StateP &lam, u32 f, const int x[3])
 {
-    const uint32_t c = S.wcode[cell_of(g, x0)] >> (8 * A);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t k = (c >> (2 * q)) & 3u;
-        w[2 * q] = k == 0u ? 1.0 : (k == 1u ? 0.0 : 0.5);
-        w[2 * q + 1] = 1.0 - w[2 * q];
+    double v = lam.b[D][f];
+    if (x[D] == 0) {
+        const u32 s = D == 0 ? 1u : (D == 1 ? (u32)g.n[0] : (u32)g.n[0] * (u32)g.n[1]);
+        v += lam.b[D][f + (u32)g.n[D] * s];
     }
+    return v;
 }
-
-// lam_next = lam_out with each periodic duplicate face folded into face 0 (the
-// step writes face n as a copy of face 0); the half-step cotangent `half`
-// starts at zero
-__global__ void k_ad_init(Geom g, StateP lo, StateW next, StateW half)
+template <int D>
+__device__ __forceinline__ double base_face(const Geom &g, const AdBase &base, u32 f, const int x[3])
 {
-    const idx_t N = (idx_t)g.n[0] * g.n[1] * g.n[2];
-    const idx_t t = (idx_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < N)
-        for (int f = 0; f < 5; ++f) {
-            next.u[f][t] = lo.u[f][t];
-            half.u[f][t] = 0.0;
-        }
-    for (int d = 0; d < 3; ++d) {
-        const idx_t nf = N / g.n[d] * (g.n[d] + 1);
-        if (t >= nf) continue;
-        const int nx = g.n[0] + (d == 0), ny = g.n[1] + (d == 1);
-        const int i = (int)(t % nx), j = (int)((t / nx) % ny), k = (int)(t / ((idx_t)nx * ny));
-        const int e[3] = {i, j, k};
-        double v = lo.b[d][t];
-        if (e[d] == g.n[d]) v = 0.0;  // the duplicate itself carries nothing
-        if (e[d] == 0) {
-            int q[3] = {i, j, k};
-            q[d] = g.n[d];
-            v += lo.b[d][face_store(g, d, q[0], q[1], q[2])];
-        }
-        next.b[d][t] = v;
-        half.b[d][t] = 0.0;
-    }
+    return base.add ? folded<D>(g, base.lam, f, x) + base.half.b[D][f] : 0.0;
 }
-
-// out = a + b (cells and faces): lam_in starts as lam_next (U^{n+1} contains
-// U^n with unit weight) plus the half-step cotangent
-__global__ void k_ad_add(Geom g, StateW out, StateP a, StateP b)
+// the duplicate plane itself carries nothing
+template <int D>
+__device__ __forceinline__ void clear_duplicate(const Geom &g, const StateW &lacc, u32 f, const int x[3])
 {
-    const idx_t N = (idx_t)g.n[0] * g.n[1] * g.n[2];
-    const idx_t t = (idx_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < N)
-        for (int f = 0; f < 5; ++f) out.u[f][t] = a.u[f][t] + b.u[f][t];
-    for (int d = 0; d < 3; ++d) {
-        const idx_t nf = N / g.n[d] * (g.n[d] + 1);
-        if (t < nf) out.b[d][t] = a.b[d][t] + b.b[d][t];
+    if (x[D] == 0) {
+        const u32 s = D == 0 ? 1u : (D == 1 ? (u32)g.n[0] : (u32)g.n[0] * (u32)g.n[1]);
+        lacc.b[D][f + (u32)g.n[D] * s] = 0.0;
     }
 }
 
 // edge-field cotangents (curl of the face update transposed): the face update
-// is b_x -= cy (Ez(j+1) - Ez(j)) - cz (Ey(k+1) - Ey(k)) and cyclically
+// is b_x -= cy (Ez(j+1) - Ez(j)) - cz (Ey(k+1) - Ey(k)) and cyclically, and
+// the upwind codes of the edges.  fold: lout's duplicate faces count for face 0.
 // zero_lw: also clears the cell's primitive cotangents S.lw, into which the
 // reconstruction transposes that follow add
-__global__ void k_ad_edges(Geom g, StateP lout, Sides sd, AdStage S, const double *dt_dev,
+__global__ void k_ad_edges(Geom g, StateP lout, int fold, Sides sd, AdStage S, const double *dt_dev,
                            double factor, int zero_lw)
 {
-    const idx_t N = (idx_t)g.n[0] * g.n[1] * g.n[2];
-    const idx_t t = (idx_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const u32 N = (u32)g.n[0] * (u32)g.n[1] * (u32)g.n[2];
+    const u32 t = blockIdx.x * (u32)kBlock + threadIdx.x;
     if (t >= N) return;
     int x[3];
     cell_coords(g, t, x);
     const int i = x[0], j = x[1], k = x[2];
+    const int im = i > 0 ? i - 1 : g.n[0] - 1, jm = j > 0 ? j - 1 : g.n[1] - 1,
+              km = k > 0 ? k - 1 : g.n[2] - 1;
     const double cx = factor * dt_dev[0] / g.dl[0], cy = factor * dt_dev[0] / g.dl[1],
                  cz = factor * dt_dev[0] / g.dl[2];
-    auto lb = [&](int d, int a, int b2, int c2) {
-        return lout.b[d][face_store(g, d, wrapc(a, g.n[0]), wrapc(b2, g.n[1]), wrapc(c2, g.n[2]))];
+    auto bx = [&](int a, int b, int c) {
+        const u32 f = face_at<0>(g, a, b, c);
+        return fold ? folded<0>(g, lout, f, x) : lout.b[0][f];
     };
-    S.le[0][t] = cz * (lb(1, i, j, k) - lb(1, i, j, k - 1)) + cy * (lb(2, i, j - 1, k) - lb(2, i, j, k));
-    S.le[1][t] = cz * (lb(0, i, j, k - 1) - lb(0, i, j, k)) + cx * (lb(2, i, j, k) - lb(2, i - 1, j, k));
-    S.le[2][t] = cy * (lb(0, i, j, k) - lb(0, i, j - 1, k)) + cx * (lb(1, i - 1, j, k) - lb(1, i, j, k));
-    S.wcode[t] = edge_code<0>(g, sd, x) | (edge_code<1>(g, sd, x) << 8) | (edge_code<2>(g, sd, x) << 16);
+    auto by = [&](int a, int b, int c) {
+        const u32 f = face_at<1>(g, a, b, c);
+        return fold ? folded<1>(g, lout, f, x) : lout.b[1][f];
+    };
+    auto bz = [&](int a, int b, int c) {
+        const u32 f = face_at<2>(g, a, b, c);
+        return fold ? folded<2>(g, lout, f, x) : lout.b[2][f];
+    };
+    const double x0 = bx(i, j, k), y0 = by(i, j, k), z0 = bz(i, j, k);
+    S.le[0][t] = cz * (y0 - by(i, j, km)) + cy * (bz(i, jm, k) - z0);
+    S.le[1][t] = cz * (bx(i, j, km) - x0) + cx * (z0 - bz(im, j, k));
+    S.le[2][t] = cy * (x0 - bx(i, jm, k)) + cx * (by(im, j, k) - y0);
+    S.wcode[t] = edge_code<0>(g, sd, x, t) | (edge_code<1>(g, sd, x, t) << 8) |
+                 (edge_code<2>(g, sd, x, t) << 16);
     if (zero_lw)
         for (int f = 0; f < 8; ++f) S.lw[f][t] = 0.0;
 }
 
-// cotangents of the 7 fluxes of the face of axis D at x (the low face of cell x)
+// cotangents of the 7 fluxes of the face of axis D at x (the low face of cell
+// x, flat index t)
 template <int D>
 __device__ __forceinline__ void flux_cotangent(const Geom &g, const StateP &lout,
-                                               const AdStage &S, const int x[3], idx_t t,
+                                               const AdStage &S, const int x[3], u32 t,
                                                double c, double lf[7])
 {
-    int l[3] = {x[0], x[1], x[2]};
-    l[D] -= 1;
-    const idx_t cl = cell_of(g, l);
+    const u32 cl = t + step_lo<D>(g, x);
     // cell update u -= c (F(x + e_D) - F(x))
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
         const int f = lab_cons(D, q);
         lf[q] = c * (lout.u[f][t] - lout.u[f][cl]);
     }
-    // F_D[B_t1] enters the edges E_A, A = D + 2, as -F: at x (weights w3h, w4h)
-    // and at x + e_C, C = D + 1 (weights w3l, w4l)
+    const u32 code = S.wcode[t];
+    // F_D[B_t1] enters the edges E_A, A = D + 2, as -F: at x (weights of the
+    // high sides of terms 3 and 4) and at x + e_C, C = D + 1 (low sides)
     {
         constexpr int A = (D + 2) % 3, C = (A + 2) % 3;
-        double w[8];
-        edge_weights<A>(g, S, x, w);
-        double acc = -0.25 * (1.0 + w[5] + w[7]) * S.le[A][t];
-        int y[3] = {x[0], x[1], x[2]};
-        y[C] += 1;
-        edge_weights<A>(g, S, y, w);
-        acc += -0.25 * (1.0 + w[4] + w[6]) * S.le[A][cell_of(g, y)];
-        lf[5] = acc;
+        const u32 y = t + step_hi<C>(g, x);
+        const u32 cx = code >> (8 * A), cy = S.wcode[y] >> (8 * A);
+        const double wx = 1.0 + 0.5 * (double)(high2(cx, 2) + high2(cx, 3));
+        const double wy = 1.0 + 0.5 * (double)(low2(cy, 2) + low2(cy, 3));
+        lf[5] = -0.25 * wx * S.le[A][t] + -0.25 * wy * S.le[A][y];
     }
-    // F_D[B_t2] enters the edges E_A, A = D + 1, as +F: at x (weights w1h, w2h)
-    // and at x + e_B, B = D + 2 (weights w1l, w2l)
+    // F_D[B_t2] enters the edges E_A, A = D + 1, as +F: at x (high sides of
+    // terms 1 and 2) and at x + e_B, B = D + 2 (low sides)
     {
         constexpr int A = (D + 1) % 3, B = (A + 1) % 3;
-        double w[8];
-        edge_weights<A>(g, S, x, w);
-        double acc = 0.25 * (1.0 + w[1] + w[3]) * S.le[A][t];
-        int y[3] = {x[0], x[1], x[2]};
-        y[B] += 1;
-        edge_weights<A>(g, S, y, w);
-        acc += 0.25 * (1.0 + w[0] + w[2]) * S.le[A][cell_of(g, y)];
-        lf[6] = acc;
+        const u32 y = t + step_hi<B>(g, x);
+        const u32 cx = code >> (8 * A), cy = S.wcode[y] >> (8 * A);
+        const double wx = 1.0 + 0.5 * (double)(high2(cx, 0) + high2(cx, 1));
+        const double wy = 1.0 + 0.5 * (double)(low2(cy, 0) + low2(cy, 1));
+        lf[6] = 0.25 * wx * S.le[A][t] + 0.25 * wy * S.le[A][y];
     }
 }
 
-// faces of axis D of the PCM stage: flux cotangents, then HLLD reversed at
-// the forward states (the cell primitives).  The cotangents of the face's two
-// states are stored per cell and axis (as the high state of the left cell and
-// the low state of the right cell) for the next transpose.  A reconstructing
-// stage takes k_ad_faces_row (x) and k_ad_faces_march (y, z).  Two waves per
-// SIMD (256 registers and a short spill) beat one wave with 280 registers.
-template <int D>
-__global__ __launch_bounds__(kBlock, 2) void k_ad_faces(Geom g, Prims P, StateP st, StateP lout,
-                                                     AdStage S, StateW lacc,
-                                                     const double *dt_dev, double factor)
+// cotangent of -(v x B)_A at cell x from the four A-edges around it
+template <int A>
+__device__ __forceinline__ double eref_cotangent(const Geom &g, const AdStage &S, const int x[3],
+                                                 u32 t)
 {
-    const idx_t N = (idx_t)g.n[0] * g.n[1] * g.n[2];
-    const idx_t t = (idx_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= N) return;
-    int x[3];
-    cell_coords(g, t, x);
-    double lf[7];
-    flux_cotangent<D>(g, lout, S, x, t, factor * dt_dev[0] / g.dl[D], lf);
-    auto at = [&](int off) {
-        int q[3] = {x[0], x[1], x[2]};
-        q[D] += off;
-        return pidx(g, q[0], q[1], q[2]);
+    constexpr int B = (A + 1) % 3, C = (A + 2) % 3;
+    // the cell is r00 of edge x, r10 of edge x + e_B, r01 of edge x + e_C and
+    // r11 of edge x + e_B + e_C
+    const u32 sb = step_hi<B>(g, x), sc = step_hi<C>(g, x);
+    auto code = [&](u32 y) { return S.wcode[y] >> (8 * A); };
+    const u32 c0 = code(t), c1 = code(t + sb), c2 = code(t + sc), c3 = code(t + sb + sc);
+    double acc = 0.5 * (double)(high2(c0, 0) + high2(c0, 2)) * S.le[A][t];
+    acc += 0.5 * (double)(low2(c1, 0) + high2(c1, 3)) * S.le[A][t + sb];
+    acc += 0.5 * (double)(high2(c2, 1) + low2(c2, 2)) * S.le[A][t + sc];
+    acc += 0.5 * (double)(low2(c3, 1) + low2(c3, 3)) * S.le[A][t + sb + sc];
+    return -0.25 * acc;
+}
+
+// reference fields -(v x B) and primitive recovery (Sec. 2.1; B_cc = face
+// average) of a cell reversed: its primitive cotangents lw become those of its
+// conserved variables, written to lacc.u on top of the base, and lb of each of
+// its six faces (half to either side).  A floored quantity is a constant.
+__device__ __forceinline__ void cell_rev(const Geom &g, const StateP &st, const Prims &P,
+                                         const AdStage &S, const AdBase &base, const StateW &lacc,
+                                         const int x[3], u32 t, double lw[8], double lb[3])
+{
+    const int i = x[0], j = x[1], k = x[2];
+    {
+        const u32 o = prim_at(g, i, j, k);
+        const double vx = P.w[1][o], vy = P.w[2][o], vz = P.w[3][o];
+        const double bx = P.w[5][o], by = P.w[6][o], bz = P.w[7][o];
+        const double ex = eref_cotangent<0>(g, S, x, t), ey = eref_cotangent<1>(g, S, x, t),
+                     ez = eref_cotangent<2>(g, S, x, t);
+        lw[1] += bz * ey - by * ez;
+        lw[2] += -bz * ex + bx * ez;
+        lw[3] += by * ex - bx * ey;
+        lw[5] += -vz * ey + vy * ez;
+        lw[6] += vz * ex - vx * ez;
+        lw[7] += -vy * ex + vx * ey;
+    }
+    const u32 f0 = face_at<0>(g, i, j, k), f1 = face_at<1>(g, i, j, k);
+    const double bc[3] = {0.5 * (st.b[0][f0] + st.b[0][f0 + step_hi<0>(g, x)]),
+                          0.5 * (st.b[1][f1] + st.b[1][f1 + step_hi<1>(g, x)]),
+                          0.5 * (st.b[2][t] + st.b[2][t + step_hi<2>(g, x)])};
+    double d = st.u[0][t];
+    const bool dfloor = !(d >= kFloorRho);
+    if (dfloor) d = kFloorRho;
+    const double id = mrcp(d);
+    const double v[3] = {st.u[1][t] * id, st.u[2][t] * id, st.u[3][t] * id};
+    const double ke = 0.5 * d * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+    const double me = 0.5 * (bc[0] * bc[0] + bc[1] * bc[1] + bc[2] * bc[2]);
+    const double p = (g.gamma - 1.0) * (st.u[4][t] - ke - me);
+    const bool pfloor = !(p >= kFloorP);
+    const double gm1 = g.gamma - 1.0;
+    const double lp = pfloor ? 0.0 : lw[4];
+    const double v2 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
+    double lrho = dfloor ? 0.0 : lw[0] + lp * gm1 * 0.5 * v2;
+    auto put = [&](int f, double a) {
+        lacc.u[f][t] = base.add ? base.lam.u[f][t] + base.half.u[f][t] + a : a;
     };
-    const W7 wl = w7_at(P, D, at(-1));
-    const W7 wr = w7_at(P, D, at(0));
-    const idx_t fo = face_store(g, D, x[0], x[1], x[2]);
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        if (!dfloor) lrho -= lw[1 + l] * v[l] * id;
+        put(1 + l, lw[1 + l] * id - lp * gm1 * v[l]);
+        lb[l] = 0.5 * (lw[5 + l] - lp * gm1 * bc[l]);
+    }
+    put(0, lrho);
+    put(4, lp * gm1);
+}
+
+// PCM stage: flux cotangents, then HLLD reversed at the forward states (the
+// cell primitives), then primitive recovery, without a pass over memory per
+// face.  The x kernel writes the sum of the cotangents of a cell's two x-face
+// states, the y march adds those of the y-faces, the z march those of the
+// z-faces and reverses the finished cell: about 125 doubles moved per cell
+// where storing both states' cotangents of every face moved 200.  Bound by
+// load latency (one wave per SIMD in the marches, 300 registers): 64^3 27 + 28
+// + 49 us (faces and gather: 80 + 36), 128^3 188 + 222 + 406 (568 + 262).
+//
+// x: items (row, face 0 .. nx) of every row in one flat sequence (face nx is
+// face 0 again), blocks of kBlock items overlapping by one; the cotangent of a
+// face's left state goes to the item on the left through LDS.  The x kernel
+// also starts the z-faces' cotangents, which the z march's segments share.
+__host__ __device__ __forceinline__ idx_t ad_pcm_row_blocks(const Geom &g)
+{
+    const idx_t items = (idx_t)(g.n[0] + 1) * g.n[1] * g.n[2];
+    return (items - 1 + kBlock - 2) / (kBlock - 1);
+}
+
+__global__ __launch_bounds__(kBlock, 2) void k_ad_pcm_row(Geom g, Prims P, StateP st, StateP lout,
+                                                          AdStage S, AdBase base, StateW lacc,
+                                                          const double *dt_dev, double factor)
+{
+    __shared__ double lds[7][kBlock];
+    const u32 per_row = (u32)g.n[0] + 1, items = per_row * (u32)g.n[1] * (u32)g.n[2];
+    const int tid = threadIdx.x;
+    const u32 q = blockIdx.x * (u32)(kBlock - 1) + tid;
+    const bool have = q < items;
+    const u32 row = q / per_row, k = row / (u32)g.n[1];
+    const int i = (int)(q - row * per_row);
+    const int x[3] = {i < g.n[0] ? i : 0, (int)(row - k * (u32)g.n[1]), (int)k};
     W7 aL{0, 0, 0, 0, 0, 0, 0}, aR{0, 0, 0, 0, 0, 0, 0};
-    double abn = 0.0;
-    hlld_rev(wl, wr, st.b[D][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
-    lacc.b[D][fo] += abn;
-    int l[3] = {x[0], x[1], x[2]};
-    l[D] -= 1;
-    const idx_t cl = cell_of(g, l);
+    const u32 t = cell_at(g, x[0], x[1], x[2]);
+    const bool cell = have && i < g.n[0] && tid < kBlock - 1;
+    if (have) {
+        double lf[7];
+        flux_cotangent<0>(g, lout, S, x, t, factor * dt_dev[0] / g.dl[0], lf);
+        const u32 o = prim_at(g, i, x[1], x[2]);
+        const u32 fo = face_at<0>(g, x[0], x[1], x[2]);
+        double abn = 0.0;
+        hlld_rev(w7_at(P, 0, o - 1), w7_at(P, 0, o), st.b[0][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
+        if (cell) {
+            lacc.b[0][fo] = base_face<0>(g, base, fo, x) + abn;
+            clear_duplicate<0>(g, lacc, fo, x);
+        }
+    }
     const double vl[7] = {aL.d, aL.u, aL.v, aL.w, aL.p, aL.by, aL.bz};
+#pragma unroll
+    for (int c = 0; c < 7; ++c) lds[c][tid] = vl[c];
+    __syncthreads();
+    if (!cell) return;
     const double vr[7] = {aR.d, aR.u, aR.v, aR.w, aR.p, aR.by, aR.bz};
 #pragma unroll
-    for (int s = 0; s < 7; ++s) {
-        S.lrec[D][7 + s][cl] = vl[s];  // high face of the left cell
-        S.lrec[D][s][t] = vr[s];       // low face of the right cell
+    for (int c = 0; c < 7; ++c) S.lw[lab_slot(0, c)][t] = vr[c] + lds[c][tid + 1];
+    lacc.b[2][t] = base_face<2>(g, base, t, x);
+    clear_duplicate<2>(g, lacc, t, x);
+}
+
+// y and z: one thread per column and segment of M cells, which computes its
+// faces and the one above it (whose left state is that of its top cell; the
+// normal-field cotangent stays with the segment that owns the face) and
+// carries each face's right-state cotangent to the next.
+template <int D>
+__global__ __launch_bounds__(kBlock, 1) void k_ad_pcm_march(Geom g, Prims P, StateP st, StateP lout,
+                                                            AdStage S, AdBase base, StateW lacc,
+                                                            const double *dt_dev, double factor,
+                                                            int M)
+{
+    static_assert(D == 1 || D == 2, "columns march along y or z");
+    constexpr int T = D == 1 ? 2 : 1;
+    const int nD = g.n[D];
+    const u32 cols = (u32)g.n[0] * (u32)g.n[T];
+    const u32 ncb = (cols + kBlock - 1) / kBlock;
+    const u32 seg = blockIdx.x / ncb;
+    const u32 col = (blockIdx.x - seg * ncb) * kBlock + threadIdx.x;
+    if (col >= cols) return;
+    int x[3];
+    x[T] = (int)(col / (u32)g.n[0]);
+    x[0] = (int)(col - (u32)x[T] * (u32)g.n[0]);
+    x[D] = 0;
+    const int s0 = (int)seg * M, s1 = min(s0 + M, nD);  // cells [s0, s1)
+    const double c = factor * dt_dev[0] / g.dl[D];
+    const u32 tcol = cell_at(g, x[0], x[1], x[2]), tstep = cell_stride<D>(g);
+    x[D] = s0 - 1;
+    u32 po = prim_at(g, x[0], x[1], x[2]);
+    const u32 pstep = D == 1 ? (u32)g.p[0] : (u32)g.p[0] * (u32)g.p[1];
+    // the cell below the face; the cotangent of its low-face state waits in LDS
+    // (thread-private)
+    W7 wl = w7_at(P, D, po);
+    __shared__ double alow[7][kBlock];
+    const int tid = threadIdx.x;
+    double lbn = 0.0;
+    for (int a = s0; a <= s1; ++a) {
+        po += pstep;
+        const W7 wr = w7_at(P, D, po);
+        x[D] = a < nD ? a : 0;
+        const u32 t = tcol + (u32)x[D] * tstep;
+        double lf[7];
+        flux_cotangent<D>(g, lout, S, x, t, c, lf);
+        const u32 fo = face_at<D>(g, x[0], x[1], x[2]);
+        W7 aL{0, 0, 0, 0, 0, 0, 0}, aR{0, 0, 0, 0, 0, 0, 0};
+        double abn = 0.0;
+        hlld_rev(wl, wr, st.b[D][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
+        if (D == 1 && a < s1) {
+            lacc.b[1][fo] = base_face<1>(g, base, fo, x) + abn;
+            clear_duplicate<1>(g, lacc, fo, x);
+        }
+        if (a > s0) {
+            // cell a - 1 has its face states' cotangents
+            x[D] = a - 1;
+            const u32 tc = tcol + (u32)(a - 1) * tstep;
+            const double vl[7] = {aL.d, aL.u, aL.v, aL.w, aL.p, aL.by, aL.bz};
+            double lw[8];
+            if (D == 1) {
+#pragma unroll
+                for (int q = 0; q < 7; ++q) {
+                    const int f = lab_slot(1, q);
+                    // the x sweep has no B_x component
+                    const double sum = alow[q][tid] + vl[q];
+                    S.lw[f][tc] = f == 5 ? sum : S.lw[f][tc] + sum;
+                }
+            } else {
+#pragma unroll
+                for (int f = 0; f < 8; ++f) lw[f] = S.lw[f][tc];
+#pragma unroll
+                for (int q = 0; q < 7; ++q) lw[lab_slot(2, q)] += alow[q][tid] + vl[q];
+                double lb[3];
+                cell_rev(g, st, P, S, base, lacc, x, tc, lw, lb);
+                const u32 f0 = face_at<0>(g, x[0], x[1], x[2]), f1 = face_at<1>(g, x[0], x[1], x[2]);
+                atomicAdd(&lacc.b[0][f0], lb[0]);
+                atomicAdd(&lacc.b[0][f0 + step_hi<0>(g, x)], lb[0]);
+                atomicAdd(&lacc.b[1][f1], lb[1]);
+                atomicAdd(&lacc.b[1][f1 + step_hi<1>(g, x)], lb[1]);
+                atomicAdd(&lacc.b[2][tc], lbn + lb[2]);
+                lbn = lb[2];
+            }
+        }
+        // the face's own term waits for the cell above it; the last one's (the
+        // next segment's) does not count here
+        if (D == 2) lbn = a < s1 ? lbn + abn : lbn;
+        const double vr[7] = {aR.d, aR.u, aR.v, aR.w, aR.p, aR.by, aR.bz};
+#pragma unroll
+        for (int q = 0; q < 7; ++q) alow[q][tid] = vr[q];
+        wl = wr;
+    }
+    if (D == 2) {
+        x[D] = s1 < nD ? s1 : 0;
+        atomicAdd(&lacc.b[2][tcol + (u32)x[D] * tstep], lbn);
     }
 }
 
@@ -280,18 +472,18 @@ __host__ __device__ __forceinline__ idx_t ad_march_blocks(const Geom &g, int D, 
     return ((cols + kBlock - 1) / kBlock) * ((g.n[D] + m - 1) / m);
 }
 
-// cells per segment of the adjoint marches: one block per CU at a time and
+// cells per segment of the adjoint marches: `slots` blocks at a time and
 // m + 1 reversals in a row in each, so the m up to 32 of least rounds x (m + 1)
 // (64^3, third order, against 16 and 8: faces 131 -> 44 us an axis, reversed
 // reconstructions 166 -> 104; 128^3, 32 and 16 are the same)
-static int ad_march_segment(const Geom &g, int D)
+static int ad_march_segment(const Geom &g, int D, int slots)
 {
     const int o = tile_override("admarch");
     if (o >= 1 && o <= 64) return o;
     idx_t best = 0;
     int len = 1;
     for (int m = 32; m >= 1; --m) {
-        const idx_t cost = (ad_march_blocks(g, D, m) + kNumCUs - 1) / kNumCUs * (m + 1);
+        const idx_t cost = (ad_march_blocks(g, D, m) + slots - 1) / slots * (m + 1);
         if (best == 0 || cost < best) {
             best = cost;
             len = m;
@@ -312,30 +504,29 @@ __global__ __launch_bounds__(kBlock) void k_ad_faces_march(Geom g, Prims P, Stat
     constexpr bool kChar = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PPMC;
     constexpr int R = kPpm ? 2 : 1;
     const int nD = g.n[D];
-    const idx_t cols = (idx_t)g.n[0] * g.n[T];
-    const idx_t ncb = (cols + kBlock - 1) / kBlock;
-    const idx_t b = blockIdx.x;
-    const int seg = (int)(b / ncb);
-    const idx_t col = (b - (idx_t)seg * ncb) * kBlock + threadIdx.x;
+    const u32 cols = (u32)g.n[0] * (u32)g.n[T];
+    const u32 ncb = (cols + kBlock - 1) / kBlock;
+    const u32 seg = blockIdx.x / ncb;
+    const u32 col = (blockIdx.x - seg * ncb) * kBlock + threadIdx.x;
     if (col >= cols) return;
     int x[3];
-    x[0] = (int)(col % g.n[0]);
-    x[T] = (int)(col / g.n[0]);
-    const int s0 = seg * M, s1 = min(s0 + M, nD);  // cells [s0, s1)
+    x[T] = (int)(col / (u32)g.n[0]);
+    x[0] = (int)(col - (u32)x[T] * (u32)g.n[0]);
+    x[D] = 0;
+    const int s0 = (int)seg * M, s1 = min(s0 + M, nD);  // cells [s0, s1)
     const double c = factor * dt_dev[0] / g.dl[D];
-    auto pid = [&](int along) {
-        int q[3] = {x[0], x[1], x[2]};
-        q[D] = along;
-        return pidx(g, q[0], q[1], q[2]);
-    };
+    const u32 tcol = cell_at(g, x[0], x[1], x[2]), tstep = cell_stride<D>(g);
+    x[D] = s0 - 1 - R;
+    u32 po = prim_at(g, x[0], x[1], x[2]);
+    const u32 pstep = D == 1 ? (u32)g.p[0] : (u32)g.p[0] * (u32)g.p[1];
     // stencil window of cells a - R .. a + R for a = s0 - 1
     W7 win[2 * R + 1];
     double bnc[2 * R + 1];
 #pragma unroll
     for (int q = 0; q < 2 * R + 1; ++q) {
-        const idx_t o = pid(s0 - 1 - R + q);
-        win[q] = w7_at(P, D, o);
-        bnc[q] = P.w[5 + D][o];
+        win[q] = w7_at(P, D, po);
+        bnc[q] = P.w[5 + D][po];
+        po += pstep;
     }
     W7 prev{};
     uint32_t fprev = 0;
@@ -349,17 +540,15 @@ __global__ __launch_bounds__(kBlock) void k_ad_faces_march(Geom g, Prims P, Stat
         if (a >= s0) {
             // the face a - 1/2 between the carried high state and this low state
             x[D] = a;
-            const idx_t t = cell_of(g, x);
+            const u32 t = tcol + (u32)a * tstep;
             double lf[7];
             flux_cotangent<D>(g, lout, S, x, t, c, lf);
-            const idx_t fo = face_store(g, D, x[0], x[1], x[2]);
+            const u32 fo = face_at<D>(g, x[0], x[1], x[2]);
             W7 aL{0, 0, 0, 0, 0, 0, 0}, aR{0, 0, 0, 0, 0, 0, 0};
             double abn = 0.0;
             hlld_rev(prev, fm, st.b[D][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
-            lacc.b[D][fo] += abn;
-            int l[3] = {x[0], x[1], x[2]};
-            l[D] -= 1;
-            const idx_t cl = cell_of(g, l);
+            lacc.b[D][fo] = abn;
+            const u32 cl = t + step_lo<D>(g, x);
             const double vl[7] = {aL.d, aL.u, aL.v, aL.w, aL.p, aL.by, aL.bz};
             const double vr[7] = {aR.d, aR.u, aR.v, aR.w, aR.p, aR.by, aR.bz};
 #pragma unroll
@@ -381,9 +570,9 @@ __global__ __launch_bounds__(kBlock) void k_ad_faces_march(Geom g, Prims P, Stat
                 win[q] = win[q + 1];
                 bnc[q] = bnc[q + 1];
             }
-            const idx_t o = pid(a + 1 + R);
-            win[2 * R] = w7_at(P, D, o);
-            bnc[2 * R] = P.w[5 + D][o];
+            win[2 * R] = w7_at(P, D, po);
+            bnc[2 * R] = P.w[5 + D][po];
+            po += pstep;
         }
     }
 }
@@ -411,20 +600,17 @@ __global__ __launch_bounds__(kBlock, 2) void k_ad_faces_row(Geom g, Prims P, Sta
     __shared__ double lds[7][kBlock];
     __shared__ uint32_t lfl[kBlock];
     const int nx = g.n[0];
-    const idx_t per_row = nx + 1;
-    const idx_t items = per_row * g.n[1] * g.n[2];
+    const u32 per_row = (u32)nx + 1, items = per_row * (u32)g.n[1] * (u32)g.n[2];
     const int t = threadIdx.x;
-    const idx_t q = (idx_t)blockIdx.x * (kBlock - 1) + t;
+    const u32 q = blockIdx.x * (u32)(kBlock - 1) + t;
     const bool have = q < items;
-    const idx_t row = q / per_row;
-    int x[3];
-    x[0] = (int)(q - row * per_row) - 1;
-    x[1] = (int)(row % g.n[1]);
-    x[2] = (int)(row / g.n[1]);
+    const u32 row = q / per_row, plane = row / (u32)g.n[1];
+    const int x[3] = {(int)(q - row * per_row) - 1, (int)(row - plane * (u32)g.n[1]), (int)plane};
     W7 fm{}, fp{};
     uint32_t flo = 0, fhi = 0;
     if (have) {
-        auto at = [&](int off) { return pidx(g, x[0] + off, x[1], x[2]); };
+        const u32 po = prim_at(g, x[0], x[1], x[2]);
+        auto at = [&](int off) { return po + (u32)off; };
         const double bn = P.w[5][at(0)];
         if constexpr (kPpm)
             ppmc<kChar>(w7_at(P, 0, at(-2)), w7_at(P, 0, at(-1)), w7_at(P, 0, at(0)),
@@ -443,15 +629,15 @@ __global__ __launch_bounds__(kBlock, 2) void k_ad_faces_row(Geom g, Prims P, Sta
     const W7 wl{lds[0][t - 1], lds[1][t - 1], lds[2][t - 1], lds[3][t - 1],
                 lds[4][t - 1], lds[5][t - 1], lds[6][t - 1]};
     const uint32_t fl = lfl[t - 1];
-    const idx_t tc = cell_of(g, x);
+    const u32 tc = cell_at(g, x[0], x[1], x[2]);
     double lf[7];
     flux_cotangent<0>(g, lout, S, x, tc, factor * dt_dev[0] / g.dl[0], lf);
-    const idx_t fo = face_store(g, 0, x[0], x[1], x[2]);
+    const u32 fo = face_at<0>(g, x[0], x[1], x[2]);
     W7 aL{0, 0, 0, 0, 0, 0, 0}, aR{0, 0, 0, 0, 0, 0, 0};
     double abn = 0.0;
     hlld_rev(wl, fm, st.b[0][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
-    lacc.b[0][fo] += abn;
-    const idx_t cl = cell_of(g, x[0] - 1, x[1], x[2]);
+    lacc.b[0][fo] = abn;
+    const u32 cl = tc + step_lo<0>(g, x);
     const double vl[7] = {aL.d, aL.u, aL.v, aL.w, aL.p, aL.by, aL.bz};
     const double vr[7] = {aR.d, aR.u, aR.v, aR.w, aR.p, aR.by, aR.bz};
 #pragma unroll
@@ -471,127 +657,136 @@ __global__ __launch_bounds__(kBlock, 2) void k_ad_faces_row(Geom g, Prims P, Sta
 // above it (whose cotangent the top cell needs; its normal-field cotangent
 // stays with the segment that owns it), and as soon as a cell has the
 // cotangents of both its interface states it reverses its reconstruction.
+// Bound by FP64 issue and by latency at one wave per SIMD (about 2000 of 3400
+// vector instructions per face): 128^3 PLMC 315 us per axis, 371 with 64-bit
+// index arithmetic (4280); two waves per SIMD would spill 950 bytes (1295 us).
+constexpr int kAdFusedWaves = 1;
+
 template <int D, int RECON>
-__global__ __launch_bounds__(kBlock) void k_ad_march_fused(Geom g, Prims P, StateP st,
-                                                           StateP lout, AdStage S,
-                                                           StateW lacc, const double *dt_dev,
-                                                           double factor, int M)
+__global__ __launch_bounds__(kBlock, kAdFusedWaves) void k_ad_march_fused(
+    Geom g, Prims P, StateP st, StateP lout, AdStage S, StateW lacc, const double *dt_dev,
+    double factor, int M)
 {
     static_assert(D == 1 || D == 2, "columns march along y or z");
     static_assert(RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PLMP, "linear reconstructions");
     constexpr int T = D == 1 ? 2 : 1;
     constexpr bool kChar = RECON == VLCT_RECON_PLMC;
     const int nD = g.n[D];
-    const idx_t cols = (idx_t)g.n[0] * g.n[T];
-    const idx_t ncb = (cols + kBlock - 1) / kBlock;
-    const idx_t b = blockIdx.x;
-    const int seg = (int)(b / ncb);
-    const idx_t col = (b - (idx_t)seg * ncb) * kBlock + threadIdx.x;
+    const u32 cols = (u32)g.n[0] * (u32)g.n[T];
+    const u32 ncb = (cols + kBlock - 1) / kBlock;
+    const u32 seg = blockIdx.x / ncb;
+    const u32 col = (blockIdx.x - seg * ncb) * kBlock + threadIdx.x;
     if (col >= cols) return;
     int x[3];
-    x[0] = (int)(col % g.n[0]);
-    x[T] = (int)(col / g.n[0]);
-    const int s0 = seg * M, s1 = min(s0 + M, nD);  // cells [s0, s1)
+    x[T] = (int)(col / (u32)g.n[0]);
+    x[0] = (int)(col - (u32)x[T] * (u32)g.n[0]);
+    x[D] = 0;
+    const int s0 = (int)seg * M, s1 = min(s0 + M, nD);  // cells [s0, s1)
     const double c = factor * dt_dev[0] / g.dl[D];
-    auto pid = [&](int along) {
-        int q[3] = {x[0], x[1], x[2]};
-        q[D] = along;
-        return pidx(g, q[0], q[1], q[2]);
-    };
-    // window of cells a - 2 .. a + 1 for the cell a being reconstructed
-    W7 win[4];
-    double bnc[4];
+    const u32 tcol = cell_at(g, x[0], x[1], x[2]), tstep = cell_stride<D>(g);
+    auto cell = [&](int along) { return tcol + (u32)wrapc(along, nD) * tstep; };
+    x[D] = s0 - 2;
+    u32 po = prim_at(g, x[0], x[1], x[2]);
+    const u32 pstep = D == 1 ? (u32)g.p[0] : (u32)g.p[0] * (u32)g.p[1];
+    // window of cells a - 1 .. a + 1 for the cell a being reconstructed
+    W7 win[3];
+    double bnc[3];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const idx_t o = pid(s0 - 3 + q);
-        win[q] = w7_at(P, D, o);
-        bnc[q] = P.w[5 + D][o];
+    for (int q = 0; q < 3; ++q) {
+        win[q] = w7_at(P, D, po);
+        bnc[q] = P.w[5 + D][po];
+        po += pstep;
     }
-    W7 prev{};
-    uint32_t fprev = 0;
-    double alow[7];  // cotangent of the low-face state of the cell below the face
-    // the reversal of cell m adds to the cells m - 1, m and m + 1, after which
-    // cell m - 1 has all its terms from this segment: the cells m and m + 1
-    // wait in LDS (cell c in slot c & 1, each thread its own column) and a
-    // cell leaves with one atomic add per component (segments share the two
-    // cells at each end)
-    __shared__ double pend[2][7][kBlock];
+    // in LDS, each thread its own column: cell a - 2 of the window, the high
+    // state of cell a - 1 and the cotangent of its low state, and of the
+    // reversals (that of cell m adds to the cells m - 1, m and m + 1) the sums
+    // of the two cells still waiting for terms (cell c in slot c & 1): a cell
+    // leaves with one atomic add per component (segments share the two cells
+    // at each end)
+    __shared__ double park[35][kBlock];
     const int tid = threadIdx.x;
+    auto put = [&](int s, const double v[7]) {
 #pragma unroll
-    for (int k = 0; k < 7; ++k) {
-        pend[0][k][tid] = 0.0;
-        pend[1][k][tid] = 0.0;
-    }
+        for (int q = 0; q < 7; ++q) park[s + q][tid] = v[q];
+    };
+    auto get = [&](int s) {
+        return W7{park[s][tid], park[s + 1][tid], park[s + 2][tid], park[s + 3][tid],
+                  park[s + 4][tid], park[s + 5][tid], park[s + 6][tid]};
+    };
+    auto put7 = [&](int s, const W7 &w) {
+        double v[7];
+        to_arr(w, v);
+        put(s, v);
+    };
+    constexpr int kOld = 0, kPrev = 7, kLow = 14, kPend = 21;
+#pragma unroll
+    for (int k = 0; k < 14; ++k) park[kPend + k][tid] = 0.0;
+    uint32_t fprev = 0;
     for (int a = s0 - 1; a <= s1; ++a) {
         W7 fm, fp;
-        plmc<kChar>(win[1], win[2], win[3], bnc[2], g.gamma, fm, fp);
+        plmc<kChar>(win[0], win[1], win[2], bnc[1], g.gamma, fm, fp);
         const uint32_t flo = floor_state(fm), fhi = floor_state(fp);
         if (a >= s0) {
             // the face a - 1/2
-            x[D] = a;
-            const idx_t t = cell_of(g, x);
+            x[D] = a < nD ? a : 0;
+            const u32 t = tcol + (u32)x[D] * tstep;
             double lf[7];
             flux_cotangent<D>(g, lout, S, x, t, c, lf);
-            int m[3] = {x[0], x[1], x[2]};
-            m[D] = wrapc(a, nD);
-            const idx_t fo = face_store(g, D, m[0], m[1], m[2]);
+            const u32 fo = face_at<D>(g, x[0], x[1], x[2]);
             W7 aL{0, 0, 0, 0, 0, 0, 0}, aR{0, 0, 0, 0, 0, 0, 0};
             double abn = 0.0;
-            hlld_rev(prev, fm, st.b[D][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
-            if (a < s1) lacc.b[D][fo] += abn;
-            double ahigh[7] = {aL.d, aL.u, aL.v, aL.w, aL.p, aL.by, aL.bz};
-            if (fprev & kStatusDensityFloor) ahigh[0] = 0.0;
-            if (fprev & kStatusPressureFloor) ahigh[4] = 0.0;
+            hlld_rev(get(kPrev), fm, st.b[D][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
+            if (a < s1) lacc.b[D][fo] = abn;
             if (a - 1 >= s0) {
                 // cell a - 1 has both interface cotangents: reverse its PLM
+                double ahigh[7] = {aL.d, aL.u, aL.v, aL.w, aL.p, aL.by, aL.bz}, alow[7];
+                if (fprev & kStatusDensityFloor) ahigh[0] = 0.0;
+                if (fprev & kStatusPressureFloor) ahigh[4] = 0.0;
+#pragma unroll
+                for (int k = 0; k < 7; ++k) alow[k] = park[kLow + k][tid];
                 W7 am{0, 0, 0, 0, 0, 0, 0}, a0{0, 0, 0, 0, 0, 0, 0}, ap{0, 0, 0, 0, 0, 0, 0};
                 double abc = 0.0;
-                plmc_rev<kChar>(win[0], win[1], win[2], bnc[1], g.gamma, alow, ahigh, am, a0,
+                plmc_rev<kChar>(get(kOld), win[0], win[1], bnc[0], g.gamma, alow, ahigh, am, a0,
                                 ap, abc);
                 const double vm[7] = {am.d, am.u, am.v, am.w, am.p, am.by, am.bz};
                 const double v0[7] = {a0.d, a0.u, a0.v, a0.w, a0.p, a0.by, a0.bz};
                 const double vp[7] = {ap.d, ap.u, ap.v, ap.w, ap.p, ap.by, ap.bz};
-                const int so = (a - 2) & 1, sn = (a - 1) & 1;  // slots of cells a - 2 (and a), a - 1
-                int e[3] = {x[0], x[1], x[2]};
-                e[D] = a - 2;
-                const idx_t cm = cell_of(g, e);
+                // slots of cells a - 2 (and a), a - 1
+                const int so = kPend + 7 * ((a - 2) & 1), sn = kPend + 7 * ((a - 1) & 1);
+                const u32 cm = cell(a - 2);
 #pragma unroll
                 for (int k = 0; k < 7; ++k) {
-                    atomicAdd(&S.lw[lab_slot(D, k)][cm], pend[so][k][tid] + vm[k]);
-                    pend[so][k][tid] = vp[k];
-                    pend[sn][k][tid] += v0[k];
+                    atomicAdd(&S.lw[lab_slot(D, k)][cm], park[so + k][tid] + vm[k]);
+                    park[so + k][tid] = vp[k];
+                    park[sn + k][tid] += v0[k];
                 }
-                e[D] = a - 1;
-                atomicAdd(&S.lw[5 + D][cell_of(g, e)], abc);
+                atomicAdd(&S.lw[5 + D][cell(a - 1)], abc);
             }
-            const double lo[7] = {aR.d, aR.u, aR.v, aR.w, aR.p, aR.by, aR.bz};
-#pragma unroll
-            for (int k = 0; k < 7; ++k) alow[k] = lo[k];
-            if (flo & kStatusDensityFloor) alow[0] = 0.0;
-            if (flo & kStatusPressureFloor) alow[4] = 0.0;
+            double lo[7] = {aR.d, aR.u, aR.v, aR.w, aR.p, aR.by, aR.bz};
+            if (flo & kStatusDensityFloor) lo[0] = 0.0;
+            if (flo & kStatusPressureFloor) lo[4] = 0.0;
+            put(kLow, lo);
         }
-        prev = fp;
+        put7(kPrev, fp);
         fprev = fhi;
         if (a + 1 <= s1) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                win[q] = win[q + 1];
-                bnc[q] = bnc[q + 1];
-            }
-            const idx_t o = pid(a + 2);
-            win[3] = w7_at(P, D, o);
-            bnc[3] = P.w[5 + D][o];
+            put7(kOld, win[0]);
+            win[0] = win[1];
+            win[1] = win[2];
+            bnc[0] = bnc[1];
+            bnc[1] = bnc[2];
+            win[2] = w7_at(P, D, po);
+            bnc[2] = P.w[5 + D][po];
+            po += pstep;
         }
     }
     // the cells s1 - 1 and s1 (the last reversal was that of cell s1 - 1)
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        int e[3] = {x[0], x[1], x[2]};
-        e[D] = s1 - 1 + q;
-        const idx_t cc = cell_of(g, e);
-        const int sl = (s1 - 1 + q) & 1;
+        const u32 cc = cell(s1 - 1 + q);
+        const int sl = kPend + 7 * ((s1 - 1 + q) & 1);
 #pragma unroll
-        for (int k = 0; k < 7; ++k) atomicAdd(&S.lw[lab_slot(D, k)][cc], pend[sl][k][tid]);
+        for (int k = 0; k < 7; ++k) atomicAdd(&S.lw[lab_slot(D, k)][cc], park[sl + k][tid]);
     }
 }
 
@@ -612,9 +807,9 @@ __host__ __device__ __forceinline__ idx_t ad_row_fused_blocks(const Geom &g)
 }
 
 template <int RECON>
-__global__ __launch_bounds__(kBlock) void k_ad_row_fused(Geom g, Prims P, StateP st,
-                                                         StateP lout, AdStage S, StateW lacc,
-                                                         const double *dt_dev, double factor)
+__global__ __launch_bounds__(kBlock, kAdFusedWaves) void k_ad_row_fused(
+    Geom g, Prims P, StateP st, StateP lout, AdStage S, StateW lacc, const double *dt_dev,
+    double factor)
 {
     static_assert(RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PLMP, "linear reconstructions");
     constexpr bool kChar = RECON == VLCT_RECON_PLMC;
@@ -623,17 +818,16 @@ __global__ __launch_bounds__(kBlock) void k_ad_row_fused(Geom g, Prims P, StateP
     __shared__ uint32_t lfl[kBlock];
     __shared__ uint32_t lrev[kBlock];
     const int nx = g.n[0];
-    const idx_t per_row = nx + 2;
-    const idx_t items = per_row * g.n[1] * g.n[2];
+    const u32 per_row = (u32)nx + 2, items = per_row * (u32)g.n[1] * (u32)g.n[2];
     const int t = threadIdx.x;
-    const idx_t q = (idx_t)blockIdx.x * (kBlock - 2) + t;
+    const u32 q = blockIdx.x * (u32)(kBlock - 2) + t;
     const bool have = q < items;
-    const idx_t row = q / per_row;
-    int x[3];
-    x[0] = (int)(q - row * per_row) - 1;
-    x[1] = (int)(row % g.n[1]);
-    x[2] = (int)(row / g.n[1]);
-    auto at = [&](int off) { return pidx(g, x[0] + off, x[1], x[2]); };
+    const u32 row = q / per_row, plane = row / (u32)g.n[1];
+    const int i = (int)(q - row * per_row) - 1;  // -1 .. nx
+    // the cell, or its periodic image
+    const int x[3] = {i < 0 ? nx - 1 : (i < nx ? i : 0), (int)(row - plane * (u32)g.n[1]), (int)plane};
+    const u32 po = prim_at(g, i, x[1], x[2]), tc = cell_at(g, x[0], x[1], x[2]);
+    auto at = [&](int off) { return po + (u32)off; };
     W7 fm{}, fp{};
     uint32_t flo = 0, fhi = 0;
     if (have) {
@@ -647,20 +841,19 @@ __global__ __launch_bounds__(kBlock) void k_ad_row_fused(Geom g, Prims P, StateP
     lfl[t] = fhi;
     __syncthreads();
     // the face x - 1/2 (x in 0 .. nx), between the item on the left and this one
-    const bool face = t >= 1 && have && x[0] >= 0;
+    const bool face = t >= 1 && have && i >= 0;
     double alow[7] = {0, 0, 0, 0, 0, 0, 0}, ahigh_left[7] = {0, 0, 0, 0, 0, 0, 0};
     if (face) {
         const W7 wl{lds[0][t - 1], lds[1][t - 1], lds[2][t - 1], lds[3][t - 1],
                     lds[4][t - 1], lds[5][t - 1], lds[6][t - 1]};
         const uint32_t fl = lfl[t - 1];
-        const idx_t tc = cell_of(g, x);
         double lf[7];
         flux_cotangent<0>(g, lout, S, x, tc, factor * dt_dev[0] / g.dl[0], lf);
-        const idx_t fo = face_store(g, 0, wrapc(x[0], nx), x[1], x[2]);
+        const u32 fo = face_at<0>(g, x[0], x[1], x[2]);
         W7 aL{0, 0, 0, 0, 0, 0, 0}, aR{0, 0, 0, 0, 0, 0, 0};
         double abn = 0.0;
         hlld_rev(wl, fm, st.b[0][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
-        if (t <= kBlock - 2 && x[0] < nx) lacc.b[0][fo] += abn;
+        if (t <= kBlock - 2 && i < nx) lacc.b[0][fo] = abn;
         const double vl[7] = {aL.d, aL.u, aL.v, aL.w, aL.p, aL.by, aL.bz};
         const double vr[7] = {aR.d, aR.u, aR.v, aR.w, aR.p, aR.by, aR.bz};
 #pragma unroll
@@ -678,7 +871,7 @@ __global__ __launch_bounds__(kBlock) void k_ad_row_fused(Geom g, Prims P, StateP
 #pragma unroll
     for (int c = 0; c < 7; ++c) lds[c][t] = ahigh_left[c];
     __syncthreads();
-    const bool rev = face && t <= kBlock - 2 && x[0] < nx;
+    const bool rev = face && t <= kBlock - 2 && i < nx;
     W7 am{0, 0, 0, 0, 0, 0, 0}, a0{0, 0, 0, 0, 0, 0, 0}, ap{0, 0, 0, 0, 0, 0, 0};
     double abc = 0.0;
     if (rev) {
@@ -706,81 +899,89 @@ __global__ __launch_bounds__(kBlock) void k_ad_row_fused(Geom g, Prims P, StateP
     const bool left_rev = t >= 1 && lrev[t - 1];
     const bool right_rev = lrev[t + 1] != 0u;
     const double v0[7] = {a0.d, a0.u, a0.v, a0.w, a0.p, a0.by, a0.bz};
-    const idx_t cc = cell_of(g, x);
 #pragma unroll
     for (int c = 0; c < 7; ++c) {
         double v = v0[c];
         if (left_rev) v += lds_p[c][t - 1];
         if (right_rev) v += lds[c][t + 1];
-        atomicAdd(&S.lw[lab_slot(0, c)][cc], v);
+        atomicAdd(&S.lw[lab_slot(0, c)][tc], v);
     }
     if (!left_rev) {
-        const idx_t cl = cell_of(g, x[0] - 1, x[1], x[2]);
+        const u32 cl = tc + step_lo<0>(g, x);
 #pragma unroll
         for (int c = 0; c < 7; ++c) atomicAdd(&S.lw[lab_slot(0, c)][cl], vm[c]);
     }
     if (!right_rev) {
-        const idx_t cr = cell_of(g, x[0] + 1, x[1], x[2]);
+        const u32 cr = tc + step_hi<0>(g, x);
 #pragma unroll
         for (int c = 0; c < 7; ++c) atomicAdd(&S.lw[lab_slot(0, c)][cr], vp[c]);
     }
-    atomicAdd(&S.lw[5][cc], abc);
+    atomicAdd(&S.lw[5][tc], abc);
 }
 
-// reconstruction of each cell along D reversed: cotangents of the stencil
-// states (three cells for PLM, five for PPM) and of the cell's B_cc,D
-template <int D, int RECON>
-__global__ __launch_bounds__(kBlock) void k_ad_recon(Geom g, Prims P, AdStage S)
+// parabolic reconstruction of each cell along x reversed: the cotangents of
+// the five stencil states go through LDS to the cells of the block that they
+// belong to (cells in flat order, neighbours in a row being neighbours in the
+// block), which leave with one atomic add per component; those of other
+// blocks' cells and across the periodic boundary are added one by one.
+template <int RECON>
+__global__ __launch_bounds__(kBlock) void k_ad_recon_row(Geom g, Prims P, AdStage S)
 {
-    constexpr bool kPpm = RECON == VLCT_RECON_PPMC || RECON == VLCT_RECON_PPMP;
-    constexpr bool kChar = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PPMC;
-    constexpr int kR = kPpm ? 2 : 1;  // stencil radius
-    const idx_t N = (idx_t)g.n[0] * g.n[1] * g.n[2];
-    const idx_t t = (idx_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= N) return;
+    static_assert(RECON == VLCT_RECON_PPMC || RECON == VLCT_RECON_PPMP, "parabolic reconstructions");
+    constexpr bool kChar = RECON == VLCT_RECON_PPMC;
+    __shared__ double lds[5][7][kBlock];
+    const int nx = g.n[0], tid = threadIdx.x;
+    const u32 N = (u32)nx * (u32)g.n[1] * (u32)g.n[2];
+    const u32 t = blockIdx.x * (u32)kBlock + tid;
+    const bool have = t < N;
     int x[3];
-    cell_coords(g, t, x);
-    double afm[7], afp[7];
+    cell_coords(g, have ? t : 0u, x);
+    // cells of the row in the block: offsets [lo, hi] from this one
+    const int lo = -min(tid, x[0]);
+    const int hi = min(min(kBlock - 1 - tid, nx - 1 - x[0]), 2);
+    W7 ad[5];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) ad[q] = W7{0, 0, 0, 0, 0, 0, 0};
+    double abn = 0.0;
+    if (have) {
+        double afm[7], afp[7];
+#pragma unroll
+        for (int c = 0; c < 7; ++c) {
+            afm[c] = S.lrec[0][c][t];
+            afp[c] = S.lrec[0][7 + c][t];
+        }
+        const u32 o = prim_at(g, x[0], x[1], x[2]);
+        ppmc_rev<kChar>(w7_at(P, 0, o - 2), w7_at(P, 0, o - 1), w7_at(P, 0, o), w7_at(P, 0, o + 1),
+                        w7_at(P, 0, o + 2), P.w[5][o], g.gamma, afm, afp, ad[0], ad[1], ad[2],
+                        ad[3], ad[4], abn);
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            const double v[7] = {ad[q].d, ad[q].u, ad[q].v, ad[q].w, ad[q].p, ad[q].by, ad[q].bz};
+            if (q - 2 >= lo && q - 2 <= hi) {
+#pragma unroll
+                for (int c = 0; c < 7; ++c) lds[q][c][tid] = v[c];
+            } else {
+                const u32 cc = t - (u32)x[0] + (u32)wrapc(x[0] + q - 2, nx);
+#pragma unroll
+                for (int c = 0; c < 7; ++c) atomicAdd(&S.lw[lab_slot(0, c)][cc], v[c]);
+            }
+        }
+    }
+    __syncthreads();
+    if (!have) return;
+    // the cell at offset d of the row gave this one its term 2 - d
 #pragma unroll
     for (int c = 0; c < 7; ++c) {
-        afm[c] = S.lrec[D][c][t];
-        afp[c] = S.lrec[D][7 + c][t];
-    }
-    idx_t po[2 * kR + 1];
+        double v = 0.0;
 #pragma unroll
-    for (int q = 0; q <= 2 * kR; ++q) {
-        int e[3] = {x[0], x[1], x[2]};
-        e[D] += q - kR;
-        po[q] = pidx(g, e[0], e[1], e[2]);
+        for (int d = -2; d <= 2; ++d)
+            if (d >= lo && d <= hi) v += lds[2 - d][c][tid + d];
+        atomicAdd(&S.lw[lab_slot(0, c)][t], v);
     }
-    W7 ad[2 * kR + 1];
-#pragma unroll
-    for (int q = 0; q <= 2 * kR; ++q) ad[q] = W7{0, 0, 0, 0, 0, 0, 0};
-    double abn = 0.0;
-    if (kPpm) {
-        ppmc_rev<kChar>(w7_at(P, D, po[0]), w7_at(P, D, po[1]), w7_at(P, D, po[kR]),
-                        w7_at(P, D, po[2 * kR - 1]), w7_at(P, D, po[2 * kR]),
-                        P.w[5 + D][po[kR]], g.gamma, afm, afp, ad[0], ad[1], ad[kR],
-                        ad[2 * kR - 1], ad[2 * kR], abn);
-    } else {
-        plmc_rev<kChar>(w7_at(P, D, po[0]), w7_at(P, D, po[1]), w7_at(P, D, po[2]),
-                        P.w[5 + D][po[1]], g.gamma, afm, afp, ad[0], ad[1], ad[2], abn);
-    }
-#pragma unroll
-    for (int q = 0; q <= 2 * kR; ++q) {
-        int e[3] = {x[0], x[1], x[2]};
-        e[D] += q - kR;
-        const idx_t c = cell_of(g, e);
-        const W7 &v = ad[q];
-        const double a[7] = {v.d, v.u, v.v, v.w, v.p, v.by, v.bz};
-#pragma unroll
-        for (int s = 0; s < 7; ++s) atomicAdd(&S.lw[lab_slot(D, s)][c], a[s]);
-    }
-    atomicAdd(&S.lw[5 + D][t], abn);
+    atomicAdd(&S.lw[5][t], abn);
 }
 
-// The parabolic reversals add each cell's stencil cotangents (five cells)
-// without one atomic per term.  Along y and z a thread marches a column
+// Along y and z a thread marches a column
 // segment of M cells and keeps the four cells still waiting for terms in LDS
 // (thread-private slots, cell c in slot c mod 5); a cell leaves with one
 // atomic add per component once the reversal two cells above it is done
@@ -796,42 +997,37 @@ __global__ __launch_bounds__(kBlock) void k_ad_recon_march(Geom g, Prims P, AdSt
     constexpr bool kChar = RECON == VLCT_RECON_PPMC;
     __shared__ double pend[5][7][kBlock];
     const int nD = g.n[D];
-    const idx_t cols = (idx_t)g.n[0] * g.n[T];
-    const idx_t ncb = (cols + kBlock - 1) / kBlock;
-    const idx_t b = blockIdx.x;
-    const int seg = (int)(b / ncb);
-    const idx_t col = (b - (idx_t)seg * ncb) * kBlock + threadIdx.x;
+    const u32 cols = (u32)g.n[0] * (u32)g.n[T];
+    const u32 ncb = (cols + kBlock - 1) / kBlock;
+    const u32 seg = blockIdx.x / ncb;
+    const u32 col = (blockIdx.x - seg * ncb) * kBlock + threadIdx.x;
     if (col >= cols) return;
     const int tid = threadIdx.x;
     int x[3];
-    x[0] = (int)(col % g.n[0]);
-    x[T] = (int)(col / g.n[0]);
-    const int s0 = seg * M, s1 = min(s0 + M, nD);  // cells [s0, s1)
+    x[T] = (int)(col / (u32)g.n[0]);
+    x[0] = (int)(col - (u32)x[T] * (u32)g.n[0]);
+    x[D] = 0;
+    const int s0 = (int)seg * M, s1 = min(s0 + M, nD);  // cells [s0, s1)
+    const u32 tcol = cell_at(g, x[0], x[1], x[2]), tstep = cell_stride<D>(g);
+    x[D] = s0 - 2;
+    u32 pb = prim_at(g, x[0], x[1], x[2]);  // cell c - 2
+    const u32 pstep = D == 1 ? (u32)g.p[0] : (u32)g.p[0] * (u32)g.p[1];
     auto slot = [](int c) { return (c + 10) % 5; };  // c >= -2
-    auto cell_at = [&](int along) {
-        int e[3] = {x[0], x[1], x[2]};
-        e[D] = along;
-        return cell_of(g, e);
-    };
+    auto cell = [&](int along) { return tcol + (u32)wrapc(along, nD) * tstep; };
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int k = 0; k < 7; ++k) pend[slot(s0 - 2 + q)][k][tid] = 0.0;
     for (int c = s0; c < s1; ++c) {
-        const idx_t t = cell_at(c);
+        const u32 t = tcol + (u32)c * tstep;
         double afm[7], afp[7];
 #pragma unroll
         for (int k = 0; k < 7; ++k) {
             afm[k] = S.lrec[D][k][t];
             afp[k] = S.lrec[D][7 + k][t];
         }
-        idx_t po[5];
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-            int e[3] = {x[0], x[1], x[2]};
-            e[D] = c - 2 + q;
-            po[q] = pidx(g, e[0], e[1], e[2]);
-        }
+        const u32 po[5] = {pb, pb + pstep, pb + 2 * pstep, pb + 3 * pstep, pb + 4 * pstep};
+        pb += pstep;
         W7 ad[5];
 #pragma unroll
         for (int q = 0; q < 5; ++q) ad[q] = W7{0, 0, 0, 0, 0, 0, 0};
@@ -845,7 +1041,7 @@ __global__ __launch_bounds__(kBlock) void k_ad_recon_march(Geom g, Prims P, AdSt
             v[q][0] = ad[q].d; v[q][1] = ad[q].u; v[q][2] = ad[q].v; v[q][3] = ad[q].w;
             v[q][4] = ad[q].p; v[q][5] = ad[q].by; v[q][6] = ad[q].bz;
         }
-        const idx_t cm = cell_at(c - 2);
+        const u32 cm = cell(c - 2);
         const int sm = slot(c - 2), s1m = slot(c - 1), s00 = slot(c), s1p = slot(c + 1),
                   s2p = slot(c + 2);
 #pragma unroll
@@ -861,120 +1057,49 @@ __global__ __launch_bounds__(kBlock) void k_ad_recon_march(Geom g, Prims P, AdSt
     // the cells s1 - 2 .. s1 + 1 (the last reversal was that of cell s1 - 1)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const idx_t cc = cell_at(s1 - 2 + q);
+        const u32 cc = cell(s1 - 2 + q);
         const int sl = slot(s1 - 2 + q);
 #pragma unroll
         for (int k = 0; k < 7; ++k) atomicAdd(&S.lw[lab_slot(D, k)][cc], pend[sl][k][tid]);
     }
 }
 
-// cotangent of -(v x B)_A at cell x from the four A-edges around it
-template <int A>
-__device__ __forceinline__ double eref_cotangent(const Geom &g, const AdStage &S, const int x[3])
+// a cell of a reconstructing stage, whose primitive cotangents the
+// reconstruction transposes have accumulated
+__global__ __launch_bounds__(kBlock) void k_ad_prims(Geom g, StateP st, Prims P, AdStage S,
+                                                     AdBase base, StateW lacc)
 {
-    constexpr int B = (A + 1) % 3, C = (A + 2) % 3;
-    double w[8], acc;
-    // the cell is r00 of edge x, r10 of edge x + e_B, r01 of edge x + e_C and
-    // r11 of edge x + e_B + e_C
-    edge_weights<A>(g, S, x, w);
-    acc = (w[1] + w[5]) * S.le[A][cell_of(g, x)];
-    int y[3] = {x[0], x[1], x[2]};
-    y[B] += 1;
-    edge_weights<A>(g, S, y, w);
-    acc += (w[0] + w[7]) * S.le[A][cell_of(g, y)];
-    y[B] -= 1;
-    y[C] += 1;
-    edge_weights<A>(g, S, y, w);
-    acc += (w[3] + w[4]) * S.le[A][cell_of(g, y)];
-    y[B] += 1;
-    edge_weights<A>(g, S, y, w);
-    acc += (w[2] + w[6]) * S.le[A][cell_of(g, y)];
-    return -0.25 * acc;
-}
-
-// reference fields -(v x B) and primitive recovery (Sec. 2.1; B_cc = face
-// average) reversed into the cotangents of the stage's conserved cells and
-// faces; a floored quantity is a constant.  GATHER (PCM stage): the primitive
-// cotangents are the sums of the stored face-state cotangents of the cell;
-// otherwise the reconstruction transposes have accumulated them.
-template <bool GATHER>
-__global__ __launch_bounds__(kBlock) void k_ad_prims(Geom g, StateP st, Prims P, AdStage S, StateW lacc)
-{
-    const idx_t N = (idx_t)g.n[0] * g.n[1] * g.n[2];
-    const idx_t t = (idx_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const u32 N = (u32)g.n[0] * (u32)g.n[1] * (u32)g.n[2];
+    const u32 t = blockIdx.x * (u32)kBlock + threadIdx.x;
     if (t >= N) return;
     int x[3];
     cell_coords(g, t, x);
-    const int i = x[0], j = x[1], k = x[2];
-    double lw[8];
-    if (GATHER) {
+    double lw[8], lb[3];
 #pragma unroll
-        for (int f = 0; f < 8; ++f) lw[f] = 0.0;
-#pragma unroll
-        for (int D = 0; D < 3; ++D)
-#pragma unroll
-            for (int q = 0; q < 7; ++q)
-                lw[lab_slot(D, q)] += S.lrec[D][q][t] + S.lrec[D][7 + q][t];
-    } else {
-#pragma unroll
-        for (int f = 0; f < 8; ++f) lw[f] = S.lw[f][t];
-    }
-    {
-        const idx_t o = pidx(g, i, j, k);
-        const double vx = P.w[1][o], vy = P.w[2][o], vz = P.w[3][o];
-        const double bx = P.w[5][o], by = P.w[6][o], bz = P.w[7][o];
-        const double ex = eref_cotangent<0>(g, S, x), ey = eref_cotangent<1>(g, S, x),
-                     ez = eref_cotangent<2>(g, S, x);
-        lw[1] += bz * ey - by * ez;
-        lw[2] += -bz * ex + bx * ez;
-        lw[3] += by * ex - bx * ey;
-        lw[5] += -vz * ey + vy * ez;
-        lw[6] += vz * ex - vx * ez;
-        lw[7] += -vy * ex + vx * ey;
-    }
-    const idx_t fl[3] = {face_store(g, 0, i, j, k), face_store(g, 1, i, j, k),
-                         face_store(g, 2, i, j, k)};
-    const idx_t fh[3] = {face_store(g, 0, wrapc(i + 1, g.n[0]), j, k),
-                         face_store(g, 1, i, wrapc(j + 1, g.n[1]), k),
-                         face_store(g, 2, i, j, wrapc(k + 1, g.n[2]))};
-    double bc[3];
-    for (int d = 0; d < 3; ++d) bc[d] = 0.5 * (st.b[d][fl[d]] + st.b[d][fh[d]]);
-    double d = st.u[0][t];
-    const bool dfloor = !(d >= kFloorRho);
-    if (dfloor) d = kFloorRho;
-    const double id = mrcp(d);
-    const double v[3] = {st.u[1][t] * id, st.u[2][t] * id, st.u[3][t] * id};
-    const double ke = 0.5 * d * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-    const double me = 0.5 * (bc[0] * bc[0] + bc[1] * bc[1] + bc[2] * bc[2]);
-    const double p = (g.gamma - 1.0) * (st.u[4][t] - ke - me);
-    const bool pfloor = !(p >= kFloorP);
-    const double gm1 = g.gamma - 1.0;
-    const double lp = pfloor ? 0.0 : lw[4];
-    const double v2 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
-    double lrho = dfloor ? 0.0 : lw[0] + lp * gm1 * 0.5 * v2;
-    for (int l = 0; l < 3; ++l) {
-        if (!dfloor) lrho -= lw[1 + l] * v[l] * id;
-        lacc.u[1 + l][t] += lw[1 + l] * id - lp * gm1 * v[l];
-    }
-    lacc.u[0][t] += lrho;
-    lacc.u[4][t] += lp * gm1;
-    for (int l = 0; l < 3; ++l) {
-        const double lb = 0.5 * (lw[5 + l] - lp * gm1 * bc[l]);
-        atomicAdd(&lacc.b[l][fl[l]], lb);
-        atomicAdd(&lacc.b[l][fh[l]], lb);
-    }
+    for (int f = 0; f < 8; ++f) lw[f] = S.lw[f][t];
+    cell_rev(g, st, P, S, base, lacc, x, t, lw, lb);
+    const u32 f0 = face_at<0>(g, x[0], x[1], x[2]), f1 = face_at<1>(g, x[0], x[1], x[2]);
+    atomicAdd(&lacc.b[0][f0], lb[0]);
+    atomicAdd(&lacc.b[0][f0 + step_hi<0>(g, x)], lb[0]);
+    atomicAdd(&lacc.b[1][f1], lb[1]);
+    atomicAdd(&lacc.b[1][f1 + step_hi<1>(g, x)], lb[1]);
+    atomicAdd(&lacc.b[2][t], lb[2]);
+    atomicAdd(&lacc.b[2][t + step_hi<2>(g, x)], lb[2]);
 }
 
-// transposes of one stage: lout is the cotangent of the stage's output state,
-// st/P/sd the stage's input state, primitives and upwind sides; the result
-// is added to lacc (the cotangent of the stage's input state).
-static void stage_adjoint(const Geom &g, double factor, const StateP &lout, const StateP &st,
-                          const Prims &P, const Sides &sd, int recon, const AdStage &S,
-                          const StateW &lacc, const double *dt, hipStream_t s)
+// transposes of one stage: lout is the cotangent of the stage's output state
+// (fold: its duplicate faces count for face 0), st/P/sd the stage's input
+// state, primitives and upwind sides; lacc becomes the cotangent of the stage's
+// input state, on top of `base`.
+static void stage_adjoint(const Geom &g, double factor, const StateP &lout, bool fold,
+                          const StateP &st, const Prims &P, const Sides &sd, int recon,
+                          const AdStage &S, const AdBase &base, const StateW &lacc,
+                          const double *dt, hipStream_t s)
 {
     const unsigned gc = nblocks((size_t)g.n[0] * g.n[1] * g.n[2]);
-    k_ad_edges<<<gc, kBlock, 0, s>>>(g, lout, sd, S, dt, factor, recon != VLCT_RECON_PCM);
-    const int m1 = ad_march_segment(g, 1), m2 = ad_march_segment(g, 2);
+    k_ad_edges<<<gc, kBlock, 0, s>>>(g, lout, fold, sd, S, dt, factor, recon != VLCT_RECON_PCM);
+    const int slots = kNumCUs;
+    const int m1 = ad_march_segment(g, 1, slots), m2 = ad_march_segment(g, 2, slots);
     const unsigned b1 = (unsigned)ad_march_blocks(g, 1, m1), b2 = (unsigned)ad_march_blocks(g, 2, m2);
 #define VLCT_AD_FACES(R)                                                                   \
     k_ad_faces_row<R><<<(unsigned)ad_row_blocks(g), kBlock, 0, s>>>(g, P, st, lout, S,     \
@@ -988,13 +1113,14 @@ static void stage_adjoint(const Geom &g, double factor, const StateP &lout, cons
     k_ad_march_fused<1, R><<<b1, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor, m1); \
     k_ad_march_fused<2, R><<<b2, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor, m2);
 #define VLCT_AD_RECON(R)                                                                   \
-    k_ad_recon<0, R><<<gc, kBlock, 0, s>>>(g, P, S);                                       \
+    k_ad_recon_row<R><<<gc, kBlock, 0, s>>>(g, P, S);                                      \
     k_ad_recon_march<1, R><<<b1, kBlock, 0, s>>>(g, P, S, m1);                             \
     k_ad_recon_march<2, R><<<b2, kBlock, 0, s>>>(g, P, S, m2);
     if (recon == VLCT_RECON_PCM) {
-        k_ad_faces<0><<<gc, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor);
-        k_ad_faces<1><<<gc, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor);
-        k_ad_faces<2><<<gc, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor);
+        k_ad_pcm_row<<<(unsigned)ad_pcm_row_blocks(g), kBlock, 0, s>>>(g, P, st, lout, S, base,
+                                                                       lacc, dt, factor);
+        k_ad_pcm_march<1><<<b1, kBlock, 0, s>>>(g, P, st, lout, S, base, lacc, dt, factor, m1);
+        k_ad_pcm_march<2><<<b2, kBlock, 0, s>>>(g, P, st, lout, S, base, lacc, dt, factor, m2);
     } else if (recon == VLCT_RECON_PLMC) {
         VLCT_AD_FUSED(VLCT_RECON_PLMC)
     } else if (recon == VLCT_RECON_PLMP) {
@@ -1009,10 +1135,7 @@ static void stage_adjoint(const Geom &g, double factor, const StateP &lout, cons
 #undef VLCT_AD_FACES
 #undef VLCT_AD_FUSED
 #undef VLCT_AD_RECON
-    if (recon == VLCT_RECON_PCM)
-        k_ad_prims<true><<<gc, kBlock, 0, s>>>(g, st, P, S, lacc);
-    else
-        k_ad_prims<false><<<gc, kBlock, 0, s>>>(g, st, P, S, lacc);
+    if (recon != VLCT_RECON_PCM) k_ad_prims<<<gc, kBlock, 0, s>>>(g, st, P, S, base, lacc);
 }
 
 // workspace of the adjoint: forward intermediates and cotangents.  Without a
@@ -1112,11 +1235,10 @@ static int adjoint_core(const vlct_grid *vg, const Geom &g, const AdLayout &L, c
     Prims P[2];
     for (int h = 0; h < 2; ++h)
         for (int f = 0; f < 8; ++f) P[h].w[f] = arr(L.prims[h] + f * align_up(L.prims_len * 8));
-    StateW lnext, lhalf;
+    StateW lhalf;
     for (int f = 0; f < 8; ++f) {
-        double *c = arr(L.lnext[f]), *e = arr(L.lhalf[f]);
-        if (f < 5) { lnext.u[f] = c; lhalf.u[f] = e; }
-        else { lnext.b[f - 5] = c; lhalf.b[f - 5] = e; }
+        double *e = arr(L.lhalf[f]);
+        if (f < 5) lhalf.u[f] = e; else lhalf.b[f - 5] = e;
     }
     AdStage S;
     for (int a = 0; a < 3; ++a) S.le[a] = arr(L.le + a * L.cell_pitch);
@@ -1132,15 +1254,13 @@ static int adjoint_core(const vlct_grid *vg, const Geom &g, const AdLayout &L, c
         if (rc) return rc;
     }
 
-    // reverse: corrector stage into mu = lhalf, then lam_in += mu + predictor^T mu
-    const StateW lin = as_mut(lam_in);
-    const unsigned gf = nblocks((size_t)(g.n[0] + 1) * (g.n[1] + 1) * (g.n[2] + 1));
-    k_ad_init<<<gf, kBlock, 0, s>>>(g, as_const(lam_out), lnext, lhalf);
-    stage_adjoint(g, 1.0, as_const(lnext), hc, P[1], sides[1], vg->recon, S, lhalf,
+    // reverse: corrector stage into mu = lhalf, then lam_in = lam_out (U^{n+1}
+    // contains U^n with unit weight) + mu + predictor^T mu
+    const StateP lam = as_const(lam_out), mu = as_const(lhalf);
+    stage_adjoint(g, 1.0, lam, true, hc, P[1], sides[1], vg->recon, S, AdBase{lam, mu, 0}, lhalf,
                   dt_dev, s);
-    k_ad_add<<<gf, kBlock, 0, s>>>(g, lin, as_const(lnext), as_const(lhalf));
-    stage_adjoint(g, 0.5, as_const(lhalf), sin, P[0], sides[0], VLCT_RECON_PCM, S, lin,
-                  dt_dev, s);
+    stage_adjoint(g, 0.5, mu, false, sin, P[0], sides[0], VLCT_RECON_PCM, S, AdBase{lam, mu, 1},
+                  as_mut(lam_in), dt_dev, s);
     return hipGetLastError() == hipSuccess ? VLCT_OK : VLCT_EHIP;
 }
 
@@ -1152,14 +1272,13 @@ static int adjoint_core(const vlct_grid *vg, const Geom &g, const AdLayout &L, c
 __global__ void k_curl_potential(Geom g, const double *ax, const double *ay, const double *az,
                                  double *bx, double *by, double *bz)
 {
-    const idx_t N = (idx_t)g.n[0] * g.n[1] * g.n[2];
-    const idx_t t = (idx_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const u32 N = (u32)g.n[0] * (u32)g.n[1] * (u32)g.n[2];
+    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= N) return;
     int x[3];
     cell_coords(g, t, x);
     const int i = x[0], j = x[1], k = x[2];
-    const idx_t ip = cell_of(g, i + 1, j, k), jp = cell_of(g, i, j + 1, k),
-                kp = cell_of(g, i, j, k + 1);
+    const u32 ip = t + step_hi<0>(g, x), jp = t + step_hi<1>(g, x), kp = t + step_hi<2>(g, x);
     const double vx = (az[jp] - az[t]) / g.dl[1] - (ay[kp] - ay[t]) / g.dl[2];
     const double vy = (ax[kp] - ax[t]) / g.dl[2] - (az[ip] - az[t]) / g.dl[0];
     const double vz = (ay[ip] - ay[t]) / g.dl[0] - (ax[jp] - ax[t]) / g.dl[1];
@@ -1175,8 +1294,8 @@ __global__ void k_curl_potential(Geom g, const double *ax, const double *ay, con
 __global__ void k_curl_potential_adjoint(Geom g, const double *lbx, const double *lby,
                                          const double *lbz, double *lax, double *lay, double *laz)
 {
-    const idx_t N = (idx_t)g.n[0] * g.n[1] * g.n[2];
-    const idx_t t = (idx_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const u32 N = (u32)g.n[0] * (u32)g.n[1] * (u32)g.n[2];
+    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= N) return;
     int x[3];
     cell_coords(g, t, x);
