@@ -66,19 +66,25 @@ VLCT_DEV void fast_sq_rev(const FastSq &q, double i2d, double idc, double bn, do
 // ---------------------------------------------------------------------------
 // HLLD reverse: (a_L, a_R, a_bn) += J^T a_f, J = d f / d(L, R, bn) of hlld()
 // ---------------------------------------------------------------------------
-VLCT_DEV void hlld_rev(const W7 &L, const W7 &R, double bn, double gam, double gm1i,
-                       const double a_f[7], W7 &aL, W7 &aR, double &a_bn_out)
+// again(L, R) fetches the two states once more: with them waiting elsewhere,
+// neither they nor what follows from them in a few operations is kept in
+// registers through the middle of the reverse
+template <class Again>
+VLCT_DEV void hlld_rev(const W7 &L0, const W7 &R0, double bn, double gam, double gm1i,
+                       const double a_f[7], W7 &aL, W7 &aR, double &a_bn_out, Again again)
 {
+    W7 L = L0, R = R0;
     // ---- forward (the formulas of hlld(), intermediates kept)
     const double bn2 = bn * bn;
-    const double pbL = 0.5 * (bn2 + L.by * L.by + L.bz * L.bz);
-    const double pbR = 0.5 * (bn2 + R.by * R.by + R.bz * R.bz);
-    const double ptL = L.p + pbL;
-    const double ptR = R.p + pbR;
-    const double u2L = L.u * L.u + L.v * L.v + L.w * L.w;
-    const double u2R = R.u * R.u + R.v * R.v + R.w * R.w;
-    const double eL = L.p * gm1i + 0.5 * L.d * u2L + pbL;
-    const double eR = R.p * gm1i + 0.5 * R.d * u2R + pbR;
+    double ptL, ptR, u2L, u2R, eL, eR;
+    auto side = [&](const W7 &X, double &pt, double &u2, double &e) {
+        const double pb = 0.5 * (bn2 + X.by * X.by + X.bz * X.bz);
+        pt = X.p + pb;
+        u2 = X.u * X.u + X.v * X.v + X.w * X.w;
+        e = X.p * gm1i + 0.5 * X.d * u2 + pb;
+    };
+    side(L, ptL, u2L, eL);
+    side(R, ptR, u2R, eR);
     // c_f = num rq, rq = 1 / sqrt(2 rho num), num = gP + B^2 + disc; then
     // 1 / c_f = 2 rho rq and 1 / (2 rho) = num rq^2
     auto fast_fwd = [&](const W7 &X, FastSq &q, double &rq) {
@@ -101,8 +107,8 @@ VLCT_DEV void hlld_rev(const W7 &L, const W7 &R, double bn, double gam, double g
     const bool umaxR = takes_second_max(L.u, R.u);
     const double sL = (uminR ? R.u : L.u) - cmax;
     const double sR = (umaxR ? R.u : L.u) + cmax;
-    const double qL = (sL - L.u) * L.d;
-    const double qR = (sR - R.u) * R.d;
+    double qL = (sL - L.u) * L.d;
+    double qR = (sR - R.u) * R.d;
     const double iq = mrcp(qR - qL);
     const double num_m = qR * R.u - qL * L.u - ptR + ptL;
     const double sM = num_m * iq;
@@ -148,7 +154,7 @@ VLCT_DEV void hlld_rev(const W7 &L, const W7 &R, double bn, double gam, double g
     const double vbss = sM * bn + vss * byss + wss * bzss;
 
     const bool left = sM >= 0.0;
-    const W7 &X = left ? L : R;
+    const W7 X = left ? L : R;
     const double S = left ? sL : sR;
     const double pt = left ? ptL : ptR;
     const double e = left ? eL : eR;
@@ -311,6 +317,20 @@ VLCT_DEV void hlld_rev(const W7 &L, const W7 &R, double bn, double gam, double g
         a_ds[0] = a_ds[0] + a_rL * (0.5 * irL);
         a_ds[1] = a_ds[1] + a_rR * (0.5 * irR);
     }
+    // the states again, and what they give at once
+    again(L, R);
+    side(L, ptL, u2L, eL);
+    side(R, ptR, u2R, eR);
+    qL = (sL - L.u) * L.d;
+    qR = (sR - R.u) * R.d;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const W7 &Y = a == 0 ? L : R;
+        const double S2 = a == 0 ? sL : sR;
+        su[a] = S2 - Y.u;
+        ssm[a] = S2 - sM;
+        vb[a] = Y.u * bn + Y.v * Y.by + Y.w * Y.bz;
+    }
     // single-star states of both sides
     double aLs[7] = {0, 0, 0, 0, 0, 0, 0}, aRs[7] = {0, 0, 0, 0, 0, 0, 0};  // d u v w (p unused) by bz
     double a_S2[2] = {0.0, 0.0}, a_pt2[2] = {0.0, 0.0}, a_e2[2] = {0.0, 0.0};
@@ -456,6 +476,11 @@ VLCT_DEV void hlld_rev(const W7 &L, const W7 &R, double bn, double gam, double g
     aR.by = aR.by + a_byR + aRs[5] + sy * aXby;
     aR.bz = aR.bz + a_bzR + aRs[6] + sy * aXbz;
     a_bn_out = a_bn_out + a_bn;
+}
+VLCT_DEV void hlld_rev(const W7 &L, const W7 &R, double bn, double gam, double gm1i,
+                       const double a_f[7], W7 &aL, W7 &aR, double &a_bn_out)
+{
+    hlld_rev(L, R, bn, gam, gm1i, a_f, aL, aR, a_bn_out, [](W7 &, W7 &) {});
 }
 
 // ---------------------------------------------------------------------------
@@ -871,11 +896,15 @@ VLCT_DEV int clamp_pick(double x0, double nb, double v)
     return lo_nb ? 2 : 1;
 }
 
-template <bool CHAR>
-VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, const W7 &wpp,
-                       double bn, double gam, const double a_fm[7], const double a_fp[7],
-                       W7 &a_wmm, W7 &a_wm, W7 &a_w0, W7 &a_wp, W7 &a_wpp, double &a_bn)
+// state(q), q = 0 .. 4: the stencil's states; fetched once more for the last
+// transposes, so that they and their snapped differences are not kept in
+// registers through the middle of the reverse
+template <bool CHAR, class State>
+VLCT_DEV void ppmc_rev(State state, double bn, double gam, const double a_fm[7],
+                       const double a_fp[7], W7 &a_wmm, W7 &a_wm, W7 &a_w0, W7 &a_wp, W7 &a_wpp,
+                       double &a_bn)
 {
+    const W7 w0 = state(2);
     // ---- forward (the steps of ppmc, the quantities the reverse needs kept)
     Eigen E;
     double fv, fb;
@@ -892,19 +921,15 @@ VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, 
     to_arr(w0, x0);
 #pragma unroll
     for (int c = 0; c < 7; ++c) base[c] = kPpmTie * (fabs(x0[c]) + floor_c[c]);
-    to_arr(wmm, xn[0]);
-    to_arr(wm, xn[1]);
-    to_arr(wp, xn[2]);
-    to_arr(wpp, xn[3]);
-    bool tie[4][7];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < 4; ++q) {
+        to_arr(state(q < 2 ? q : q + 1), xn[q]);
 #pragma unroll
         for (int c = 0; c < 7; ++c) {
             const double d = xn[q][c] - x0[c];
-            tie[q][c] = fabs(d) <= ppm_tol(xn[q][c], base[c]);
-            xs[q][c] = tie[q][c] ? 0.0 : d;
+            xs[q][c] = fabs(d) <= ppm_tol(xn[q][c], base[c]) ? 0.0 : d;
         }
+    }
     double a[4][7];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -1101,15 +1126,24 @@ VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, 
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         double a_xs[7] = {0, 0, 0, 0, 0, 0, 0};
+        bool tie[7];
+        double xq[7], ds[7];
+        to_arr(state(q < 2 ? q : q + 1), xq);
+#pragma unroll
+        for (int c = 0; c < 7; ++c) {
+            const double d = xq[c] - x0[c];
+            tie[c] = fabs(d) <= ppm_tol(xq[c], kPpmTie * (fabs(x0[c]) + floor_c[c]));
+            ds[c] = tie[c] ? 0.0 : d;
+        }
         if (CHAR) {
-            project_rev(E, xs[q], a_a[q], a_xs, EA);
+            project_rev(E, ds, a_a[q], a_xs, EA);
         } else {
 #pragma unroll
             for (int c = 0; c < 7; ++c) a_xs[c] = a_a[q][c];
         }
 #pragma unroll
         for (int c = 0; c < 7; ++c)
-            if (!tie[q][c]) {
+            if (!tie[c]) {
                 a_xn[q][c] = a_xn[q][c] + a_xs[c];
                 a_x0[c] = a_x0[c] - a_xs[c];
             }
@@ -1130,6 +1164,15 @@ VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, 
             o.p = o.p + v[4]; o.by = o.by + v[5]; o.bz = o.bz + v[6];
         }
     }
+}
+template <bool CHAR>
+VLCT_DEV void ppmc_rev(const W7 &wmm, const W7 &wm, const W7 &w0, const W7 &wp, const W7 &wpp,
+                       double bn, double gam, const double a_fm[7], const double a_fp[7],
+                       W7 &a_wmm, W7 &a_wm, W7 &a_w0, W7 &a_wp, W7 &a_wpp, double &a_bn)
+{
+    const W7 *st[5] = {&wmm, &wm, &w0, &wp, &wpp};
+    ppmc_rev<CHAR>([&](int q) { return *st[q]; }, bn, gam, a_fm, a_fp, a_wmm, a_wm, a_w0, a_wp,
+                   a_wpp, a_bn);
 }
 
 }  // namespace vlct

@@ -204,57 +204,125 @@ __global__ void k_ad_edges(Geom g, StateP lout, int fold, Sides sd, AdStage S, c
 }
 
 // cotangents of the 7 fluxes of the face of axis D at x (the low face of cell
-// x, flat index t)
+// x, flat index t): its loads, then its arithmetic, so that a march can issue
+// the loads ahead of other work
+struct FluxLoads {
+    double hi[5], lo[5], e5x, e5y, e6x, e6y;
+    u32 code, c5, c6;
+};
+template <int D>
+__device__ __forceinline__ FluxLoads flux_loads(const Geom &g, const StateP &lout,
+                                                const AdStage &S, const int x[3], u32 t)
+{
+    FluxLoads v;
+    const u32 cl = t + step_lo<D>(g, x);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        const int f = lab_cons(D, q);
+        v.hi[q] = lout.u[f][t];
+        v.lo[q] = lout.u[f][cl];
+    }
+    constexpr int A5 = (D + 2) % 3, C5 = (A5 + 2) % 3, A6 = (D + 1) % 3, B6 = (A6 + 1) % 3;
+    const u32 y5 = t + step_hi<C5>(g, x), y6 = t + step_hi<B6>(g, x);
+    v.code = S.wcode[t];
+    v.c5 = S.wcode[y5];
+    v.c6 = S.wcode[y6];
+    v.e5x = S.le[A5][t];
+    v.e5y = S.le[A5][y5];
+    v.e6x = S.le[A6][t];
+    v.e6y = S.le[A6][y6];
+    return v;
+}
+template <int D>
+__device__ __forceinline__ void flux_combine(const FluxLoads &v, double c, double lf[7])
+{
+    // cell update u -= c (F(x + e_D) - F(x))
+#pragma unroll
+    for (int q = 0; q < 5; ++q) lf[q] = c * (v.hi[q] - v.lo[q]);
+    // F_D[B_t1] enters the edges E_A, A = D + 2, as -F: at x (weights of the
+    // high sides of terms 3 and 4) and at x + e_C, C = D + 1 (low sides)
+    {
+        constexpr int A = (D + 2) % 3;
+        const u32 cx = v.code >> (8 * A), cy = v.c5 >> (8 * A);
+        const double wx = 1.0 + 0.5 * (double)(high2(cx, 2) + high2(cx, 3));
+        const double wy = 1.0 + 0.5 * (double)(low2(cy, 2) + low2(cy, 3));
+        lf[5] = -0.25 * wx * v.e5x + -0.25 * wy * v.e5y;
+    }
+    // F_D[B_t2] enters the edges E_A, A = D + 1, as +F: at x (high sides of
+    // terms 1 and 2) and at x + e_B, B = D + 2 (low sides)
+    {
+        constexpr int A = (D + 1) % 3;
+        const u32 cx = v.code >> (8 * A), cy = v.c6 >> (8 * A);
+        const double wx = 1.0 + 0.5 * (double)(high2(cx, 0) + high2(cx, 1));
+        const double wy = 1.0 + 0.5 * (double)(low2(cy, 0) + low2(cy, 1));
+        lf[6] = 0.25 * wx * v.e6x + 0.25 * wy * v.e6y;
+    }
+}
 template <int D>
 __device__ __forceinline__ void flux_cotangent(const Geom &g, const StateP &lout,
                                                const AdStage &S, const int x[3], u32 t,
                                                double c, double lf[7])
 {
-    const u32 cl = t + step_lo<D>(g, x);
-    // cell update u -= c (F(x + e_D) - F(x))
-#pragma unroll
-    for (int q = 0; q < 5; ++q) {
-        const int f = lab_cons(D, q);
-        lf[q] = c * (lout.u[f][t] - lout.u[f][cl]);
-    }
-    const u32 code = S.wcode[t];
-    // F_D[B_t1] enters the edges E_A, A = D + 2, as -F: at x (weights of the
-    // high sides of terms 3 and 4) and at x + e_C, C = D + 1 (low sides)
-    {
-        constexpr int A = (D + 2) % 3, C = (A + 2) % 3;
-        const u32 y = t + step_hi<C>(g, x);
-        const u32 cx = code >> (8 * A), cy = S.wcode[y] >> (8 * A);
-        const double wx = 1.0 + 0.5 * (double)(high2(cx, 2) + high2(cx, 3));
-        const double wy = 1.0 + 0.5 * (double)(low2(cy, 2) + low2(cy, 3));
-        lf[5] = -0.25 * wx * S.le[A][t] + -0.25 * wy * S.le[A][y];
-    }
-    // F_D[B_t2] enters the edges E_A, A = D + 1, as +F: at x (high sides of
-    // terms 1 and 2) and at x + e_B, B = D + 2 (low sides)
-    {
-        constexpr int A = (D + 1) % 3, B = (A + 1) % 3;
-        const u32 y = t + step_hi<B>(g, x);
-        const u32 cx = code >> (8 * A), cy = S.wcode[y] >> (8 * A);
-        const double wx = 1.0 + 0.5 * (double)(high2(cx, 0) + high2(cx, 1));
-        const double wy = 1.0 + 0.5 * (double)(low2(cy, 0) + low2(cy, 1));
-        lf[6] = 0.25 * wx * S.le[A][t] + 0.25 * wy * S.le[A][y];
-    }
+    flux_combine<D>(flux_loads<D>(g, lout, S, x, t), c, lf);
 }
 
-// cotangent of -(v x B)_A at cell x from the four A-edges around it
+// The cell reversal: its loads, then its arithmetic.
+// Edge fields around cell x: E_A of the edges x, x + e_B, x + e_C and
+// x + e_B + e_C, of which the cell is r00, r10, r01 and r11, and the upwind
+// codes of the cell's seven edge positions (offset bits x, y, z).
+struct CellLoads {
+    double le[3][4], v[3], b[3], flo[3], fhi[3], u[5], base[5];
+    u32 code[7];
+};
 template <int A>
-__device__ __forceinline__ double eref_cotangent(const Geom &g, const AdStage &S, const int x[3],
-                                                 u32 t)
+__device__ __forceinline__ void edge_loads(const AdStage &S, u32 t, const u32 hi[3], double le[4])
 {
     constexpr int B = (A + 1) % 3, C = (A + 2) % 3;
-    // the cell is r00 of edge x, r10 of edge x + e_B, r01 of edge x + e_C and
-    // r11 of edge x + e_B + e_C
-    const u32 sb = step_hi<B>(g, x), sc = step_hi<C>(g, x);
-    auto code = [&](u32 y) { return S.wcode[y] >> (8 * A); };
-    const u32 c0 = code(t), c1 = code(t + sb), c2 = code(t + sc), c3 = code(t + sb + sc);
-    double acc = 0.5 * (double)(high2(c0, 0) + high2(c0, 2)) * S.le[A][t];
-    acc += 0.5 * (double)(low2(c1, 0) + high2(c1, 3)) * S.le[A][t + sb];
-    acc += 0.5 * (double)(high2(c2, 1) + low2(c2, 2)) * S.le[A][t + sc];
-    acc += 0.5 * (double)(low2(c3, 1) + low2(c3, 3)) * S.le[A][t + sb + sc];
+    le[0] = S.le[A][t];
+    le[1] = S.le[A][t + hi[B]];
+    le[2] = S.le[A][t + hi[C]];
+    le[3] = S.le[A][t + hi[B] + hi[C]];
+}
+__device__ __forceinline__ CellLoads cell_loads(const Geom &g, const StateP &st, const Prims &P,
+                                                const AdStage &S, const AdBase &base,
+                                                const int x[3], u32 t)
+{
+    CellLoads c;
+    const u32 hi[3] = {step_hi<0>(g, x), step_hi<1>(g, x), step_hi<2>(g, x)};
+#pragma unroll
+    for (int m = 0; m < 7; ++m)
+        c.code[m] = S.wcode[t + (m & 1 ? hi[0] : 0u) + (m & 2 ? hi[1] : 0u) + (m & 4 ? hi[2] : 0u)];
+    edge_loads<0>(S, t, hi, c.le[0]);
+    edge_loads<1>(S, t, hi, c.le[1]);
+    edge_loads<2>(S, t, hi, c.le[2]);
+    const u32 o = prim_at(g, x[0], x[1], x[2]);
+    const u32 f[3] = {face_at<0>(g, x[0], x[1], x[2]), face_at<1>(g, x[0], x[1], x[2]), t};
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        c.v[l] = P.w[1 + l][o];
+        c.b[l] = P.w[5 + l][o];
+        c.flo[l] = st.b[l][f[l]];
+        c.fhi[l] = st.b[l][f[l] + hi[l]];
+    }
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        c.u[q] = st.u[q][t];
+        c.base[q] = base.add ? base.lam.u[q][t] + base.half.u[q][t] : 0.0;
+    }
+    return c;
+}
+
+// cotangent of -(v x B)_A at the cell from the four A-edges around it
+template <int A>
+__device__ __forceinline__ double eref_cotangent(const CellLoads &c)
+{
+    constexpr int B = (A + 1) % 3, C = (A + 2) % 3;
+    auto code = [&](int m) { return c.code[m] >> (8 * A); };
+    const u32 c0 = code(0), c1 = code(1 << B), c2 = code(1 << C), c3 = code((1 << B) + (1 << C));
+    double acc = 0.5 * (double)(high2(c0, 0) + high2(c0, 2)) * c.le[A][0];
+    acc += 0.5 * (double)(low2(c1, 0) + high2(c1, 3)) * c.le[A][1];
+    acc += 0.5 * (double)(high2(c2, 1) + low2(c2, 2)) * c.le[A][2];
+    acc += 0.5 * (double)(low2(c3, 1) + low2(c3, 3)) * c.le[A][3];
     return -0.25 * acc;
 }
 
@@ -262,17 +330,13 @@ __device__ __forceinline__ double eref_cotangent(const Geom &g, const AdStage &S
 // average) of a cell reversed: its primitive cotangents lw become those of its
 // conserved variables, written to lacc.u on top of the base, and lb of each of
 // its six faces (half to either side).  A floored quantity is a constant.
-__device__ __forceinline__ void cell_rev(const Geom &g, const StateP &st, const Prims &P,
-                                         const AdStage &S, const AdBase &base, const StateW &lacc,
-                                         const int x[3], u32 t, double lw[8], double lb[3])
+__device__ __forceinline__ void cell_rev(const Geom &g, const CellLoads &c, const AdBase &base,
+                                         const StateW &lacc, u32 t, double lw[8], double lb[3])
 {
-    const int i = x[0], j = x[1], k = x[2];
     {
-        const u32 o = prim_at(g, i, j, k);
-        const double vx = P.w[1][o], vy = P.w[2][o], vz = P.w[3][o];
-        const double bx = P.w[5][o], by = P.w[6][o], bz = P.w[7][o];
-        const double ex = eref_cotangent<0>(g, S, x, t), ey = eref_cotangent<1>(g, S, x, t),
-                     ez = eref_cotangent<2>(g, S, x, t);
+        const double vx = c.v[0], vy = c.v[1], vz = c.v[2];
+        const double bx = c.b[0], by = c.b[1], bz = c.b[2];
+        const double ex = eref_cotangent<0>(c), ey = eref_cotangent<1>(c), ez = eref_cotangent<2>(c);
         lw[1] += bz * ey - by * ez;
         lw[2] += -bz * ex + bx * ez;
         lw[3] += by * ex - bx * ey;
@@ -280,26 +344,22 @@ __device__ __forceinline__ void cell_rev(const Geom &g, const StateP &st, const 
         lw[6] += vz * ex - vx * ez;
         lw[7] += -vy * ex + vx * ey;
     }
-    const u32 f0 = face_at<0>(g, i, j, k), f1 = face_at<1>(g, i, j, k);
-    const double bc[3] = {0.5 * (st.b[0][f0] + st.b[0][f0 + step_hi<0>(g, x)]),
-                          0.5 * (st.b[1][f1] + st.b[1][f1 + step_hi<1>(g, x)]),
-                          0.5 * (st.b[2][t] + st.b[2][t + step_hi<2>(g, x)])};
-    double d = st.u[0][t];
+    const double bc[3] = {0.5 * (c.flo[0] + c.fhi[0]), 0.5 * (c.flo[1] + c.fhi[1]),
+                          0.5 * (c.flo[2] + c.fhi[2])};
+    double d = c.u[0];
     const bool dfloor = !(d >= kFloorRho);
     if (dfloor) d = kFloorRho;
     const double id = mrcp(d);
-    const double v[3] = {st.u[1][t] * id, st.u[2][t] * id, st.u[3][t] * id};
+    const double v[3] = {c.u[1] * id, c.u[2] * id, c.u[3] * id};
     const double ke = 0.5 * d * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
     const double me = 0.5 * (bc[0] * bc[0] + bc[1] * bc[1] + bc[2] * bc[2]);
-    const double p = (g.gamma - 1.0) * (st.u[4][t] - ke - me);
+    const double p = (g.gamma - 1.0) * (c.u[4] - ke - me);
     const bool pfloor = !(p >= kFloorP);
     const double gm1 = g.gamma - 1.0;
     const double lp = pfloor ? 0.0 : lw[4];
     const double v2 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
     double lrho = dfloor ? 0.0 : lw[0] + lp * gm1 * 0.5 * v2;
-    auto put = [&](int f, double a) {
-        lacc.u[f][t] = base.add ? base.lam.u[f][t] + base.half.u[f][t] + a : a;
-    };
+    auto put = [&](int f, double a) { lacc.u[f][t] = base.add ? c.base[f] + a : a; };
 #pragma unroll
     for (int l = 0; l < 3; ++l) {
         if (!dfloor) lrho -= lw[1 + l] * v[l] * id;
@@ -310,14 +370,43 @@ __device__ __forceinline__ void cell_rev(const Geom &g, const StateP &st, const 
     put(4, lp * gm1);
 }
 
+// a face's two states wait in LDS (each thread its own slots) while HLLD is
+// reversed, which fetches them again (hlld_rev): 44 registers that two waves
+// per SIMD would otherwise spill
+template <int B>
+struct ParkedStates {
+    double (*s)[B];
+    int tid;
+    __device__ __forceinline__ void put(int o, const W7 &w) const
+    {
+        double v[7];
+        to_arr(w, v);
+#pragma unroll
+        for (int q = 0; q < 7; ++q) s[o + q][tid] = v[q];
+    }
+    __device__ __forceinline__ W7 get(int o) const
+    {
+        return W7{s[o][tid],     s[o + 1][tid], s[o + 2][tid], s[o + 3][tid],
+                  s[o + 4][tid], s[o + 5][tid], s[o + 6][tid]};
+    }
+    __device__ __forceinline__ void operator()(W7 &L, W7 &R) const
+    {
+        asm volatile("" ::: "memory");
+        L = get(0);
+        R = get(7);
+    }
+};
+
 // PCM stage: flux cotangents, then HLLD reversed at the forward states (the
 // cell primitives), then primitive recovery, without a pass over memory per
 // face.  The x kernel writes the sum of the cotangents of a cell's two x-face
 // states, the y march adds those of the y-faces, the z march those of the
 // z-faces and reverses the finished cell: about 125 doubles moved per cell
-// where storing both states' cotangents of every face moved 200.  Bound by
-// load latency (one wave per SIMD in the marches, 300 registers): 64^3 27 + 28
-// + 49 us (faces and gather: 80 + 36), 128^3 188 + 222 + 406 (568 + 262).
+// where storing both states' cotangents of every face moved 200.  The marches
+// run one wave per SIMD, whose spare registers hold the next face's and the
+// cell's loads during a reversal: 128^3 171 + 156 + 270 us, 222 + 406 for the
+// marches without loads ahead (75% of their cycles waiting), 568 + 262 as face
+// kernels and a gather; 64^3 26 + 26 + 42 us (80 + 36).
 //
 // x: items (row, face 0 .. nx) of every row in one flat sequence (face nx is
 // face 0 again), blocks of kBlock items overlapping by one; the cotangent of a
@@ -333,7 +422,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_ad_pcm_row(Geom g, Prims P, State
                                                           AdStage S, AdBase base, StateW lacc,
                                                           const double *dt_dev, double factor)
 {
-    __shared__ double lds[7][kBlock];
+    __shared__ double lds[7][kBlock], park[14][kBlock];
     const u32 per_row = (u32)g.n[0] + 1, items = per_row * (u32)g.n[1] * (u32)g.n[2];
     const int tid = threadIdx.x;
     const u32 q = blockIdx.x * (u32)(kBlock - 1) + tid;
@@ -350,7 +439,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_ad_pcm_row(Geom g, Prims P, State
         const u32 o = prim_at(g, i, x[1], x[2]);
         const u32 fo = face_at<0>(g, x[0], x[1], x[2]);
         double abn = 0.0;
-        hlld_rev(w7_at(P, 0, o - 1), w7_at(P, 0, o), st.b[0][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
+        const ParkedStates<kBlock> states{park, tid};
+        const W7 wl = w7_at(P, 0, o - 1), wr = w7_at(P, 0, o);
+        states.put(0, wl);
+        states.put(7, wr);
+        hlld_rev(wl, wr, st.b[0][fo], g.gamma, g.gm1i, lf, aL, aR, abn, states);
+        __builtin_amdgcn_sched_barrier(0);
         if (cell) {
             lacc.b[0][fo] = base_face<0>(g, base, fo, x) + abn;
             clear_duplicate<0>(g, lacc, fo, x);
@@ -396,48 +490,75 @@ __global__ __launch_bounds__(kBlock, 1) void k_ad_pcm_march(Geom g, Prims P, Sta
     x[D] = s0 - 1;
     u32 po = prim_at(g, x[0], x[1], x[2]);
     const u32 pstep = D == 1 ? (u32)g.p[0] : (u32)g.p[0] * (u32)g.p[1];
-    // the cell below the face; the cotangent of its low-face state waits in LDS
-    // (thread-private)
-    W7 wl = w7_at(P, D, po);
-    __shared__ double alow[7][kBlock];
+    // the face's two states and the cotangent of the low-face state of the cell
+    // below wait in LDS (thread-private)
+    __shared__ double alow[7][kBlock], park[14][kBlock];
     const int tid = threadIdx.x;
+    const ParkedStates<kBlock> states{park, tid};
+    states.put(0, w7_at(P, D, po));
     double lbn = 0.0;
-    for (int a = s0; a <= s1; ++a) {
-        po += pstep;
-        const W7 wr = w7_at(P, D, po);
+    // the loads of face a, a face ahead of its reversal
+    FluxLoads fl;
+    W7 wr;
+    double bn;
+    auto load_face = [&](int a) {
         x[D] = a < nD ? a : 0;
-        const u32 t = tcol + (u32)x[D] * tstep;
+        fl = flux_loads<D>(g, lout, S, x, tcol + (u32)x[D] * tstep);
+        bn = st.b[D][face_at<D>(g, x[0], x[1], x[2])];
+        po += pstep;
+        wr = w7_at(P, D, po);
+    };
+    load_face(s0);
+    for (int a = s0; a <= s1; ++a) {
         double lf[7];
-        flux_cotangent<D>(g, lout, S, x, t, c, lf);
+        flux_combine<D>(fl, c, lf);
+        const double bna = bn;
+        const W7 wra = wr;
+        states.put(7, wra);
+        if (a < s1) load_face(a + 1);
+        // what this face and the cell below it read and add to
+        double own = 0.0, lw[8];
+        CellLoads cl;
+        x[D] = a < nD ? a : 0;
         const u32 fo = face_at<D>(g, x[0], x[1], x[2]);
+        if (D == 1 && a < s1) own = base_face<1>(g, base, fo, x);
+        const u32 tc = tcol + (u32)(a - 1) * tstep;
+        if (a > s0) {
+#pragma unroll
+            for (int f = 0; f < 8; ++f)
+                if (D == 2 || (f != 5 && f != 6)) lw[f] = S.lw[f][tc];
+            if (D == 2) {
+                x[D] = a - 1;
+                cl = cell_loads(g, st, P, S, base, x, tc);
+                x[D] = a < nD ? a : 0;
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
         W7 aL{0, 0, 0, 0, 0, 0, 0}, aR{0, 0, 0, 0, 0, 0, 0};
         double abn = 0.0;
-        hlld_rev(wl, wr, st.b[D][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
+        hlld_rev(states.get(0), wra, bna, g.gamma, g.gm1i, lf, aL, aR, abn, states);
+        states.put(0, states.get(7));
         if (D == 1 && a < s1) {
-            lacc.b[1][fo] = base_face<1>(g, base, fo, x) + abn;
+            lacc.b[1][fo] = own + abn;
             clear_duplicate<1>(g, lacc, fo, x);
         }
         if (a > s0) {
             // cell a - 1 has its face states' cotangents
             x[D] = a - 1;
-            const u32 tc = tcol + (u32)(a - 1) * tstep;
             const double vl[7] = {aL.d, aL.u, aL.v, aL.w, aL.p, aL.by, aL.bz};
-            double lw[8];
             if (D == 1) {
 #pragma unroll
                 for (int q = 0; q < 7; ++q) {
                     const int f = lab_slot(1, q);
                     // the x sweep has no B_x component
                     const double sum = alow[q][tid] + vl[q];
-                    S.lw[f][tc] = f == 5 ? sum : S.lw[f][tc] + sum;
+                    S.lw[f][tc] = f == 5 ? sum : lw[f] + sum;
                 }
             } else {
 #pragma unroll
-                for (int f = 0; f < 8; ++f) lw[f] = S.lw[f][tc];
-#pragma unroll
                 for (int q = 0; q < 7; ++q) lw[lab_slot(2, q)] += alow[q][tid] + vl[q];
                 double lb[3];
-                cell_rev(g, st, P, S, base, lacc, x, tc, lw, lb);
+                cell_rev(g, cl, base, lacc, tc, lw, lb);
                 const u32 f0 = face_at<0>(g, x[0], x[1], x[2]), f1 = face_at<1>(g, x[0], x[1], x[2]);
                 atomicAdd(&lacc.b[0][f0], lb[0]);
                 atomicAdd(&lacc.b[0][f0 + step_hi<0>(g, x)], lb[0]);
@@ -453,7 +574,6 @@ __global__ __launch_bounds__(kBlock, 1) void k_ad_pcm_march(Geom g, Prims P, Sta
         const double vr[7] = {aR.d, aR.u, aR.v, aR.w, aR.p, aR.by, aR.bz};
 #pragma unroll
         for (int q = 0; q < 7; ++q) alow[q][tid] = vr[q];
-        wl = wr;
     }
     if (D == 2) {
         x[D] = s1 < nD ? s1 : 0;
@@ -577,9 +697,14 @@ __global__ __launch_bounds__(kBlock) void k_ad_faces_march(Geom g, Prims P, Stat
     }
 }
 
+// blocks of the reconstructing x kernels: one wave, so that no barrier makes
+// four waves of a CU wait for each other's loads (fused PLMC x kernel at 128^3
+// 398 -> 366 us; 369 with 128 threads)
+constexpr int kAdRow = 64;
+
 // faces of axis x with a reconstructing corrector: items (row, cell) with
 // cells -1 .. nx-1 of every row in one flat sequence; a block reconstructs
-// kBlock consecutive items once each, hands the high-face states to the right
+// kAdRow consecutive items once each, hands the high-face states to the right
 // neighbour through LDS, and each item with a left neighbour in its block and
 // row takes the face between them (consecutive blocks overlap by one item).
 // Per face: flux cotangents, HLLD reversed, the cotangents of the two floored
@@ -587,22 +712,22 @@ __global__ __launch_bounds__(kBlock) void k_ad_faces_march(Geom g, Prims P, Stat
 __host__ __device__ __forceinline__ idx_t ad_row_blocks(const Geom &g)
 {
     const idx_t items = (idx_t)(g.n[0] + 1) * g.n[1] * g.n[2];
-    return (items - 1 + kBlock - 2) / (kBlock - 1);
+    return (items - 1 + kAdRow - 2) / (kAdRow - 1);
 }
 
 template <int RECON>
-__global__ __launch_bounds__(kBlock, 2) void k_ad_faces_row(Geom g, Prims P, StateP st,
+__global__ __launch_bounds__(kAdRow, 2) void k_ad_faces_row(Geom g, Prims P, StateP st,
                                                          StateP lout, AdStage S, StateW lacc,
                                                          const double *dt_dev, double factor)
 {
     constexpr bool kPpm = RECON == VLCT_RECON_PPMC || RECON == VLCT_RECON_PPMP;
     constexpr bool kChar = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PPMC;
-    __shared__ double lds[7][kBlock];
-    __shared__ uint32_t lfl[kBlock];
+    __shared__ double lds[7][kAdRow];
+    __shared__ uint32_t lfl[kAdRow];
     const int nx = g.n[0];
     const u32 per_row = (u32)nx + 1, items = per_row * (u32)g.n[1] * (u32)g.n[2];
     const int t = threadIdx.x;
-    const u32 q = blockIdx.x * (u32)(kBlock - 1) + t;
+    const u32 q = blockIdx.x * (u32)(kAdRow - 1) + t;
     const bool have = q < items;
     const u32 row = q / per_row, plane = row / (u32)g.n[1];
     const int x[3] = {(int)(q - row * per_row) - 1, (int)(row - plane * (u32)g.n[1]), (int)plane};
@@ -658,8 +783,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_ad_faces_row(Geom g, Prims P, Sta
 // stays with the segment that owns it), and as soon as a cell has the
 // cotangents of both its interface states it reverses its reconstruction.
 // Bound by FP64 issue and by latency at one wave per SIMD (about 2000 of 3400
-// vector instructions per face): 128^3 PLMC 315 us per axis, 371 with 64-bit
-// index arithmetic (4280); two waves per SIMD would spill 950 bytes (1295 us).
+// vector instructions per face, 68% of cycles issuing): 128^3 PLMC 308 us per
+// axis, 371 with 64-bit index arithmetic (4280); two waves per SIMD would spill
+// 950 bytes (1295 us).
 constexpr int kAdFusedWaves = 1;
 
 template <int D, int RECON>
@@ -688,66 +814,80 @@ __global__ __launch_bounds__(kBlock, kAdFusedWaves) void k_ad_march_fused(
     x[D] = s0 - 2;
     u32 po = prim_at(g, x[0], x[1], x[2]);
     const u32 pstep = D == 1 ? (u32)g.p[0] : (u32)g.p[0] * (u32)g.p[1];
-    // window of cells a - 1 .. a + 1 for the cell a being reconstructed
-    W7 win[3];
-    double bnc[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        win[q] = w7_at(P, D, po);
-        bnc[q] = P.w[5 + D][po];
-        po += pstep;
-    }
-    // in LDS, each thread its own column: cell a - 2 of the window, the high
-    // state of cell a - 1 and the cotangent of its low state, and of the
-    // reversals (that of cell m adds to the cells m - 1, m and m + 1) the sums
-    // of the two cells still waiting for terms (cell c in slot c & 1): a cell
-    // leaves with one atomic add per component (segments share the two cells
-    // at each end)
-    __shared__ double park[35][kBlock];
+    // What a thread keeps from cell to cell waits in LDS (its own slots), so
+    // that the two reversals have the registers to themselves: the face's two
+    // states (the low one's cell is a - 1), the high state of cell a, the
+    // cotangent of the low state of cell a - 1, the cells a - 2 .. a + 1 of the
+    // window (cell c in slot c & 3, with its B_n), and of the reversals (that of
+    // cell m adds to the cells m - 1, m and m + 1) the sums of the two cells
+    // still waiting for terms (cell c in slot c & 1): a cell leaves with one
+    // atomic add per component (segments share the two cells at each end)
+    constexpr int kNext = 14, kLow = 21, kPend = 28, kWin = 42;
+    __shared__ double park[kWin + 32][kBlock];
     const int tid = threadIdx.x;
-    auto put = [&](int s, const double v[7]) {
+    const ParkedStates<kBlock> states{park, tid};
+    auto win = [&](int c) { return states.get(kWin + 8 * (c & 3)); };
+    auto winb = [&](int c) { return park[kWin + 8 * (c & 3) + 7][tid]; };
+    auto load = [&](int c) {
+        states.put(kWin + 8 * (c & 3), w7_at(P, D, po));
+        park[kWin + 8 * (c & 3) + 7][tid] = P.w[5 + D][po];
+        po += pstep;
+    };
 #pragma unroll
-        for (int q = 0; q < 7; ++q) park[s + q][tid] = v[q];
-    };
-    auto get = [&](int s) {
-        return W7{park[s][tid], park[s + 1][tid], park[s + 2][tid], park[s + 3][tid],
-                  park[s + 4][tid], park[s + 5][tid], park[s + 6][tid]};
-    };
-    auto put7 = [&](int s, const W7 &w) {
-        double v[7];
-        to_arr(w, v);
-        put(s, v);
-    };
-    constexpr int kOld = 0, kPrev = 7, kLow = 14, kPend = 21;
+    for (int q = 0; q < 3; ++q) load(s0 - 2 + q);
 #pragma unroll
     for (int k = 0; k < 14; ++k) park[kPend + k][tid] = 0.0;
     uint32_t fprev = 0;
     for (int a = s0 - 1; a <= s1; ++a) {
-        W7 fm, fp;
-        plmc<kChar>(win[0], win[1], win[2], bnc[1], g.gamma, fm, fp);
-        const uint32_t flo = floor_state(fm), fhi = floor_state(fp);
+        // the loads of this face and of the window's next cell, ahead of the
+        // reconstruction and the reversals
+        x[D] = a < 0 ? nD - 1 : (a < nD ? a : 0);
+        const u32 t = tcol + (u32)x[D] * tstep;
+        const FluxLoads fl = flux_loads<D>(g, lout, S, x, t);
+        const u32 fo = face_at<D>(g, x[0], x[1], x[2]);
+        const double bn = st.b[D][fo];
+        W7 ahead{0, 0, 0, 0, 0, 0, 0};
+        double ahead_b = 0.0;
+        if (a < s1) {
+            ahead = w7_at(P, D, po);
+            ahead_b = P.w[5 + D][po];
+            po += pstep;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t flo, fhi;
+        {
+            W7 fm, fp;
+            plmc<kChar>(win(a - 1), win(a), win(a + 1), winb(a), g.gamma, fm, fp);
+            flo = floor_state(fm);
+            fhi = floor_state(fp);
+            states.put(7, fm);
+            states.put(kNext, fp);
+        }
         if (a >= s0) {
             // the face a - 1/2
-            x[D] = a < nD ? a : 0;
-            const u32 t = tcol + (u32)x[D] * tstep;
             double lf[7];
-            flux_cotangent<D>(g, lout, S, x, t, c, lf);
-            const u32 fo = face_at<D>(g, x[0], x[1], x[2]);
+            flux_combine<D>(fl, c, lf);
             W7 aL{0, 0, 0, 0, 0, 0, 0}, aR{0, 0, 0, 0, 0, 0, 0};
             double abn = 0.0;
-            hlld_rev(get(kPrev), fm, st.b[D][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
+            hlld_rev(states.get(0), states.get(7), bn, g.gamma, g.gm1i, lf, aL, aR, abn,
+                     states);
             if (a < s1) lacc.b[D][fo] = abn;
+            double alow[7];
+#pragma unroll
+            for (int k = 0; k < 7; ++k) alow[k] = park[kLow + k][tid];
+            if (flo & kStatusDensityFloor) aR.d = 0.0;
+            if (flo & kStatusPressureFloor) aR.p = 0.0;
+            states.put(kLow, aR);
             if (a - 1 >= s0) {
                 // cell a - 1 has both interface cotangents: reverse its PLM
-                double ahigh[7] = {aL.d, aL.u, aL.v, aL.w, aL.p, aL.by, aL.bz}, alow[7];
+                double ahigh[7] = {aL.d, aL.u, aL.v, aL.w, aL.p, aL.by, aL.bz};
                 if (fprev & kStatusDensityFloor) ahigh[0] = 0.0;
                 if (fprev & kStatusPressureFloor) ahigh[4] = 0.0;
-#pragma unroll
-                for (int k = 0; k < 7; ++k) alow[k] = park[kLow + k][tid];
                 W7 am{0, 0, 0, 0, 0, 0, 0}, a0{0, 0, 0, 0, 0, 0, 0}, ap{0, 0, 0, 0, 0, 0, 0};
                 double abc = 0.0;
-                plmc_rev<kChar>(get(kOld), win[0], win[1], bnc[0], g.gamma, alow, ahigh, am, a0,
-                                ap, abc);
+                asm volatile("" ::: "memory");
+                plmc_rev<kChar>(win(a - 2), win(a - 1), win(a), winb(a - 1), g.gamma, alow, ahigh,
+                                am, a0, ap, abc);
                 const double vm[7] = {am.d, am.u, am.v, am.w, am.p, am.by, am.bz};
                 const double v0[7] = {a0.d, a0.u, a0.v, a0.w, a0.p, a0.by, a0.bz};
                 const double vp[7] = {ap.d, ap.u, ap.v, ap.w, ap.p, ap.by, ap.bz};
@@ -762,23 +902,11 @@ __global__ __launch_bounds__(kBlock, kAdFusedWaves) void k_ad_march_fused(
                 }
                 atomicAdd(&S.lw[5 + D][cell(a - 1)], abc);
             }
-            double lo[7] = {aR.d, aR.u, aR.v, aR.w, aR.p, aR.by, aR.bz};
-            if (flo & kStatusDensityFloor) lo[0] = 0.0;
-            if (flo & kStatusPressureFloor) lo[4] = 0.0;
-            put(kLow, lo);
         }
-        put7(kPrev, fp);
+        states.put(0, states.get(kNext));
         fprev = fhi;
-        if (a + 1 <= s1) {
-            put7(kOld, win[0]);
-            win[0] = win[1];
-            win[1] = win[2];
-            bnc[0] = bnc[1];
-            bnc[1] = bnc[2];
-            win[2] = w7_at(P, D, po);
-            bnc[2] = P.w[5 + D][po];
-            po += pstep;
-        }
+        states.put(kWin + 8 * ((a + 2) & 3), ahead);
+        park[kWin + 8 * ((a + 2) & 3) + 7][tid] = ahead_b;
     }
     // the cells s1 - 1 and s1 (the last reversal was that of cell s1 - 1)
 #pragma unroll
@@ -792,7 +920,7 @@ __global__ __launch_bounds__(kBlock, kAdFusedWaves) void k_ad_march_fused(
 
 // x faces of a linear-reconstruction stage with the reconstruction transposed
 // in the same kernel: items (row, cell) with cells -1 .. nx of every row in
-// one flat sequence, blocks of kBlock items overlapping by two.  Each item
+// one flat sequence, blocks of kAdRow items overlapping by two.  Each item
 // reconstructs its cell and hands the high-face state to the right through
 // LDS; each item with a left neighbour in its block and row takes the face
 // between them and hands the left state's cotangent back; each item whose
@@ -803,24 +931,24 @@ __global__ __launch_bounds__(kBlock, kAdFusedWaves) void k_ad_march_fused(
 __host__ __device__ __forceinline__ idx_t ad_row_fused_blocks(const Geom &g)
 {
     const idx_t items = (idx_t)(g.n[0] + 2) * g.n[1] * g.n[2];
-    return (items - 1 + kBlock - 3) / (kBlock - 2);  // items 1 .. items-1 at t in [1, kBlock-2]
+    return (items - 1 + kAdRow - 3) / (kAdRow - 2);  // items 1 .. items-1 at t in [1, kAdRow-2]
 }
 
 template <int RECON>
-__global__ __launch_bounds__(kBlock, kAdFusedWaves) void k_ad_row_fused(
+__global__ __launch_bounds__(kAdRow, kAdFusedWaves) void k_ad_row_fused(
     Geom g, Prims P, StateP st, StateP lout, AdStage S, StateW lacc, const double *dt_dev,
     double factor)
 {
     static_assert(RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PLMP, "linear reconstructions");
     constexpr bool kChar = RECON == VLCT_RECON_PLMC;
-    __shared__ double lds[7][kBlock];
-    __shared__ double lds_p[7][kBlock];
-    __shared__ uint32_t lfl[kBlock];
-    __shared__ uint32_t lrev[kBlock];
+    __shared__ double lds[7][kAdRow];
+    __shared__ double lds_p[7][kAdRow];
+    __shared__ uint32_t lfl[kAdRow];
+    __shared__ uint32_t lrev[kAdRow];
     const int nx = g.n[0];
     const u32 per_row = (u32)nx + 2, items = per_row * (u32)g.n[1] * (u32)g.n[2];
     const int t = threadIdx.x;
-    const u32 q = blockIdx.x * (u32)(kBlock - 2) + t;
+    const u32 q = blockIdx.x * (u32)(kAdRow - 2) + t;
     const bool have = q < items;
     const u32 row = q / per_row, plane = row / (u32)g.n[1];
     const int i = (int)(q - row * per_row) - 1;  // -1 .. nx
@@ -853,7 +981,7 @@ __global__ __launch_bounds__(kBlock, kAdFusedWaves) void k_ad_row_fused(
         W7 aL{0, 0, 0, 0, 0, 0, 0}, aR{0, 0, 0, 0, 0, 0, 0};
         double abn = 0.0;
         hlld_rev(wl, fm, st.b[0][fo], g.gamma, g.gm1i, lf, aL, aR, abn);
-        if (t <= kBlock - 2 && i < nx) lacc.b[0][fo] = abn;
+        if (t <= kAdRow - 2 && i < nx) lacc.b[0][fo] = abn;
         const double vl[7] = {aL.d, aL.u, aL.v, aL.w, aL.p, aL.by, aL.bz};
         const double vr[7] = {aR.d, aR.u, aR.v, aR.w, aR.p, aR.by, aR.bz};
 #pragma unroll
@@ -871,7 +999,7 @@ __global__ __launch_bounds__(kBlock, kAdFusedWaves) void k_ad_row_fused(
 #pragma unroll
     for (int c = 0; c < 7; ++c) lds[c][t] = ahigh_left[c];
     __syncthreads();
-    const bool rev = face && t <= kBlock - 2 && i < nx;
+    const bool rev = face && t <= kAdRow - 2 && i < nx;
     W7 am{0, 0, 0, 0, 0, 0, 0}, a0{0, 0, 0, 0, 0, 0, 0}, ap{0, 0, 0, 0, 0, 0, 0};
     double abc = 0.0;
     if (rev) {
@@ -923,22 +1051,24 @@ __global__ __launch_bounds__(kBlock, kAdFusedWaves) void k_ad_row_fused(
 // the five stencil states go through LDS to the cells of the block that they
 // belong to (cells in flat order, neighbours in a row being neighbours in the
 // block), which leave with one atomic add per component; those of other
-// blocks' cells and across the periodic boundary are added one by one.
+// blocks' cells and across the periodic boundary are added one by one.  Bound
+// by FP64 latency at one wave per SIMD and 512 registers: 64^3 PPMC 122 -> 90
+// us with the stencil parked in LDS (spills 268 -> 36 bytes) and 35 -> 7 adds.
 template <int RECON>
-__global__ __launch_bounds__(kBlock) void k_ad_recon_row(Geom g, Prims P, AdStage S)
+__global__ __launch_bounds__(kAdRow) void k_ad_recon_row(Geom g, Prims P, AdStage S)
 {
     static_assert(RECON == VLCT_RECON_PPMC || RECON == VLCT_RECON_PPMP, "parabolic reconstructions");
     constexpr bool kChar = RECON == VLCT_RECON_PPMC;
-    __shared__ double lds[5][7][kBlock];
+    __shared__ double lds[5][7][kAdRow], win[35][kAdRow];
     const int nx = g.n[0], tid = threadIdx.x;
     const u32 N = (u32)nx * (u32)g.n[1] * (u32)g.n[2];
-    const u32 t = blockIdx.x * (u32)kBlock + tid;
+    const u32 t = blockIdx.x * (u32)kAdRow + tid;
     const bool have = t < N;
     int x[3];
     cell_coords(g, have ? t : 0u, x);
     // cells of the row in the block: offsets [lo, hi] from this one
     const int lo = -min(tid, x[0]);
-    const int hi = min(min(kBlock - 1 - tid, nx - 1 - x[0]), 2);
+    const int hi = min(min(kAdRow - 1 - tid, nx - 1 - x[0]), 2);
     W7 ad[5];
 #pragma unroll
     for (int q = 0; q < 5; ++q) ad[q] = W7{0, 0, 0, 0, 0, 0, 0};
@@ -950,10 +1080,17 @@ __global__ __launch_bounds__(kBlock) void k_ad_recon_row(Geom g, Prims P, AdStag
             afm[c] = S.lrec[0][c][t];
             afp[c] = S.lrec[0][7 + c][t];
         }
+        // the stencil waits in LDS (each thread its own)
         const u32 o = prim_at(g, x[0], x[1], x[2]);
-        ppmc_rev<kChar>(w7_at(P, 0, o - 2), w7_at(P, 0, o - 1), w7_at(P, 0, o), w7_at(P, 0, o + 1),
-                        w7_at(P, 0, o + 2), P.w[5][o], g.gamma, afm, afp, ad[0], ad[1], ad[2],
-                        ad[3], ad[4], abn);
+        const ParkedStates<kAdRow> cells{win, tid};
+#pragma unroll
+        for (int q = 0; q < 5; ++q) cells.put(7 * q, w7_at(P, 0, o + (u32)(q - 2)));
+        ppmc_rev<kChar>(
+            [&](int q) {
+                asm volatile("" ::: "memory");  // not kept from the first fetch
+                return cells.get(7 * q);
+            },
+            P.w[5][o], g.gamma, afm, afp, ad[0], ad[1], ad[2], ad[3], ad[4], abn);
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
             const double v[7] = {ad[q].d, ad[q].u, ad[q].v, ad[q].w, ad[q].p, ad[q].by, ad[q].bz};
@@ -981,13 +1118,13 @@ __global__ __launch_bounds__(kBlock) void k_ad_recon_row(Geom g, Prims P, AdStag
     atomicAdd(&S.lw[5][t], abn);
 }
 
-// Along y and z a thread marches a column
-// segment of M cells and keeps the four cells still waiting for terms in LDS
-// (thread-private slots, cell c in slot c mod 5); a cell leaves with one
-// atomic add per component once the reversal two cells above it is done
-// (segments share two cells at each end, so every departure stays atomic).
-// The cell's own B_n cotangent comes from its reversal alone and is added
-// in place.
+// Along y and z a thread marches a column segment of M cells and keeps the
+// stencil's cells and the four cells still waiting for terms in LDS; a cell
+// leaves with one atomic add per component once the reversal two cells above
+// it is done (segments share two cells at each end, so every departure stays
+// atomic).  The cell's own B_n cotangent comes from its reversal alone and is
+// added in place.  64^3 PPMC, segments of 4: 104 -> 84 us with the stencil in
+// LDS, fetched again by the last transposes (spills 304 -> 52 bytes).
 template <int D, int RECON>
 __global__ __launch_bounds__(kBlock) void k_ad_recon_march(Geom g, Prims P, AdStage S, int M)
 {
@@ -995,7 +1132,9 @@ __global__ __launch_bounds__(kBlock) void k_ad_recon_march(Geom g, Prims P, AdSt
     static_assert(RECON == VLCT_RECON_PPMC || RECON == VLCT_RECON_PPMP, "parabolic reconstructions");
     constexpr int T = D == 1 ? 2 : 1;
     constexpr bool kChar = RECON == VLCT_RECON_PPMC;
-    __shared__ double pend[5][7][kBlock];
+    // the stencil's cells (with their B_n) and the cells waiting for terms, cell
+    // c in slot c mod 5 (each thread its own column)
+    __shared__ double pend[5][7][kBlock], win[40][kBlock];
     const int nD = g.n[D];
     const u32 cols = (u32)g.n[0] * (u32)g.n[T];
     const u32 ncb = (cols + kBlock - 1) / kBlock;
@@ -1018,6 +1157,16 @@ __global__ __launch_bounds__(kBlock) void k_ad_recon_march(Geom g, Prims P, AdSt
     for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int k = 0; k < 7; ++k) pend[slot(s0 - 2 + q)][k][tid] = 0.0;
+    const ParkedStates<kBlock> cells{win, tid};
+    auto load = [&](int c, const W7 &w, double bn) {
+        cells.put(8 * slot(c), w);
+        win[8 * slot(c) + 7][tid] = bn;
+    };
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        load(s0 - 2 + q, w7_at(P, D, pb), P.w[5 + D][pb]);
+        pb += pstep;
+    }
     for (int c = s0; c < s1; ++c) {
         const u32 t = tcol + (u32)c * tstep;
         double afm[7], afp[7];
@@ -1026,15 +1175,18 @@ __global__ __launch_bounds__(kBlock) void k_ad_recon_march(Geom g, Prims P, AdSt
             afm[k] = S.lrec[D][k][t];
             afp[k] = S.lrec[D][7 + k][t];
         }
-        const u32 po[5] = {pb, pb + pstep, pb + 2 * pstep, pb + 3 * pstep, pb + 4 * pstep};
-        pb += pstep;
         W7 ad[5];
 #pragma unroll
         for (int q = 0; q < 5; ++q) ad[q] = W7{0, 0, 0, 0, 0, 0, 0};
         double abn = 0.0;
-        ppmc_rev<kChar>(w7_at(P, D, po[0]), w7_at(P, D, po[1]), w7_at(P, D, po[2]),
-                        w7_at(P, D, po[3]), w7_at(P, D, po[4]), P.w[5 + D][po[2]], g.gamma,
-                        afm, afp, ad[0], ad[1], ad[2], ad[3], ad[4], abn);
+        const int sm = slot(c - 2), s1m = slot(c - 1), s00 = slot(c), s1p = slot(c + 1),
+                  s2p = slot(c + 2);
+        ppmc_rev<kChar>(
+            [&](int q) {
+                asm volatile("" ::: "memory");  // not kept from the first fetch
+                return cells.get(8 * slot(c - 2 + q));
+            },
+            win[8 * s00 + 7][tid], g.gamma, afm, afp, ad[0], ad[1], ad[2], ad[3], ad[4], abn);
         double v[5][7];
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
@@ -1042,8 +1194,6 @@ __global__ __launch_bounds__(kBlock) void k_ad_recon_march(Geom g, Prims P, AdSt
             v[q][4] = ad[q].p; v[q][5] = ad[q].by; v[q][6] = ad[q].bz;
         }
         const u32 cm = cell(c - 2);
-        const int sm = slot(c - 2), s1m = slot(c - 1), s00 = slot(c), s1p = slot(c + 1),
-                  s2p = slot(c + 2);
 #pragma unroll
         for (int k = 0; k < 7; ++k) {
             atomicAdd(&S.lw[lab_slot(D, k)][cm], pend[sm][k][tid] + v[0][k]);
@@ -1053,6 +1203,10 @@ __global__ __launch_bounds__(kBlock) void k_ad_recon_march(Geom g, Prims P, AdSt
             pend[s2p][k][tid] = v[4][k];
         }
         S.lw[5 + D][t] += abn;
+        if (c + 1 < s1) {  // in the slot of cell c - 2
+            load(c + 3, w7_at(P, D, pb), P.w[5 + D][pb]);
+            pb += pstep;
+        }
     }
     // the cells s1 - 2 .. s1 + 1 (the last reversal was that of cell s1 - 1)
 #pragma unroll
@@ -1077,7 +1231,7 @@ __global__ __launch_bounds__(kBlock) void k_ad_prims(Geom g, StateP st, Prims P,
     double lw[8], lb[3];
 #pragma unroll
     for (int f = 0; f < 8; ++f) lw[f] = S.lw[f][t];
-    cell_rev(g, st, P, S, base, lacc, x, t, lw, lb);
+    cell_rev(g, cell_loads(g, st, P, S, base, x, t), base, lacc, t, lw, lb);
     const u32 f0 = face_at<0>(g, x[0], x[1], x[2]), f1 = face_at<1>(g, x[0], x[1], x[2]);
     atomicAdd(&lacc.b[0][f0], lb[0]);
     atomicAdd(&lacc.b[0][f0 + step_hi<0>(g, x)], lb[0]);
@@ -1097,23 +1251,24 @@ static void stage_adjoint(const Geom &g, double factor, const StateP &lout, bool
                           const double *dt, hipStream_t s)
 {
     const unsigned gc = nblocks((size_t)g.n[0] * g.n[1] * g.n[2]);
+    const unsigned gr = (unsigned)(((idx_t)g.n[0] * g.n[1] * g.n[2] + kAdRow - 1) / kAdRow);
     k_ad_edges<<<gc, kBlock, 0, s>>>(g, lout, fold, sd, S, dt, factor, recon != VLCT_RECON_PCM);
     const int slots = kNumCUs;
     const int m1 = ad_march_segment(g, 1, slots), m2 = ad_march_segment(g, 2, slots);
     const unsigned b1 = (unsigned)ad_march_blocks(g, 1, m1), b2 = (unsigned)ad_march_blocks(g, 2, m2);
 #define VLCT_AD_FACES(R)                                                                   \
-    k_ad_faces_row<R><<<(unsigned)ad_row_blocks(g), kBlock, 0, s>>>(g, P, st, lout, S,     \
+    k_ad_faces_row<R><<<(unsigned)ad_row_blocks(g), kAdRow, 0, s>>>(g, P, st, lout, S,     \
                                                                      lacc, dt, factor);    \
     k_ad_faces_march<1, R><<<b1, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor, m1); \
     k_ad_faces_march<2, R><<<b2, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor, m2);
 #define VLCT_AD_FUSED(R)                                                                   \
-    k_ad_row_fused<R><<<(unsigned)ad_row_fused_blocks(g), kBlock, 0, s>>>(g, P, st, lout,  \
+    k_ad_row_fused<R><<<(unsigned)ad_row_fused_blocks(g), kAdRow, 0, s>>>(g, P, st, lout,  \
                                                                            S, lacc, dt,    \
                                                                            factor);        \
     k_ad_march_fused<1, R><<<b1, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor, m1); \
     k_ad_march_fused<2, R><<<b2, kBlock, 0, s>>>(g, P, st, lout, S, lacc, dt, factor, m2);
 #define VLCT_AD_RECON(R)                                                                   \
-    k_ad_recon_row<R><<<gc, kBlock, 0, s>>>(g, P, S);                                      \
+    k_ad_recon_row<R><<<gr, kAdRow, 0, s>>>(g, P, S);                                      \
     k_ad_recon_march<1, R><<<b1, kBlock, 0, s>>>(g, P, S, m1);                             \
     k_ad_recon_march<2, R><<<b2, kBlock, 0, s>>>(g, P, S, m2);
     if (recon == VLCT_RECON_PCM) {
