@@ -1187,12 +1187,14 @@ struct Inst {
 
 __device__ __forceinline__ bool retired(const Inst &I) { return I.active && !I.active[0]; }
 
-constexpr int kPackChunk = 4;  // records per pack launch (kernel-argument size)
+constexpr int kPackChunk = 6;  // records per pack launch (4 KiB of kernel arguments)
 struct PackArgs {
     Inst rec[kPackChunk];
     Inst *tab;
     int first, n;
 };
+
+static_assert(sizeof(PackArgs) <= 4096, "kernel arguments");
 
 // writes instance records into the device table (records travel as kernel
 // arguments, so a step needs no host-to-device copy and can be captured)
