@@ -28,7 +28,7 @@ sys.path.insert(0, ROOT)
 # reconstruction (each cell's serves its two faces) and one HLLD solve; a
 # predictor cell three PCM HLLD solves plus its primitives, edge fields and
 # updates.
-FLOPS_PER_FACE = {1: 268.0, 2: 640.0, 3: 1067.0, 4: 359.0, 5: 746.1}
+FLOPS_PER_FACE = {1: 268.0, 2: 580.0, 3: 970.8, 4: 338.0, 5: 652.5}
 FLOPS_PER_PRED_CELL = 999.0
 # MI355X FP64 vector peak: 256 CUs x 4 SIMDs x 16 lanes x 2 (FMA) x 2.4 GHz.
 PEAK_FP64_TFLOPS = 78.6
@@ -41,15 +41,16 @@ STEP_MIN_BYTES_PER_CELL = 16 * F64
 # ghost cells for the ghost-layer primitive kernel):
 #   predictor  reads U^n (5 cell + 3 face fields), writes U^{n+1/2} (8) and
 #              the interior half-step primitives (8)
-#   prims      (ghost layers) reads 8 fields, writes 8 primitives
-#   ct_update  reads 5 cell + 3 face fields of U^n, 3 axes x 7 flux components
-#              and the upwind bytes, 6 primitives (v, B_cc for -v x B); writes
-#              5 + 3 fields (the CFL maxima of the new state cost no bytes)
+#   prims      (ghost layers) copies 8 primitives of the image
+#   flux_recon_hlld, flux_pcm_hlld  8 primitives + the normal field in, the 5
+#              conserved values of a cell in and out, two EMFs and the upwind
+#              byte out, per face (and cell)
+#   ct_update  reads 6 primitives (v, B_cc for -v x B), 3 axes x 2 EMFs and the
+#              upwind bytes, 3 base faces, and the 5 cell fields for the CFL
+#              maxima of the new state; writes 3 face fields
 #   dt         reads 5 cell + 3 face fields (vlct_cfl_dt and in-place steps)
-#   flux_recon_hlld  8 primitives + normal field in, 7 flux components + the
-#              upwind byte out, per face
-BYTES_PER_UNIT = {"predictor": 24 * F64, "prims": 16 * F64, "ct_update": 43 * F64 + 3,
-                  "dt": 8 * F64, "flux_recon_hlld": 16 * F64 + 1, "flux_pcm_hlld": 16 * F64 + 1}
+BYTES_PER_UNIT = {"predictor": 24 * F64, "prims": 16 * F64, "ct_update": 23 * F64 + 3,
+                  "dt": 8 * F64, "flux_recon_hlld": 21 * F64 + 1, "flux_pcm_hlld": 21 * F64 + 1}
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "hbm_counters_turbulence_plmc_256.json")
 VALU_FILE = os.path.join(ROOT, "profiles", "fp64_valu_turbulence_plmc_256.json")
 SOURCES = ("paper_2402_05240_amd/csrc/vlct.hip", "paper_2402_05240_amd/csrc/vlct_common.hpp",
@@ -441,15 +442,11 @@ def kernel_family(name):
     """Kernel family of a device kernel name as rocprofv3 prints it."""
     if "k_ad_" in name or "k_curl" in name or "k_pack_sides" in name:
         for key, fam in (("k_ad_march_fused", "adj_march_fused"),
-                         ("k_ad_row_fused", "adj_row_fused"),
-                         ("k_ad_faces", "adj_faces"), ("k_ad_recon", "adj_recon"),
+                         ("k_ad_row_fused", "adj_row_fused"), ("k_ad_pcm", "adj_pcm"),
+                         ("k_ad_faces", "adj_faces_recon"), ("k_ad_recon", "adj_recon"),
                          ("k_ad_prims", "adj_prims"), ("k_ad_edges", "adj_edges"),
                          ("k_pack_sides", "tape_sides"), ("k_curl", "curl")):
             if key in name:
-                if fam == "adj_faces":
-                    # k_ad_faces<D>: PCM stage; k_ad_faces_row / _march: reconstructing stage
-                    return "adj_faces_recon" if ("_row" in name or "_march" in name) \
-                        else "adj_faces_pcm"
                 return fam
         return "adj_other"
     if "k_pred" in name:
@@ -461,7 +458,7 @@ def kernel_family(name):
     if "k_dt_" in name:
         return "dt"
     if "k_flux" in name:
-        # template arguments <..., RECON>; RECON 1 is the PCM predictor
+        # template arguments <..., RECON>; RECON 1 is the PCM corrector
         targs = name[name.index("<") + 1:name.index(">")].replace(" ", "").split(",")
         return "flux_pcm_hlld" if targs[-1] == "1" else "flux_recon_hlld"
     if "copyBuffer" in name:

@@ -91,8 +91,8 @@ typedef struct vlct_state {
 
 /* Bytes of device workspace vlct_step / vlct_cfl_dt need for this grid
  * (0 if the descriptor is invalid).  The workspace holds the half-step state,
- * ghost-padded primitives and face fluxes; its contents are scratch between
- * calls. */
+ * ghost-padded primitives and the faces' electromotive forces; its contents
+ * are scratch between calls. */
 size_t vlct_workspace_bytes(const vlct_grid *g);
 
 /* CFL time step of state `s` (Sec. 2.2 Step 1, Eq. dt):

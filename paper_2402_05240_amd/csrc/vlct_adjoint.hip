@@ -14,12 +14,12 @@
 //   edges   : edge-field cotangents from the face cotangents (curl transposed)
 //   faces   : flux cotangents (flux differences transposed; B_t1/B_t2 fluxes
 //             gathered from the two edges that use each, with the upwind
-//             weights of the forward fluxes), then HLLD reversed (the y and
-//             z faces of a reconstructing stage by column marches that
-//             reconstruct each cell once)
+//             weights of the forward fluxes), then HLLD reversed (x by rows,
+//             y and z by column marches; each cell reconstructed once)
 //   recon   : PLMC/PLMP/PPMC/PPMP reversed per cell and axis (corrector only)
 //   prims   : reference fields -(v x B) gathered from the 12 edges around the
-//             cell and reversed, then primitive recovery reversed
+//             cell and reversed, then primitive recovery reversed (the
+//             predictor's in the march of its z faces)
 // The forward intermediates (primitives, fluxes with their upwind indicators,
 // the half-step state) are recomputed by the step's own kernels.  Periodic
 // boundaries: a ghost cell or ghost flux row holds exactly the values of its
@@ -1424,16 +1424,29 @@ static int adjoint_core(const vlct_grid *vg, const Geom &g, const AdLayout &L, c
 // and the transpose of that map.  A_x at (i, j-1/2, k-1/2), A_y at
 // (i-1/2, j, k-1/2), A_z at (i-1/2, j-1/2, k), each stored like a cell array.
 // ---------------------------------------------------------------------------
+// (64-bit indices: unlike the adjoint's, these arrays alone may hold 2^32 cells)
+__device__ __forceinline__ idx_t cell_of(const Geom &g, int i, int j, int k)
+{
+    return cell_store(g, wrapc(i, g.n[0]), wrapc(j, g.n[1]), wrapc(k, g.n[2]));
+}
+__device__ __forceinline__ void cell_coords(const Geom &g, idx_t t, int x[3])
+{
+    x[0] = (int)(t % g.n[0]);
+    x[1] = (int)((t / g.n[0]) % g.n[1]);
+    x[2] = (int)(t / ((idx_t)g.n[0] * g.n[1]));
+}
+
 __global__ void k_curl_potential(Geom g, const double *ax, const double *ay, const double *az,
                                  double *bx, double *by, double *bz)
 {
-    const u32 N = (u32)g.n[0] * (u32)g.n[1] * (u32)g.n[2];
-    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
+    const idx_t N = (idx_t)g.n[0] * g.n[1] * g.n[2];
+    const idx_t t = (idx_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= N) return;
     int x[3];
     cell_coords(g, t, x);
     const int i = x[0], j = x[1], k = x[2];
-    const u32 ip = t + step_hi<0>(g, x), jp = t + step_hi<1>(g, x), kp = t + step_hi<2>(g, x);
+    const idx_t ip = cell_of(g, i + 1, j, k), jp = cell_of(g, i, j + 1, k),
+                kp = cell_of(g, i, j, k + 1);
     const double vx = (az[jp] - az[t]) / g.dl[1] - (ay[kp] - ay[t]) / g.dl[2];
     const double vy = (ax[kp] - ax[t]) / g.dl[2] - (az[ip] - az[t]) / g.dl[0];
     const double vz = (ay[ip] - ay[t]) / g.dl[0] - (ax[jp] - ax[t]) / g.dl[1];
@@ -1449,8 +1462,8 @@ __global__ void k_curl_potential(Geom g, const double *ax, const double *ay, con
 __global__ void k_curl_potential_adjoint(Geom g, const double *lbx, const double *lby,
                                          const double *lbz, double *lax, double *lay, double *laz)
 {
-    const u32 N = (u32)g.n[0] * (u32)g.n[1] * (u32)g.n[2];
-    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
+    const idx_t N = (idx_t)g.n[0] * g.n[1] * g.n[2];
+    const idx_t t = (idx_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= N) return;
     int x[3];
     cell_coords(g, t, x);
@@ -1551,7 +1564,7 @@ int vlct_step_adjoint(const vlct_grid *vg, const vlct_state *in, const vlct_stat
             sides[h].s[d] = side[h][d];
         }
     // forward intermediates at U^n (the kernels of vlct_step); the cells that
-    // the corrector fluxes update go to an array that k_ad_init fills later
+    // the corrector fluxes update go to an array that nothing reads
     StateW unused;
     for (int f = 0; f < 8; ++f) {
         if (f < 5) unused.u[f] = arr(L.lnext[f]); else unused.b[f - 5] = arr(L.lnext[f]);
