@@ -773,7 +773,7 @@ __device__ __forceinline__ void ct_body(const Geom &g, const Prims &P, const Flu
 // barriers.  Against the form that kept every EMF and reference of two planes
 // in LDS, dealt the edges out by division and loaded U^n twice per plane
 // (2321 vector instructions, 116 LDS accesses; now 1801 and 81): 256^3 2.04 ->
-// 1.54 ms, 128^3 0.284 -> 0.225 ms, 32^3 52 -> 45 us (17 with tiles of 256
+// 1.54 ms, 128^3 0.284 -> 0.225 ms, 32^3 52 -> 45 us (19 with tiles of 256
 // threads and one plane).
 // ---------------------------------------------------------------------------
 constexpr int kPredThreads = 512;

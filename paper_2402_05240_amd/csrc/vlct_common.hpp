@@ -324,9 +324,9 @@ inline Geom make_geom(const vlct_grid *vg, const Slots &slots = Slots())
     const int nz = g.n[2];
     // corrector marches: 16 cells per segment where that is four blocks per CU
     // or more (256^3: 0.73 ms per axis, 0.75 with 8); below, the m up to 32 that
-    // minimises rounds of blocks x (m + 1) Riemann solves in a row (both axes,
-    // against 8: 32^3 16 -> with m = 1 ... 125 -> 98 us a step, 512 x 16 x 16
-    // 180 -> 142, 64^3 142 -> 131, 128^3 608 -> 590)
+    // minimises rounds of blocks x (m + 1) Riemann solves in a row (against 8
+    // everywhere: 32^3 step 125 -> 98 us with 1, 512 x 16 x 16 PPMC 180 -> 142
+    // with 3, 64^3 142 -> 131 with 5, 128^3 608 -> 590 with 19)
     for (int d = 1; d <= 2; ++d) {
         const long long cols = ((long long)(g.n[0] + 2) * (g.n[3 - d] + 2) + kBlock - 1) / kBlock;
         auto blocks = [&](int m) { return cols * ((g.n[d] + m - 1) / m); };
@@ -345,8 +345,9 @@ inline Geom make_geom(const vlct_grid *vg, const Slots &slots = Slots())
     // fused predictor, one block per CU at a time: the 32 x 13 tile with the
     // planes (a power of two) of least cost where no choice fills at most six
     // rounds, else the cheapest choice.  A plane takes a lone block of 512
-    // threads 7.0 us and one of 256 threads 4.6 (32^3: 6 planes in 3 blocks 45
-    // us, 3 in 28 smaller ones 17; 100 x 75 x 50: 47 -> 37 us)
+    // threads 7.0 us and one of 256 threads 4.6 (32^3: 4 planes of the 32 x 13
+    // tile 45 us, 1 plane of a smaller one 19; 64^3 step 142 -> 135 us with 3
+    // planes for 4, 80^3 220 -> 202 with 20 x 20 tiles of 5)
     g.pr_tx = kPredTx;
     g.pr_ty = kPredTy;
     double best = -1.0;
@@ -368,8 +369,9 @@ inline Geom make_geom(const vlct_grid *vg, const Slots &slots = Slots())
     }
     // CT update: 8 to 32 planes of the 32 x 13 tile where that is four blocks
     // per CU or more; below, the cheapest choice, a lone block taking 1.65 us a
-    // plane and a round of several per CU 1.4 (32^3 21 -> 9 us, 96^3 60 -> 40,
-    // 100 x 75 x 50 33 -> 23)
+    // plane and a round of several per CU 1.4 (32^3 21 -> 10 us; 96^3 PPMC step
+    // 402 -> 382 us with 5 planes for 8, 100 x 75 x 50 154 -> 145 with 20 x 20
+    // tiles of 2)
     g.ct_tx = kPredTx;
     g.ct_ty = kPredTy;
     const long long cols = ct_tiles(g);
