@@ -1612,9 +1612,16 @@ static void batch_records(int count, const vlct_grid *grids, const vlct_state *i
     for (int s = 0; s < kSlots; ++s) total[s] = 0;
     double cells = 0.0;
     for (int i = 0; i < count; ++i) cells += (double)grids[i].nx * grids[i].ny * grids[i].nz;
+    std::unordered_map<uint64_t, Geom> chosen;
     for (int i = 0; i < count; ++i) {
-        Geom g = make_geom(&grids[i], batch_slots(&grids[i], cells));
-        const Layout L = layout(g);  // of the unplanned geometry, as the size query counts it
+        Geom g = grid_geom(&grids[i]);
+        // instances of the same size and boundaries share one choice
+        uint64_t key = 0;
+        for (int d = 0; d < 3; ++d) key = key << 14 | (uint64_t)g.n[d] << 1 | (uint64_t)g.bc[d];
+        const auto [it, first] = chosen.try_emplace(key, g);
+        if (first) choose_tiles(it->second, batch_slots(&grids[i], cells));
+        copy_tiles(g, it->second);
+        const Layout L = layout(g);
         plan_tiles(g, plan ? plan[i] : 0);
         const Bound B = bind(L, static_cast<char *>(ws) + off);
         off += L.total;
@@ -1741,14 +1748,14 @@ extern "C" {
 size_t vlct_workspace_bytes(const vlct_grid *g)
 {
     if (!grid_ok(g)) return 0;
-    return layout(make_geom(g)).total;
+    return layout(grid_geom(g)).total;
 }
 
 int vlct_cfl_dt(const vlct_grid *vg, const vlct_state *s, double *dt_dev, void *ws,
                 size_t ws_bytes, void *stream)
 {
     if (!grid_ok(vg) || !state_ok(s) || !dt_dev) return VLCT_EINVAL;
-    const Geom g = make_geom(vg);
+    const Geom g = grid_geom(vg);
     const Layout L = layout(g);
     if (!ws || ws_bytes < L.total) return VLCT_EWORKSPACE;
     const Bound B = bind(L, ws);
@@ -1780,7 +1787,7 @@ int vlct_step_noalloc(const vlct_grid *vg, const vlct_state *in, const vlct_stat
                       void *stream)
 {
     if (!grid_ok(vg) || !state_ok(in) || !state_ok(out) || !dt_dev) return VLCT_EINVAL;
-    if (layout(make_geom(vg)).total > kScratchBytes) return VLCT_ESCRATCH;
+    if (layout(grid_geom(vg)).total > kScratchBytes) return VLCT_ESCRATCH;
     void *ws = nullptr;
     const int rc = scratch_address(&ws);
     if (rc) return rc;
@@ -1861,7 +1868,7 @@ size_t vlct_batch_workspace_bytes(const vlct_grid *grids, int count)
     size_t tot = batch_table_bytes(count);
     for (int i = 0; i < count; ++i) {
         if (!grid_ok(&grids[i])) return 0;
-        tot += layout(make_geom(&grids[i])).total;
+        tot += layout(grid_geom(&grids[i])).total;
     }
     return tot;
 }

@@ -598,7 +598,8 @@ __host__ __device__ __forceinline__ idx_t ad_march_blocks(const Geom &g, int D, 
 // reconstructions 166 -> 104; 128^3, 32 and 16 are the same)
 static int ad_march_segment(const Geom &g, int D, int slots)
 {
-    const int o = tile_override("admarch");
+    const char *env = std::getenv("VLCT_TILES");
+    const int o = env ? tile_override(env, "admarch") : 0;
     if (o >= 1 && o <= 64) return o;
     idx_t best = 0;
     int len = 1;
@@ -1504,7 +1505,7 @@ int vlct_curl_potential(const vlct_grid *vg, const double *ax, const double *ay,
 {
     if (!grid_ok(vg) || !ax || !ay || !az || !bx || !by || !bz) return VLCT_EINVAL;
     if (!periodic_grid(vg)) return VLCT_EUNSUPPORTED;
-    const Geom g = make_geom(vg);
+    const Geom g = grid_geom(vg);
     const size_t N = (size_t)g.n[0] * g.n[1] * g.n[2];
     k_curl_potential<<<nblocks(N), kBlock, 0, static_cast<hipStream_t>(stream)>>>(g, ax, ay, az,
                                                                                  bx, by, bz);
@@ -1517,7 +1518,7 @@ int vlct_curl_potential_adjoint(const vlct_grid *vg, const double *lbx, const do
 {
     if (!grid_ok(vg) || !lbx || !lby || !lbz || !lax || !lay || !laz) return VLCT_EINVAL;
     if (!periodic_grid(vg)) return VLCT_EUNSUPPORTED;
-    const Geom g = make_geom(vg);
+    const Geom g = grid_geom(vg);
     const size_t N = (size_t)g.n[0] * g.n[1] * g.n[2];
     k_curl_potential_adjoint<<<nblocks(N), kBlock, 0, static_cast<hipStream_t>(stream)>>>(
         g, lbx, lby, lbz, lax, lay, laz);
@@ -1527,13 +1528,13 @@ int vlct_curl_potential_adjoint(const vlct_grid *vg, const double *lbx, const do
 size_t vlct_adjoint_workspace_bytes(const vlct_grid *g)
 {
     if (!grid_ok(g)) return 0;
-    return ad_layout(make_geom(g), false).total;
+    return ad_layout(grid_geom(g), false).total;
 }
 
 size_t vlct_adjoint_taped_workspace_bytes(const vlct_grid *g)
 {
     if (!grid_ok(g)) return 0;
-    return ad_layout(make_geom(g), true).total;
+    return ad_layout(grid_geom(g), true).total;
 }
 
 int vlct_step_adjoint(const vlct_grid *vg, const vlct_state *in, const vlct_state *lam_out,
@@ -1585,7 +1586,7 @@ int vlct_step_adjoint_taped(const vlct_grid *vg, const vlct_state *in, const vlc
 {
     int rc = adjoint_args(vg, in, lam_out, lam_in, dt_dev);
     if (rc) return rc;
-    const Geom g = make_geom(vg);
+    const Geom g = grid_geom(vg);
     const AdLayout L = ad_layout(g, true);
     const TapeLayout T = tape_layout(g.n);
     if (!ws || ws_bytes < L.total || !tape || tape_bytes < T.total) return VLCT_EWORKSPACE;

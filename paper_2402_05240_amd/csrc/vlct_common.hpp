@@ -209,11 +209,9 @@ inline bool grid_ok(const vlct_grid *g)
 // size-dependent choices.  Every choice computes the
 // same per-cell and per-face arithmetic; the forward results are bitwise the
 // same, the adjoint's equal to the summation order of its accumulations.
-// Returns 0 when `key` is not set.
-inline int tile_override(const char *key)
+// Returns the value of `key` in that string, 0 when it is not set.
+inline int tile_override(const char *env, const char *key)
 {
-    const char *env = std::getenv("VLCT_TILES");
-    if (!env || !*env) return 0;
     const size_t kl = std::strlen(key);
     for (const char *p = env; *p;) {
         if (std::strncmp(p, key, kl) == 0 && p[kl] == '=') return std::atoi(p + kl + 1);
@@ -303,9 +301,13 @@ struct Slots {
     int march = kNumCUs, pred = kNumCUs, ct = kNumCUs;
 };
 
-inline Geom make_geom(const vlct_grid *vg, const Slots &slots = Slots())
+// the grid alone: what sizes, layouts and the kernels without tiles need.  The
+// tiles are for choose_tiles, whose search takes the host 1 to 4 us a grid: a
+// batched step makes it once per size and boundary (2048 runs of one cell,
+// bound by the host: 4.01 ms with two searches per run, 1.93 so).
+inline Geom grid_geom(const vlct_grid *vg)
 {
-    Geom g;
+    Geom g{};
     g.n[0] = vg->nx;
     g.n[1] = vg->ny;
     g.n[2] = vg->nz;
@@ -320,6 +322,11 @@ inline Geom make_geom(const vlct_grid *vg, const Slots &slots = Slots())
     g.gamma = vg->gamma;
     g.gm1i = 1.0 / (vg->gamma - 1.0);
     g.cfl = vg->cfl;
+    return g;
+}
+
+inline void choose_tiles(Geom &g, const Slots &slots)
+{
     const int ex = g.n[0] + (g.bc[0] == VLCT_BC_OUTFLOW), ey = g.n[1] + (g.bc[1] == VLCT_BC_OUTFLOW);
     const int nz = g.n[2];
     // corrector marches: 16 cells per segment where that is four blocks per CU
@@ -388,8 +395,10 @@ inline Geom make_geom(const vlct_grid *vg, const Slots &slots = Slots())
             g.ct_planes = ct.planes;
         }
     }
-    auto forced = [](const char *key, int &v, int lo, int hi) {
-        const int o = tile_override(key);
+    const char *env = std::getenv("VLCT_TILES");
+    if (!env || !*env) return;
+    auto forced = [env](const char *key, int &v, int lo, int hi) {
+        const int o = tile_override(env, key);
         if (o >= lo && o <= hi) v = o;
     };
     forced("ct", g.ct_planes, 1, kMaxN);
@@ -408,6 +417,25 @@ inline Geom make_geom(const vlct_grid *vg, const Slots &slots = Slots())
         g.pr_tx = prx;
         g.pr_ty = kTileThreads / (prx + 2) - 2;
     }
+}
+
+// the tiles chosen for a grid of the same size and boundaries
+inline void copy_tiles(Geom &g, const Geom &from)
+{
+    g.march[1] = from.march[1];
+    g.march[2] = from.march[2];
+    g.pr_tx = from.pr_tx;
+    g.pr_ty = from.pr_ty;
+    g.pred_slab = from.pred_slab;
+    g.ct_tx = from.ct_tx;
+    g.ct_ty = from.ct_ty;
+    g.ct_planes = from.ct_planes;
+}
+
+inline Geom make_geom(const vlct_grid *vg)
+{
+    Geom g = grid_geom(vg);
+    choose_tiles(g, Slots());
     return g;
 }
 
