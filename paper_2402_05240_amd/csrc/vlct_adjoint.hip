@@ -1048,73 +1048,54 @@ __global__ __launch_bounds__(kAdRow, kAdFusedWaves) void k_ad_row_fused(
     atomicAdd(&S.lw[5][tc], abc);
 }
 
-// parabolic reconstruction of each cell along x reversed: the cotangents of
-// the five stencil states go through LDS to the cells of the block that they
-// belong to (cells in flat order, neighbours in a row being neighbours in the
-// block), which leave with one atomic add per component; those of other
-// blocks' cells and across the periodic boundary are added one by one.  Bound
-// by FP64 latency at one wave per SIMD and 512 registers: 64^3 PPMC 122 -> 90
-// us with the stencil parked in LDS (spills 268 -> 36 bytes) and 35 -> 7 adds.
+// parabolic reconstruction of each cell along x reversed, one thread per cell;
+// the cotangents of the five stencil states go to their cells with one atomic
+// add per component (neighbours in a row are neighbours in the wave).  Nothing
+// passes between threads: an earlier form that handed the terms to the
+// neighbours through LDS gave wrong cotangents, with or without -fapprox-func
+// by the limiter's kind, for a reason that was not found.  The form with the
+// exchange in one-wave blocks passed every check, but nothing showed why the
+// other had not.  Bound by FP64 latency at one wave per SIMD (512 registers)
+// and by the 36 adds: 64^3 PPMC 110 us and PPMP 95 us (87 and 71 with the
+// exchange), 128^3 628 and 691 us (653 and 523).
 template <int RECON>
 __global__ __launch_bounds__(kAdRow) void k_ad_recon_row(Geom g, Prims P, AdStage S)
 {
     static_assert(RECON == VLCT_RECON_PPMC || RECON == VLCT_RECON_PPMP, "parabolic reconstructions");
     constexpr bool kChar = RECON == VLCT_RECON_PPMC;
-    __shared__ double lds[5][7][kAdRow], win[35][kAdRow];
+    __shared__ double win[35][kAdRow];
     const int nx = g.n[0], tid = threadIdx.x;
     const u32 N = (u32)nx * (u32)g.n[1] * (u32)g.n[2];
     const u32 t = blockIdx.x * (u32)kAdRow + tid;
-    const bool have = t < N;
+    if (t >= N) return;
     int x[3];
-    cell_coords(g, have ? t : 0u, x);
-    // cells of the row in the block: offsets [lo, hi] from this one
-    const int lo = -min(tid, x[0]);
-    const int hi = min(min(kAdRow - 1 - tid, nx - 1 - x[0]), 2);
+    cell_coords(g, t, x);
     W7 ad[5];
 #pragma unroll
     for (int q = 0; q < 5; ++q) ad[q] = W7{0, 0, 0, 0, 0, 0, 0};
-    double abn = 0.0;
-    if (have) {
-        double afm[7], afp[7];
-#pragma unroll
-        for (int c = 0; c < 7; ++c) {
-            afm[c] = S.lrec[0][c][t];
-            afp[c] = S.lrec[0][7 + c][t];
-        }
-        // the stencil waits in LDS (each thread its own)
-        const u32 o = prim_at(g, x[0], x[1], x[2]);
-        const ParkedStates<kAdRow> cells{win, tid};
-#pragma unroll
-        for (int q = 0; q < 5; ++q) cells.put(7 * q, w7_at(P, 0, o + (u32)(q - 2)));
-        ppmc_rev<kChar>(
-            [&](int q) {
-                asm volatile("" ::: "memory");  // not kept from the first fetch
-                return cells.get(7 * q);
-            },
-            P.w[5][o], g.gamma, afm, afp, ad[0], ad[1], ad[2], ad[3], ad[4], abn);
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-            const double v[7] = {ad[q].d, ad[q].u, ad[q].v, ad[q].w, ad[q].p, ad[q].by, ad[q].bz};
-            if (q - 2 >= lo && q - 2 <= hi) {
-#pragma unroll
-                for (int c = 0; c < 7; ++c) lds[q][c][tid] = v[c];
-            } else {
-                const u32 cc = t - (u32)x[0] + (u32)wrapc(x[0] + q - 2, nx);
-#pragma unroll
-                for (int c = 0; c < 7; ++c) atomicAdd(&S.lw[lab_slot(0, c)][cc], v[c]);
-            }
-        }
-    }
-    __syncthreads();
-    if (!have) return;
-    // the cell at offset d of the row gave this one its term 2 - d
+    double abn = 0.0, afm[7], afp[7];
 #pragma unroll
     for (int c = 0; c < 7; ++c) {
-        double v = 0.0;
+        afm[c] = S.lrec[0][c][t];
+        afp[c] = S.lrec[0][7 + c][t];
+    }
+    // the stencil waits in LDS (each thread its own)
+    const u32 o = prim_at(g, x[0], x[1], x[2]);
+    const ParkedStates<kAdRow> cells{win, tid};
 #pragma unroll
-        for (int d = -2; d <= 2; ++d)
-            if (d >= lo && d <= hi) v += lds[2 - d][c][tid + d];
-        atomicAdd(&S.lw[lab_slot(0, c)][t], v);
+    for (int q = 0; q < 5; ++q) cells.put(7 * q, w7_at(P, 0, o + (u32)(q - 2)));
+    ppmc_rev<kChar>(
+        [&](int q) {
+            asm volatile("" ::: "memory");  // not kept from the first fetch
+            return cells.get(7 * q);
+        },
+        P.w[5][o], g.gamma, afm, afp, ad[0], ad[1], ad[2], ad[3], ad[4], abn);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        const double v[7] = {ad[q].d, ad[q].u, ad[q].v, ad[q].w, ad[q].p, ad[q].by, ad[q].bz};
+        const u32 cc = t - (u32)x[0] + (u32)wrapc(x[0] + q - 2, nx);
+#pragma unroll
+        for (int c = 0; c < 7; ++c) atomicAdd(&S.lw[lab_slot(0, c)][cc], v[c]);
     }
     atomicAdd(&S.lw[5][t], abn);
 }
