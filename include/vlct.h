@@ -192,16 +192,18 @@ int vlct_step_batch_until(int count, const vlct_grid *grids, const vlct_state *s
                           double *t_dev, const double *t_end_dev, const uint8_t *plan, void *ws,
                           size_t ws_bytes, void *stream);
 
-/* Autotuner for a batch: writes into plan[count] (host) the tiles that make
- * the batched step fastest, found by timing it on this batch: instances are
+/* Autotuner for a batch: writes into plan[count] (host) tiles that make the
+ * batched step faster, found by timing it on this batch: instances are
  * grouped by nx (<= 24, <= 48, <= 96, larger) and each group's CT tile, then
  * its march segment, is changed while the rest of the batch keeps its current
- * choice, keeping a change that makes the whole step at least 1% faster.
- * Each trial times `reps` (1..100) batched steps after one untimed step.  The
- * trial steps read `in` and overwrite `out` (every instance must be out of
- * place, else VLCT_EINVAL; next dt and status are not written).  Unlike the
- * step calls, this call synchronises with the host (it creates and destroys
- * two HIP events) and must not be captured into a graph. */
+ * choice, keeping a change that makes the whole step at least 1% faster in
+ * every one of five timings taken in turn with the choice it replaces.  The
+ * plan found is kept only if it beats the untuned step in the same way; else
+ * every byte is 0.  Each timing takes `reps` (1..100) batched steps after one
+ * untimed step.  The trial steps read `in` and overwrite `out` (every instance
+ * must be out of place, else VLCT_EINVAL; next dt and status are not written).
+ * Unlike the step calls, this call synchronises with the host (it creates and
+ * destroys two HIP events) and must not be captured into a graph. */
 int vlct_batch_tune(int count, const vlct_grid *grids, const vlct_state *in,
                     const vlct_state *out, const double *dt_dev, void *ws, size_t ws_bytes,
                     void *stream, int reps, uint8_t *plan);

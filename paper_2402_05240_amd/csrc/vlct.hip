@@ -21,6 +21,7 @@
 #include <unordered_map>
 #include <vector>
 
+#include "batch_tune.hpp"
 #include "vlct_common.hpp"
 #include "mhd_physics.hpp"
 
@@ -2034,48 +2035,14 @@ int vlct_batch_tune(int count, const vlct_grid *grids, const vlct_state *in,
         ms /= (float)reps;
         return VLCT_OK;
     };
-    // size classes by the x extent (the CT tile's long side): <= 24, <= 48, <= 96, larger;
-    // each class's CT tile, then its march segment, is changed while the rest
-    // of the batch keeps its current choice, and kept if the whole batched step
-    // gets at least 1% faster
-    std::vector<int> cls(count);
-    for (int i = 0; i < count; ++i) {
-        const int nx = grids[i].nx;
-        cls[i] = nx <= 24 ? 0 : (nx <= 48 ? 1 : (nx <= 96 ? 2 : 3));
-    }
-    std::vector<uint8_t> cur(count, 0);
-    float best = 0.0f;
-    int rc = time_plan(cur, best);
-    for (int c = 0; c < 4 && !rc; ++c) {
-        bool present = false;
-        for (int i = 0; i < count; ++i) present |= cls[i] == c;
-        if (!present) continue;
-        for (int field = 0; field < 2 && !rc; ++field) {
-            const int nv = field == 0 ? kCtVariants : kMarchVariants;
-            for (int v = 0; v < nv && !rc; ++v) {
-                std::vector<uint8_t> trial = cur;
-                bool changed = false;
-                for (int i = 0; i < count; ++i) {
-                    if (cls[i] != c) continue;
-                    const uint8_t b = field == 0 ? (uint8_t)((trial[i] & 0xF0) | v)
-                                                 : (uint8_t)((trial[i] & 0x0F) | (v << 4));
-                    changed |= b != trial[i];
-                    trial[i] = b;
-                }
-                if (!changed) continue;
-                float ms = 0.0f;
-                rc = time_plan(trial, ms);
-                if (!rc && ms < 0.99f * best) {
-                    best = ms;
-                    cur = trial;
-                }
-            }
-        }
-    }
+    std::vector<int> nx(count);
+    for (int i = 0; i < count; ++i) nx[i] = grids[i].nx;
+    std::vector<uint8_t> best;
+    const int rc = tune_plan(nx, kCtVariants, kMarchVariants, time_plan, best);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
-    for (int i = 0; i < count; ++i) plan[i] = cur[i];
+    std::copy(best.begin(), best.end(), plan);
     return VLCT_OK;
 }
 
