@@ -163,11 +163,13 @@ int vlct_step_batch(int count, const vlct_grid *grids, const vlct_state *in,
 
 /* Per-instance tile plan: vlct_step_batch with plan[i] (HOST array of `count`
  * bytes, NULL = all zero) choosing instance i's tiles: low nibble the columns
- * of a CT block, its one-cell ring included (0: vlct_step's own choice,
- * 1: 32 x 16, 2: 16 x 32), high nibble the corrector march segment along y and
- * z (0: 16 cells, 1: 32, 2: 8).  Every plan gives the same results bit for bit
- * (the tiles only regroup the same per-cell and per-face arithmetic);
- * VLCT_EINVAL for an unknown variant. */
+ * of a CT block, its one-cell ring included (1: 32 x 16, 2: 16 x 32), high
+ * nibble the corrector march segment along y and z (1: 32 cells, 2: 8).  0 in
+ * either nibble is the size-dependent choice for the instance's share, by
+ * cells, of the chip (vlct_step chooses for the whole chip).  A segment whose
+ * addresses would not fit 32 bits stays at that choice.  Every plan gives the
+ * same results bit for bit (the tiles only regroup the same per-cell and
+ * per-face arithmetic); VLCT_EINVAL for an unknown variant. */
 int vlct_step_batch_plan(int count, const vlct_grid *grids, const vlct_state *in,
                          const vlct_state *out, const double *dt_dev, double *next_dt_dev,
                          uint32_t *status_dev, const uint8_t *plan, void *ws, size_t ws_bytes,

@@ -33,9 +33,10 @@ namespace vlct {
 constexpr int kRowCells = kBlock - 2;  // cells a block of the x kernel updates
 
 // tile variants a batched step can give each instance (its plan byte: CT tile
-// in the low nibble, march segment in the high nibble); variant 0 of the tile
-// is the single-instance choice, the others fix the block's columns (ring
-// included) at 32 x 16 and 16 x 32
+// in the low nibble, march segment in the high nibble); variant 0 is the
+// size-dependent choice for the instance's share of the chip, the others fix
+// the block's columns (ring included) at 32 x 16 and 16 x 32, the segment at 32
+// and 8 cells
 constexpr int kCtVariants = 3;
 constexpr int kMarchVariants = 3;  // march segments: automatic, 32 and 8 cells
 constexpr int kCtThreads = 512;
