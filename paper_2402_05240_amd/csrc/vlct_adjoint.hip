@@ -581,7 +581,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_ad_pcm_march(Geom g, Prims P, Sta
     }
 }
 
-// faces of axis D = y or z with a reconstructing corrector, one thread per
+// faces of axis D = y or z with a parabolic corrector, one thread per
 // column (i, j or k) and segment of M cells along D: each cell is
 // reconstructed once and its high-face state carried to the next face.  Per
 // face the same work as k_ad_faces_row.
@@ -620,10 +620,10 @@ __global__ __launch_bounds__(kBlock) void k_ad_faces_march(Geom g, Prims P, Stat
                                                            double factor, int M)
 {
     static_assert(D == 1 || D == 2, "columns march along y or z");
+    static_assert(RECON == VLCT_RECON_PPMC || RECON == VLCT_RECON_PPMP, "parabolic reconstructions");
     constexpr int T = D == 1 ? 2 : 1;
-    constexpr bool kPpm = RECON == VLCT_RECON_PPMC || RECON == VLCT_RECON_PPMP;
-    constexpr bool kChar = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PPMC;
-    constexpr int R = kPpm ? 2 : 1;
+    constexpr bool kChar = RECON == VLCT_RECON_PPMC;
+    constexpr int R = 2;
     const int nD = g.n[D];
     const u32 cols = (u32)g.n[0] * (u32)g.n[T];
     const u32 ncb = (cols + kBlock - 1) / kBlock;
@@ -653,10 +653,7 @@ __global__ __launch_bounds__(kBlock) void k_ad_faces_march(Geom g, Prims P, Stat
     uint32_t fprev = 0;
     for (int a = s0 - 1; a < s1; ++a) {
         W7 fm, fp;
-        if constexpr (kPpm)
-            ppmc<kChar>(win[0], win[1], win[2], win[3], win[4], bnc[2], g.gamma, fm, fp);
-        else
-            plmc<kChar>(win[0], win[1], win[2], bnc[1], g.gamma, fm, fp);
+        ppmc<kChar>(win[0], win[1], win[2], win[3], win[4], bnc[2], g.gamma, fm, fp);
         const uint32_t flo = floor_state(fm), fhi = floor_state(fp);
         if (a >= s0) {
             // the face a - 1/2 between the carried high state and this low state
@@ -703,7 +700,7 @@ __global__ __launch_bounds__(kBlock) void k_ad_faces_march(Geom g, Prims P, Stat
 // 398 -> 366 us; 369 with 128 threads)
 constexpr int kAdRow = 64;
 
-// faces of axis x with a reconstructing corrector: items (row, cell) with
+// faces of axis x with a parabolic corrector: items (row, cell) with
 // cells -1 .. nx-1 of every row in one flat sequence; a block reconstructs
 // kAdRow consecutive items once each, hands the high-face states to the right
 // neighbour through LDS, and each item with a left neighbour in its block and
@@ -721,8 +718,8 @@ __global__ __launch_bounds__(kAdRow, 2) void k_ad_faces_row(Geom g, Prims P, Sta
                                                          StateP lout, AdStage S, StateW lacc,
                                                          const double *dt_dev, double factor)
 {
-    constexpr bool kPpm = RECON == VLCT_RECON_PPMC || RECON == VLCT_RECON_PPMP;
-    constexpr bool kChar = RECON == VLCT_RECON_PLMC || RECON == VLCT_RECON_PPMC;
+    static_assert(RECON == VLCT_RECON_PPMC || RECON == VLCT_RECON_PPMP, "parabolic reconstructions");
+    constexpr bool kChar = RECON == VLCT_RECON_PPMC;
     __shared__ double lds[7][kAdRow];
     __shared__ uint32_t lfl[kAdRow];
     const int nx = g.n[0];
@@ -738,12 +735,8 @@ __global__ __launch_bounds__(kAdRow, 2) void k_ad_faces_row(Geom g, Prims P, Sta
         const u32 po = prim_at(g, x[0], x[1], x[2]);
         auto at = [&](int off) { return po + (u32)off; };
         const double bn = P.w[5][at(0)];
-        if constexpr (kPpm)
-            ppmc<kChar>(w7_at(P, 0, at(-2)), w7_at(P, 0, at(-1)), w7_at(P, 0, at(0)),
-                        w7_at(P, 0, at(1)), w7_at(P, 0, at(2)), bn, g.gamma, fm, fp);
-        else
-            plmc<kChar>(w7_at(P, 0, at(-1)), w7_at(P, 0, at(0)), w7_at(P, 0, at(1)), bn,
-                        g.gamma, fm, fp);
+        ppmc<kChar>(w7_at(P, 0, at(-2)), w7_at(P, 0, at(-1)), w7_at(P, 0, at(0)),
+                    w7_at(P, 0, at(1)), w7_at(P, 0, at(2)), bn, g.gamma, fm, fp);
         flo = floor_state(fm);
         fhi = floor_state(fp);
     }
