@@ -37,8 +37,9 @@ __device__ __forceinline__ idx_t xcd_block(idx_t n)
 // address elements by 32-bit byte offsets from it: the load and store
 // instructions take a scalar base plus a 32-bit vector offset, so an element
 // costs one 32-bit add at most instead of a 64-bit index product and sum.
-// Offsets stay below 4 GiB: the largest box is a z march of 22 padded planes
-// of at most 4102^2 doubles, 3.0 GB.
+// Offsets stay below 4 GiB: the largest box is a z march's, its cells and six
+// more padded planes of at most 4102^2 doubles; 16 cells always fit (3.0 GB),
+// longer marches where march_fits says so.
 // Accesses go through the global address space explicitly: pointers that a
 // batched kernel reads from its instance table would otherwise be generic and
 // take flat instructions, which have no scalar base.
@@ -205,7 +206,7 @@ inline bool grid_ok(const vlct_grid *g)
 // read at every call, holds comma-separated key=value pairs (ct=N and pred=N or
 // predslab=N planes per CT and predictor block, cttile=NX and predtile=NX columns
 // along x of their tiles, march=N cells per corrector march segment, 1 to 32,
-// admarch=8|16 cells per adjoint march segment) that replace the
+// admarch=N cells per adjoint march segment, 1 to 64) that replace the
 // size-dependent choices.  Every choice computes the
 // same per-cell and per-face arithmetic; the forward results are bitwise the
 // same, the adjoint's equal to the summation order of its accumulations.
@@ -289,7 +290,8 @@ inline TileChoice choose_tile(int ex, int ey, int nz, int slots, Unit unit)
     return best;
 }
 
-// a march of m cells keeps its byte offsets (padded planes) below 2^32
+// a march of m cells, with the stencil beyond either end, keeps its byte offsets
+// (padded planes) below 2^32
 inline bool march_fits(const Geom &g, int m)
 {
     return (idx_t)g.p[0] * g.p[1] * 8 * (m + 6) < (idx_t)1 << 32;
