@@ -8,7 +8,7 @@
 // with (n, t1, t2) the cyclic permutation (x,y,z), (y,z,x), (z,x,y) of the
 // axes (Table emf and its note); the normal field B_n is a parameter.
 #pragma once
-#ifndef VLCT_HOST_COUNT
+#if !defined(VLCT_HOST_COUNT) && !defined(VLCT_HOST_ESTIMATES)
 #include <hip/hip_runtime.h>
 #define VLCT_DEV __device__ __forceinline__
 #else
@@ -18,6 +18,13 @@
 namespace vlct {
 
 #ifndef VLCT_HOST_COUNT
+#ifdef VLCT_HOST_ESTIMATES  // a host test of the chains supplies its own
+double rsq_estimate(double x);
+double rcp_estimate(double x);
+#else
+VLCT_DEV double rsq_estimate(double x) { return __builtin_amdgcn_rsq(x); }
+VLCT_DEV double rcp_estimate(double x) { return __builtin_amdgcn_rcp(x); }
+#endif
 // Roots and quotients from the hardware estimates (v_rsq_f64, v_rcp_f64, about
 // 23 correct bits), refined by the shortest chain that keeps the rounding of
 // the longer ones it replaced: over 2^20 random arguments msqrt, mrcp and mdiv
@@ -31,11 +38,11 @@ namespace vlct {
 
 // square root, x >= 0: one Goldschmidt step (46 bits), then one correction
 // with the residual, whose factor needs only the estimate's bits.  The
-// estimate is taken of max(x, 1e-300), which maps zero to zero without a
-// select (rsq(0) is infinite).
+// estimate is taken of at least the smallest normal number, which maps zero to
+// zero without a select (rsq(0) is infinite).
 VLCT_DEV double msqrt(double x)
 {
-    const double y = __builtin_amdgcn_rsq(fmax(x, 1.0e-300));
+    const double y = rsq_estimate(fmax(x, 0x1p-1022));
     double g = x * y;
     const double h = 0.5 * y;
     g = fma(g, fma(-g, h, 0.5), g);
@@ -46,14 +53,14 @@ VLCT_DEV double msqrt(double x)
 // both the root and its reciprocal are needed.
 VLCT_DEV double mrsqrt(double x)
 {
-    const double y = __builtin_amdgcn_rsq(x);
+    const double y = rsq_estimate(x);
     const double e = fma(-x * y, y, 1.0);
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 // reciprocal: the third-order step y (1 + e + e^2), e = 1 - x y
 VLCT_DEV double mrcp(double x)
 {
-    const double y = __builtin_amdgcn_rcp(x);
+    const double y = rcp_estimate(x);
     const double e = fma(-x, y, 1.0);
     return fma(y, fma(e, e, e), y);
 }
@@ -61,7 +68,7 @@ VLCT_DEV double mrcp(double x)
 // corrected with its residual
 VLCT_DEV double mdiv(double a, double b)
 {
-    double y = __builtin_amdgcn_rcp(b);
+    double y = rcp_estimate(b);
     y = fma(fma(-b, y, 1.0), y, y);
     const double q = a * y;
     return fma(fma(-b, q, a), y, q);
