@@ -1,11 +1,16 @@
 // mhd_adjoint.hpp -- reverse derivatives of the per-state physics of
 // mhd_physics.hpp (Caddy & Schneider, "Cholla-MHD", Sec. 2.2 Steps 3 and 6):
 // HLLD, the characteristic eigen-system with its projections, and the PLMC /
-// PLMP reconstructions.  Each function re-evaluates its forward formulas in
-// FP64 (same operations, so the same branches), then applies the chain rule in
-// reverse order.  Every branch of the forward evaluation (wave-speed min/max,
-// HLLD fan region and degeneracy fallback, noise snapping, limiter choice,
-// clamps) is held fixed: the result is the derivative of the branch taken.
+// PLMP / PPMC / PPMP reconstructions.  Each function re-evaluates its forward
+// formulas in FP64, then applies the chain rule in reverse order.  Every branch
+// of the forward evaluation (wave-speed min/max, HLLD fan region and degeneracy
+// fallback, noise snapping, limiter choice, clamps) is held fixed: the result is
+// the derivative of the branch taken.  The branch is found again from the same
+// quantities, not by the same instructions: contraction and, in PPM, the form of
+// the limiter differ (ppmc factors the common sign out of its minmod, ppmc_rev
+// tests the signs and keeps which candidate won), so a decision that hangs on the
+// last bit, or on products of second differences that underflow, may fall to the
+// other side of its tie.
 // Naming: a_x is the cotangent (adjoint) of the forward quantity x.
 #pragma once
 #include "mhd_physics.hpp"
